@@ -80,17 +80,17 @@ using la::ENTRY_VOID;
 using la::NSUB;
 
 // reset: two blocks per environment, for the worlds of episodes 0 and 1
+template <bool PERLIN>
 __global__ __launch_bounds__(WG_THREADS) void k_reset(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
-                                                 const uint64_t* __restrict__ seeds, Lists ls, const Luts* __restrict__ luts, int perlin,
+                                                 const uint64_t* __restrict__ seeds, Lists ls, const Luts* __restrict__ luts,
                                                  uint32_t* __restrict__ unlocks)
 {
     if (blockIdx.x == 0) la::reset_counters(ls);
-    __shared__ uint16_t s_lat[LAT_BLOCKS * 8];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     const uint32_t env = blockIdx.x >> 1, ep = blockIdx.x & 1u;
     const uint64_t seed = seeds[env];
     const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
-    if (perlin) worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, lo, hi, env, ep, nullptr, 0, WG_THREADS, luts->perlin_cs);
-    else worldgen_block(maps + map_offset(env, ep), s_lat, lo, hi, env, ep);
+    worldgen_block<WG_THREADS, PERLIN>(maps + map_offset(env, ep), s_lat, lo, hi, env, ep, nullptr, 0, luts->perlin_cs);
     if (ep == 0) {
         if (threadIdx.x < REC_DWORDS)
             reinterpret_cast<uint32_t*>(recs + (size_t)env * 8)[threadIdx.x] = fresh_record_word(threadIdx.x, lo, hi, 0u);
@@ -102,17 +102,17 @@ __global__ __launch_bounds__(WG_THREADS) void k_reset(uint4* __restrict__ recs, 
 // ended in the previous launch.
 template <bool PERLIN>
 __device__ __forceinline__ void regeneration_block(uint8_t* __restrict__ maps, const Lists& ls, uint32_t seq, uint32_t count,
-                                                   uint32_t rb, uint32_t nrb, uint16_t* s_lat, const uint32_t* __restrict__ perlin_cs)
+                                                   uint32_t rb, uint32_t nrb, uint32_t* s_lat, const uint32_t* __restrict__ perlin_cs)
 {
     const uint4* list = la::consumed_sub_list(ls, seq, rb);
-    // two blocks per world, one half each: a regeneration block is then as short as it can be with
-    // one run of 8 cells per thread, and the tail it adds to the launch is half as long
+    // two blocks per world, one half (32 columns) each: a regeneration block is then as short as it can be
+    // with one run of 8 cells per thread, and the tail it adds to the launch is half as long
     const uint32_t pair = rb / NSUB, half = pair & 1u;
     for (uint32_t i = pair >> 1; i < count; i += nrb / NSUB / 2) {
         const uint4 entry = list[i];
         if (entry.x == ENTRY_VOID) continue;
         worldgen_block<BLOCK, PERLIN>(maps + map_offset(entry.x, entry.w), s_lat, entry.y, entry.z, entry.x, entry.w, nullptr,
-                                      (int)half * (WG_THREADS / 2), WG_THREADS / 2, perlin_cs);
+                                      (int)half * (STRIPS / 2), perlin_cs);
         if (threadIdx.x == 0) ls.tags[2 * entry.x + half] = make_uint2(entry.w, seq);
     }
 }
@@ -133,7 +133,7 @@ __device__ __forceinline__ void regeneration_block(uint8_t* __restrict__ maps, c
 // The walk over the units is in regen_units.hpp (plain arithmetic, unit-tested on the host).
 template <bool PERLIN>
 __device__ __forceinline__ void regeneration_share(uint8_t* __restrict__ maps, const Lists& ls, uint32_t seq, uint32_t count, uint32_t sub,
-                                                   bool helper, uint32_t index, uint32_t per_sub, uint32_t nq, uint16_t* s_lat,
+                                                   bool helper, uint32_t index, uint32_t per_sub, uint32_t nq, uint32_t* s_lat,
                                                    const uint32_t* __restrict__ perlin_cs)
 {
     const uint4* list = la::consumed_sub_list(ls, seq, sub);
@@ -142,7 +142,7 @@ __device__ __forceinline__ void regeneration_share(uint8_t* __restrict__ maps, c
         const uint32_t half = w.u & 1u;
         if (entry.x != ENTRY_VOID) {
             worldgen_block<BLOCK, PERLIN>(maps + map_offset(entry.x, entry.w), s_lat, entry.y, entry.z, entry.x, entry.w, nullptr,
-                                          (int)half * (WG_THREADS / 2), WG_THREADS / 2, perlin_cs);
+                                          (int)half * (STRIPS / 2), perlin_cs);
             if (threadIdx.x == 0) ls.tags[2 * entry.x + half] = make_uint2(entry.w, seq);
         }
     }
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
     // SHARE: every block reads the length of one sub-list of the consumed list, a regeneration block
     // its own, a step block the one it appends to (see regeneration_share)
     constexpr bool SHARE = G == 4;
-    static_assert(!SHARE || sizeof(s_list) >= LAT_BLOCKS * 8 * sizeof(uint16_t), "the list of finished episodes doubles as lattice scratch");
+    static_assert(EPB * LY::STRIDE >= LAT_WORDS, "the environments' area, empty until the records are parked, doubles as lattice scratch");
     const la::Ticket ticket = la::enter_launch(ls, SHARE || regen_role, regen_role ? rb : blockIdx.x);
     const uint32_t seq = ticket.seq, regen_count = ticket.regen_count;
     auto leave = [&]() { la::leave_launch(ls, ticket); };
@@ -187,15 +187,15 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
 
     if (regen_role) {
         if (SHARE)
-            regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, false, rb / NSUB, per_sub, nq, reinterpret_cast<uint16_t*>(s_env), luts->perlin_cs);
+            regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, false, rb / NSUB, per_sub, nq, s_env, luts->perlin_cs);
         else if (rb / NSUB / 2 < regen_count)
-            regeneration_block<PERLIN>(maps, ls, seq, regen_count, rb, nrb, reinterpret_cast<uint16_t*>(s_env), luts->perlin_cs);
+            regeneration_block<PERLIN>(maps, ls, seq, regen_count, rb, nrb, s_env, luts->perlin_cs);
         leave();
         return;
     }
     // this block's share of the worlds owed from the previous launch, while its records arrive
     if (SHARE && first_helper_unit(blockIdx.x / NSUB, per_sub) < 2u * regen_count)
-        regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, true, blockIdx.x / NSUB, per_sub, nq, reinterpret_cast<uint16_t*>(s_list), luts->perlin_cs);
+        regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, true, blockIdx.x / NSUB, per_sub, nq, s_env, luts->perlin_cs);
 
     if (tid == 0) s_ndone = 0;
     __syncthreads();
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
 template <bool PERLIN>
 __global__ __launch_bounds__(BLOCK) void k_drain(uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
 {
-    __shared__ uint16_t s_lat[LAT_BLOCKS * 8];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     const uint32_t rb = blockIdx.x, nrb = gridDim.x;
     const la::Ticket ticket = la::enter_launch(ls, true, rb);
     if (rb / NSUB / 2 < ticket.regen_count) regeneration_block<PERLIN>(maps, ls, ticket.seq, ticket.regen_count, rb, nrb, s_lat, luts->perlin_cs);
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
 {
     constexpr int EPB = Grp<G>::EPB;
     __shared__ uint32_t s_env[EPB * LDS_ENV_DWORDS];
-    __shared__ uint16_t s_lat[LAT_BLOCKS * 8];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ uint8_t s_queue[EPB];        // ring of environments (index in the block) waiting for a new spare world
     __shared__ uint8_t s_urgent[EPB];       // environments whose episode ended without a spare world
     __shared__ uint8_t s_spare_ok[EPB], s_pending[EPB];
@@ -317,8 +317,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         const uint32_t tenv = (uint32_t)(blockIdx.x * EPB + gt), ep = rt[RW_EPISODE] + 1u, lo = rt[RW_SEED_LO], hi = rt[RW_SEED_HI];
 #pragma unroll 1
         for (int half = 0; half < 2; ++half)
-            worldgen_block<BLOCK, PERLIN, false>(maps + map_offset(tenv, ep), s_lat, lo, hi, tenv, ep, start_win, half * BLOCK, BLOCK,
-                                          luts->perlin_cs);
+            worldgen_block<BLOCK, PERLIN>(maps + map_offset(tenv, ep), s_lat, lo, hi, tenv, ep, start_win, half * (STRIPS / 2), luts->perlin_cs);
     };
 
     // steps, then as many turns without a step as it takes to generate the spare worlds still owed
@@ -430,7 +429,7 @@ __global__ __launch_bounds__(WG_THREADS) void k_reset_list(uint4* __restrict__ r
                                                       const uint8_t* __restrict__ done, Lists ls, Params p, int envs_per_step_block)
 {
     constexpr int G = 16;
-    __shared__ uint16_t s_lat[LAT_BLOCKS * 8];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ uint32_t s_env[LDS_ENV_DWORDS];
     __shared__ uint32_t s_rank[WG_THREADS / 64];
     const int tid = threadIdx.x;
@@ -482,7 +481,7 @@ __global__ __launch_bounds__(WG_THREADS) void k_reset_list(uint4* __restrict__ r
         if (tid == 96 && !pool) la::append_after_step(ls, env / (uint32_t)envs_per_step_block, make_uint4(env, lo, hi, ep + 1u));
         // ends with a block barrier
         if (p.worldgen == CRAFTAX_WORLDGEN_PERLIN)
-            worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, wlo, whi, wenv, wep, s_env + LDS_WIN, 0, WG_THREADS, luts->perlin_cs);
+            worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, wlo, whi, wenv, wep, s_env + LDS_WIN, 0, luts->perlin_cs);
         else worldgen_block(maps + map_offset(env, ep), s_lat, wlo, whi, wenv, wep, s_env + LDS_WIN);
         if (kSymbolic && obs != nullptr && tid < G) {
             // scalars of a fresh episode: empty inventory, vitals 9, facing down, noon, awake
@@ -640,11 +639,11 @@ __global__ __launch_bounds__(BLOCK) void k_import(uint4* __restrict__ recs, uint
 __global__ __launch_bounds__(WG_THREADS) void k_import_spare(const uint4* __restrict__ recs, uint8_t* __restrict__ maps, Lists ls, int first,
                                                              const Luts* __restrict__ luts, int perlin)
 {
-    __shared__ uint16_t s_lat[LAT_BLOCKS * 8];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     const uint32_t env = (uint32_t)first + blockIdx.x;
     const uint32_t* r = reinterpret_cast<const uint32_t*>(recs + (size_t)env * 8);
     const uint32_t ep = r[RW_EPISODE] + 1u, lo = r[RW_SEED_LO], hi = r[RW_SEED_HI];
-    if (perlin) worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, lo, hi, env, ep, nullptr, 0, WG_THREADS, luts->perlin_cs);
+    if (perlin) worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, lo, hi, env, ep, nullptr, 0, luts->perlin_cs);
     else worldgen_block(maps + map_offset(env, ep), s_lat, lo, hi, env, ep);
     if (threadIdx.x < 2) ls.tags[2 * env + threadIdx.x] = make_uint2(ep, 0u);
 }
@@ -703,7 +702,7 @@ __global__ __launch_bounds__(WG_THREADS) void k_mutate_noise(uint4* __restrict__
                                                             const Luts* __restrict__ luts, uint16_t* __restrict__ theta, int first,
                                                             uint32_t k0, uint32_t k1, uint32_t round, uint32_t amplitude)
 {
-    __shared__ uint16_t s_lat[LAT_BLOCKS * 8];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ uint16_t s_theta[LAT_BLOCKS * 8];
     const int tid = threadIdx.x;
     const uint32_t env = (uint32_t)first + blockIdx.x;
@@ -725,7 +724,7 @@ __global__ __launch_bounds__(WG_THREADS) void k_mutate_noise(uint4* __restrict__
         }
     }
     __syncthreads();   // every thread has read the record before the new one is written below
-    worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, lo, hi, env, ep, nullptr, 0, WG_THREADS, luts->perlin_cs, s_theta);
+    worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, lo, hi, env, ep, nullptr, 0, luts->perlin_cs, s_theta);
     if (tid < REC_DWORDS) r[tid] = fresh_record_word(tid, lo, hi, ep);
 }
 
@@ -1180,7 +1179,7 @@ static int check_kernels(const craftax_config* cfg, int lanes, std::string* err)
     }
 #undef CRAFTAX_CHECK_MODE
 #undef CRAFTAX_CHECK_ROLLOUT
-    ok = ok && fits("k_reset", (const void*)k_reset, WG_THREADS) && fits("k_import_spare", (const void*)k_import_spare, WG_THREADS) &&
+    ok = ok && (perlin ? fits("k_reset", (const void*)k_reset<true>, WG_THREADS) : fits("k_reset", (const void*)k_reset<false>, WG_THREADS)) && fits("k_import_spare", (const void*)k_import_spare, WG_THREADS) &&
          fits("k_mutate_noise", (const void*)k_mutate_noise, WG_THREADS);
     return ok ? CRAFTAX_OK : CRAFTAX_E_CONFIG;
 }
@@ -1285,8 +1284,11 @@ int craftax_reset(void* state, const uint64_t* seeds, int n, void* stream)
         return rc ? fail(rc, err) : rc;
     }
     const Ptrs q = pointers(state, s);
-    hipLaunchKernelGGL(k_reset, dim3(2u * (unsigned)n), dim3(WG_THREADS), 0, (hipStream_t)stream, q.recs, q.maps, seeds, q.ls, q.luts,
-                       (int)(s.cfg.worldgen == CRAFTAX_WORLDGEN_PERLIN), make_params(state, s).unlocks);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(2u * (unsigned)n), dim3(WG_THREADS), 0, (hipStream_t)stream, q.recs, q.maps, seeds, q.ls, q.luts,
+                           make_params(state, s).unlocks);
+    };
+    if (s.cfg.worldgen == CRAFTAX_WORLDGEN_PERLIN) go(k_reset<true>); else go(k_reset<false>);
     const int rc = check_launch("craftax_reset");
     if (rc == CRAFTAX_OK) update_state(state, true, false);
     return rc;

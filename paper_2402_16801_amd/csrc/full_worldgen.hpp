@@ -49,19 +49,56 @@ __device__ inline bool on_corridor(int x, int y, int x0, int y0, int x1, int y1)
 // result equals the row-first bilinear formula ((a(256-wx)+b wx)(256-wy) + (c(256-wx)+d wx) wy) >> 16
 // because nothing is rounded before the final shift.  The callers'
 // runs of 4 cells start at a multiple of 4, so a run lies inside one lattice cell.
+__device__ inline uint32_t column(const uint16_t* lat, int width, int ix, int iy, uint32_t wy)
+{
+    return (uint32_t)lat[CX_IDX(iy * width + ix, width * width)] * (256u - wy) + (uint32_t)lat[CX_IDX((iy + 1) * width + ix, width * width)] * wy;
+}
+__device__ inline uint32_t across(uint32_t left, uint32_t right, uint32_t wx)
+{
+    return (left * (256u - wx) + right * wx) >> 16;
+}
+
+constexpr int PERLIN_GAIN = cx::PERLIN_GAIN;
+template <int S>
+__device__ inline int64_t perlin_fade(int k)
+{
+    const int F = k * k * k * (6 * k * k - 15 * k * S + 10 * S * S);
+    return S == 16 ? (int64_t)((F + 8) >> 4) : (int64_t)(2 * F);
+}
+__device__ inline int64_t perlin_blend(int64_t p, int64_t q, int64_t w) { return p + (((q - p) * w) >> 16); }
+template <int S>
+__device__ inline uint32_t perlin(const uint16_t* lat, int width, const uint32_t* __restrict__ cs, int x, int y)
+{
+    static_assert(S == 8 || S == 16, "lattice spacing");
+    constexpr int SHIFT = S == 16 ? 4 : 3;
+    const int ix = x >> SHIFT, iy = y >> SHIFT, kx = x & (S - 1), ky = y & (S - 1);
+    int64_t dot[2][2];
+#pragma unroll
+    for (int cy = 0; cy < 2; ++cy)
+#pragma unroll
+        for (int cx = 0; cx < 2; ++cx) {
+            const uint32_t g = cs[lat[CX_IDX((iy + cy) * width + ix + cx, width * width)] >> 6];
+            dot[cy][cx] = (int64_t)((int)(int16_t)(g & 0xFFFFu) * (kx - cx * S) + (int)(int16_t)(g >> 16) * (ky - cy * S));
+        }
+    const int64_t wx = perlin_fade<S>(kx), wy = perlin_fade<S>(ky);
+    const int64_t n = perlin_blend(perlin_blend(dot[0][0], dot[0][1], wx), perlin_blend(dot[1][0], dot[1][1], wx), wy);
+    const int64_t v = 32768 + ((n * PERLIN_GAIN) >> (10 + SHIFT));
+    return (uint32_t)(v < 0 ? 0 : (v > 65535 ? 65535 : v));
+}
+
 struct Field8 { uint32_t l, r; };
 __device__ inline Field8 field8(const uint16_t* lat, int x0, int y)
 {
     const uint32_t wy = cx::smooth8(y & 7);
-    return { cx::column(lat, 7, x0 >> 3, y >> 3, wy), cx::column(lat, 7, (x0 >> 3) + 1, y >> 3, wy) };
+    return { column(lat, 7, x0 >> 3, y >> 3, wy), column(lat, 7, (x0 >> 3) + 1, y >> 3, wy) };
 }
 __device__ inline Field8 field16(const uint16_t* lat, int x0, int y)
 {
     const uint32_t wy = cx::smooth16(y & 15);
-    return { cx::column(lat, 4, x0 >> 4, y >> 4, wy), cx::column(lat, 4, (x0 >> 4) + 1, y >> 4, wy) };
+    return { column(lat, 4, x0 >> 4, y >> 4, wy), column(lat, 4, (x0 >> 4) + 1, y >> 4, wy) };
 }
-__device__ inline uint32_t at8(const Field8& f, int x) { return cx::across(f.l, f.r, cx::smooth8(x & 7)); }
-__device__ inline uint32_t at16(const Field8& f, int x) { return cx::across(f.l, f.r, cx::smooth16(x & 15)); }
+__device__ inline uint32_t at8(const Field8& f, int x) { return across(f.l, f.r, cx::smooth8(x & 7)); }
+__device__ inline uint32_t at16(const Field8& f, int x) { return across(f.l, f.r, cx::smooth16(x & 15)); }
 
 // Cell functions, one per kind of floor: block id | item << 8.
 __device__ inline int classify_overworld(const GenLayout& L, int Wn, int Mn, int Cn, int Fn, int x, int y, int u)
@@ -312,7 +349,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
                                             uint8_t* start_wi = nullptr, int first_run = 0, int runs = GEN_THREADS,
                                             const uint32_t* __restrict__ perlin_cs = nullptr, const uint16_t* theta_f = nullptr)
 {
-    const bool perlin = CAN_PERLIN && perlin_cs != nullptr;
+    const bool use_perlin = CAN_PERLIN && perlin_cs != nullptr;
     static_assert(NT >= 64, "the layout phase uses the first wavefront");
     const int tid0 = threadIdx.x;
     // Layout phase, all in the first wavefront and with one Philox call for the whole wave: every
@@ -404,17 +441,17 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
 #pragma unroll 1
         for (int j = 0; j < 4; ++j) one(j);
     };
-    if (CAN_PERLIN && perlin && f == 0) {
+    if (CAN_PERLIN && use_perlin && f == 0) {
         cells([&](int j) {
-            const int Wn = (int)((3u * cx::perlin<16>(s_lat, 4, perlin_cs, x + j, y) + cx::perlin<8>(s_lat + 32, 7, perlin_cs, x + j, y)) >> 2);
-            const int Mn = (int)((3u * cx::perlin<16>(s_lat + 16, 4, perlin_cs, x + j, y) + cx::perlin<8>(s_lat + 81, 7, perlin_cs, x + j, y)) >> 2);
-            put(j, classify_overworld(L, Wn, Mn, (int)cx::perlin<8>(s_lat + 130, 7, perlin_cs, x + j, y),
-                                      (int)cx::perlin<8>(s_lat + 179, 7, perlin_cs, x + j, y), x + j, y, draw(j)));
+            const int Wn = (int)((3u * perlin<16>(s_lat, 4, perlin_cs, x + j, y) + perlin<8>(s_lat + 32, 7, perlin_cs, x + j, y)) >> 2);
+            const int Mn = (int)((3u * perlin<16>(s_lat + 16, 4, perlin_cs, x + j, y) + perlin<8>(s_lat + 81, 7, perlin_cs, x + j, y)) >> 2);
+            put(j, classify_overworld(L, Wn, Mn, (int)perlin<8>(s_lat + 130, 7, perlin_cs, x + j, y),
+                                      (int)perlin<8>(s_lat + 179, 7, perlin_cs, x + j, y), x + j, y, draw(j)));
         });
-    } else if (CAN_PERLIN && perlin && is_cave(f)) {
+    } else if (CAN_PERLIN && use_perlin && is_cave(f)) {
         const uint64_t opened = L.row_mask[M_CAVE_OPEN][CX_IDX(y, W)] >> x;   // the run lies in one row
         cells([&](int j) {
-            put(j, classify_cave_masked(L, f, (int)cx::perlin<8>(s_lat, 7, perlin_cs, x + j, y), (int)cx::perlin<8>(s_lat + 49, 7, perlin_cs, x + j, y),
+            put(j, classify_cave_masked(L, f, (int)perlin<8>(s_lat, 7, perlin_cs, x + j, y), (int)perlin<8>(s_lat + 49, 7, perlin_cs, x + j, y),
                                         x + j, y, draw(j), (opened >> j) & 1ull));
         });
     } else if (f == 0) {
