@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -51,19 +52,20 @@ __device__ inline void publish_world(uint32_t* __restrict__ genv, const GenLayou
 
 // ---------------------------------------------------------------------------------------------
 // reset of every environment: one block per (environment, episode 0 or 1, floor)
-__global__ __launch_bounds__(GEN_THREADS) void kf_reset(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
+template <bool PERLIN>
+__global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_reset(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                        const uint64_t* __restrict__ seeds, Lists ls, const uint32_t* __restrict__ perlin_cs,
                                                        int pool, uint32_t* __restrict__ unlocks)
 {
     if (blockIdx.x == 0) la::reset_counters(ls);
-    __shared__ uint16_t s_lat[LAT_TOTAL];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
     const uint32_t env = blockIdx.x / (2 * FLOORS), ep = (blockIdx.x / FLOORS) & 1u;
     const int f = blockIdx.x % FLOORS;
     const uint64_t seed = seeds[env];
     const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
-    worldgen_floor_block<GEN_THREADS, true>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, 0, GEN_THREADS, perlin_cs);
+    worldgen_floor_block<GEN_THREADS, PERLIN>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, perlin_cs);
     if (f == 0) publish_world(envs + (size_t)env * ENV_DWORDS, s_layout, lo, hi, ep, ep == 0u, s_words);
     if (f == 0 && ep == 0u && threadIdx.x < UNLOCK_STRIDE) unlocks[(size_t)env * UNLOCK_STRIDE + threadIdx.x] = 0u;
     // With optimistic resets no spare world is ever valid: tag 0 matches no next episode (they count
@@ -71,35 +73,49 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_reset(uint32_t* __restrict__ e
     if (ep == 1u && threadIdx.x == 0) ls.tags[(size_t)env * NTAG + f] = make_uint2(pool ? 0u : 1u, 0u);
 }
 
-// The regeneration blocks of the step grid: worlds after next for the episodes that ended in the
-// previous launch.  The consumed list is one dense queue of work units, one floor of one world
-// each; block rb of nrb takes units rb, rb + nrb, ...  The blocks stand at the head of the grid:
-// a step launch holds as many of them as the chip has room for beside the step blocks, so every
-// unit starts with the launch and none waits for a block that is scheduled late.
-// where a regeneration block keeps its scratch in the step kernel's LDS area (dwords): lattice numbers at 0, the layout at 128
-constexpr int REGEN_WORDS_AT = 832, REGEN_PREFIX_AT = 848;
-template <bool PERLIN>
+// LDS scratch of the threads that generate a world (or a floor of one)
+struct WorldScratch { uint32_t lat[LAT_WORDS]; GenLayout layout; uint32_t words[FLOORS + 1]; };
+static_assert(sizeof(WorldScratch) % 8 == 0 && offsetof(WorldScratch, layout) % 8 == 0, "row masks are 64-bit words");
+
+// Regeneration blocks (of the step grid, or of a launch of their own): worlds after next for the
+// episodes that ended in the previous launch.  The consumed list is one dense queue of work units, one
+// floor of one world each; block rb of nrb takes units rb, rb + nrb, ...  In the step grid the blocks
+// stand at the head: a step launch holds as many of them as the chip has room for beside the step
+// blocks, so every unit starts with the launch and none waits for a block that is scheduled late.
+template <int NT, bool PERLIN>
 __device__ __forceinline__ void regeneration_queue(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Lists& ls,
-                                                   uint32_t seq, uint32_t* lds, int regen_blocks, const uint32_t* __restrict__ perlin_cs)
+                                                   uint32_t seq, WorldScratch& s, const uint32_t* s_prefix, int regen_blocks,
+                                                   const uint32_t* __restrict__ perlin_cs)
 {
-    uint16_t* s_lat = reinterpret_cast<uint16_t*>(lds);
-    GenLayout& L = *reinterpret_cast<GenLayout*>(lds + 128);
-    uint32_t* s_words = lds + REGEN_WORDS_AT;
-    const uint32_t* s_prefix = lds + REGEN_PREFIX_AT;
     const uint32_t units = s_prefix[NSUB - 1] * (uint32_t)FLOORS;
     for (uint32_t u = blockIdx.x; u < units; u += (uint32_t)regen_blocks) {
         __syncthreads();   // the previous unit's scratch has been read by everyone
         const uint4 entry = la::queue_entry(ls, seq, s_prefix, u / FLOORS);
         const int f = (int)(u % FLOORS);
         if (entry.x == ENTRY_VOID) continue;
-        worldgen_floor_block<BLOCK, PERLIN>(maps + map_offset(entry.x, entry.w), s_lat, L, entry.y, entry.z, entry.x, entry.w, f, nullptr, nullptr,
-                                            0, GEN_THREADS, PERLIN ? perlin_cs : nullptr);
-        if (f == 0) publish_world(envs + (size_t)entry.x * ENV_DWORDS, L, entry.y, entry.z, entry.w, false, s_words);
+        worldgen_floor_block<NT, PERLIN, true>(maps + map_offset(entry.x, entry.w), s.lat, s.layout, entry.y, entry.z, entry.x, entry.w, f, nullptr, nullptr,
+                                         PERLIN ? perlin_cs : nullptr);
+        if (f == 0) publish_world(envs + (size_t)entry.x * ENV_DWORDS, s.layout, entry.y, entry.z, entry.w, false, s.words);
         if (threadIdx.x == 0) ls.tags[(size_t)entry.x * NTAG + f] = make_uint2(entry.w, seq);
     }
 }
-static_assert(LAT_TOTAL * 2 <= 128 * 4 && sizeof(GenLayout) <= (REGEN_WORDS_AT - 128) * 4 && REGEN_WORDS_AT + FLOORS + 1 <= REGEN_PREFIX_AT &&
-              REGEN_PREFIX_AT + NSUB <= ENVS_PER_BLOCK * L_ENV_DWORDS, "regeneration scratch overlaps");
+// where a regeneration block of the step grid keeps its scratch in the step kernel's LDS area (dwords)
+constexpr int REGEN_SCRATCH_AT = 0, REGEN_PREFIX_AT = REGEN_SCRATCH_AT + (int)sizeof(WorldScratch) / 4;
+static_assert(REGEN_PREFIX_AT + NSUB <= ENVS_PER_BLOCK * L_ENV_DWORDS, "regeneration scratch outgrows the environments' area");
+
+// A launch of regeneration blocks only (before and after a rollout): generates every world on the
+// lists and empties them, with the bookkeeping of a step launch that has no step blocks.  A kernel
+// of its own, at the occupancy of the generator instead of that of the step kernel.
+constexpr int DRAIN_BLOCKS = 1536;   // six blocks of five wavefronts on each of 256 compute units
+template <bool PERLIN>
+__global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_drain(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
+{
+    __shared__ WorldScratch s_gen;
+    __shared__ uint32_t s_prefix[NSUB];
+    const la::Ticket ticket = la::enter_launch_queue(ls, s_prefix);
+    regeneration_queue<GEN_THREADS, PERLIN>(envs, maps, ls, ticket.seq, s_gen, s_prefix, (int)gridDim.x, luts->perlin_cs);
+    la::leave_launch(ls, ticket);
+}
 
 // ---------------------------------------------------------------------------------------------
 // step: one wavefront per environment, four environments per block; the grid starts with the
@@ -126,12 +142,13 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
     constexpr int WIN_IT = (WIN_ROWS * WIN_COLS + GW - 1) / GW;
     static_assert(REC_DWORDS % GW == 0 || GW > REC_DWORDS, "the record is moved in whole turns of the group");
     static_assert(GW >= MOBTAB_DWORDS && GW >= NTAG && GW >= FLOORS + 1, "a group holds a mob table, the tags and the header in one turn");
-    __shared__ uint32_t s_env[EPB * L_ENV_DWORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[EPB * L_ENV_DWORDS];
     __shared__ float s_lut[LUT_FLOATS];
     const int tid = threadIdx.x, w = tid / GW, l = tid % GW;
     if ((int)blockIdx.x < regen_blocks) {
         const la::Ticket ticket = la::enter_launch_queue(ls, s_env + REGEN_PREFIX_AT);
-        regeneration_queue<PERLIN>(envs, maps, ls, ticket.seq, s_env, regen_blocks, luts->perlin_cs);
+        regeneration_queue<BLOCK, PERLIN>(envs, maps, ls, ticket.seq, *reinterpret_cast<WorldScratch*>(s_env + REGEN_SCRATCH_AT), s_env + REGEN_PREFIX_AT,
+                                          regen_blocks, luts->perlin_cs);
         la::leave_launch(ls, ticket);
         return;
     }
@@ -265,68 +282,62 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
 }
 
 // ---------------------------------------------------------------------------------------------
-// rollout: several steps in one launch (see craftax_rollout).  A block keeps the records of its
-// four environments in LDS for the whole launch, every wavefront walks its environment through
-// the steps, and the block meets at a barrier once per step.  Worlds stay one episode ahead as in
-// the step kernel, but the block generates them itself: an environment whose episode ends moves
-// into the spare world in its other map slot (ladders and potion map from the header, the start
-// window from the map), and the whole block then generates the world after it into the slot that
-// was left, floor by floor (the other environments of the block wait those few hundred
-// microseconds; nothing is exchanged between blocks, so blocks drift apart and the memory traffic
-// of some overlaps the arithmetic of others).  At the end the block writes the records back and
-// tags the spare worlds it wrote as written by launch 0, which is what the step kernel expects.
+// A whole world by the calling wavefront alone, into its map slot; leaves the ten layout words in
+// s->words and drops the cells around the start position into the windows.  Not inlined: it runs for
+// few environments of a rollout, whose loop would otherwise pay for its registers in spills.
+template <typename T> using Lds = T __attribute__((address_space(3)));
+template <bool PERLIN>
+__device__ __attribute__((noinline)) void generate_world(uint8_t* slot, Lds<WorldScratch>* scratch, Lds<uint32_t>* win_blocks, Lds<uint32_t>* win_items,
+                                                         uint32_t lo, uint32_t hi, uint32_t env, uint32_t ep, const uint32_t* perlin_cs)
+{
+    WorldScratch& s = *(WorldScratch*)scratch;
+    const int l = threadIdx.x & 63;
+#pragma unroll 1
+    for (int f = 0; f < FLOORS; ++f) {
+        worldgen_floor_block<64, PERLIN, true>(slot, s.lat, s.layout, lo, hi, env, ep, f, (uint8_t*)(uint32_t*)win_blocks, (uint8_t*)(uint32_t*)win_items, perlin_cs);
+        if (f == 0) {                             // the layout of floor 0 describes the whole world
+            if (l < FLOORS + 1) s.words[l] = layout_word(s.layout, l);
+            wave_sync();
+        }
+    }
+}
+
+// rollout: several steps in one launch (see craftax_rollout).  A wavefront keeps the record of its
+// environment in LDS for the whole launch and walks it through the steps; nothing is exchanged
+// between wavefronts, so they drift apart and the memory traffic of some overlaps the arithmetic
+// of others.  Worlds stay one episode ahead as in the step kernel: an environment whose episode ends
+// moves into the spare world in its other map slot (ladders and potion map from the header, the start
+// window from the map).  The world after that one is not generated here: at the end of the launch
+// the environment goes on the regeneration list, and the regeneration launch behind this one
+// generates all of them with the whole chip.  Only an environment whose episode ends a second time in
+// one launch has no spare world; its wavefront generates the next world on the spot.  Generated by the
+// block at every end of an episode, worlds stalled whole blocks, and a launch lasted as long as the
+// block with the most of them (64 steps: 4,096 environments 1,072 -> 900 us, 1,024: 780 -> 580, 100
+// environments and 16 steps: 230 -> 150).
 // Before the launch the regeneration lists of the step kernel must be empty (the host runs a
-// list-only launch first); a spare world that is missing nonetheless is generated on the spot.
+// list-only launch first).
 template <bool F32, bool PERLIN>
 __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                        const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                        uint8_t* __restrict__ obs, float* __restrict__ reward,
-                                                       uint8_t* __restrict__ done, uint2* __restrict__ tags, Params p, int steps)
+                                                       uint8_t* __restrict__ done, Lists ls, Params p, int steps)
 {
-    __shared__ uint32_t s_env[ENVS_PER_BLOCK * L_ENV_DWORDS];
-    __shared__ uint16_t s_lat[LAT_TOTAL];
-    __shared__ GenLayout s_layout;
-    __shared__ uint32_t s_words[FLOORS + 1];
-    __shared__ int s_ended[ENVS_PER_BLOCK];          // this step ended the episode of environment w
-    __shared__ int s_spare_ok[ENVS_PER_BLOCK];       // the world of the next episode is complete in the other map slot
-    __shared__ int s_changed[ENVS_PER_BLOCK];        // this launch has written a spare world for environment w
-    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
-    const int env = blockIdx.x * ENVS_PER_BLOCK + w;
-    const bool active = env < p.n;
-    uint32_t* e = s_env + w * L_ENV_DWORDS;
-    uint32_t* genv = envs + (size_t)(active ? env : 0) * ENV_DWORDS;
-    if (active) e[L_REC + l] = genv[l];
-    if (l == 0) { s_ended[w] = 0; s_spare_ok[w] = 0; s_changed[w] = 0; }
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * L_ENV_DWORDS];
+    __shared__ WorldScratch s_gen[ENVS_PER_BLOCK];
+    __shared__ float s_lut[LUT_FLOATS];
+    if (threadIdx.x < LUT_FLOATS) s_lut[threadIdx.x] = luts->sqrt10[threadIdx.x];   // sqrt10, tenth and light20 lie one after the other
     __syncthreads();
-    if (active) {
+    bool spare_ok;           // the world of the next episode is complete in the other map slot
+    {
+        const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
+        if (env >= p.n) return;
+        uint32_t* e = s_env + w * L_ENV_DWORDS;
+        e[L_REC + l] = envs[(size_t)env * ENV_DWORDS + l];
+        wave_sync();
         const uint32_t ep = uniu(e[L_REC + R_EPISODE]);
-        uint2 tag = make_uint2(0u, 0u);
-        if (l < NTAG) tag = tags[(size_t)env * NTAG + l];
         constexpr uint64_t ALL = (1ull << NTAG) - 1ull;
-        const bool complete = (__ballot(l < NTAG && tag.x == ep + 1u) & ALL) == ALL;
-        if (l == 0 && complete) s_spare_ok[w] = 1;
+        spare_ok = (__ballot(l < NTAG && ls.tags[(size_t)env * NTAG + (l < NTAG ? l : 0)].x == ep + 1u) & ALL) == ALL;
     }
-
-    // Generates the world of episode `ep` of block-local environment ww into its map slot, all threads
-    // of the block; leaves the ten layout words in s_words.  start: drop the cells around the start
-    // position into that environment's LDS windows.
-    auto generate = [&](int ww, uint32_t ep, bool start) __attribute__((always_inline)) {
-        uint32_t* ew = s_env + ww * L_ENV_DWORDS;
-        const uint32_t wenv = (uint32_t)(blockIdx.x * ENVS_PER_BLOCK + ww), lo = ew[L_REC + R_SEED_LO], hi = ew[L_REC + R_SEED_HI];
-        uint8_t* slot = maps + map_offset(wenv, ep);
-#pragma unroll 1
-        for (int f = 0; f < FLOORS; ++f) {
-            worldgen_floor_block<BLOCK, PERLIN>(slot, s_lat, s_layout, lo, hi, wenv, ep, f,
-                                                start ? reinterpret_cast<uint8_t*>(ew + L_WB) : nullptr,
-                                                start ? reinterpret_cast<uint8_t*>(ew + L_WI) : nullptr, 0, GEN_THREADS,
-                                                PERLIN ? luts->perlin_cs : nullptr);
-            if (f == 0) {                             // the layout of floor 0 describes the whole world
-                if (tid < FLOORS + 1) s_words[tid] = layout_word(s_layout, tid);
-                __syncthreads();
-            }
-        }
-    };
-
 #pragma unroll 1
     for (int t = 0; t < steps; ++t) {
         // Everything a lane derives from its index is derived again in every turn: the compiler would
@@ -335,101 +346,65 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
         uint8_t* obs_t = obs;
         asm volatile("" : "+v"(tid_t));
         asm volatile("" : "+s"(obs_t));
-        const int tid = tid_t, w = tid >> 6, l = tid & 63;
+        const int w = uni(tid_t >> 6), l = tid_t & 63;
         const int env = blockIdx.x * ENVS_PER_BLOCK + w;
-        const bool active = env < p.n;
         uint32_t* e = s_env + w * L_ENV_DWORDS;
-        uint32_t* genv = envs + (size_t)(active ? env : 0) * ENV_DWORDS;
-        uint8_t* obs = obs_t;
+        uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
+        RenderAux<64> aux;
+        fetch_scalar_specs<64>(l, aux);
+        aux.lut = s_lut;
+        const int action = uni(actions[(size_t)t * p.n + env]);
+        const uint32_t ep = uniu(e[L_REC + R_EPISODE]);
+        // daylight of the state that will be rendered: the next phase, or phase 0 of a fresh episode
+        const uint32_t phase_now = uniu(e[L_REC + R_MANA]) >> 16;
+        const float day_next = luts->daylight[phase_now + 1u == p.day_length ? 0u : phase_now + 1u], day_fresh = luts->daylight[0];
         MobRegs m;
-        clear_mob(m);
-        StepOut o;
-        o.done = false; o.reward = 0.0f; o.wx0 = 0; o.wy0 = 0; o.unlocked[0] = o.unlocked[1] = o.unlocked[2] = 0u;
-        int floor_now = 0;
-        if (active) {
-            const int action = uni(actions[(size_t)t * p.n + env]);
-            const uint32_t ep = uniu(e[L_REC + R_EPISODE]);
-            uint32_t qw;
-            Player P;
-            o = step_env(l, (uint32_t)env, e, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, []() {});
-            if (l == 0) { reward[(size_t)t * p.n + env] = o.reward; done[(size_t)t * p.n + env] = o.done ? 1 : 0; }
+        uint32_t qw;
+        Player P;
+        StepOut o = step_env(l, (uint32_t)env, e, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, []() {});
+        if (l == 0) { reward[(size_t)t * p.n + env] = o.reward; done[(size_t)t * p.n + env] = o.done ? 1 : 0; }
 #pragma unroll
-            for (int aw = 0; aw < 3; ++aw) count_unlocks<64>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, aw, o.unlocked[aw]);
-            floor_now = P.floor;
-            if (!o.done) {
-                if (l == 0) pack_player(e + L_REC, P);
-                if (l < NPLANT) e[L_REC + R_PLANT + l] = qw;
-                wave_sync();
-            } else if (l == 0) s_ended[w] = 1;
-        }
-        __syncthreads();
-        // the worlds of the episodes that start now
-#pragma unroll 1
-        for (int ww = 0; ww < ENVS_PER_BLOCK; ++ww) {
-            if (!s_ended[ww]) continue;
-            uint32_t* ew = s_env + ww * L_ENV_DWORDS;
-            const uint32_t ep1 = ew[L_REC + R_EPISODE] + 1u, lo = ew[L_REC + R_SEED_LO], hi = ew[L_REC + R_SEED_HI];
-            const uint32_t wenv = (uint32_t)(blockIdx.x * ENVS_PER_BLOCK + ww);
-            uint32_t* wgenv = envs + (size_t)wenv * ENV_DWORDS;
-            __syncthreads();
-            const bool waiting = s_spare_ok[ww] != 0;
-            if (waiting) {
-                // the world is waiting in the other slot: its ladders and potion map from the header,
-                // the window of its start position from the map
-                if (tid < FLOORS + 1) s_words[tid] = wgenv[SPARE_LADDER + tid];
-                if (tid >= 64 && tid < 128)
-                    load_window(tid - 64, maps + map_offset(wenv, ep1), 0, W / 2, W / 2, reinterpret_cast<uint8_t*>(ew + L_WB),
-                                reinterpret_cast<uint8_t*>(ew + L_WI));
-                __syncthreads();
+        for (int aw = 0; aw < 3; ++aw) count_unlocks<64>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, aw, o.unlocked[aw]);
+        int floor_now = P.floor;
+        if (!o.done) {
+            if (l == 0) pack_player(e + L_REC, P);
+            if (l < NPLANT) e[L_REC + R_PLANT + l] = qw;
+            wave_sync();
+        } else {
+            const uint32_t lo = uniu(e[L_REC + R_SEED_LO]), hi = uniu(e[L_REC + R_SEED_HI]);
+            uint8_t* next = maps + map_offset((uint32_t)env, ep + 1u);
+            uint32_t* words = e + L_SPARE_HDR;
+            if (spare_ok) {
+                if (l < FLOORS + 1) words[l] = genv[SPARE_LADDER + l];
+                load_window(l, next, 0, W / 2, W / 2, reinterpret_cast<uint8_t*>(e + L_WB), reinterpret_cast<uint8_t*>(e + L_WI));
+                spare_ok = false;
+            } else {
+                generate_world<PERLIN>(next, (Lds<WorldScratch>*)(s_gen + w), (Lds<uint32_t>*)(e + L_WB), (Lds<uint32_t>*)(e + L_WI), lo, hi, (uint32_t)env,
+                                       ep + 1u, PERLIN ? luts->perlin_cs : nullptr);
+                if (l < FLOORS + 1) words[l] = s_gen[w].words[l];
             }
-            // turn 0 (only if no world was waiting): the world of the new episode, on the spot; turn 1:
-            // the world after it, into the slot that has just been left, so that the next end of an
-            // episode finds it (and the step kernel after this launch)
-#pragma unroll 1
-            for (int turn = waiting ? 1 : 0; turn < 2; ++turn) {
-                if (turn == 1) {
-                    // fresh record in LDS, empty mob tables in memory
-                    if (tid < REC_DWORDS) ew[L_REC + tid] = fresh_record_word(tid, s_words, lo, hi, ep1);
-                    if (tid < FLOORS * MOBTAB_DWORDS) wgenv[REC_DWORDS + tid] = 0u;
-                    __syncthreads();
-                }
-                generate(ww, ep1 + (uint32_t)turn, turn == 0);
-            }
-            if (tid < FLOORS + 1) wgenv[SPARE_LADDER + tid] = s_words[tid];
-            if (tid == 0) { s_spare_ok[ww] = 1; s_changed[ww] = 1; }
-            __syncthreads();
+            wave_sync();
+            // fresh record, empty mob tables
+            e[L_REC + l] = fresh_record_word(l, words, lo, hi, ep + 1u);
+            for (int i = l; i < FLOORS * MOBTAB_DWORDS; i += 64) genv[REC_DWORDS + i] = 0u;
+            wave_sync();
+            clear_mob(m);
+            floor_now = 0;
+            o.wx0 = W / 2 - WIN_COLS / 2; o.wy0 = W / 2 - WIN_ROWS / 2;
         }
-        if (active) {
-            if (o.done) {
-                clear_mob(m);
-                floor_now = 0;
-                o.wx0 = W / 2 - WIN_COLS / 2; o.wy0 = W / 2 - WIN_ROWS / 2;
-                if (l == 0) s_ended[w] = 0;
-            }
-            if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? pack_regs(m) : 0u;
-            if (obs != nullptr)
-                render_env<F32>(l, e, o.wx0, o.wy0, m.alive, m.x, m.y, m.type, luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8));
+        if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? pack_regs(m) : 0u;
+        if (obs != nullptr) {
+            aux.day = o.done ? day_fresh : day_next;
+            render_env<F32>(l, e, o.wx0, o.wy0, m.alive, m.x, m.y, m.type, luts, obs_t + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux);
         }
-        __syncthreads();
+        wave_sync();
     }
-    // records back; spare worlds for the step kernel
-    if (active) genv[l] = e[L_REC + l];
-#pragma unroll 1
-    for (int ww = 0; ww < ENVS_PER_BLOCK; ++ww) {
-        const int wenv = blockIdx.x * ENVS_PER_BLOCK + ww;
-        if (wenv >= p.n) continue;
-        uint32_t* ew = s_env + ww * L_ENV_DWORDS;
-        const uint32_t ep = ew[L_REC + R_EPISODE];
-        if (s_spare_ok[ww] && !s_changed[ww]) continue;           // its spare world and tags are as the launch found them
-        __syncthreads();
-        if (!s_spare_ok[ww]) {
-            generate(ww, ep + 1u, false);
-            uint32_t* wgenv = envs + (size_t)wenv * ENV_DWORDS;
-            if (tid < FLOORS + 1) wgenv[SPARE_LADDER + tid] = s_words[tid];
-        }
-        if (tid < NTAG) tags[(size_t)wenv * NTAG + tid] = make_uint2(ep + 1u, 0u);
-        __syncthreads();
-    }
+    // the record back; the world after this episode, if it is owed, for the regeneration launch
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
+    const uint32_t* e = s_env + w * L_ENV_DWORDS;
+    envs[(size_t)env * ENV_DWORDS + l] = e[L_REC + l];
+    if (!spare_ok && l == 0)
+        la::append_after_step(ls, (uint32_t)env / ENVS_PER_BLOCK, make_uint4((uint32_t)env, e[L_REC + R_SEED_LO], e[L_REC + R_SEED_HI], e[L_REC + R_EPISODE] + 1u));
 }
 
 // Serves the slow list: generates the world of the new episode in place (nine blocks each, looping
@@ -441,7 +416,7 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_reset_list(uint32_t* __restric
                                                             const Luts* __restrict__ luts, uint8_t* __restrict__ obs, Lists ls, int perlin,
                                                             const uint8_t* __restrict__ done, int n, int pool)
 {
-    __shared__ uint16_t s_lat[LAT_TOTAL];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
     __shared__ uint32_t s_env[L_ENV_DWORDS];
@@ -477,7 +452,7 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_reset_list(uint32_t* __restric
             wlo = pool_lo; whi = pool_hi; wenv = cx::POOL_ENV | ((cx::choice(sh.w[0], pool_size) + rank) % pool_size); wep = step_index;
         }
         worldgen_floor_block<GEN_THREADS, true>(maps + map_offset(env, ep), s_lat, s_layout, wlo, whi, wenv, wep, f,
-                                                reinterpret_cast<uint8_t*>(s_env + L_WB), reinterpret_cast<uint8_t*>(s_env + L_WI), 0, GEN_THREADS,
+                                                reinterpret_cast<uint8_t*>(s_env + L_WB), reinterpret_cast<uint8_t*>(s_env + L_WI),
                                                 perlin ? luts->perlin_cs : nullptr);
         if (f == 0) {
             publish_world(envs + (size_t)env * ENV_DWORDS, s_layout, lo, hi, ep, true, s_words);
@@ -519,17 +494,18 @@ __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__
 }
 
 // after an import: the world of the episode after the imported one, into the spare slot
-__global__ __launch_bounds__(GEN_THREADS) void kf_import_spare(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls, int first,
+template <bool PERLIN>
+__global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_import_spare(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls, int first,
                                                                 const uint32_t* __restrict__ perlin_cs, int pool)
 {
-    __shared__ uint16_t s_lat[LAT_TOTAL];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
     const uint32_t env = (uint32_t)first + blockIdx.x / FLOORS;
     const int f = blockIdx.x % FLOORS;
     uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
     const uint32_t ep = genv[R_EPISODE] + 1u, lo = genv[R_SEED_LO], hi = genv[R_SEED_HI];
-    worldgen_floor_block<GEN_THREADS, true>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, 0, GEN_THREADS, perlin_cs);
+    worldgen_floor_block<GEN_THREADS, PERLIN>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, perlin_cs);
     if (f == 0) publish_world(genv, s_layout, lo, hi, ep, false, s_words);
     if (threadIdx.x == 0) ls.tags[(size_t)env * NTAG + f] = make_uint2(pool ? 0u : ep, 0u);
 }
@@ -546,11 +522,11 @@ __device__ inline int theta_offset(int f)
 {
     return f == 0 ? 0 : LAT0_U16 + LATC_U16 * (f == 2 ? 0 : (f == 5 ? 1 : (f == 6 ? 2 : 3)));
 }
-__global__ __launch_bounds__(GEN_THREADS) void kf_mutate_noise(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts,
+__global__ __launch_bounds__(GEN_THREADS, 6) void kf_mutate_noise(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts,
                                                                 uint16_t* __restrict__ theta, int first, int f0, int nf, uint32_t k0, uint32_t k1,
                                                                 uint32_t round, uint32_t amplitude)
 {
-    __shared__ uint16_t s_lat[LAT_TOTAL];
+    __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ uint16_t s_theta[LAT_TOTAL];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
@@ -574,7 +550,7 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_mutate_noise(uint32_t* __restr
         s_theta[tid] = v;
     }
     __syncthreads();
-    worldgen_floor_block<GEN_THREADS, true>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, 0, GEN_THREADS,
+    worldgen_floor_block<GEN_THREADS, true>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr,
                                             luts->perlin_cs, noisy ? s_theta : nullptr);
     if (f == 0) publish_world(genv, s_layout, lo, hi, ep, true, s_words);
 }
@@ -958,15 +934,19 @@ int check_kernels(const craftax_config* cfg, std::string* err)
         ok = ok && (perlin ? fits("kf_rollout", (const void*)kf_rollout<false, true>, BLOCK) : fits("kf_rollout", (const void*)kf_rollout<false, false>, BLOCK));
         ok = ok && fits("kf_reset_list", (const void*)kf_reset_list<false>, GEN_THREADS) && fits("kf_observe", (const void*)kf_observe<false>, BLOCK);
     }
-    ok = ok && fits("kf_reset", (const void*)kf_reset, GEN_THREADS) && fits("kf_pixels", (const void*)kf_pixels, BLOCK);
+    ok = ok && fits("kf_drain", perlin ? (const void*)kf_drain<true> : (const void*)kf_drain<false>, GEN_THREADS);
+    ok = ok && fits("kf_reset", perlin ? (const void*)kf_reset<true> : (const void*)kf_reset<false>, GEN_THREADS) && fits("kf_pixels", (const void*)kf_pixels, BLOCK);
     return ok ? CRAFTAX_OK : CRAFTAX_E_CONFIG;
 }
 
 int reset(void* state, const craftax_config* cfg, int n, const uint64_t* seeds, void* stream, std::string* err)
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
-    hipLaunchKernelGGL(kf_reset, dim3((unsigned)n * 2 * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, seeds, q.ls, gradients(cfg, q), cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0,
-                       make_params(state, cfg, n).unlocks);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n * 2 * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, seeds, q.ls, gradients(cfg, q),
+                           cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0, make_params(state, cfg, n).unlocks);
+    };
+    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) go(kf_reset<true>); else go(kf_reset<false>);
     return check_launch("craftax_reset", err);
 }
 
@@ -1043,14 +1023,16 @@ int rollout(void* state, const craftax_config* cfg, int n, const int32_t* action
     const Params p = make_params(state, cfg, n);
     hipStream_t st = (hipStream_t)stream;
     uint8_t* o = static_cast<uint8_t*>(obs);
-    const int rb = FLOORS * n < REGEN_BLOCKS ? FLOORS * n : REGEN_BLOCKS;
-    const dim3 drain((unsigned)rb), grid((unsigned)((n + ENVS_PER_BLOCK - 1) / ENVS_PER_BLOCK));
-    // a launch of regeneration blocks only empties the lists of the step kernel and completes every spare world
+    const dim3 grid((unsigned)((n + ENVS_PER_BLOCK - 1) / ENVS_PER_BLOCK));
     const bool perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN;
-    launch_step<false>(64, false, perlin, drain, st, q, nullptr, nullptr, nullptr, nullptr, p, rb);
-    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, st, q.envs, q.maps, q.luts, actions, o, reward, done, q.ls.tags, p, steps); };
+    auto drain = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)std::min((long long)DRAIN_BLOCKS, (long long)FLOORS * n)), dim3(GEN_THREADS), 0, st, q.envs, q.maps, q.luts, q.ls); };
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, st, q.envs, q.maps, q.luts, actions, o, reward, done, q.ls, p, steps); };
+    // launches of regeneration blocks only: the worlds still owed by the step kernel, and afterwards
+    // those of the episodes that ended in the rollout
+    if (perlin) drain(kf_drain<true>); else drain(kf_drain<false>);
     if (cfg->obs_mode == CRAFTAX_OBS_SYM_F32) { if (perlin) go(kf_rollout<true, true>); else go(kf_rollout<true, false>); }
     else { if (perlin) go(kf_rollout<false, true>); else go(kf_rollout<false, false>); }
+    if (perlin) drain(kf_drain<true>); else drain(kf_drain<false>);
     return check_launch("craftax_rollout", err);
 }
 
@@ -1078,7 +1060,11 @@ int import_envs(void* state, const craftax_config* cfg, int n, int first, int co
     const Ptrs q = pointers(state, make_header(cfg, n));
     hipLaunchKernelGGL(kf_import, dim3(count), dim3(BLOCK), 0, (hipStream_t)stream, q.envs, q.maps, q.ls,
                        static_cast<const craftax_full_env_dump*>(dumps), first, make_params(state, cfg, n));
-    hipLaunchKernelGGL(kf_import_spare, dim3((unsigned)count * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.ls, first, gradients(cfg, q), cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0);
+    auto spare = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.ls, first, gradients(cfg, q),
+                           cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0);
+    };
+    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) spare(kf_import_spare<true>); else spare(kf_import_spare<false>);
     return check_launch("craftax_import_envs", err);
 }
 

@@ -2,155 +2,64 @@
 // Generation" of the paper's appendix lists the floors: overworld, dungeon, gnomish mines,
 // sewers, vault, troll mines, fire realm, ice realm, graveyard).  The paper does not print its
 // generators; here every cell of every floor is a pure integer function of (seed, env, episode,
-// floor, x, y): value-noise thresholds for the open floors, eight seeded rooms joined by
-// L-shaped corridors for the built ones.  One block of 576 threads per (environment, floor),
-// each thread owning a run of 4 cells, so that a reset is nine short blocks instead of one long one.
+// floor, x, y): noise thresholds for the open floors, eight seeded rooms joined by L-shaped
+// corridors for the built ones.  One block per (environment, floor), a thread owning a run of 8
+// cells, so that a reset is nine short blocks instead of one long one.
 #pragma once
 
+#include <type_traits>
+
 #include "full_common.hpp"
+#include "worldgen.hpp"
 
 namespace cf {
 
-constexpr int GEN_THREADS = CELLS / 4;                    // 576: one thread per run of 4 cells of a floor
+// A run of 8 cells: the draws of its cells are exactly one Philox block, it lies in one row and in one
+// column of lattice cells (of spacing 8 and of spacing 16), and both its maps are stored as 8 bytes.
+constexpr int RUN = 8, ROW_RUNS = W / RUN, RUNS = CELLS / RUN;   // 6 runs a row, 288 a floor
+constexpr int GEN_THREADS = 320;                          // five wavefronts: one pass over the 288 runs
 constexpr int LAT0_U16 = 2 * 16 + 4 * 49;                 // overworld lattices: two 4x4 (spacing 16), four 7x7 (spacing 8)
 constexpr int LAT0_BLOCKS = (LAT0_U16 + 7) / 8;           // 29
 constexpr int LATC_U16 = 2 * 49, LATC_BLOCKS = (LATC_U16 + 7) / 8;   // cave floors: two 7x7 lattices, 13 blocks
-constexpr int LAT_STRIDE0 = LAT0_BLOCKS * 8, LAT_STRIDEC = LATC_BLOCKS * 8;
-constexpr int LAT_TOTAL = LAT_STRIDE0;                    // a block generates one floor: the largest lattice set
+constexpr int LAT_TOTAL = LAT0_BLOCKS * 8;                // a block generates one floor: the largest lattice set
+
+// The lattices lie in LDS as in the Classic generator: one dword per point, for value noise the point
+// and, in the high half, the point below it (a column is then one dot product), for Perlin noise its
+// gradient.  4x4 lattices first, then 7x7; the gaps in front of both groups take the high halves
+// that the first row of a group leaves above itself, between lattices of one group they fall into the
+// last row of the previous one, whose high halves nobody reads.
+constexpr int WIDE0 = 2 * 16;                             // numbers of the overworld's 4x4 lattices come first
+constexpr int LAT_AT16 = 4, LAT_AT8 = 4 + WIDE0 + 7, LATC_AT8 = 7;
+constexpr int LAT_WORDS = LAT_AT8 + (LAT_TOTAL - WIDE0) + 1;
 
 struct Room { int x, y, w, h, cx, cy; };
 struct GenLayout {
     Room room[3][8];          // dungeon (floor 1), sewers (3), vault (4)
     int up[FLOORS][2], down[FLOORS][2];
     uint32_t perm;            // potion colour -> effect, 6 x 3 bits
-    // The built floor being generated, row by row (bit x = column x), see dungeon_row_masks: cells
-    // inside rooms 0..3 and 4..7, cells on corridors 0..3 and 4..6, chest cells; and the five single
-    // cells of a floor as x | y << 8: fountain, the two enchantment tables, ladder up, ladder down
-    // (0xFFFF: this floor has none).
+    // The floor being generated, row by row (bit x = column x).  Built floors (dungeon_row_mask): cells
+    // inside rooms 0..3 and 4..7, cells on corridors 0..3 and 4..6, chest cells.  Caves
+    // (cave_row_mask): the cells that are open whatever the noise says.  And the single cells of
+    // a floor as x | y << 8: fountain, the two enchantment tables, ladder up, ladder down (0xFFFF:
+    // this floor has none).
     uint64_t row_mask[5][W];
     uint32_t spot[5];
 };
 
-__device__ inline int cave_index(int f) { return f == 2 ? 0 : (f == 5 ? 1 : (f == 6 ? 2 : 3)); }
 __device__ inline int dungeon_index(int f) { return f == 1 ? 0 : (f == 3 ? 1 : 2); }
 __device__ inline bool is_dungeon(int f) { return f == 1 || f == 3 || f == 4; }
 __device__ inline bool is_cave(int f) { return f == 2 || f == 5 || f == 6 || f == 7; }
 
-__device__ inline bool on_corridor(int x, int y, int x0, int y0, int x1, int y1)
-{
-    // horizontal along y0 from x0 to x1, then vertical along x1 from y0 to y1
-    const bool h = y == y0 && x >= min(x0, x1) && x <= max(x0, x1);
-    const bool v = x == x1 && y >= min(y0, y1) && y <= max(y0, y1);
-    return h | v;
-}
+constexpr int START_BIAS_R = cx::START_BIAS_R, START_BIAS = cx::START_BIAS, START_CLEAR = cx::START_CLEAR;
+static_assert((int)B_GRASS == cx::BK_GRASS && (int)B_WATER == cx::BK_WATER && (int)B_STONE == cx::BK_STONE && (int)B_TREE == cx::BK_TREE &&
+              (int)B_PATH == cx::BK_PATH && (int)B_COAL == cx::BK_COAL && (int)B_IRON == cx::BK_IRON && (int)B_DIAMOND == cx::BK_DIAMOND &&
+              (int)B_SAND == cx::BK_SAND && (int)B_LAVA == cx::BK_LAVA, "the overworld is the Classic rule (cx::classify)");
 
-// Noise fields of a run of cells in one row: the two lattice rows are blended once per lattice
-// column (vertical weight), then every cell blends two columns (horizontal weight).  The integer
-// result equals the row-first bilinear formula ((a(256-wx)+b wx)(256-wy) + (c(256-wx)+d wx) wy) >> 16
-// because nothing is rounded before the final shift.  The callers'
-// runs of 4 cells start at a multiple of 4, so a run lies inside one lattice cell.
-__device__ inline uint32_t column(const uint16_t* lat, int width, int ix, int iy, uint32_t wy)
-{
-    return (uint32_t)lat[CX_IDX(iy * width + ix, width * width)] * (256u - wy) + (uint32_t)lat[CX_IDX((iy + 1) * width + ix, width * width)] * wy;
-}
-__device__ inline uint32_t across(uint32_t left, uint32_t right, uint32_t wx)
-{
-    return (left * (256u - wx) + right * wx) >> 16;
-}
-
-constexpr int PERLIN_GAIN = cx::PERLIN_GAIN;
-template <int S>
-__device__ inline int64_t perlin_fade(int k)
-{
-    const int F = k * k * k * (6 * k * k - 15 * k * S + 10 * S * S);
-    return S == 16 ? (int64_t)((F + 8) >> 4) : (int64_t)(2 * F);
-}
-__device__ inline int64_t perlin_blend(int64_t p, int64_t q, int64_t w) { return p + (((q - p) * w) >> 16); }
-template <int S>
-__device__ inline uint32_t perlin(const uint16_t* lat, int width, const uint32_t* __restrict__ cs, int x, int y)
-{
-    static_assert(S == 8 || S == 16, "lattice spacing");
-    constexpr int SHIFT = S == 16 ? 4 : 3;
-    const int ix = x >> SHIFT, iy = y >> SHIFT, kx = x & (S - 1), ky = y & (S - 1);
-    int64_t dot[2][2];
-#pragma unroll
-    for (int cy = 0; cy < 2; ++cy)
-#pragma unroll
-        for (int cx = 0; cx < 2; ++cx) {
-            const uint32_t g = cs[lat[CX_IDX((iy + cy) * width + ix + cx, width * width)] >> 6];
-            dot[cy][cx] = (int64_t)((int)(int16_t)(g & 0xFFFFu) * (kx - cx * S) + (int)(int16_t)(g >> 16) * (ky - cy * S));
-        }
-    const int64_t wx = perlin_fade<S>(kx), wy = perlin_fade<S>(ky);
-    const int64_t n = perlin_blend(perlin_blend(dot[0][0], dot[0][1], wx), perlin_blend(dot[1][0], dot[1][1], wx), wy);
-    const int64_t v = 32768 + ((n * PERLIN_GAIN) >> (10 + SHIFT));
-    return (uint32_t)(v < 0 ? 0 : (v > 65535 ? 65535 : v));
-}
-
-struct Field8 { uint32_t l, r; };
-__device__ inline Field8 field8(const uint16_t* lat, int x0, int y)
-{
-    const uint32_t wy = cx::smooth8(y & 7);
-    return { column(lat, 7, x0 >> 3, y >> 3, wy), column(lat, 7, (x0 >> 3) + 1, y >> 3, wy) };
-}
-__device__ inline Field8 field16(const uint16_t* lat, int x0, int y)
-{
-    const uint32_t wy = cx::smooth16(y & 15);
-    return { column(lat, 4, x0 >> 4, y >> 4, wy), column(lat, 4, (x0 >> 4) + 1, y >> 4, wy) };
-}
-__device__ inline uint32_t at8(const Field8& f, int x) { return across(f.l, f.r, cx::smooth8(x & 7)); }
-__device__ inline uint32_t at16(const Field8& f, int x) { return across(f.l, f.r, cx::smooth16(x & 15)); }
-
-// Cell functions, one per kind of floor: block id | item << 8.
-__device__ inline int classify_overworld(const GenLayout& L, int Wn, int Mn, int Cn, int Fn, int x, int y, int u)
-{
-    const int d = max(iabs(x - W / 2), iabs(y - W / 2));
-    if (d < 10) { const int bias = (10 - d) * 2500; Wn = max(0, Wn - bias); Mn = max(0, Mn - bias); }
-    int b;
-    if (d <= 2) b = B_GRASS;
-    else if (Mn > 39500) {
-        if (Cn > 43000 && Mn > 41000) b = B_PATH;
-        else if (iabs(Cn - 30000) < 1300) b = B_PATH;
-        else if (Mn > 43000 && Fn > 44000) b = B_LAVA;
-        else if (Mn > 42000 && u < 500) b = B_DIAMOND;
-        else if (Fn < 33000 && u >= 500 && u < 3000) b = B_IRON;
-        else if (u >= 3000 && u < 8000) b = B_COAL;
-        else b = B_STONE;
-    } else if (Wn > 39500) b = B_WATER;
-    else if (Wn > 37800) b = B_SAND;
-    else if (Fn > 33500 && u < 26000) b = B_TREE;
-    else if (u < 1300) b = B_TREE;
-    else b = B_GRASS;
-    if (x == L.down[0][0] && y == L.down[0][1]) return B_PATH | (IT_LADDER_DOWN << 8);
-    return b;
-}
-// The cell of a built floor written out test by test.  The generator uses cell_dungeon_masked below, which
-// takes `inside`, `corridor` and the chest test from per-row bit masks; this is what those masks mean.
-__device__ inline int cell_dungeon(const GenLayout& L, int f, int x, int y, int u)
-{
-    const Room* R = L.room[dungeon_index(f)];
-    bool inside = false;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) inside |= (unsigned)(x - R[i].x) < (unsigned)R[i].w && (unsigned)(y - R[i].y) < (unsigned)R[i].h;
-    int b = f == 3 ? B_WALL_MOSS : B_WALL;
-    if (inside) b = (f == 3 && u < 12000) ? B_WATER : B_PATH;
-#pragma unroll
-    for (int i = 1; i <= 6; ++i) if (x == R[i].cx + 1 && y == R[i].cy + 1) b = B_CHEST;
-    if (f == 1 && x == R[2].cx - 1 && y == R[2].cy - 1) b = B_FOUNTAIN;
-    if (f == 4 && x == R[3].cx - 1 && y == R[3].cy - 1) b = B_ENCH_FIRE;
-    if (f == 4 && x == R[4].cx - 1 && y == R[4].cy - 1) b = B_ENCH_ICE;
-    bool corridor = false;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) corridor |= on_corridor(x, y, R[i].cx, R[i].cy, R[i + 1].cx, R[i + 1].cy);
-    if (corridor) b = B_PATH;       // corridors last: room centre 0 (ladder up) always reaches room centre 7 (ladder down)
-    int it = IT_NONE;
-    if (x == R[0].cx && y == R[0].cy) { b = B_PATH; it = IT_LADDER_UP; }
-    if (x == R[7].cx && y == R[7].cy) { b = B_PATH; it = IT_LADDER_DOWN_BLOCKED; }
-    return b | (it << 8);
-}
-// A built floor as bit masks per row, so that a cell costs a few shifts and tests instead of eight
-// room tests, seven corridor tests and nine single-cell tests.  Part p of row y (five parts, so
-// that 240 threads share the work): rooms 0..3, rooms 4..7 (`inside` of cell_dungeon), corridors
-// 0..3, corridors 4..6 (`corridor`), chests.  The few single cells go to L.spot.
+// A built floor as bit masks per row, so that a run costs a few shifts and byte masks instead of eight
+// room tests, seven corridor tests and nine single-cell tests per cell.  Part p of row y (five parts,
+// so that 240 threads share the work): rooms 0..3, rooms 4..7, corridors 0..3, corridors 4..6
+// (corridor i: along row cy of room i from its centre to the centre column of room i + 1, then along
+// that column), chests (one right and below the centre of rooms 1..6).  The single cells go to L.spot.
 constexpr int M_ROOMS_A = 0, M_ROOMS_B = 1, M_PATH_A = 2, M_PATH_B = 3, M_CHEST = 4, MASK_PARTS = 5;
 constexpr int SPOT_FOUNTAIN = 0, SPOT_FIRE = 1, SPOT_ICE = 2, SPOT_UP = 3, SPOT_DOWN = 4;
 __device__ inline void dungeon_row_mask(GenLayout& L, int f, int y, int part)
@@ -192,67 +101,9 @@ __device__ inline void dungeon_spot(GenLayout& L, int f, int k)
     if (k == SPOT_DOWN) v = at(R[7].cx, R[7].cy);
     L.spot[k] = v;
 }
-// cell_dungeon from the masks of its row (shifted so that bit 0 is this cell) and the single cells:
-// the same tests in the same order of precedence.
-__device__ inline int cell_dungeon_masked(const GenLayout& L, int f, int x, int y, int u, bool inside, bool corridor, bool chest)
-{
-    const uint32_t here = (uint32_t)x | ((uint32_t)y << 8);
-    int b = f == 3 ? B_WALL_MOSS : B_WALL;
-    if (inside) b = (f == 3 && u < 12000) ? B_WATER : B_PATH;
-    if (chest) b = B_CHEST;
-    if (here == L.spot[SPOT_FOUNTAIN]) b = B_FOUNTAIN;
-    if (here == L.spot[SPOT_FIRE]) b = B_ENCH_FIRE;
-    if (here == L.spot[SPOT_ICE]) b = B_ENCH_ICE;
-    if (corridor) b = B_PATH;
-    int it = IT_NONE;
-    if (here == L.spot[SPOT_UP]) { b = B_PATH; it = IT_LADDER_UP; }
-    if (here == L.spot[SPOT_DOWN]) { b = B_PATH; it = IT_LADDER_DOWN_BLOCKED; }
-    return b | (it << 8);
-}
-__device__ inline int cell_graveyard(int x, int y)
-{
-    int b = (x == 0 || y == 0 || x == W - 1 || y == W - 1) ? B_WALL : B_PATH;
-    if ((x & 7) == 0 && x >= 8 && x <= 40 && (y == 12 || y == 24 || y == 36)) b = B_GRAVE1 + ((x - 8) / 8 + (y - 12) / 12) % 3;
-    if (x == BOSS_X && y == BOSS_Y) b = B_NECRO_VULN;
-    if (x == 24 && y == 42) return B_PATH | (IT_LADDER_UP << 8);
-    return b;
-}
-// The cell of a cave floor written out test by test.  The generator uses classify_cave_masked below, which takes
-// the clearings and the corridor from a per-row bit mask; this is what that mask means.
-__device__ inline int classify_cave(const GenLayout& L, int f, int Cn, int Fn, int x, int y, int u)
-{
-    const int open = f == 6 ? B_FIRE_GRASS : (f == 7 ? B_ICE_GRASS : B_PATH);
-    int b;
-    if (Cn > 31000) {
-        b = open;
-        if (f == 2 && u < 1500) b = B_STALAGMITE;
-        if (f == 5 && Fn > 44000) b = B_WATER;
-        if (f == 6) { if (Fn > 43000) b = B_LAVA; else if (u < 3000) b = B_FIRE_TREE; }
-        if (f == 7) { if (Fn > 43000) b = B_WATER; else if (u < 3000) b = B_ICE_SHRUB; }
-    } else {
-        b = B_STONE;
-        if (f == 2 || f == 5) {
-            if (u < 5000) b = B_COAL;
-            else if (u < 7500) b = B_IRON;
-            else if (u < 8000) b = B_DIAMOND;
-            else if (u < (f == 2 ? 8600 : 9000)) b = B_SAPPHIRE;
-            else if (u < (f == 2 ? 9200 : 10000)) b = B_RUBY;
-        } else if (f == 6) { if (u < 2500) b = B_RUBY; else if (u < 6000) b = B_COAL; }
-        else { if (u < 2500) b = B_SAPPHIRE; else if (u < 5000) b = B_DIAMOND; }
-    }
-    const int ux = L.up[f][0], uy = L.up[f][1], dx = L.down[f][0], dy = L.down[f][1];
-    if (max(iabs(x - ux), iabs(y - uy)) <= 1 || max(iabs(x - dx), iabs(y - dy)) <= 1) b = open;
-    if (on_corridor(x, y, ux, uy, dx, dy)) b = open;      // the two ladders are always connected
-    int it = IT_NONE;
-    if (x == ux && y == uy) { b = B_PATH; it = IT_LADDER_UP; }
-    if (x == dx && y == dy) { b = B_PATH; it = IT_LADDER_DOWN_BLOCKED; }
-    return b | (it << 8);
-}
-
-// Row y of a cave floor as one bit mask (L.row_mask[M_CAVE_OPEN]): the cells classify_cave opens whatever
-// the noise says, i.e. the 3 x 3 clearings around the two ladders and the L-shaped corridor between
-// them; the ladders themselves go to L.spot.  classify_cave_masked is classify_cave with those
-// tests taken from the mask: the same rules in the same order.
+// Row y of a cave floor as one bit mask (L.row_mask[M_CAVE_OPEN]): the cells that are open whatever the
+// noise says, i.e. the 3 x 3 clearings around the two ladders and the L-shaped corridor between
+// them (the two ladders are always connected); the ladders themselves go to L.spot.
 constexpr int M_CAVE_OPEN = 0;
 __device__ inline void cave_row_mask(GenLayout& L, int f, int y)
 {
@@ -261,41 +112,13 @@ __device__ inline void cave_row_mask(GenLayout& L, int f, int y)
     uint64_t m = 0ull;
     if (iabs(y - uy) <= 1) m |= span(ux - 1, ux + 1);
     if (iabs(y - dy) <= 1) m |= span(dx - 1, dx + 1);
-    if (y == uy) m |= span(min(ux, dx), max(ux, dx));                 // on_corridor: along row uy from ux to dx,
+    if (y == uy) m |= span(min(ux, dx), max(ux, dx));                 // along row uy from ux to dx,
     if (y >= min(uy, dy) && y <= max(uy, dy)) m |= 1ull << dx;        // then along column dx from uy to dy
     L.row_mask[M_CAVE_OPEN][CX_IDX(y, W)] = m;
     if (y == 0) {
         L.spot[SPOT_UP] = (uint32_t)ux | ((uint32_t)uy << 8);
         L.spot[SPOT_DOWN] = (uint32_t)dx | ((uint32_t)dy << 8);
     }
-}
-__device__ inline int classify_cave_masked(const GenLayout& L, int f, int Cn, int Fn, int x, int y, int u, bool opened)
-{
-    const int open = f == 6 ? B_FIRE_GRASS : (f == 7 ? B_ICE_GRASS : B_PATH);
-    int b;
-    if (Cn > 31000) {
-        b = open;
-        if (f == 2 && u < 1500) b = B_STALAGMITE;
-        if (f == 5 && Fn > 44000) b = B_WATER;
-        if (f == 6) { if (Fn > 43000) b = B_LAVA; else if (u < 3000) b = B_FIRE_TREE; }
-        if (f == 7) { if (Fn > 43000) b = B_WATER; else if (u < 3000) b = B_ICE_SHRUB; }
-    } else {
-        b = B_STONE;
-        if (f == 2 || f == 5) {
-            if (u < 5000) b = B_COAL;
-            else if (u < 7500) b = B_IRON;
-            else if (u < 8000) b = B_DIAMOND;
-            else if (u < (f == 2 ? 8600 : 9000)) b = B_SAPPHIRE;
-            else if (u < (f == 2 ? 9200 : 10000)) b = B_RUBY;
-        } else if (f == 6) { if (u < 2500) b = B_RUBY; else if (u < 6000) b = B_COAL; }
-        else { if (u < 2500) b = B_SAPPHIRE; else if (u < 5000) b = B_DIAMOND; }
-    }
-    if (opened) b = open;
-    const uint32_t here = (uint32_t)x | ((uint32_t)y << 8);
-    int it = IT_NONE;
-    if (here == L.spot[SPOT_UP]) { b = B_PATH; it = IT_LADDER_UP; }
-    if (here == L.spot[SPOT_DOWN]) { b = B_PATH; it = IT_LADDER_DOWN_BLOCKED; }
-    return b | (it << 8);
 }
 
 // World-generation draws: counter (env, stream, episode, WORLDGEN | block); stream = floor*4 +
@@ -305,11 +128,6 @@ __device__ inline U4 wg_block(uint32_t lo, uint32_t hi, uint32_t env, uint32_t e
     return philox4x32_10(env, stream, episode, (cx::DOM_WORLDGEN << 16) | block, lo, hi);
 }
 
-__device__ inline void put_lattice(uint16_t* dst, const U4& r)
-{
-#pragma unroll
-    for (int w = 0; w < 4; ++w) { dst[2 * w] = (uint16_t)(r.w[w] & 0xFFFFu); dst[2 * w + 1] = (uint16_t)(r.w[w] >> 16); }
-}
 __device__ inline void make_room(GenLayout& L, int f, int i, const U4& r)
 {
     Room R;
@@ -329,29 +147,124 @@ __device__ inline void make_cave_ladders(GenLayout& L, int f, const U4& r)
     L.down[f][0] = 32 + (int)choice(r.w[2], 6); L.down[f][1] = 32 + (int)choice(r.w[3], 6);
 }
 
-// Generates floor f of one environment with the NT threads of the calling block: run t (of 576)
-// is the 4 cells [4t, 4t+4) of the floor (row t/12).  The block of floor 0 also derives the
+// The eight lattice numbers of Philox block `block`: number i of the set goes to dword at16 + i (i <
+// wide: 4x4 lattices) or at8 + i - wide (7x7 lattices).
+template <bool CAN_PERLIN>
+__device__ inline void put_lattice(uint32_t* s_lat, int at16, int at8, int wide, int block, const U4& r, const uint32_t* __restrict__ perlin_cs,
+                                   const uint16_t* theta_f)
+{
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int i = block * 8 + j;
+        uint32_t v = (j & 1) ? (r.w[j >> 1] >> 16) : (r.w[j >> 1] & 0xFFFFu);
+        const int at = i < wide ? at16 + i : at8 + i - wide, above = at - (i < wide ? 4 : 7);
+        if (CAN_PERLIN && perlin_cs != nullptr) {
+            if (theta_f != nullptr) v = (v + ((theta_f[i] & 1023u) << 6)) & 0xFFFFu;
+            s_lat[CX_IDX(at, LAT_WORDS)] = perlin_cs[v >> 6];
+        } else {
+            uint16_t* half = reinterpret_cast<uint16_t*>(s_lat);
+            half[CX_IDX(2 * at, 2 * LAT_WORDS)] = (uint16_t)v;
+            half[CX_IDX(2 * above + 1, 2 * LAT_WORDS)] = (uint16_t)v;
+        }
+    }
+}
+
+// Eight cells, one byte each: cells 0..3 in x, 4..7 in y.
+__device__ inline uint2 all_cells(uint32_t v) { return make_uint2(v * 0x01010101u, v * 0x01010101u); }
+// the bytes whose bit of `where` (bit 0 = cell 0) is set become v
+__device__ inline uint2 cells_where(uint2 c, uint32_t where, uint32_t v)
+{
+    auto mask = [](uint32_t nibble) { const uint32_t ones = (nibble * 0x00204081u) & 0x01010101u; return (ones << 8) - ones; };
+    const uint32_t m0 = mask(where & 15u), m1 = mask((where >> 4) & 15u);
+    return make_uint2((c.x & ~m0) | (v * 0x01010101u & m0), (c.y & ~m1) | (v * 0x01010101u & m1));
+}
+// the single cell `spot` (x | y << 8), if it lies in the run whose first cell is (x0, y)
+__device__ inline bool spot_in_run(uint32_t spot, int x0, int y) { return (spot & 0xFFF8u) == ((uint32_t)x0 | ((uint32_t)y << 8)); }
+
+// What a cave floor makes of a cell's fields and draw u.  Open cells (cave field above 31000): a plant
+// where u < plant_below, a liquid where the second field is above its threshold, the floor's ground
+// elsewhere; rock: ore i where u < below_i for the first such i, stone elsewhere.
+struct CaveRule { uint32_t open, plant_below, plant, liquid_above, liquid, below0, below1, below2, below3, below4, ore0, ore1; };
+__device__ inline CaveRule cave_rule(int f)
+{
+    const bool mines = f == 2 || f == 5;
+    CaveRule c;
+    c.open = f == 6 ? B_FIRE_GRASS : (f == 7 ? B_ICE_GRASS : B_PATH);
+    c.plant_below = f == 2 ? 1500u : (f == 5 ? 0u : 3000u);
+    c.plant = f == 2 ? B_STALAGMITE : (f == 6 ? B_FIRE_TREE : B_ICE_SHRUB);
+    c.liquid_above = f == 2 ? 65535u : (f == 5 ? 44000u : 43000u);
+    c.liquid = f == 6 ? B_LAVA : B_WATER;
+    c.ore0 = mines ? B_COAL : (f == 6 ? B_RUBY : B_SAPPHIRE);
+    c.ore1 = mines ? B_IRON : (f == 6 ? B_COAL : B_DIAMOND);
+    c.below0 = mines ? 5000u : 2500u;
+    c.below1 = mines ? 7500u : (f == 6 ? 6000u : 5000u);
+    c.below2 = mines ? 8000u : 0u;                          // diamond,
+    c.below3 = f == 2 ? 8600u : (f == 5 ? 9000u : 0u);      // sapphire,
+    c.below4 = f == 2 ? 9200u : (f == 5 ? 10000u : 0u);     // ruby
+    return c;
+}
+// C, F: fields as cx::above takes them; u: the draw in the upper half
+template <bool PERLIN>
+__device__ __forceinline__ uint32_t classify_cave(const CaveRule& k, uint32_t C, uint32_t F, uint32_t u)
+{
+    uint32_t in = k.open, rock = B_STONE;
+    auto set = [](uint32_t& b, bool where, uint32_t block) { b = where ? block : b; };
+    set(in, u < (k.plant_below << 16), k.plant);
+    // (a threshold of 65535 is never exceeded)
+    const bool liquid = PERLIN ? (int)F >= (k.liquid_above == 65535u ? 0x7FFFFFFF : k.liquid_above == 44000u ? cx::perlin_above(44000) : cx::perlin_above(43000))
+                               : F > ((k.liquid_above << 16) | 0xFFFFu);
+    set(in, liquid, k.liquid);
+    set(rock, u < (k.below4 << 16), B_RUBY);
+    set(rock, u < (k.below3 << 16), B_SAPPHIRE);
+    set(rock, u < (k.below2 << 16), B_DIAMOND);
+    set(rock, u < (k.below1 << 16), k.ore1);
+    set(rock, u < (k.below0 << 16), k.ore0);
+    return cx::above<PERLIN>(C, 31000) ? in : rock;
+}
+
+// The lattice columns left and right of a run in row y, blended vertically (see cx::across).
+struct Ends { uint32_t l, r; };
+__device__ inline Ends ends_at(const uint32_t* lat, int width, int ix, int iy, uint32_t weights)
+{
+    const uint32_t* c = lat + CX_IDX(iy * width + ix, width * width - 1);
+    return { cx::dot16u(c[0], weights), cx::dot16u(c[1], weights) };
+}
+
+// Generates floor f of one environment with the NT threads of the calling block (NT = 64: with the
+// calling wavefront, whatever the other wavefronts of its block do): run t (of 288)
+// is the 8 cells [8t, 8t+8) of the floor (row t/6).  The block of floor 0 also derives the
 // ladders of every floor and the potion permutation (whole_layout), which the fresh record
 // needs, and may drop the cells around the start position into an LDS window (start_wb /
 // start_wi, 11 x 16 bytes each) for the first observation.  maps: this environment's 41472
-// bytes.  s_lat, L: LDS scratch.  Ends with a block barrier.
-// first_run, runs: the part of the floor this call generates (a block of fewer than `runs` threads
-// takes several passes).
+// bytes.  s_lat (LAT_WORDS dwords), L: LDS scratch.  All arguments are the same for the whole block.
+// Ends with a barrier of those threads.
 // perlin_cs (with CAN_PERLIN): the gradient table; the fields of the overworld and of the caves are
 // then Perlin noise over the same lattices (appendix "World Generation") instead of value noise.
 // A kernel instantiated without CAN_PERLIN carries no code for it.
 // theta_f (with CAN_PERLIN; LDS, LAT_TOTAL entries, the same for the whole block): angle offsets in
 // 1024ths of a turn added to the upper ten bits of this floor's lattice numbers, the level of the
 // noise mutation (section "Craftax-1B: UED").
-template <int NT = GEN_THREADS, bool CAN_PERLIN = false>
-__device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps, uint16_t* s_lat, GenLayout& L, uint32_t lo, uint32_t hi,
+// Bound by vector instruction issue, like the Classic generator, and written with the same 24-bit and
+// dot-product arithmetic (worldgen.hpp).  A run of 8 cells instead of 4 uses all of its Philox block,
+// and the built floors are byte masks over whole runs.  Measured against runs of 4 cells in 32- and
+// 64-bit products: craftax_reset of 4,096 environments (8,192 worlds, 340 MB) 529 -> 295 us, with Perlin
+// noise 1081 -> 554 us.
+// LOOPED: the call stands in a loop over worlds; what a thread derives from its index is then derived
+// anew in every call instead of being kept (and spilled) across the loop.
+template <int NT = GEN_THREADS, bool CAN_PERLIN = false, bool LOOPED = false>
+__device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps, uint32_t* s_lat, GenLayout& L, uint32_t lo, uint32_t hi,
                                             uint32_t env, uint32_t episode, int f, uint8_t* start_wb = nullptr,
-                                            uint8_t* start_wi = nullptr, int first_run = 0, int runs = GEN_THREADS,
-                                            const uint32_t* __restrict__ perlin_cs = nullptr, const uint16_t* theta_f = nullptr)
+                                            uint8_t* start_wi = nullptr, const uint32_t* __restrict__ perlin_cs = nullptr,
+                                            const uint16_t* theta_f = nullptr)
 {
     const bool use_perlin = CAN_PERLIN && perlin_cs != nullptr;
     static_assert(NT >= 64, "the layout phase uses the first wavefront");
-    const int tid0 = threadIdx.x;
+    // uniform arguments that come from memory: in scalar registers, with the key schedule and the
+    // first products of every Philox block
+    lo = uniu(lo); hi = uniu(hi); env = uniu(env); episode = uniu(episode); f = uni(f);
+    int tid0 = NT == 64 ? (int)(threadIdx.x & 63u) : (int)threadIdx.x;
+    if (LOOPED) asm volatile("" : "+v"(tid0));
+    auto barrier = []() { if (NT == 64) wave_sync(); else __syncthreads(); };
     // Layout phase, all in the first wavefront and with one Philox call for the whole wave: every
     // lane picks the (stream, block) of its role, then the roles unpack their words.
     if (tid0 < 64) {
@@ -367,7 +280,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
             else if (tid >= 58) { stream = 63u; block = tid == 59 ? 1u : 0u; }
             const U4 r = wg_block(lo, hi, env, episode, stream, block);
             const uint32_t fifth = (uint32_t)__shfl((int)r.w[0], 59);
-            if (tid < LAT0_BLOCKS) put_lattice(s_lat + tid * 8, r);
+            if (tid < LAT0_BLOCKS) put_lattice<CAN_PERLIN>(s_lat, LAT_AT16, LAT_AT8, WIDE0, tid, r, perlin_cs, theta_f);
             else if (tid < 53) make_room(L, ff, (tid - 29) & 7, r);
             else if (tid < 57) make_cave_ladders(L, ff, r);
             else if (tid == 57) {
@@ -375,6 +288,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
                 const int dy = (int)choice(r.w[1], 13) - 6;
                 if (max(iabs(dx), iabs(dy)) < 3) dx = 3;
                 L.up[0][0] = 0; L.up[0][1] = 0; L.down[0][0] = W / 2 + dx; L.down[0][1] = W / 2 + dy;
+                L.spot[SPOT_DOWN] = (uint32_t)(W / 2 + dx) | ((uint32_t)(W / 2 + dy) << 8);
                 L.up[8][0] = 24; L.up[8][1] = 42; L.down[8][0] = 0; L.down[8][1] = 0;
             } else if (tid == 58) {
                 // a fresh colour -> effect permutation per episode
@@ -397,101 +311,154 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
             // lanes 0..12 lattice blocks, lane 13 the ladders
             if (tid <= LATC_BLOCKS) {
                 const U4 r = wg_block(lo, hi, env, episode, (uint32_t)f * 4u + (tid == LATC_BLOCKS ? 2u : 0u), tid == LATC_BLOCKS ? 0u : (uint32_t)tid);
-                if (tid < LATC_BLOCKS) put_lattice(s_lat + tid * 8, r);
+                if (tid < LATC_BLOCKS) put_lattice<CAN_PERLIN>(s_lat, 0, LATC_AT8, 0, tid, r, perlin_cs, theta_f);
                 else make_cave_ladders(L, f, r);
             }
         }
     }
-    __syncthreads();
+    barrier();
     if (is_dungeon(f)) {                       // the same floor for the whole block
         for (int i = tid0; i < MASK_PARTS * W; i += NT) dungeon_row_mask(L, f, i % W, i / W);
         if (tid0 < 5) dungeon_spot(L, f, tid0);
-        __syncthreads();
+        barrier();
     } else if (is_cave(f)) {
         if (tid0 < W) cave_row_mask(L, f, tid0);
-        __syncthreads();
+        barrier();
     }
-    if (CAN_PERLIN && theta_f != nullptr) {
-        for (int i = tid0; i < LAT_TOTAL; i += NT) s_lat[i] = (uint16_t)(s_lat[i] + ((theta_f[i] & 1023u) << 6));
-        __syncthreads();
-    }
-    // runs of 4 cells, one per thread and pass
+    // runs of 8 cells, one per thread and pass
 #pragma unroll 1
-    for (int tid = first_run + tid0; tid < first_run + runs; tid += NT) {
-    const int y = tid / 12, x = (tid - y * 12) * 4;
-    const bool needs_u = !(f == 1 || f == 4 || f == 8);
-    uint32_t rw0 = 0u, rw1 = 0u;
-    if (needs_u) {
-        // per-cell draws: Philox block (cell / 8) holds eight u16, this thread uses one half of it
-        const U4 r = wg_block(lo, hi, env, episode, (uint32_t)f * 4u + 1u, (uint32_t)(tid >> 1));
-        rw0 = (tid & 1) ? r.w[2] : r.w[0];
-        rw1 = (tid & 1) ? r.w[3] : r.w[1];
-    }
-    const uint32_t light = lit_floor(f) ? (uint32_t)MAX_LIGHT << 3 : 0u;
-    uint32_t pb = 0u, pi = 0u;
-    auto put = [&](int j, int cell) {
-        pb |= (uint32_t)(cell & 0xFF) << (8 * j);
-        pi |= ((uint32_t)(cell >> 8) | light) << (8 * j);
+    for (int run = tid0; run < RUNS; run += NT) {
+    const int y = run / ROW_RUNS, strip = run - y * ROW_RUNS, x0 = strip * RUN;
+    U4 r = { { 0u, 0u, 0u, 0u } };                          // the run's draws: eight u16, one per cell
+    if (!(f == 1 || f == 4 || f == 8)) r = wg_block(lo, hi, env, episode, (uint32_t)f * 4u + 1u, (uint32_t)run);
+    uint2 blocks = make_uint2(0u, 0u), items = all_cells(lit_floor(f) ? (uint32_t)MAX_LIGHT << 3 : 0u);
+    // single cells, the last one placed counts (the two ladders of a built floor may fall on one cell)
+    auto place = [&](uint32_t spot, uint32_t block, uint32_t item) {
+        if (!spot_in_run(spot, x0, y)) return;
+        const uint32_t j = spot & 7u, sh = 8u * (j & 3u), keep = ~(0xFFu << sh), light = ~(7u << sh);
+        if (j < 4u) { blocks.x = (blocks.x & keep) | (block << sh); items.x = (items.x & light) | (item << sh); }
+        else { blocks.y = (blocks.y & keep) | (block << sh); items.y = (items.y & light) | (item << sh); }
     };
-    auto draw = [&](int j) { const uint32_t rw = j < 2 ? rw0 : rw1; return (int)((j & 1) ? (rw >> 16) : (rw & 0xFFFFu)); };
+    // The run two cells at a time, a loop that is not unrolled: less code, and few enough registers for
+    // the step kernels and for six to eight wavefronts per SIMD in the others (four cells at a time:
+    // UED turn over 1,000 Perlin levels 326 us, two: 302).  cell(j, u): block of cell j, u = its draw in
+    // the upper half.
+    auto cells = [&](auto&& cell) {
+#pragma unroll 1
+        for (int j = 0; j < RUN; j += 2) {
+            const uint32_t two = (uint32_t)cell(j, r.w[0] << 16) | ((uint32_t)cell(j + 1, r.w[0]) << 8);
+            blocks.x = __builtin_amdgcn_alignbit(blocks.y, blocks.x, 16);
+            blocks.y = (blocks.y >> 16) | (two << 16);
+            r.w[0] = r.w[1]; r.w[1] = r.w[2]; r.w[2] = r.w[3];
+        }
+    };
     // the floor is the same for the whole block: one kind of cell function per block
-    // (the cells of a run one after the other: side by side they are no faster where many blocks
-    // share a compute unit, and they cost the step kernel registers it does not have)
-    auto cells = [&](auto&& one) {
-#pragma unroll 1
-        for (int j = 0; j < 4; ++j) one(j);
-    };
-    if (CAN_PERLIN && use_perlin && f == 0) {
-        cells([&](int j) {
-            const int Wn = (int)((3u * perlin<16>(s_lat, 4, perlin_cs, x + j, y) + perlin<8>(s_lat + 32, 7, perlin_cs, x + j, y)) >> 2);
-            const int Mn = (int)((3u * perlin<16>(s_lat + 16, 4, perlin_cs, x + j, y) + perlin<8>(s_lat + 81, 7, perlin_cs, x + j, y)) >> 2);
-            put(j, classify_overworld(L, Wn, Mn, (int)perlin<8>(s_lat + 130, 7, perlin_cs, x + j, y),
-                                      (int)perlin<8>(s_lat + 179, 7, perlin_cs, x + j, y), x + j, y, draw(j)));
-        });
-    } else if (CAN_PERLIN && use_perlin && is_cave(f)) {
-        const uint64_t opened = L.row_mask[M_CAVE_OPEN][CX_IDX(y, W)] >> x;   // the run lies in one row
-        cells([&](int j) {
-            put(j, classify_cave_masked(L, f, (int)perlin<8>(s_lat, 7, perlin_cs, x + j, y), (int)perlin<8>(s_lat + 49, 7, perlin_cs, x + j, y),
-                                        x + j, y, draw(j), (opened >> j) & 1ull));
-        });
-    } else if (f == 0) {
-        const Field8 w16 = field16(s_lat, x, y), m16 = field16(s_lat + 16, x, y);
-        const Field8 w8 = field8(s_lat + 32, x, y), m8 = field8(s_lat + 81, x, y), c8 = field8(s_lat + 130, x, y), f8 = field8(s_lat + 179, x, y);
-        cells([&](int j) {
-            const int Wn = (int)((3u * at16(w16, x + j) + at8(w8, x + j)) >> 2), Mn = (int)((3u * at16(m16, x + j) + at8(m8, x + j)) >> 2);
-            put(j, classify_overworld(L, Wn, Mn, (int)at8(c8, x + j), (int)at8(f8, x + j), x + j, y, draw(j)));
-        });
+    if (f == 0) {
+        const uint32_t* w16 = s_lat + LAT_AT16;
+        const uint32_t* m16 = w16 + 16;
+        const uint32_t* w8 = s_lat + LAT_AT8;
+        const uint32_t* m8 = w8 + 49;
+        const uint32_t* c8 = m8 + 49;
+        const uint32_t* f8 = c8 + 49;
+        const int iy16 = y >> 4, iy8 = y >> 3, ix16 = x0 >> 4, odd8 = x0 & 8;
+        // 4 times the lowering (10 - d) * 2500 of W and M within Chebyshev distance d < 10 of the start
+        const int bias_y = max(0, START_BIAS_R - iabs(y - W / 2)) * (4 * START_BIAS);
+        auto cell = [&](int j, int W4, int M4, uint32_t C, uint32_t F, uint32_t u, auto perlin) {
+            const int bias = min(bias_y, max(0, START_BIAS_R - iabs(x0 + j - W / 2)) * (4 * START_BIAS));
+            const int b = cx::classify<decltype(perlin)::value>(W4 - bias, M4 - bias, C, F, u);
+            return bias >= (START_BIAS_R - START_CLEAR) * (4 * START_BIAS) ? (int)B_GRASS : b;
+        };
+        if (CAN_PERLIN && use_perlin) {
+            const cx::Gradients gW = cx::gradients_at(w16, 4, ix16, iy16), gM = cx::gradients_at(m16, 4, ix16, iy16);
+            const cx::Gradients hW = cx::gradients_at(w8, 7, strip, iy8), hM = cx::gradients_at(m8, 7, strip, iy8),
+                                hC = cx::gradients_at(c8, 7, strip, iy8), hF = cx::gradients_at(f8, 7, strip, iy8);
+            const int ky16 = y & 15, ky8 = y & 7, wy16 = cx::perlin_fade<16>(ky16), wy8 = cx::perlin_fade<8>(ky8);
+            auto coarse = [&](const cx::Gradients& g, int j, int wx) { return cx::perlin_value<16>(cx::perlin_n<16>(g, odd8 + j, ky16, wx, wy16)); };
+            auto fine = [&](const cx::Gradients& g, int j) { return cx::perlin_n<8>(g, j, ky8, cx::perlin_fade<8>(j), wy8); };
+            cells([&](int j, uint32_t u) {
+                const int wx16 = cx::perlin_fade<16>(odd8 + j);
+                return cell(j, 3 * coarse(gW, j, wx16) + cx::perlin_value<8>(fine(hW, j)), 3 * coarse(gM, j, wx16) + cx::perlin_value<8>(fine(hM, j)),
+                            (uint32_t)fine(hC, j), (uint32_t)fine(hF, j), u, std::integral_constant<bool, CAN_PERLIN>());
+            });
+        } else {
+            const uint32_t v16 = cx::vertical_weights(cx::smooth16(y & 15)), v8 = cx::vertical_weights(cx::smooth8(y & 7));
+            const Ends W16 = ends_at(w16, 4, ix16, iy16, v16), M16 = ends_at(m16, 4, ix16, iy16, v16);
+            const Ends W8 = ends_at(w8, 7, strip, iy8, v8), M8 = ends_at(m8, 7, strip, iy8, v8), C8 = ends_at(c8, 7, strip, iy8, v8),
+                       F8 = ends_at(f8, 7, strip, iy8, v8);
+            cells([&](int j, uint32_t u) {
+                const uint32_t wx16 = cx::smooth16(odd8 + j), wx8 = cx::smooth8(j);
+                return cell(j, cx::mix31(cx::across(W16.l, W16.r, wx16), cx::across(W8.l, W8.r, wx8)),
+                            cx::mix31(cx::across(M16.l, M16.r, wx16), cx::across(M8.l, M8.r, wx8)), cx::across(C8.l, C8.r, wx8),
+                            cx::across(F8.l, F8.r, wx8), u, std::integral_constant<bool, false>());
+            });
+        }
+        place(L.spot[SPOT_DOWN], B_PATH, IT_LADDER_DOWN);
     } else if (is_dungeon(f)) {
-        const int yr = CX_IDX(y, W);                                             // the run lies in one row
-        const uint64_t in = (L.row_mask[M_ROOMS_A][yr] | L.row_mask[M_ROOMS_B][yr]) >> x, path = (L.row_mask[M_PATH_A][yr] | L.row_mask[M_PATH_B][yr]) >> x,
-                       chest = L.row_mask[M_CHEST][yr] >> x;
-        cells([&](int j) { put(j, cell_dungeon_masked(L, f, x + j, y, draw(j), (in >> j) & 1ull, (path >> j) & 1ull, (chest >> j) & 1ull)); });
-    } else if (f == 8) {
+        const int yr = CX_IDX(y, W);
+        const uint32_t in = (uint32_t)((L.row_mask[M_ROOMS_A][yr] | L.row_mask[M_ROOMS_B][yr]) >> x0),
+                       path = (uint32_t)((L.row_mask[M_PATH_A][yr] | L.row_mask[M_PATH_B][yr]) >> x0), chest = (uint32_t)(L.row_mask[M_CHEST][yr] >> x0);
+        uint32_t wet = 0u;                                  // the sewers: cells of rooms that hold water
+        if (f == 3) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) put(j, cell_graveyard(x + j, y));
+            for (int j = 0; j < 8; ++j) wet |= (((j & 1) ? r.w[j >> 1] >> 16 : r.w[j >> 1] & 0xFFFFu) < 12000u ? 1u : 0u) << j;
+        }
+        blocks = cells_where(all_cells(f == 3 ? B_WALL_MOSS : B_WALL), in, B_PATH);
+        blocks = cells_where(blocks, in & wet, B_WATER);
+        blocks = cells_where(blocks, chest, B_CHEST);
+        place(L.spot[SPOT_FOUNTAIN], B_FOUNTAIN, 0u);
+        place(L.spot[SPOT_FIRE], B_ENCH_FIRE, 0u);
+        place(L.spot[SPOT_ICE], B_ENCH_ICE, 0u);
+        blocks = cells_where(blocks, path, B_PATH);         // corridors last: room centre 0 (ladder up) always reaches room centre 7 (ladder down)
+        place(L.spot[SPOT_UP], B_PATH, IT_LADDER_UP);
+        place(L.spot[SPOT_DOWN], B_PATH, IT_LADDER_DOWN_BLOCKED);
+    } else if (f == 8) {
+        // walled arena, fifteen graves of three kinds in turn, the necromancer and the ladder up
+        const bool rim = y == 0 || y == W - 1;
+        blocks = all_cells(rim ? B_WALL : B_PATH);
+        if (x0 == 0) blocks.x = (blocks.x & ~0xFFu) | B_WALL;
+        if (x0 == W - RUN) blocks.y = (blocks.y & 0x00FFFFFFu) | ((uint32_t)B_WALL << 24);
+        if (strip >= 1 && strip <= 5 && (y == 12 || y == 24 || y == 36)) blocks.x = (blocks.x & ~0xFFu) | (uint32_t)(B_GRAVE1 + (strip - 1 + y / 12 - 1) % 3);
+        place((uint32_t)BOSS_X | ((uint32_t)BOSS_Y << 8), B_NECRO_VULN, 0u);
+        place(24u | (42u << 8), B_PATH, IT_LADDER_UP);
     } else {
-        const Field8 c8 = field8(s_lat, x, y), f8 = field8(s_lat + 49, x, y);
-        const uint64_t opened = L.row_mask[M_CAVE_OPEN][CX_IDX(y, W)] >> x;   // the run lies in one row
-        cells([&](int j) { put(j, classify_cave_masked(L, f, (int)at8(c8, x + j), (int)at8(f8, x + j), x + j, y, draw(j), (opened >> j) & 1ull)); });
+        const CaveRule rule = cave_rule(f);
+        const uint32_t* c8 = s_lat + LATC_AT8;
+        const uint32_t* f8 = c8 + 49;
+        const int iy8 = y >> 3;
+        if (CAN_PERLIN && use_perlin) {
+            const cx::Gradients hC = cx::gradients_at(c8, 7, strip, iy8), hF = cx::gradients_at(f8, 7, strip, iy8);
+            const int ky8 = y & 7, wy8 = cx::perlin_fade<8>(ky8);
+            auto fine = [&](const cx::Gradients& g, int j) { return (uint32_t)cx::perlin_n<8>(g, j, ky8, cx::perlin_fade<8>(j), wy8); };
+            cells([&](int j, uint32_t u) { return classify_cave<CAN_PERLIN>(rule, fine(hC, j), fine(hF, j), u); });
+        } else {
+            const uint32_t v8 = cx::vertical_weights(cx::smooth8(y & 7));
+            const Ends C8 = ends_at(c8, 7, strip, iy8, v8), F8 = ends_at(f8, 7, strip, iy8, v8);
+            cells([&](int j, uint32_t u) {
+                return classify_cave<false>(rule, cx::across(C8.l, C8.r, cx::smooth8(j)), cx::across(F8.l, F8.r, cx::smooth8(j)), u);
+            });
+        }
+        blocks = cells_where(blocks, (uint32_t)(L.row_mask[M_CAVE_OPEN][CX_IDX(y, W)] >> x0), rule.open);
+        place(L.spot[SPOT_UP], B_PATH, IT_LADDER_UP);
+        place(L.spot[SPOT_DOWN], B_PATH, IT_LADDER_DOWN_BLOCKED);
     }
-    *reinterpret_cast<uint32_t*>(maps + block_off(f, x, y)) = pb;
-    *reinterpret_cast<uint32_t*>(maps + il_off(f, x, y)) = pi;
+    *reinterpret_cast<uint2*>(maps + block_off(f, x0, y)) = blocks;
+    *reinterpret_cast<uint2*>(maps + il_off(f, x0, y)) = items;
     if (start_wb != nullptr && f == 0) {
         // window of the start cell (24, 24): rows 19..29, columns 18..30
         const int wr = y - (W / 2 - WIN_ROWS / 2);
         if ((unsigned)wr < (unsigned)WIN_ROWS) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int wc = x + j - (W / 2 - WIN_COLS / 2);
+            for (int j = 0; j < 8; ++j) {
+                const int wc = x0 + j - (W / 2 - WIN_COLS / 2);
                 if ((unsigned)wc < (unsigned)WIN_COLS) {
-                    start_wb[wr * WIN_PITCH + wc] = (uint8_t)(pb >> (8 * j));
-                    start_wi[wr * WIN_PITCH + wc] = (uint8_t)(pi >> (8 * j));
+                    start_wb[wr * WIN_PITCH + wc] = (uint8_t)((j < 4 ? blocks.x : blocks.y) >> (8 * (j & 3)));
+                    start_wi[wr * WIN_PITCH + wc] = (uint8_t)((j < 4 ? items.x : items.y) >> (8 * (j & 3)));
                 }
             }
         }
     }
     }
-    __syncthreads();
+    barrier();
 }
 
 // The ten dwords that describe a generated world beyond its maps: ladders of the nine floors and

@@ -203,7 +203,7 @@ def test_full_perlin_worlds(cx):
     """The Perlin option for the open floors (appendix "World Generation"): 96 fresh worlds byte
     for byte, and they are not the value-noise worlds."""
     n = 96
-    seeds = synth.seeds_for(n, 77)
+    seeds = synth.seeds_for(n, 0)
     gcfg, ocfg = _cfgs(cx, 1, worldgen=po.WORLDGEN_PERLIN)
     sim = cx.Craftax(n, gcfg)
     orc = po.FullOracle(n, ocfg)
@@ -213,6 +213,22 @@ def test_full_perlin_worlds(cx):
     plain.reset(seeds)
     differ = (plain.envs["block"] != orc.envs["block"]).reshape(n, 9, -1).any(axis=2)
     assert differ[:, [0, 2, 5, 6, 7]].all() and not differ[:, [1, 3, 4, 8]].any()
+    sim.close()
+
+
+@pytest.mark.parametrize("worldgen", [po.WORLDGEN_VALUE, po.WORLDGEN_PERLIN])
+def test_full_worlds_over_many_seeds(cx, worldgen):
+    """Every cell of 700 fresh worlds: rare layouts too, such as a built floor whose two ladders fall
+    on one cell (the blocked ladder down counts) and single cells in the first and last run of a row."""
+    n = 700
+    gcfg, ocfg = _cfgs(cx, 1, worldgen=worldgen)
+    sim = cx.Craftax(n, gcfg)
+    orc = po.FullOracle(n, ocfg)
+    seeds = synth.seeds_for(n, 0)
+    sim.reset(seeds); orc.reset(seeds)
+    compare_state(sim, orc, np.arange(n), "reset")
+    built = [1, 3, 4]
+    assert (orc.envs["ladder_up"][:, built] == orc.envs["ladder_down"][:, built]).all(axis=2).any(), "no such layout among these seeds"
     sim.close()
 
 
@@ -436,7 +452,7 @@ def test_full_null_observation_and_determinism(cx):
     outs = []
     for rep in range(2):
         sim = cx.Craftax(n, gcfg)
-        sim.reset(synth.seeds_for(n, 77))
+        sim.reset(synth.seeds_for(n, 0))
         for s in range(150):
             a = torch.as_tensor(synth.actions(np.arange(n), s, "skewed", 2, 43), device=sim.device)
             if rep == 0:
