@@ -39,6 +39,9 @@ __device__ inline uint32_t pack_regs(const MobRegs& m)
 
 // What the block that generated floor 0 of a world leaves behind for the environment: as the
 // current world (fresh record, empty mob tables) or as the spare world (its ladders and potion map).
+// SAME_EPISODE: the record already holds this episode and seed (blocks of other floors may be reading
+// them): those three words are left alone.
+template <bool SAME_EPISODE = false>
 __device__ inline void publish_world(uint32_t* __restrict__ genv, const GenLayout& L, uint32_t lo, uint32_t hi, uint32_t ep,
                                      bool current, uint32_t* s_layout_words)
 {
@@ -46,7 +49,8 @@ __device__ inline void publish_world(uint32_t* __restrict__ genv, const GenLayou
     if (tid < FLOORS + 1) s_layout_words[tid] = layout_word(L, tid);
     __syncthreads();
     if (current) {
-        if (tid < SPARE_LADDER) genv[tid] = tid < REC_DWORDS ? fresh_record_word(tid, s_layout_words, lo, hi, ep) : 0u;
+        const bool identity = tid == R_EPISODE || tid == R_SEED_LO || tid == R_SEED_HI;
+        if (tid < SPARE_LADDER && !(SAME_EPISODE && identity)) genv[tid] = tid < REC_DWORDS ? fresh_record_word(tid, s_layout_words, lo, hi, ep) : 0u;
     } else if (tid < FLOORS + 1) genv[SPARE_LADDER + tid] = s_layout_words[tid];
 }
 
@@ -493,44 +497,28 @@ __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__
                     obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8));
 }
 
-// after an import: the world of the episode after the imported one, into the spare slot
-template <bool PERLIN>
-__global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_import_spare(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls, int first,
-                                                                const uint32_t* __restrict__ perlin_cs, int pool)
-{
-    __shared__ uint32_t s_lat[LAT_WORDS];
-    __shared__ GenLayout s_layout;
-    __shared__ uint32_t s_words[FLOORS + 1];
-    const uint32_t env = (uint32_t)first + blockIdx.x / FLOORS;
-    const int f = blockIdx.x % FLOORS;
-    uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
-    const uint32_t ep = genv[R_EPISODE] + 1u, lo = genv[R_SEED_LO], hi = genv[R_SEED_HI];
-    worldgen_floor_block<GEN_THREADS, PERLIN>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, perlin_cs);
-    if (f == 0) publish_world(genv, s_layout, lo, hi, ep, false, s_words);
-    if (threadIdx.x == 0) ls.tags[(size_t)env * NTAG + f] = make_uint2(pool ? 0u : ep, 0u);
-}
-
-// Noise mutation (section "Craftax-1B: UED"): one block per (environment, floor) of the floors
-// f0 .. f0 + nf - 1.  The level is the vector of the Perlin angles of every noise lattice: the
-// overworld's 228, then 98 for each of the cave floors 2, 5, 6, 7.  The block of a floor adds to its
-// own segment a uniform offset in [-amplitude, amplitude] per element (u16 number i of stream
-// (round, 1) of the mutation domain, i counted over the whole vector) and generates the floor of
-// the current episode again from the turned lattice; the block of floor 0 then starts the episode
-// over.  Floor 0 runs in a launch of its own after the others: its block rewrites the record the
-// others read their seed and episode from.
+// Noise mutation (section "Craftax-1B: UED"): one block per (environment, floor).  The level is the
+// vector of the Perlin angles of every noise lattice: the overworld's 228, then 98 for each of the
+// cave floors 2, 5, 6, 7.  The block of a floor adds to its own segment a uniform offset in
+// [-amplitude, amplitude] per element (u16 number i of stream (round, 1) of the mutation domain, i
+// counted over the whole vector) and generates the floor of the current episode again from the
+// turned lattice; the block of floor 0 also starts the episode over.  It writes every word of the
+// record but the episode and the seed, which the other blocks read and which stay as they are, so one
+// launch does it all (floor 0 in a launch of its own behind the others: 131 us for 1,000
+// levels, one launch: 92).
 __device__ inline int theta_offset(int f)
 {
     return f == 0 ? 0 : LAT0_U16 + LATC_U16 * (f == 2 ? 0 : (f == 5 ? 1 : (f == 6 ? 2 : 3)));
 }
 __global__ __launch_bounds__(GEN_THREADS, 6) void kf_mutate_noise(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts,
-                                                                uint16_t* __restrict__ theta, int first, int f0, int nf, uint32_t k0, uint32_t k1,
+                                                                uint16_t* __restrict__ theta, int first, uint32_t k0, uint32_t k1,
                                                                 uint32_t round, uint32_t amplitude)
 {
     __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ uint16_t s_theta[LAT_TOTAL];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
-    const int tid = threadIdx.x, slot = blockIdx.x / nf, f = f0 + blockIdx.x % nf;
+    const int tid = threadIdx.x, slot = blockIdx.x / FLOORS, f = blockIdx.x % FLOORS;
     const uint32_t env = (uint32_t)first + (uint32_t)slot;
     uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
     const uint32_t ep = genv[R_EPISODE], lo = genv[R_SEED_LO], hi = genv[R_SEED_HI];
@@ -552,25 +540,30 @@ __global__ __launch_bounds__(GEN_THREADS, 6) void kf_mutate_noise(uint32_t* __re
     __syncthreads();
     worldgen_floor_block<GEN_THREADS, true>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr,
                                             luts->perlin_cs, noisy ? s_theta : nullptr);
-    if (f == 0) publish_world(genv, s_layout, lo, hi, ep, true, s_words);
+    if (f == 0) publish_world<true>(genv, s_layout, lo, hi, ep, true, s_words);
 }
 
 // ---------------------------------------------------------------------------------------------
-// canonical dumps: one block per environment
-__global__ __launch_bounds__(BLOCK) void kf_export(const uint32_t* __restrict__ envs, const uint8_t* __restrict__ maps,
+// canonical dumps: one block per (environment, floor), a thread moving runs of 8 cells of all three maps of
+// the dump (63 KB, so a copy with some arithmetic: byte by byte, one block per environment, 1,000
+// dumps took 34 us, now 16.5, 6.3 TB/s of the dumps and maps); the block of floor 0 also unpacks the record.  A dump is a multiple of 8
+// bytes long; the pieces are moved without assuming more than byte alignment of the caller's array.
+__device__ inline uint2 load8(const uint8_t* p) { uint2 v; __builtin_memcpy(&v, p, 8); return v; }
+__device__ inline void store8(uint8_t* p, uint2 v) { __builtin_memcpy(p, &v, 8); }
+__global__ __launch_bounds__(GEN_THREADS) void kf_export(const uint32_t* __restrict__ envs, const uint8_t* __restrict__ maps,
                                                   craftax_full_env_dump* __restrict__ dumps, int first)
 {
-    const int env = first + blockIdx.x, tid = threadIdx.x;
-    craftax_full_env_dump* d = dumps + blockIdx.x;
+    const int slot = blockIdx.x / FLOORS, floor = blockIdx.x % FLOORS, env = first + slot, tid = threadIdx.x;
+    craftax_full_env_dump* d = dumps + slot;
     const uint32_t* r = envs + (size_t)env * ENV_DWORDS;
-    const uint8_t* em = maps + map_offset((uint32_t)env, r[R_EPISODE]);
-    for (int i = tid; i < FLOORS * CELLS; i += BLOCK) {
-        const int f = i / CELLS, c = i - f * CELLS;
-        const uint32_t il = em[(size_t)f * 2 * CELLS + CELLS + c];
-        d->block[f][c] = em[(size_t)f * 2 * CELLS + c];
-        d->item[f][c] = (uint8_t)(il & 7u);
-        d->light[f][c] = (uint8_t)(il >> 3);
+    if (tid < RUNS) {
+        const uint8_t* em = maps + map_offset((uint32_t)env, r[R_EPISODE]) + (size_t)floor * 2 * CELLS + tid * RUN;
+        const uint2 b = *reinterpret_cast<const uint2*>(em), il = *reinterpret_cast<const uint2*>(em + CELLS);
+        store8(d->block[floor] + tid * RUN, b);
+        store8(d->item[floor] + tid * RUN, make_uint2(il.x & 0x07070707u, il.y & 0x07070707u));
+        store8(d->light[floor] + tid * RUN, make_uint2((il.x >> 3) & 0x1F1F1F1Fu, (il.y >> 3) & 0x1F1F1F1Fu));
     }
+    if (floor != 0) return;
     if (tid == 0) {
         d->px = r[R_POS] & 0xFF; d->py = (r[R_POS] >> 8) & 0xFF; d->dir = (r[R_POS] >> 16) & 0xFF; d->floor = (r[R_POS] >> 24) & 0xF;
         const uint32_t fl = r[R_FLAGS], at = r[R_ATTR];
@@ -612,26 +605,13 @@ __global__ __launch_bounds__(BLOCK) void kf_export(const uint32_t* __restrict__ 
     }
 }
 
-// Import packs into the record's bit fields: counts 0..99, vitals 0..31, counters -128..127, mob
-// hp 0..31, cooldown 0..15, creature type 0..18, experience 0..15, coordinates 0..47, floor 0..8,
-// block ids 1..36, items 0..4, light 0..20 (every state the rules can reach is); values outside
-// are brought into range so that no kernel ever indexes beyond its tables or buffers.
-__global__ __launch_bounds__(BLOCK) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
-                                                  const craftax_full_env_dump* __restrict__ dumps, int first, Params p)
+// The record of an import (all threads of the block call).
+__device__ inline void import_record(uint32_t* __restrict__ r, const Lists& ls, uint32_t env, const craftax_full_env_dump* __restrict__ d, const Params& p)
 {
-    const int env = first + blockIdx.x, tid = threadIdx.x;
-    const craftax_full_env_dump* d = dumps + blockIdx.x;
-    uint8_t* em = maps + map_offset((uint32_t)env, d->episode);
-    la::cancel_entries(ls, (uint32_t)env);   // whatever was queued for this environment belongs to the episode that is being replaced
-    uint32_t* r = envs + (size_t)env * ENV_DWORDS;
-    for (int i = tid; i < FLOORS * CELLS; i += BLOCK) {
-        const int f = i / CELLS, c = i - f * CELLS;
-        const uint32_t b = d->block[f][c], it = d->item[f][c];
-        em[(size_t)f * 2 * CELLS + c] = (uint8_t)(b - 1u < (uint32_t)(B_COUNT - 1) ? b : (uint32_t)B_OOB);
-        em[(size_t)f * 2 * CELLS + CELLS + c] = (uint8_t)((it <= 4u ? it : 0u) | ((uint32_t)min((int)d->light[f][c], 20) << 3));
-    }
     __shared__ uint32_t s[ENV_DWORDS];
-    s[tid] = 0u;
+    const int tid = threadIdx.x;
+    la::cancel_entries(ls, env);   // whatever was queued for this environment belongs to the episode that is being replaced
+    if (tid < ENV_DWORDS) s[tid] = 0u;
     __syncthreads();
     if (tid == 0) {
         s[R_POS] = (uint32_t)min((int)d->px, W - 1) | ((uint32_t)min((int)d->py, W - 1) << 8) | ((uint32_t)(d->dir & 7) << 16) |
@@ -678,7 +658,53 @@ __global__ __launch_bounds__(BLOCK) void kf_import(uint32_t* __restrict__ envs, 
         s[R_PLANT + tid - 128] = (u.alive & 1) ? (1u | ((uint32_t)min((int)u.x, W - 1) << 1) | ((uint32_t)min((int)u.y, W - 1) << 7) | ((uint32_t)u.age << 16)) : 0u;
     }
     __syncthreads();
-    if (tid < SPARE_LADDER) r[tid] = s[tid];   // the spare world's description is written by kf_import_spare
+    if (tid < SPARE_LADDER) r[tid] = s[tid];   // the spare world's description follows
+}
+
+// Import packs into the record's bit fields: counts 0..99, vitals 0..31, counters -128..127, mob
+// hp 0..31, cooldown 0..15, creature type 0..18, experience 0..15, coordinates 0..47, floor 0..8,
+// block ids 1..36, items 0..4, light 0..20 (every state the rules can reach is); values outside
+// are brought into range so that no kernel ever indexes beyond its tables or buffers.
+// One block per (environment, floor): it takes the floor in, and generates the same floor of the world
+// of the next episode into the spare slot, so that the copy of some blocks overlaps the arithmetic of
+// others; the block of floor 0 also packs the record.  (A copy byte by byte and a second launch for
+// the spare worlds: 50 + 87 us for 1,000 Perlin worlds, now 101.)
+template <bool PERLIN>
+__global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
+                                                                        const craftax_full_env_dump* __restrict__ dumps, int first, Params p,
+                                                                        const uint32_t* __restrict__ perlin_cs, int pool)
+{
+    __shared__ WorldScratch s_gen;
+    const int slot = blockIdx.x / FLOORS, floor = blockIdx.x % FLOORS, env = first + slot, tid = threadIdx.x;
+    const craftax_full_env_dump* d = dumps + slot;
+    const uint32_t lo = (uint32_t)d->seed, hi = (uint32_t)(d->seed >> 32), ep = d->episode;
+    uint32_t* r = envs + (size_t)env * ENV_DWORDS;
+    if (tid < RUNS) {
+        const uint2 b = load8(d->block[floor] + tid * RUN), it = load8(d->item[floor] + tid * RUN), light = load8(d->light[floor] + tid * RUN);
+        auto blocks = [](uint32_t four) {
+            uint32_t out = 0u;
+#pragma unroll
+            for (int i = 0; i < 32; i += 8) { const uint32_t v = (four >> i) & 0xFFu; out |= (v - 1u < (uint32_t)(B_COUNT - 1) ? v : (uint32_t)B_OOB) << i; }
+            return out;
+        };
+        auto items = [](uint32_t four_items, uint32_t four_lights) {
+            uint32_t out = 0u;
+#pragma unroll
+            for (int i = 0; i < 32; i += 8) {
+                const uint32_t v = (four_items >> i) & 0xFFu;
+                out |= ((v <= 4u ? v : 0u) | (min((four_lights >> i) & 0xFFu, 20u) << 3)) << i;
+            }
+            return out;
+        };
+        uint8_t* em = maps + map_offset((uint32_t)env, ep) + (size_t)floor * 2 * CELLS + tid * RUN;
+        *reinterpret_cast<uint2*>(em) = make_uint2(blocks(b.x), blocks(b.y));
+        *reinterpret_cast<uint2*>(em + CELLS) = make_uint2(items(it.x, light.x), items(it.y, light.y));
+    }
+    if (floor == 0) import_record(r, ls, (uint32_t)env, d, p);
+    worldgen_floor_block<GEN_THREADS, PERLIN>(maps + map_offset((uint32_t)env, ep + 1u), s_gen.lat, s_gen.layout, lo, hi, (uint32_t)env, ep + 1u, floor, nullptr,
+                                              nullptr, perlin_cs);
+    if (floor == 0) publish_world(r, s_gen.layout, lo, hi, ep + 1u, false, s_gen.words);
+    if (tid == 0) ls.tags[(size_t)env * NTAG + floor] = make_uint2(pool ? 0u : ep + 1u, 0u);
 }
 
 // Level mutation of the overworld (section "Craftax-1B: UED"), as for Classic: up to 32 tries, try
@@ -1050,7 +1076,7 @@ int observe(void* state, const craftax_config* cfg, int n, void* obs, void* stre
 int export_envs(const void* state, const craftax_config* cfg, int n, int first, int count, void* dumps, void* stream, std::string* err)
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
-    hipLaunchKernelGGL(kf_export, dim3(count), dim3(BLOCK), 0, (hipStream_t)stream, q.envs, q.maps,
+    hipLaunchKernelGGL(kf_export, dim3((unsigned)count * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps,
                        static_cast<craftax_full_env_dump*>(dumps), first);
     return check_launch("craftax_export_envs", err);
 }
@@ -1058,13 +1084,12 @@ int export_envs(const void* state, const craftax_config* cfg, int n, int first, 
 int import_envs(void* state, const craftax_config* cfg, int n, int first, int count, const void* dumps, void* stream, std::string* err)
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
-    hipLaunchKernelGGL(kf_import, dim3(count), dim3(BLOCK), 0, (hipStream_t)stream, q.envs, q.maps, q.ls,
-                       static_cast<const craftax_full_env_dump*>(dumps), first, make_params(state, cfg, n));
-    auto spare = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.ls, first, gradients(cfg, q),
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.ls,
+                           static_cast<const craftax_full_env_dump*>(dumps), first, make_params(state, cfg, n), gradients(cfg, q),
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0);
     };
-    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) spare(kf_import_spare<true>); else spare(kf_import_spare<false>);
+    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) go(kf_import<true>); else go(kf_import<false>);
     return check_launch("craftax_import_envs", err);
 }
 
@@ -1082,10 +1107,8 @@ int mutate_noise(void* state, const craftax_config* cfg, int n, int first, int c
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
     const uint32_t k0 = (uint32_t)mutation_seed, k1 = (uint32_t)(mutation_seed >> 32);
-    hipLaunchKernelGGL(kf_mutate_noise, dim3((unsigned)count * (FLOORS - 1)), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, theta,
-                       first, 1, FLOORS - 1, k0, k1, round, amplitude);
-    hipLaunchKernelGGL(kf_mutate_noise, dim3((unsigned)count), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, theta, first, 0, 1,
-                       k0, k1, round, amplitude);
+    hipLaunchKernelGGL(kf_mutate_noise, dim3((unsigned)count * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, theta,
+                       first, k0, k1, round, amplitude);
     return check_launch("craftax_mutate_noise", err);
 }
 
