@@ -146,7 +146,8 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
     constexpr int WIN_IT = (WIN_ROWS * WIN_COLS + GW - 1) / GW;
     static_assert(REC_DWORDS % GW == 0 || GW > REC_DWORDS, "the record is moved in whole turns of the group");
     static_assert(GW >= MOBTAB_DWORDS && GW >= NTAG && GW >= FLOORS + 1, "a group holds a mob table, the tags and the header in one turn");
-    __shared__ __attribute__((aligned(16))) uint32_t s_env[EPB * L_ENV_DWORDS];
+    constexpr int ENV_DWORDS_LDS = GW == 64 ? L_STAGED_DWORDS : L_ENV_DWORDS;
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[EPB * ENV_DWORDS_LDS];
     __shared__ float s_lut[LUT_FLOATS];
     const int tid = threadIdx.x, w = tid / GW, l = tid % GW;
     if ((int)blockIdx.x < regen_blocks) {
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
     const uint32_t seq = ticket.seq;
     __syncthreads();                                          // the conversion tables are in LDS
     if (active) {
-        uint32_t* e = s_env + w * L_ENV_DWORDS;
+        uint32_t* e = s_env + w * ENV_DWORDS_LDS;
 #pragma unroll
         for (int it = 0; it < REC_IT; ++it) if (l + GW * it < REC_DWORDS) e[L_REC + l + GW * it] = rec_word[it];
         const int action = G::uni(action_raw);
@@ -326,7 +327,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
                                                        uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                        uint8_t* __restrict__ done, Lists ls, Params p, int steps)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * L_ENV_DWORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * L_STAGED_DWORDS];
     __shared__ WorldScratch s_gen[ENVS_PER_BLOCK];
     __shared__ float s_lut[LUT_FLOATS];
     if (threadIdx.x < LUT_FLOATS) s_lut[threadIdx.x] = luts->sqrt10[threadIdx.x];   // sqrt10, tenth and light20 lie one after the other
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
     {
         const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
         if (env >= p.n) return;
-        uint32_t* e = s_env + w * L_ENV_DWORDS;
+        uint32_t* e = s_env + w * L_STAGED_DWORDS;
         e[L_REC + l] = envs[(size_t)env * ENV_DWORDS + l];
         wave_sync();
         const uint32_t ep = uniu(e[L_REC + R_EPISODE]);
@@ -352,7 +353,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
         asm volatile("" : "+s"(obs_t));
         const int w = uni(tid_t >> 6), l = tid_t & 63;
         const int env = blockIdx.x * ENVS_PER_BLOCK + w;
-        uint32_t* e = s_env + w * L_ENV_DWORDS;
+        uint32_t* e = s_env + w * L_STAGED_DWORDS;
         uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
         RenderAux<64> aux;
         fetch_scalar_specs<64>(l, aux);
@@ -405,7 +406,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
     }
     // the record back; the world after this episode, if it is owed, for the regeneration launch
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
-    const uint32_t* e = s_env + w * L_ENV_DWORDS;
+    const uint32_t* e = s_env + w * L_STAGED_DWORDS;
     envs[(size_t)env * ENV_DWORDS + l] = e[L_REC + l];
     if (!spare_ok && l == 0)
         la::append_after_step(ls, (uint32_t)env / ENVS_PER_BLOCK, make_uint4((uint32_t)env, e[L_REC + R_SEED_LO], e[L_REC + R_SEED_HI], e[L_REC + R_EPISODE] + 1u));
@@ -423,7 +424,7 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_reset_list(uint32_t* __restric
     __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
-    __shared__ uint32_t s_env[L_ENV_DWORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[L_STAGED_DWORDS];
     __shared__ uint32_t s_rank[(GEN_THREADS + 63) / 64];
     // Optimistic resets (pool != 0): the world comes from this step's pool.  The step kernel has
     // already advanced the launch number: it is the index of the step just done + 2.  The pool is
@@ -480,11 +481,11 @@ template <bool F32>
 __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__ envs, const uint8_t* __restrict__ maps,
                                                    const Luts* __restrict__ luts, uint8_t* __restrict__ obs, int n)
 {
-    __shared__ uint32_t s_env[ENVS_PER_BLOCK * L_ENV_DWORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * L_STAGED_DWORDS];
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int env = blockIdx.x * ENVS_PER_BLOCK + w;
     if (env >= n) return;
-    uint32_t* e = s_env + w * L_ENV_DWORDS;
+    uint32_t* e = s_env + w * L_STAGED_DWORDS;
     const uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
     e[L_REC + l] = genv[l];
     wave_sync();

@@ -1,8 +1,8 @@
 // Symbolic observation of full Craftax (appendix "Observation Space"): 9 x 11 cells around the
 // player, per cell one-hot block (37) + item (5) + creature (40: five slot classes of eight
 // types) + light; cells darker than 0.05 are blank; then the 51 scalars of the inventory table.
-// The wave stages the one-hot bytes as bits in LDS and expands them while streaming out whole
-// cache lines (byte layout) or floats (flat layout).
+// The wave stages the bytes in LDS and streams them out as whole cache lines (byte layout) or floats
+// (flat layout).
 #pragma once
 
 #include "full_common.hpp"
@@ -113,18 +113,141 @@ __device__ inline int creature_channel(int k, int type)
 // one-hot nibble -> four bytes of 0/1
 __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x00204081u) & 0x01010101u; }
 
-// e: the wave's LDS area holding the packed record (current), the two windows with origin
-// (wx0, wy0) on the current floor; m_*: this lane's mob slot.  F32 = false: writes the
-// 8448-byte layout; F32 = true: writes float[8268] (+ zero padding to 33152 bytes).
-// The one-hot bytes are staged as single bits (a few LDS atomics per cell) next to a light level
-// per cell; every lane then expands 16 bits at a time into one 16-byte piece of the output, so
-// that a wavefront writes whole cache lines.
+// The observation of one environment by a whole wavefront.  e: its LDS area (L_STAGED_DWORDS) with the
+// packed record (current) and the two windows with origin (wx0, wy0) on the current floor; m_*:
+// this lane's mob slot.  F32 = false: writes the 8448-byte layout; F32 = true: writes float[8268]
+// (+ zero padding to 33152 bytes).  The windows are used up: the bytes are staged over them.
+//
+// An observation of 8217 cell bytes holds at most 396 that are not zero.  They are set one by one in a
+// cleared LDS area, which the lanes then read back in 16-byte pieces and store as whole cache lines.
+// LDS moves 128 bytes per clock beside the vector units, which bound the step kernels; in the earlier form
+// (the channels as single bits, every piece expanded from 16 of them) a quarter of the vector
+// instructions of a step expanded bits.  Measured: a step of 4,096 environments 18.3 -> 16.7 us, of
+// 32,768 115 -> 110, a rollout of 64 steps and 4,096 environments 897 -> 805 us.  The area covers 5,120 bytes at a time, so that five blocks of the step
+// kernel still share a compute unit.  A lane owns the cells l and l + 64; the second one lies in the
+// second part, the first one may reach into it.
+// For the float layout a staged byte v stands for v / 140: 140 is the 1 of a one-hot channel and 7 * level
+// the light level / 20.  Multiplying by the float nearest to 1/140 gives exactly those floats.
+constexpr int STAGE_BYTES = (L_STAGED_DWORDS - L_STAGE) * 4, STAGE_REST = CELL_BYTES - STAGE_BYTES;
+constexpr float F32_UNIT = 1.0f / 140.0f;
+constexpr bool staged_floats_are_exact()
+{
+    for (int lv = 0; lv <= MAX_LIGHT; ++lv) if ((float)(7 * lv) * F32_UNIT != (float)((double)lv / 20.0)) return false;
+    return true;
+}
+static_assert(staged_floats_are_exact(), "light levels through staged bytes");
+static_assert(STAGE_BYTES % 1024 == 0 && 64 * NCHAN >= STAGE_BYTES && NCELL <= 128, "the second cell of a lane lies in the second part");
+template <bool F32>
+__device__ __forceinline__ void render_staged(const int l, uint32_t* e, const int wx0, const int wy0, const int m_alive, const int m_x,
+                                              const int m_y, const int m_type, const Luts* __restrict__ luts, uint8_t* __restrict__ out,
+                                              const RenderAux<64>* aux)
+{
+    const uint32_t* rec = e + L_REC;
+    const uint8_t* wb = reinterpret_cast<const uint8_t*>(e + L_WB);
+    const uint8_t* wi = reinterpret_cast<const uint8_t*>(e + L_WI);
+    uint32_t* cre = e + L_CRE;
+    uint8_t* stage = reinterpret_cast<uint8_t*>(e + L_STAGE);
+    constexpr uint32_t ONE = F32 ? 140u : 1u, LIGHT = F32 ? 7u : 1u;
+    const uint32_t pos = uniu(rec[R_POS]);
+    const int px = pos & 0xFF, py = (pos >> 8) & 0xFF;
+    const int corner = (py - VROWS / 2 - wy0) * WIN_PITCH + px - VCOLS / 2 - wx0;    // upper left cell of the view in the windows
+    // everything the staging area is about to cover goes to registers first; beyond the edge of the
+    // map the windows hold B_OOB at full light
+    uint32_t il[2], block[2];
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const int cell = min(l + 64 * it, NCELL - 1), r = cell / VCOLS, at = CX_IDX(corner + r * WIN_PITCH + cell - r * VCOLS, WIN_ROWS * WIN_PITCH);
+        il[it] = wi[at];
+        block[it] = wb[at] & 63u;
+    }
+    if (l + 64 >= NCELL) il[1] = 0u;
+    // the creature of a cell is the one in its lowest slot, and is seen where there is light
+    const int vr = m_y - (py - VROWS / 2), vc = m_x - (px - VCOLS / 2), m_cell = vr * VCOLS + vc;
+    const bool in_view = l < NSLOT && m_alive && (unsigned)vr < (unsigned)VROWS && (unsigned)vc < (unsigned)VCOLS;
+    uint32_t m_byte = 0xFFFFFFFFu;
+    if (in_view) cre[CX_IDX(m_cell, NCELL)] = 0xFFFFFFFFu;
+    wave_sync();
+    if (in_view) atomicMin(&cre[CX_IDX(m_cell, NCELL)], (uint32_t)l);
+    wave_sync();
+    if (in_view && cre[CX_IDX(m_cell, NCELL)] == (uint32_t)l && (wi[CX_IDX(corner + vr * WIN_PITCH + vc, WIN_ROWS * WIN_PITCH)] >> 3) != 0)
+        m_byte = (uint32_t)(m_cell * NCHAN + creature_channel(l, m_type));
+    const float scalar = l >= NVEC ? 0.0f : (aux != nullptr ? scalar_value_fast(l, aux->spec[0], rec, aux->lut, aux->day) : scalar_value(l, rec, luts));
+    wave_sync();
+    // part 0: bytes 0 .. STAGE_BYTES - 1; part 1: the rest
+    auto fill = [&](int part) {
+        const uint32_t first = part == 0 ? 0u : (uint32_t)STAGE_BYTES, size = part == 0 ? (uint32_t)STAGE_BYTES : (uint32_t)STAGE_REST;
+        uint4* clear = reinterpret_cast<uint4*>(stage) + l;
+#pragma unroll
+        for (int k = 0; k < STAGE_BYTES / 1024; ++k) if (part == 0 || k * 1024 < STRIDE_U8 - STAGE_BYTES) clear[64 * k] = make_uint4(0u, 0u, 0u, 0u);
+        wave_sync();
+        auto put = [&](uint32_t at, uint32_t v) { if (at - first < size) stage[CX_IDX(at - first, STAGE_BYTES)] = (uint8_t)v; };
+#pragma unroll
+        for (int it = 0; it < 2; ++it) {
+            if (it == 1 && part == 0) continue;
+            if ((il[it] >> 3) != 0u) {              // cells darker than 0.05 stay blank
+                const uint32_t base = (uint32_t)((l + 64 * it) * NCHAN);
+                put(base + block[it], ONE);
+                put(base + 37u + (il[it] & 7u), ONE);
+                put(base + 82u, LIGHT * (il[it] >> 3));
+            }
+        }
+        put(m_byte, ONE);
+    };
+    if (!F32) {
+        typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
+        piece_t* dst = reinterpret_cast<piece_t*>(out) + l;
+        const piece_t* src = reinterpret_cast<const piece_t*>(stage) + l;
+        constexpr int PIECES = STRIDE_U8 / 16, HEAD = STAGE_BYTES / 16;
+        fill(0);
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < HEAD / 64; ++k) __builtin_nontemporal_store(src[64 * k], dst + 64 * k);   // 16-byte streaming stores
+        wave_sync();
+        fill(1);
+        if (l < NVEC) reinterpret_cast<float*>(stage + (VEC_OFFSET - STAGE_BYTES))[l] = scalar;
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < (PIECES - HEAD + 63) / 64; ++k)
+            if (64 * k + 64 <= PIECES - HEAD || l < PIECES - HEAD - 64 * k) __builtin_nontemporal_store(src[64 * k], dst + HEAD + 64 * k);
+    } else {
+        float4* dst = reinterpret_cast<float4*>(out) + l;
+        const uint32_t* src = reinterpret_cast<const uint32_t*>(stage) + l;
+        auto floats = [](uint32_t four) {
+            return make_float4((float)(four & 0xFFu) * F32_UNIT, (float)((four >> 8) & 0xFFu) * F32_UNIT, (float)((four >> 16) & 0xFFu) * F32_UNIT, (float)(four >> 24) * F32_UNIT);
+        };
+        // pieces of four floats; from TAIL on they hold scalars (after one last light level)
+        constexpr int PIECES = STRIDE_F32 / 16, HEAD = STAGE_BYTES / 4, TAIL = CELL_BYTES / 4, TAIL_AT = 3328;
+        static_assert(TAIL_AT % 16 == 0 && TAIL_AT >= STRIDE_U8 - STAGE_BYTES && TAIL_AT + 16 * (PIECES - TAIL) <= STAGE_BYTES && CELL_BYTES == 4 * TAIL + 1, "tail of the float layout");
+        fill(0);
+        wave_sync();
+#pragma unroll 5
+        for (int k = 0; k < HEAD / 64; ++k) dst[64 * k] = floats(src[64 * k]);
+        wave_sync();
+        fill(1);
+        float* tail = reinterpret_cast<float*>(stage + TAIL_AT);
+        if (l < NVEC) tail[1 + l] = scalar;
+        if (l >= NVEC) tail[1 + l] = 0.0f;
+        if (l < 4 * (PIECES - TAIL) - 65) tail[65 + l] = 0.0f;
+        if (l == NCELL - 1 - 64) tail[0] = (float)(LIGHT * (il[1] >> 3)) * F32_UNIT;
+        wave_sync();
+#pragma unroll 4
+        for (int k = 0; k < (TAIL - HEAD) / 64; ++k) dst[HEAD + 64 * k] = floats(src[64 * k]);
+        constexpr int LEFT = (TAIL - HEAD) % 64, LAST = TAIL - LEFT;
+        if (l < LEFT) dst[LAST] = floats(src[LAST - HEAD]);
+        if (l < PIECES - TAIL) dst[TAIL] = reinterpret_cast<const float4*>(tail)[l];
+    }
+}
+
+// The same by GW < 64 lanes of a wavefront, whose areas have no room for staged bytes (L_ENV_DWORDS): the
+// one-hot bytes are staged as single bits (a few LDS atomics per cell) next to a light level per cell;
+// every lane then expands 16 bits at a time into one 16-byte piece of the output.
 // GW: lanes that render this environment (see Lanes); l: the calling lane's number among them.
 template <bool F32, int GW = 64>
 __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int wx0, const int wy0, const int m_alive, const int m_x,
                                   const int m_y, const int m_type, const Luts* __restrict__ luts, uint8_t* __restrict__ out,
                                   const RenderAux<GW>* aux = nullptr)
 {
+    if constexpr (GW == 64) { render_staged<F32>(l, e, wx0, wy0, m_alive, m_x, m_y, m_type, luts, out, aux); return; } else {
     using G = Lanes<GW>;
     const uint32_t* rec = e + L_REC;
     const uint8_t* wb = reinterpret_cast<const uint8_t*>(e + L_WB);
@@ -191,9 +314,8 @@ __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int w
         }
     };
     if (!F32) {
-        constexpr int PIECE_UNROLL = GW == 64 ? 9 : 3;
-        uint4* dst = reinterpret_cast<uint4*>(out);
-#pragma unroll PIECE_UNROLL
+                uint4* dst = reinterpret_cast<uint4*>(out);
+#pragma unroll 3
         for (int it = 0; it < (STRIDE_U8 / 16 + GW - 1) / GW; ++it) {
             const int j = l + GW * it;
             if (j < STRIDE_U8 / 16) {
@@ -237,6 +359,7 @@ __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int w
                 dst[4 * j + q] = make_float4(v[0], v[1], v[2], v[3]);
             }
         }
+    }
     }
 }
 
