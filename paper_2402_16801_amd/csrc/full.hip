@@ -30,13 +30,6 @@ constexpr int RESET_SLOTS = 64;    // environments served at once by kf_reset_li
 constexpr int MAX_ENVS_PER_STEP_BLOCK = 16;   // a step block holds 4 environments (a wavefront each) or 16 (16 lanes each)
 constexpr int REGEN_BLOCKS = 256;  // regeneration blocks at the head of the step grid: with 1,024 step blocks (4,096 environments) they fill the chip exactly
 
-__device__ inline uint32_t pack_regs(const MobRegs& m)
-{
-    Mob o;
-    o.alive = m.alive; o.x = m.x; o.y = m.y; o.dir = m.dir; o.hp = m.hp; o.cd = m.cd; o.type = m.type;
-    return pack_mob(o);
-}
-
 // What the block that generated floor 0 of a world leaves behind for the environment: as the
 // current world (fresh record, empty mob tables) or as the spare world (its ladders and potion map).
 // SAME_EPISODE: the record already holds this episode and seed (blocks of other floors may be reading
@@ -231,7 +224,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         uint32_t list_at = 0u;
         int floor_now = P.floor;
         if (!o.done) {
-            if (l == 0) pack_player(e + L_REC, P);
+            if (l == 0) pack_player(e + L_REC, P, o.t);
             if (l < NPLANT) e[L_REC + R_PLANT + l] = qw;
             wave_sync();
         } else {
@@ -275,10 +268,10 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         if (write_back) {
 #pragma unroll
             for (int it = 0; it < REC_IT; ++it) if (l + GW * it < REC_DWORDS) genv[l + GW * it] = e[L_REC + l + GW * it];
-            if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? pack_regs(m) : 0u;
+            if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
             if (obs != nullptr) {
                 aux.day = o.done ? day_fresh : day_next;
-                render_env<F32, GW>(l, e, o.wx0, o.wy0, m.alive, m.x, m.y, m.type, luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux);
+                render_env<F32, GW>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux);
             }
         }
         if (queued && l == 0) la::commit_entry(ls, seq, step_block, list_at, make_uint4((uint32_t)env, lo, hi, ep + 2u));
@@ -372,7 +365,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
         for (int aw = 0; aw < 3; ++aw) count_unlocks<64>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, aw, o.unlocked[aw]);
         int floor_now = P.floor;
         if (!o.done) {
-            if (l == 0) pack_player(e + L_REC, P);
+            if (l == 0) pack_player(e + L_REC, P, o.t);
             if (l < NPLANT) e[L_REC + R_PLANT + l] = qw;
             wave_sync();
         } else {
@@ -397,10 +390,10 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
             floor_now = 0;
             o.wx0 = W / 2 - WIN_COLS / 2; o.wy0 = W / 2 - WIN_ROWS / 2;
         }
-        if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? pack_regs(m) : 0u;
+        if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
         if (obs != nullptr) {
             aux.day = o.done ? day_fresh : day_next;
-            render_env<F32>(l, e, o.wx0, o.wy0, m.alive, m.x, m.y, m.type, luts, obs_t + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux);
+            render_env<F32>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs_t + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux);
         }
         wave_sync();
     }
