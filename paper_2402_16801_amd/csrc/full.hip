@@ -326,13 +326,19 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
     if (threadIdx.x < LUT_FLOATS) s_lut[threadIdx.x] = luts->sqrt10[threadIdx.x];   // sqrt10, tenth and light20 lie one after the other
     __syncthreads();
     bool spare_ok;           // the world of the next episode is complete in the other map slot
+    MobRegs m;               // the mob table of the current floor; in memory it is brought up to date when the player leaves the floor and at the end
+    int action_next;         // fetched a step ahead
     {
         const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
         if (env >= p.n) return;
         uint32_t* e = s_env + w * L_STAGED_DWORDS;
-        e[L_REC + l] = envs[(size_t)env * ENV_DWORDS + l];
+        const uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
+        e[L_REC + l] = genv[l];
+        if (l == 0) e[L_WINKEY] = 0u;
         wave_sync();
         const uint32_t ep = uniu(e[L_REC + R_EPISODE]);
+        m.w = l < NSLOT ? genv[REC_DWORDS + (uniu(e[L_REC + R_POS]) >> 24) * MOBTAB_DWORDS + l] : 0u;
+        action_next = actions[env];
         constexpr uint64_t ALL = (1ull << NTAG) - 1ull;
         spare_ok = (__ballot(l < NTAG && ls.tags[(size_t)env * NTAG + (l < NTAG ? l : 0)].x == ep + 1u) & ALL) == ALL;
     }
@@ -351,19 +357,18 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
         RenderAux<64> aux;
         fetch_scalar_specs<64>(l, aux);
         aux.lut = s_lut;
-        const int action = uni(actions[(size_t)t * p.n + env]);
+        const int action = uni(action_next);
+        if (t + 1 < steps) action_next = actions[(size_t)(t + 1) * p.n + env];
         const uint32_t ep = uniu(e[L_REC + R_EPISODE]);
         // daylight of the state that will be rendered: the next phase, or phase 0 of a fresh episode
         const uint32_t phase_now = uniu(e[L_REC + R_MANA]) >> 16;
         const float day_next = luts->daylight[phase_now + 1u == p.day_length ? 0u : phase_now + 1u], day_fresh = luts->daylight[0];
-        MobRegs m;
         uint32_t qw;
         Player P;
-        StepOut o = step_env(l, (uint32_t)env, e, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, []() {});
+        StepOut o = step_env<64, true>(l, (uint32_t)env, e, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, []() {});
         if (l == 0) { reward[(size_t)t * p.n + env] = o.reward; done[(size_t)t * p.n + env] = o.done ? 1 : 0; }
 #pragma unroll
         for (int aw = 0; aw < 3; ++aw) count_unlocks<64>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, aw, o.unlocked[aw]);
-        int floor_now = P.floor;
         if (!o.done) {
             if (l == 0) pack_player(e + L_REC, P, o.t);
             if (l < NPLANT) e[L_REC + R_PLANT + l] = qw;
@@ -387,10 +392,9 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
             for (int i = l; i < FLOORS * MOBTAB_DWORDS; i += 64) genv[REC_DWORDS + i] = 0u;
             wave_sync();
             clear_mob(m);
-            floor_now = 0;
+            if (l == 0) e[L_WINKEY] = window_key(0, W / 2, W / 2);
             o.wx0 = W / 2 - WIN_COLS / 2; o.wy0 = W / 2 - WIN_ROWS / 2;
         }
-        if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
         if (obs != nullptr) {
             aux.day = o.done ? day_fresh : day_next;
             render_env<F32>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs_t + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux);
@@ -400,7 +404,9 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
     // the record back; the world after this episode, if it is owed, for the regeneration launch
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
     const uint32_t* e = s_env + w * L_STAGED_DWORDS;
-    envs[(size_t)env * ENV_DWORDS + l] = e[L_REC + l];
+    uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
+    genv[l] = e[L_REC + l];
+    if (l < MOBTAB_DWORDS) genv[REC_DWORDS + (uniu(e[L_REC + R_POS]) >> 24) * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
     if (!spare_ok && l == 0)
         la::append_after_step(ls, (uint32_t)env / ENVS_PER_BLOCK, make_uint4((uint32_t)env, e[L_REC + R_SEED_LO], e[L_REC + R_SEED_HI], e[L_REC + R_EPISODE] + 1u));
 }

@@ -332,8 +332,9 @@ constexpr int L_SPARE_WI = 636;                  // 44 dwords: its item/light wi
 constexpr int L_SPARE_TAG = 680;                 // 54 dwords reserved; the 9 (episode, launch) tags of the spare world use 18
 constexpr int L_SPARE_HDR = 734;                 // 10 dwords: ladders and potion map of the spare world
 constexpr int L_ENV_DWORDS = 744;
-// A whole wavefront stages observation bytes from L_STAGE on (see render_staged), over everything but the record.
-constexpr int L_STAGE = 64, L_STAGED_DWORDS = L_STAGE + 5120 / 4;
+// A whole wavefront stages observation bytes from L_STAGE on (see render_staged), over everything but the
+// record and the windows.  L_WINKEY (rollout): what the windows were loaded for (see window_key), or 0.
+constexpr int L_STAGE = 152, STAGE_BYTES = 5120, L_WINKEY = L_STAGE + STAGE_BYTES / 4, L_STAGED_DWORDS = L_WINKEY + 4;
 static_assert(L_STAGED_DWORDS >= L_ENV_DWORDS && L_STAGE % 4 == 0 && L_STAGED_DWORDS % 4 == 0, "staging area");
 constexpr int ENVS_PER_BLOCK = 4, BLOCK = 256;
 

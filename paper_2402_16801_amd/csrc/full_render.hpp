@@ -116,7 +116,7 @@ __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x0020408
 // The observation of one environment by a whole wavefront.  e: its LDS area (L_STAGED_DWORDS) with the
 // packed record (current) and the two windows with origin (wx0, wy0) on the current floor; m_*:
 // this lane's mob slot.  F32 = false: writes the 8448-byte layout; F32 = true: writes float[8268]
-// (+ zero padding to 33152 bytes).  The windows are used up: the bytes are staged over them.
+// (+ zero padding to 33152 bytes).
 //
 // An observation of 8217 cell bytes holds at most 396 that are not zero.  They are set one by one in a
 // cleared LDS area, which the lanes then read back in 16-byte pieces and store as whole cache lines.
@@ -128,7 +128,7 @@ __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x0020408
 // second part, the first one may reach into it.
 // For the float layout a staged byte v stands for v / 140: 140 is the 1 of a one-hot channel and 7 * level
 // the light level / 20.  Multiplying by the float nearest to 1/140 gives exactly those floats.
-constexpr int STAGE_BYTES = (L_STAGED_DWORDS - L_STAGE) * 4, STAGE_REST = CELL_BYTES - STAGE_BYTES;
+constexpr int STAGE_REST = CELL_BYTES - STAGE_BYTES;
 constexpr float F32_UNIT = 1.0f / 140.0f;
 constexpr bool staged_floats_are_exact()
 {
@@ -151,8 +151,7 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     const uint32_t pos = uniu(rec[R_POS]);
     const int px = pos & 0xFF, py = (pos >> 8) & 0xFF;
     const int corner = (py - VROWS / 2 - wy0) * WIN_PITCH + px - VCOLS / 2 - wx0;    // upper left cell of the view in the windows
-    // everything the staging area is about to cover goes to registers first; beyond the edge of the
-    // map the windows hold B_OOB at full light
+    // beyond the edge of the map the windows hold B_OOB at full light
     uint32_t il[2], block[2];
 #pragma unroll
     for (int it = 0; it < 2; ++it) {

@@ -141,9 +141,14 @@ enum Intent : int { N_NONE = 0, N_DAMAGE, N_DAMAGE_DIE, N_DIE, N_MOVE, N_SHOOT, 
 
 // e: this wave's LDS area with the record loaded.  genv: the environment's 1024-byte block in
 // HBM.  maps: its floors.  m, qw: this lane's mob slot (current floor) and plant word.
+// KEEP (kernels that keep an environment from step to step): m comes in as the last step left it, and the
+// windows are only loaded if those in LDS are not the ones around the player's current position;
+// every change a step makes to the maps inside the windows is made in the windows too, so kept ones
+// equal fresh ones.
 // after_load: called once the loads of the current window have been issued and stored, before the
 // wave waits for them (the caller parks data it fetched earlier there).
-template <int GW = 64, typename AfterLoad>
+__device__ inline uint32_t window_key(int f, int x, int y) { return 0x80000000u | (uint32_t)x | ((uint32_t)y << 8) | ((uint32_t)f << 16); }
+template <int GW = 64, bool KEEP = false, typename AfterLoad>
 __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uint32_t* e, uint32_t* __restrict__ genv,
                                    uint8_t* __restrict__ maps, const Luts* __restrict__ luts, const int action_in,
                                    const Params& p, MobRegs& m, uint32_t& qw, Player& P, AfterLoad&& after_load)
@@ -163,16 +168,17 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
     auto misc = [&](int i) { return (uint32_t)G::get((int)rnd.w[3], i); };
 
     // mob table of the current floor and the window around the player
-    {
-        m.w = l < NSLOT ? genv[REC_DWORDS + P.floor * MOBTAB_DWORDS + l] : 0u;
-    }
+    if (!KEEP) m.w = l < NSLOT ? genv[REC_DWORDS + P.floor * MOBTAB_DWORDS + l] : 0u;
     qw = l < NPLANT ? rec[R_PLANT + l] : 0u;
     int q_alive = qw & 1u, q_x = (qw >> 1) & 63u, q_y = (qw >> 7) & 63u, q_age = (int)(qw >> 16);
     // block under every plant (floor 0), fetched before anything is stored this step
     int q_block = B_INVALID;
     if (q_alive) q_block = maps[block_off(0, q_x, q_y)];
     int wx0 = P.px - WIN_COLS / 2, wy0 = P.py - WIN_ROWS / 2;
-    load_window<GW>(l, maps, P.floor, P.px, P.py, wb, wi);
+    if (!KEEP || G::uniu(e[L_WINKEY]) != window_key(P.floor, P.px, P.py)) {
+        load_window<GW>(l, maps, P.floor, P.px, P.py, wb, wi);
+        if (KEEP && l == 0) e[L_WINKEY] = window_key(P.floor, P.px, P.py);
+    }
     after_load();
     wave_sync();
 
@@ -280,6 +286,7 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
         wave_sync();
         wx0 = x - WIN_COLS / 2; wy0 = y - WIN_ROWS / 2;
         load_window<GW>(l, maps, nf, x, y, wb, wi);
+        if (KEEP && l == 0) e[L_WINKEY] = window_key(nf, x, y);
         wave_sync();
     };
     auto stock = [&](int item, int n) { const int have = P.inv.get(item); P.inv.add(item, min(INV_MAX, have + n) - have); };
