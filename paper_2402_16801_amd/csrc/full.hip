@@ -42,15 +42,17 @@ __device__ inline void publish_world(uint32_t* __restrict__ genv, const GenLayou
     if (tid < FLOORS + 1) s_layout_words[tid] = layout_word(L, tid);
     __syncthreads();
     if (current) {
-        const bool identity = tid == R_EPISODE || tid == R_SEED_LO || tid == R_SEED_HI;
-        if (tid < SPARE_LADDER && !(SAME_EPISODE && identity)) genv[tid] = tid < REC_DWORDS ? fresh_record_word(tid, s_layout_words, lo, hi, ep) : 0u;
+        for (int i = tid; i < SPARE_LADDER; i += blockDim.x) {
+            const bool identity = i == R_EPISODE || i == R_SEED_LO || i == R_SEED_HI;
+            if (!(SAME_EPISODE && identity)) genv[i] = i < REC_DWORDS ? fresh_record_word(i, s_layout_words, lo, hi, ep) : 0u;
+        }
     } else if (tid < FLOORS + 1) genv[SPARE_LADDER + tid] = s_layout_words[tid];
 }
 
 // ---------------------------------------------------------------------------------------------
 // reset of every environment: one block per (environment, episode 0 or 1, floor)
-template <bool PERLIN>
-__global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_reset(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
+template <bool PERLIN, int NT>
+__global__ __launch_bounds__(NT, PERLIN ? 6 : 8) void kf_reset(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                        const uint64_t* __restrict__ seeds, Lists ls, const uint32_t* __restrict__ perlin_cs,
                                                        int pool, uint32_t* __restrict__ unlocks)
 {
@@ -62,9 +64,9 @@ __global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_reset(uint32_t
     const int f = blockIdx.x % FLOORS;
     const uint64_t seed = seeds[env];
     const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
-    worldgen_floor_block<GEN_THREADS, PERLIN>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, perlin_cs);
+    worldgen_floor_block<NT, PERLIN>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, perlin_cs);
     if (f == 0) publish_world(envs + (size_t)env * ENV_DWORDS, s_layout, lo, hi, ep, ep == 0u, s_words);
-    if (f == 0 && ep == 0u && threadIdx.x < UNLOCK_STRIDE) unlocks[(size_t)env * UNLOCK_STRIDE + threadIdx.x] = 0u;
+    if (f == 0 && ep == 0u) for (int i = threadIdx.x; i < UNLOCK_STRIDE; i += NT) unlocks[(size_t)env * UNLOCK_STRIDE + i] = 0u;
     // With optimistic resets no spare world is ever valid: tag 0 matches no next episode (they count
     // from 1), so the step kernel hands every finished episode to kf_reset_list.
     if (ep == 1u && threadIdx.x == 0) ls.tags[(size_t)env * NTAG + f] = make_uint2(pool ? 0u : 1u, 0u);
@@ -103,14 +105,13 @@ static_assert(REGEN_PREFIX_AT + NSUB <= ENVS_PER_BLOCK * L_ENV_DWORDS, "regenera
 // A launch of regeneration blocks only (before and after a rollout): generates every world on the
 // lists and empties them, with the bookkeeping of a step launch that has no step blocks.  A kernel
 // of its own, at the occupancy of the generator instead of that of the step kernel.
-constexpr int DRAIN_BLOCKS = 1536;   // six blocks of five wavefronts on each of 256 compute units
-template <bool PERLIN>
-__global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_drain(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
+template <bool PERLIN, int NT>
+__global__ __launch_bounds__(NT, PERLIN ? 6 : 8) void kf_drain(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
 {
     __shared__ WorldScratch s_gen;
     __shared__ uint32_t s_prefix[NSUB];
     const la::Ticket ticket = la::enter_launch_queue(ls, s_prefix);
-    regeneration_queue<GEN_THREADS, PERLIN>(envs, maps, ls, ticket.seq, s_gen, s_prefix, (int)gridDim.x, luts->perlin_cs);
+    regeneration_queue<NT, PERLIN>(envs, maps, ls, ticket.seq, s_gen, s_prefix, (int)gridDim.x, luts->perlin_cs);
     la::leave_launch(ls, ticket);
 }
 
@@ -510,7 +511,8 @@ __device__ inline int theta_offset(int f)
 {
     return f == 0 ? 0 : LAT0_U16 + LATC_U16 * (f == 2 ? 0 : (f == 5 ? 1 : (f == 6 ? 2 : 3)));
 }
-__global__ __launch_bounds__(GEN_THREADS, 6) void kf_mutate_noise(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts,
+template <int NT>
+__global__ __launch_bounds__(NT, 6) void kf_mutate_noise(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts,
                                                                 uint16_t* __restrict__ theta, int first, uint32_t k0, uint32_t k1,
                                                                 uint32_t round, uint32_t amplitude)
 {
@@ -523,11 +525,11 @@ __global__ __launch_bounds__(GEN_THREADS, 6) void kf_mutate_noise(uint32_t* __re
     uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
     const uint32_t ep = genv[R_EPISODE], lo = genv[R_SEED_LO], hi = genv[R_SEED_HI];
     const bool noisy = f == 0 || is_cave(f);
-    if (tid < LAT_TOTAL) {
+    for (int k = tid; k < LAT_TOTAL; k += NT) {
         uint16_t v = 0;
         const int len = f == 0 ? LAT0_U16 : LATC_U16;
-        if (noisy && tid < len) {
-            const int i = theta_offset(f) + tid;
+        if (noisy && k < len) {
+            const int i = theta_offset(f) + k;
             uint16_t* th = theta + (size_t)slot * CRAFTAX_FULL_THETA_LEN + i;
             const cx::U4 d = cx::philox4x32_10(env, round, 1u, (cx::DOM_MUTATE << 16) | (uint32_t)(i >> 3), k0, k1);
             const uint32_t w = d.w[(i >> 1) & 3], d16 = (i & 1) ? (w >> 16) : (w & 0xFFFFu);
@@ -535,10 +537,10 @@ __global__ __launch_bounds__(GEN_THREADS, 6) void kf_mutate_noise(uint32_t* __re
             v = (uint16_t)(((int)(*th & 1023u) + u) & 1023);
             *th = v;
         }
-        s_theta[tid] = v;
+        s_theta[k] = v;
     }
     __syncthreads();
-    worldgen_floor_block<GEN_THREADS, true>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr,
+    worldgen_floor_block<NT, true>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr,
                                             luts->perlin_cs, noisy ? s_theta : nullptr);
     if (f == 0) publish_world<true>(genv, s_layout, lo, hi, ep, true, s_words);
 }
@@ -606,12 +608,13 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_export(const uint32_t* __restr
 }
 
 // The record of an import (all threads of the block call).
+template <int NT>
 __device__ inline void import_record(uint32_t* __restrict__ r, const Lists& ls, uint32_t env, const craftax_full_env_dump* __restrict__ d, const Params& p)
 {
     __shared__ uint32_t s[ENV_DWORDS];
     const int tid = threadIdx.x;
     la::cancel_entries(ls, env);   // whatever was queued for this environment belongs to the episode that is being replaced
-    if (tid < ENV_DWORDS) s[tid] = 0u;
+    for (int i = tid; i < ENV_DWORDS; i += NT) s[i] = 0u;
     __syncthreads();
     if (tid == 0) {
         s[R_POS] = (uint32_t)min((int)d->px, W - 1) | ((uint32_t)min((int)d->py, W - 1) << 8) | ((uint32_t)(d->dir & 7) << 16) |
@@ -645,20 +648,20 @@ __device__ inline void import_record(uint32_t* __restrict__ r, const Lists& ls, 
         s[R_T] = d->t; s[R_EPISODE] = d->episode;
         s[R_SEED_LO] = (uint32_t)d->seed; s[R_SEED_HI] = (uint32_t)(d->seed >> 32);
     }
-    if (tid < FLOORS * NSLOT) {
-        const int f = tid / NSLOT, k = tid - f * NSLOT;
+    for (int i = tid; i < FLOORS * NSLOT; i += NT) {
+        const int f = i / NSLOT, k = i - f * NSLOT;
         const craftax_full_mob u = d->mob[f][k];
         Mob m;
         m.alive = u.alive & 1; m.x = min((int)u.x, W - 1); m.y = min((int)u.y, W - 1); m.dir = u.dir & 7; m.hp = max(0, min(31, (int)u.hp)); m.cd = min(15, (int)u.cd);
         m.type = min((int)u.type, 18);
         s[REC_DWORDS + f * MOBTAB_DWORDS + k] = pack_mob(m);
     }
-    if (tid >= 128 && tid < 128 + NPLANT) {
-        const craftax_plant u = d->plant[tid - 128];
-        s[R_PLANT + tid - 128] = (u.alive & 1) ? (1u | ((uint32_t)min((int)u.x, W - 1) << 1) | ((uint32_t)min((int)u.y, W - 1) << 7) | ((uint32_t)u.age << 16)) : 0u;
+    if (tid < NPLANT) {
+        const craftax_plant u = d->plant[tid];
+        s[R_PLANT + tid] = (u.alive & 1) ? (1u | ((uint32_t)min((int)u.x, W - 1) << 1) | ((uint32_t)min((int)u.y, W - 1) << 7) | ((uint32_t)u.age << 16)) : 0u;
     }
     __syncthreads();
-    if (tid < SPARE_LADDER) r[tid] = s[tid];   // the spare world's description follows
+    for (int i = tid; i < SPARE_LADDER; i += NT) r[i] = s[i];   // the spare world's description follows
 }
 
 // Import packs into the record's bit fields: counts 0..99, vitals 0..31, counters -128..127, mob
@@ -669,8 +672,8 @@ __device__ inline void import_record(uint32_t* __restrict__ r, const Lists& ls, 
 // of the next episode into the spare slot, so that the copy of some blocks overlaps the arithmetic of
 // others; the block of floor 0 also packs the record.  (A copy byte by byte and a second launch for
 // the spare worlds: 50 + 87 us for 1,000 Perlin worlds, now 101.)
-template <bool PERLIN>
-__global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
+template <bool PERLIN, int NT>
+__global__ __launch_bounds__(NT, PERLIN ? 6 : 8) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
                                                                         const craftax_full_env_dump* __restrict__ dumps, int first, Params p,
                                                                         const uint32_t* __restrict__ perlin_cs, int pool)
 {
@@ -679,8 +682,9 @@ __global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_import(uint32_
     const craftax_full_env_dump* d = dumps + slot;
     const uint32_t lo = (uint32_t)d->seed, hi = (uint32_t)(d->seed >> 32), ep = d->episode;
     uint32_t* r = envs + (size_t)env * ENV_DWORDS;
-    if (tid < RUNS) {
-        const uint2 b = load8(d->block[floor] + tid * RUN), it = load8(d->item[floor] + tid * RUN), light = load8(d->light[floor] + tid * RUN);
+#pragma unroll 2
+    for (int run = tid; run < RUNS; run += NT) {
+        const uint2 b = load8(d->block[floor] + run * RUN), it = load8(d->item[floor] + run * RUN), light = load8(d->light[floor] + run * RUN);
         auto blocks = [](uint32_t four) {
             uint32_t out = 0u;
 #pragma unroll
@@ -696,12 +700,12 @@ __global__ __launch_bounds__(GEN_THREADS, PERLIN ? 6 : 8) void kf_import(uint32_
             }
             return out;
         };
-        uint8_t* em = maps + map_offset((uint32_t)env, ep) + (size_t)floor * 2 * CELLS + tid * RUN;
+        uint8_t* em = maps + map_offset((uint32_t)env, ep) + (size_t)floor * 2 * CELLS + run * RUN;
         *reinterpret_cast<uint2*>(em) = make_uint2(blocks(b.x), blocks(b.y));
         *reinterpret_cast<uint2*>(em + CELLS) = make_uint2(items(it.x, light.x), items(it.y, light.y));
     }
-    if (floor == 0) import_record(r, ls, (uint32_t)env, d, p);
-    worldgen_floor_block<GEN_THREADS, PERLIN>(maps + map_offset((uint32_t)env, ep + 1u), s_gen.lat, s_gen.layout, lo, hi, (uint32_t)env, ep + 1u, floor, nullptr,
+    if (floor == 0) import_record<NT>(r, ls, (uint32_t)env, d, p);
+    worldgen_floor_block<NT, PERLIN>(maps + map_offset((uint32_t)env, ep + 1u), s_gen.lat, s_gen.layout, lo, hi, (uint32_t)env, ep + 1u, floor, nullptr,
                                               nullptr, perlin_cs);
     if (floor == 0) publish_world(r, s_gen.layout, lo, hi, ep + 1u, false, s_gen.words);
     if (tid == 0) ls.tags[(size_t)env * NTAG + floor] = make_uint2(pool ? 0u : ep + 1u, 0u);
@@ -960,19 +964,23 @@ int check_kernels(const craftax_config* cfg, std::string* err)
         ok = ok && (perlin ? fits("kf_rollout", (const void*)kf_rollout<false, true>, BLOCK) : fits("kf_rollout", (const void*)kf_rollout<false, false>, BLOCK));
         ok = ok && fits("kf_reset_list", (const void*)kf_reset_list<false>, GEN_THREADS) && fits("kf_observe", (const void*)kf_observe<false>, BLOCK);
     }
-    ok = ok && fits("kf_drain", perlin ? (const void*)kf_drain<true> : (const void*)kf_drain<false>, GEN_THREADS);
-    ok = ok && fits("kf_reset", perlin ? (const void*)kf_reset<true> : (const void*)kf_reset<false>, GEN_THREADS) && fits("kf_pixels", (const void*)kf_pixels, BLOCK);
+    ok = ok && fits("kf_drain", perlin ? (const void*)kf_drain<true, GEN_THREADS> : (const void*)kf_drain<false, GEN_THREADS>, GEN_THREADS);
+    ok = ok && fits("kf_reset", perlin ? (const void*)kf_reset<true, GEN_THREADS> : (const void*)kf_reset<false, GEN_THREADS>, GEN_THREADS) && fits("kf_pixels", (const void*)kf_pixels, BLOCK);
     return ok ? CRAFTAX_OK : CRAFTAX_E_CONFIG;
 }
+
+// is this number of worlds generated by blocks of GEN_THREADS (else by single wavefronts)?
+static bool few_floors(long long worlds) { return worlds * FLOORS <= FEW_FLOORS; }
 
 int reset(void* state, const craftax_config* cfg, int n, const uint64_t* seeds, void* stream, std::string* err)
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)n * 2 * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, seeds, q.ls, gradients(cfg, q),
+    auto go = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n * 2 * FLOORS), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, seeds, q.ls, gradients(cfg, q),
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0, make_params(state, cfg, n).unlocks);
     };
-    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) go(kf_reset<true>); else go(kf_reset<false>);
+    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) { if (few_floors(2ll * n)) go(kf_reset<true, GEN_THREADS>, GEN_THREADS); else go(kf_reset<true, FLOOR_THREADS>, FLOOR_THREADS); }
+    else { if (few_floors(2ll * n)) go(kf_reset<false, GEN_THREADS>, GEN_THREADS); else go(kf_reset<false, FLOOR_THREADS>, FLOOR_THREADS); }
     return check_launch("craftax_reset", err);
 }
 
@@ -1051,14 +1059,21 @@ int rollout(void* state, const craftax_config* cfg, int n, const int32_t* action
     uint8_t* o = static_cast<uint8_t*>(obs);
     const dim3 grid((unsigned)((n + ENVS_PER_BLOCK - 1) / ENVS_PER_BLOCK));
     const bool perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN;
-    auto drain = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)std::min((long long)DRAIN_BLOCKS, (long long)FLOORS * n)), dim3(GEN_THREADS), 0, st, q.envs, q.maps, q.luts, q.ls); };
+    auto launch_drain = [&](auto kernel, int threads, long long blocks) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(blocks, (long long)FLOORS * n)), dim3((unsigned)threads), 0, st, q.envs, q.maps, q.luts, q.ls);
+    };
+    // sixteen single wavefronts on each of 256 compute units, or six blocks
+    auto drain = [&]() {
+        if (few_floors(n)) { if (perlin) launch_drain(kf_drain<true, GEN_THREADS>, GEN_THREADS, 1536); else launch_drain(kf_drain<false, GEN_THREADS>, GEN_THREADS, 1536); }
+        else { if (perlin) launch_drain(kf_drain<true, FLOOR_THREADS>, FLOOR_THREADS, 4096); else launch_drain(kf_drain<false, FLOOR_THREADS>, FLOOR_THREADS, 4096); }
+    };
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, st, q.envs, q.maps, q.luts, actions, o, reward, done, q.ls, p, steps); };
     // launches of regeneration blocks only: the worlds still owed by the step kernel, and afterwards
     // those of the episodes that ended in the rollout
-    if (perlin) drain(kf_drain<true>); else drain(kf_drain<false>);
+    drain();
     if (cfg->obs_mode == CRAFTAX_OBS_SYM_F32) { if (perlin) go(kf_rollout<true, true>); else go(kf_rollout<true, false>); }
     else { if (perlin) go(kf_rollout<false, true>); else go(kf_rollout<false, false>); }
-    if (perlin) drain(kf_drain<true>); else drain(kf_drain<false>);
+    drain();
     return check_launch("craftax_rollout", err);
 }
 
@@ -1084,12 +1099,13 @@ int export_envs(const void* state, const craftax_config* cfg, int n, int first, 
 int import_envs(void* state, const craftax_config* cfg, int n, int first, int count, const void* dumps, void* stream, std::string* err)
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.ls,
+    auto go = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, q.ls,
                            static_cast<const craftax_full_env_dump*>(dumps), first, make_params(state, cfg, n), gradients(cfg, q),
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0);
     };
-    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) go(kf_import<true>); else go(kf_import<false>);
+    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) { if (few_floors(count)) go(kf_import<true, GEN_THREADS>, GEN_THREADS); else go(kf_import<true, FLOOR_THREADS>, FLOOR_THREADS); }
+    else { if (few_floors(count)) go(kf_import<false, GEN_THREADS>, GEN_THREADS); else go(kf_import<false, FLOOR_THREADS>, FLOOR_THREADS); }
     return check_launch("craftax_import_envs", err);
 }
 
@@ -1107,8 +1123,11 @@ int mutate_noise(void* state, const craftax_config* cfg, int n, int first, int c
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
     const uint32_t k0 = (uint32_t)mutation_seed, k1 = (uint32_t)(mutation_seed >> 32);
-    hipLaunchKernelGGL(kf_mutate_noise, dim3((unsigned)count * FLOORS), dim3(GEN_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, theta,
-                       first, k0, k1, round, amplitude);
+    auto go = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, theta, first, k0, k1,
+                           round, amplitude);
+    };
+    if (few_floors(count)) go(kf_mutate_noise<GEN_THREADS>, GEN_THREADS); else go(kf_mutate_noise<FLOOR_THREADS>, FLOOR_THREADS);
     return check_launch("craftax_mutate_noise", err);
 }
 
