@@ -372,8 +372,8 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
             case B_NECRO_VULN: {
                 // section "Boss Floor": every hit calls the next wave; eight hits win
                 unlock(P, H_DAMAGE_NECROMANCER);
-                const int hits = (int)P.f.boss_hits + 1;
-                P.f.boss_hits = (uint32_t)hits & 15u;
+                const int hits = min((int)P.f.boss_hits + 1, 15);   // the field's largest value: an import may bring it, and won stays won
+                P.f.boss_hits = (uint32_t)hits;
                 P.f.boss_vulnerable = 0;
                 if (hits >= BOSS_HITS) { unlock(P, H_DEFEAT_NECROMANCER); set_facing_block(tx, ty, B_PATH); break; }
                 set_facing_block(tx, ty, B_NECROMANCER);

@@ -225,6 +225,31 @@ def test_full_import_brings_out_of_range_values_into_range(cx):
     sim.close()
 
 
+@pytest.mark.parametrize("lanes", [64, 16])
+def test_full_boss_hit_count_stays_at_its_maximum(cx, lanes):
+    """The record holds 0..15 hits on the necromancer; a winning hit on an imported state that is
+    already there must not start the count over, which would bring the necromancer back."""
+    n, do = 8, 5
+    gcfg = cx.default_config(cx.VARIANT_CRAFTAX, group_lanes=lanes)
+    sim, orc = cx.Craftax(n, gcfg), po.FullOracle(n, po.full_default_config(), po.FULL_OBS_U8_F32)
+    seeds = synth.seeds_for(n, 31)
+    sim.reset(seeds); orc.reset(seeds)
+    e = orc.envs
+    e["floor"], e["px"], e["py"], e["dir"] = 8, 24, 7, 3      # below the necromancer, facing it
+    e["visited"] = 0x1FF
+    e["boss_hits"], e["boss_vulnerable"] = np.arange(8, 16), 1
+    sim.import_envs(orc.envs.copy())
+    for s, a in enumerate((do, 0, do, 0, 0)):
+        _step_both(sim, orc, np.full(n, a, np.int32), f"step {s}")
+        want = orc.envs.copy()
+        want["boss_hits"] = np.minimum(want["boss_hits"], 15)
+        got = sim.export_envs().view(po.FULL_ENV_DTYPE).reshape(-1)
+        for name in po.FULL_ENV_DTYPE.names:
+            assert np.array_equal(got[name], want[name]), (s, name)
+    assert (orc.envs["block"][:, 8, 6, 24] == 7).all()        # the necromancer's cell has become a path
+    sim.close()
+
+
 @pytest.mark.parametrize("variant,n,lanes", [("classic", 6000, 0), ("classic", 6000, 4), ("craftax", 3000, 0)])
 def test_death_on_the_first_step_after_an_auto_reset_and_a_swap(cx, variant, n, lanes):
     """Every environment resets in the same step (equal caps); right after that step the swap
