@@ -180,6 +180,8 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
         for (int k = 0; k < STAGE_BYTES / 1024; ++k) if (part == 0 || k * 1024 < STRIDE_U8 - STAGE_BYTES) clear[64 * k] = make_uint4(0u, 0u, 0u, 0u);
         wave_sync();
         auto put = [&](uint32_t at, uint32_t v) { if (at - first < size) stage[CX_IDX(at - first, STAGE_BYTES)] = (uint8_t)v; };
+        put(m_byte, ONE);       // before the cells: an imported creature type may fall on a light channel, which holds the light level all the same
+        wave_sync();
 #pragma unroll
         for (int it = 0; it < 2; ++it) {
             if (it == 1 && part == 0) continue;
@@ -190,7 +192,6 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
                 put(base + 82u, LIGHT * (il[it] >> 3));
             }
         }
-        put(m_byte, ONE);
     };
     if (!F32) {
         typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
@@ -296,7 +297,7 @@ __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int w
                     set_bit(cell * NCHAN + (wb[CX_IDX((y - wy0) * WIN_PITCH + (x - wx0), WIN_ROWS * WIN_PITCH)] & 63));
                     set_bit(cell * NCHAN + 37 + (il & 7));
                     const uint32_t cr = cre[cell];
-                    if (cr != 0xFFFFFFFFu) set_bit(cell * NCHAN + (int)(cr & 0xFFu));
+                    if (cr != 0xFFFFFFFFu && (cr & 0xFFu) != 82u) set_bit(cell * NCHAN + (int)(cr & 0xFFu));   // channel 82 is the light level, whatever type was imported
                 }
             }
             light[cell] = (uint8_t)lv;

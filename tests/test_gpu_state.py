@@ -250,6 +250,32 @@ def test_full_boss_hit_count_stays_at_its_maximum(cx, lanes):
     sim.close()
 
 
+@pytest.mark.parametrize("lanes", [64, 16])
+@pytest.mark.parametrize("layout", ["u8_f32", "f32"])
+def test_full_light_channel_holds_the_light_level_whatever_stands_there(cx, lanes, layout):
+    """An import accepts every creature type in every slot.  Type 8 among the player's projectiles
+    falls on channel 82 of its cell, which is the cell's light level all the same."""
+    n = 21
+    g_mode, o_mode = {"u8_f32": (cx.OBS_SYM_U8_F32, po.FULL_OBS_U8_F32), "f32": (cx.OBS_SYM_F32, po.FULL_OBS_F32)}[layout]
+    sim = cx.Craftax(n, cx.default_config(cx.VARIANT_CRAFTAX, obs_mode=g_mode, group_lanes=lanes))
+    orc = po.FullOracle(n, po.full_default_config(), o_mode)
+    seeds = synth.seeds_for(n, 12)
+    sim.reset(seeds); orc.reset(seeds)
+    orc.envs["block"][:, 0, 18:31, 16:33] = GRASS
+    places = ((25, 24, 2), (20, 22, 3), (28, 27, 1))       # cells 50, 23 and 86 of the view, flying on
+    for i in range(n):
+        orc.envs["light"][i, 0] = i                        # from dark to full light
+        for k, (x, y, d) in enumerate(places):
+            orc.envs["mob"][i, 0, 11 + k] = (1, x, y, d, 0, 0, 8, 0)
+    sim.import_envs(orc.envs.copy())
+    cx.craftax_observe(sim.state, sim.obs, n, sim.stream)
+    assert np.array_equal(sim.obs.cpu().numpy(), orc.observe()), "observation after the import"
+    for s in range(3):
+        _step_both(sim, orc, np.zeros(n, np.int32), f"step {s}")
+    assert sim.export_envs().tobytes() == orc.envs.tobytes()
+    sim.close()
+
+
 @pytest.mark.parametrize("variant,n,lanes", [("classic", 6000, 0), ("classic", 6000, 4), ("craftax", 3000, 0)])
 def test_death_on_the_first_step_after_an_auto_reset_and_a_swap(cx, variant, n, lanes):
     """Every environment resets in the same step (equal caps); right after that step the swap
