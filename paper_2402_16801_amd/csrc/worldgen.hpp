@@ -184,7 +184,7 @@ constexpr int LAT_WORDS = LAT_AT8 + (LAT_BLOCKS * 8 - 2 * LAT16_N) + 2;
 // (section "Craftax-1B: UED"): every gradient angle, the upper ten bits of its lattice number, is
 // turned by theta[i] 1024ths of a turn.
 constexpr int WG_THREADS = 512, STRIPS = MAPW / 8;
-template <int NT = WG_THREADS, bool PERLIN = false>
+template <int NT = WG_THREADS, bool PERLIN = false, bool UNROLLED = false>
 __device__ __forceinline__ void worldgen_block(uint8_t* __restrict__ map, uint32_t* s_lat, uint32_t seed_lo, uint32_t seed_hi,
                                       uint32_t env, uint32_t episode, uint32_t* start_win = nullptr, int first_strip = 0,
                                       const uint32_t* __restrict__ perlin_cs = nullptr, const uint16_t* theta = nullptr)
@@ -234,9 +234,10 @@ __device__ __forceinline__ void worldgen_block(uint8_t* __restrict__ map, uint32
         four |= (uint32_t)b << (8 * (j & 3));
     };
     // The run in two halves of four cells, a loop that is not unrolled: half the code, and few enough
-    // registers for the step kernels, which hold an environment's record meanwhile.
+    // registers for the kernels that hold an environment's record meanwhile.  UNROLLED: for blocks that
+    // generate one world after the other and last as long as the chain of a run (regeneration_block).
     auto halves = [&](auto&& cell) {
-#pragma unroll 1
+#pragma unroll (UNROLLED ? 2 : 1)
         for (int h = 0; h < 8; h += 4) {
             first = four;
             four = 0u;
