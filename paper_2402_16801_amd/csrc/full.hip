@@ -722,6 +722,7 @@ __device__ inline int swap_group(int b)
     if (b == B_GRASS || b == B_TREE) return 2;
     return 0;
 }
+constexpr int MUTATE_SWAP_THREADS = 256;
 __global__ void kf_mutate_swap(const uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, int first, int count, uint32_t k0,
                                uint32_t k1, uint32_t round, int restricted, int32_t* __restrict__ tries)
 {
@@ -936,6 +937,23 @@ RecordLayout record_layout(const void* state, const craftax_config* cfg, int n)
     return RecordLayout{q.envs, ENV_DWORDS, R_ACH, 3, R_T, R_EPISODE, make_params(state, cfg, n).unlocks, UNLOCK_STRIDE};
 }
 
+// Every kernel that is launched for a layout and a noise, with the block sizes it is launched with.
+template <bool F32, bool PERLIN, typename Fits>
+static bool kernels_fit(const Fits& fits)
+{
+    auto step = [&](const char* name, const void* eager, const void* plain) { return fits(name, eager, BLOCK) && fits(name, plain, BLOCK); };
+    auto floors = [&](const char* name, const void* blocks, const void* wavefronts) { return fits(name, blocks, GEN_THREADS) && fits(name, wavefronts, FLOOR_THREADS); };
+    return step("kf_step", (const void*)kf_step<F32, true, PERLIN, 64>, (const void*)kf_step<F32, false, PERLIN, 64>) &&
+           step("kf_step (16 lanes)", (const void*)kf_step<F32, true, PERLIN, 16>, (const void*)kf_step<F32, false, PERLIN, 16>) &&
+           fits("kf_rollout", (const void*)kf_rollout<F32, PERLIN>, BLOCK) && fits("kf_reset_list", (const void*)kf_reset_list<F32>, GEN_THREADS) &&
+           fits("kf_observe", (const void*)kf_observe<F32>, BLOCK) && fits("kf_pixels", (const void*)kf_pixels, BLOCK) &&
+           floors("kf_reset", (const void*)kf_reset<PERLIN, GEN_THREADS>, (const void*)kf_reset<PERLIN, FLOOR_THREADS>) &&
+           floors("kf_drain", (const void*)kf_drain<PERLIN, GEN_THREADS>, (const void*)kf_drain<PERLIN, FLOOR_THREADS>) &&
+           floors("kf_import", (const void*)kf_import<PERLIN, GEN_THREADS>, (const void*)kf_import<PERLIN, FLOOR_THREADS>) &&
+           (!PERLIN || floors("kf_mutate_noise", (const void*)kf_mutate_noise<GEN_THREADS>, (const void*)kf_mutate_noise<FLOOR_THREADS>)) &&
+           fits("kf_export", (const void*)kf_export, GEN_THREADS) && fits("kf_mutate_swap", (const void*)kf_mutate_swap, MUTATE_SWAP_THREADS);
+}
+
 int check_kernels(const craftax_config* cfg, std::string* err)
 {
     int dev = 0, lds = 0, threads = 0;
@@ -952,20 +970,8 @@ int check_kernels(const craftax_config* cfg, std::string* err)
         return cx::kernel_fits(cx::KernelNeeds{name, a.sharedSizeBytes, a.maxThreadsPerBlock, block}, limits, err);
     };
     const bool perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN;
-    bool ok = true;
-    if (cfg->obs_mode == CRAFTAX_OBS_SYM_F32) {
-        ok = ok && (perlin ? fits("kf_step", (const void*)kf_step<true, true, true, 64>, BLOCK) : fits("kf_step", (const void*)kf_step<true, true, false, 64>, BLOCK));
-        ok = ok && (perlin ? fits("kf_step (16 lanes)", (const void*)kf_step<true, true, true, 16>, BLOCK) : fits("kf_step (16 lanes)", (const void*)kf_step<true, true, false, 16>, BLOCK));
-        ok = ok && (perlin ? fits("kf_rollout", (const void*)kf_rollout<true, true>, BLOCK) : fits("kf_rollout", (const void*)kf_rollout<true, false>, BLOCK));
-        ok = ok && fits("kf_reset_list", (const void*)kf_reset_list<true>, GEN_THREADS) && fits("kf_observe", (const void*)kf_observe<true>, BLOCK);
-    } else {
-        ok = ok && (perlin ? fits("kf_step", (const void*)kf_step<false, true, true, 64>, BLOCK) : fits("kf_step", (const void*)kf_step<false, true, false, 64>, BLOCK));
-        ok = ok && (perlin ? fits("kf_step (16 lanes)", (const void*)kf_step<false, true, true, 16>, BLOCK) : fits("kf_step (16 lanes)", (const void*)kf_step<false, true, false, 16>, BLOCK));
-        ok = ok && (perlin ? fits("kf_rollout", (const void*)kf_rollout<false, true>, BLOCK) : fits("kf_rollout", (const void*)kf_rollout<false, false>, BLOCK));
-        ok = ok && fits("kf_reset_list", (const void*)kf_reset_list<false>, GEN_THREADS) && fits("kf_observe", (const void*)kf_observe<false>, BLOCK);
-    }
-    ok = ok && fits("kf_drain", perlin ? (const void*)kf_drain<true, GEN_THREADS> : (const void*)kf_drain<false, GEN_THREADS>, GEN_THREADS);
-    ok = ok && fits("kf_reset", perlin ? (const void*)kf_reset<true, GEN_THREADS> : (const void*)kf_reset<false, GEN_THREADS>, GEN_THREADS) && fits("kf_pixels", (const void*)kf_pixels, BLOCK);
+    const bool ok = cfg->obs_mode == CRAFTAX_OBS_SYM_F32 ? (perlin ? kernels_fit<true, true>(fits) : kernels_fit<true, false>(fits))
+                                                         : (perlin ? kernels_fit<false, true>(fits) : kernels_fit<false, false>(fits));
     return ok ? CRAFTAX_OK : CRAFTAX_E_CONFIG;
 }
 
@@ -1113,7 +1119,7 @@ int mutate_swap(void* state, const craftax_config* cfg, int n, int first, int co
                 int restricted, int32_t* tries, void* stream, std::string* err)
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
-    hipLaunchKernelGGL(kf_mutate_swap, dim3((unsigned)(((long long)count * cx::MUTATE_TRIES + 255) / 256)), dim3(256), 0, (hipStream_t)stream, q.envs, q.maps, first,
+    hipLaunchKernelGGL(kf_mutate_swap, dim3((unsigned)(((long long)count * cx::MUTATE_TRIES + MUTATE_SWAP_THREADS - 1) / MUTATE_SWAP_THREADS)), dim3(MUTATE_SWAP_THREADS), 0, (hipStream_t)stream, q.envs, q.maps, first,
                        count, (uint32_t)mutation_seed, (uint32_t)(mutation_seed >> 32), round, restricted != 0 ? 1 : 0, tries);
     return check_launch("craftax_mutate_swap", err);
 }

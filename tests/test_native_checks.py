@@ -1,7 +1,9 @@
 """Host-only native checks (no GPU): the oracle's C code under AddressSanitizer and
 UndefinedBehaviorSanitizer, and the unit test of the launch-limit rule the library applies before
 it accepts a state."""
+import itertools
 import os
+import re
 import subprocess
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -48,3 +50,24 @@ def test_launch_limit_rule(tmp_path):
     exe = str(tmp_path / "launch_limits_test")
     _run(["g++", "-O1", "-std=c++17", "-Wall", "-Wextra", "-o", exe, os.path.join(NATIVE, "launch_limits_test.cpp")])
     assert "launch_limits_test: ok" in _run([exe])
+
+
+def _kernel_instances(text):
+    """`kf_name<arguments>` in a piece of the host code, template parameters of the enclosing function as both of their values."""
+    out = set()
+    for name, args in re.findall(r"\b(kf_\w+)\s*(<[^<>;]*>)?", text):
+        args = [a.strip() for a in args.strip("<>").split(",")] if args else []
+        for values in itertools.product(*[("true", "false") if a in ("F32", "PERLIN") else (a,) for a in args]):
+            out.add((name,) + values)
+    return out
+
+
+def test_every_kernel_the_full_game_launches_is_checked_against_the_device():
+    """The full game's host code in csrc/full.hip: every kernel instance it launches is one that a state
+    is refused for if the device cannot launch it."""
+    src = open(os.path.join(ROOT, "paper_2402_16801_amd", "csrc", "full.hip")).read()
+    host = re.sub(r"//[^\n]*", "", src[src.index("namespace host {"):])
+    host = re.sub(r'"[^"\n]*"', "", host)
+    check = re.search(r"static bool kernels_fit\b.*?\n}\n", host, re.S).group(0)
+    asked, launched = _kernel_instances(check), _kernel_instances(host.replace(check, ""))
+    assert len(launched) > 20 and launched <= asked, sorted(launched - asked)
