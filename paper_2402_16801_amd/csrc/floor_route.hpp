@@ -1,0 +1,31 @@
+// Whether floors are generated by blocks of five wavefronts or by single wavefronts (full game).
+//
+// A block makes one pass over the 288 runs of a floor, a single wavefront five; but no wavefront of
+// a block works while the first one lays the floor out.  A few floors last as long as one of them, so
+// blocks are ahead; thousands are a matter of throughput, and single wavefronts are ahead.  The lines
+// lie between measured sizes (us, blocks / single wavefronts):
+//   reset, value noise      288  7.1 / 16.0   3,600 19.6 / 22.3   4,194 21.7 / 22.9   4,788 23.8 / 23.1   6,138 28.6 / 24.5   73,728 263 / 174
+//   import, value noise     288 13.3 / 23.1   3,600 30.8 / 33.6   4,194 33.6 / 34.6   4,797 36.5 / 35.6   6,138 43.6 / 38.0   18,000 114 / 87
+//   reset, Perlin noise     288 11.8 / 27.5   3,600 35.6 / 38.0   4,194 39.7 / 38.8   6,138 53.3 / 44.2
+//     6,144 single wavefronts run at once (six on each of 1,024 SIMDs); a second round costs as much as
+//     the first until it is nearly full:  7,200 61.2 / 65.6   9,720 78.6 / 84.9   11,988 94.3 / 95.0   14,400 111 / 104   73,728 525 / 343
+//   import, Perlin noise    288 18.5 / 34.9   2,592 39.6 / 42.2   3,069 43.2 / 43.1   3,600 48.0 / 46.0   9,720 104 / 97   18,000 191 / 150
+//   noise mutation          288 23.0 / 29.6   1,440 31.3 / 34.2   2,052 36.2 / 34.8   3,069 44.4 / 35.3   9,720  95 / 88   18,000 158 / 121
+// Plain C++ so that the rule itself can be tested without a GPU.
+#pragma once
+
+namespace cf {
+
+enum class FloorWork { RESET, IMPORT, MUTATE, OWED };
+
+inline bool floors_by_blocks(FloorWork work, bool perlin, long long floors)
+{
+    switch (work) {
+    case FloorWork::RESET: return perlin ? floors <= 4000 || (floors > 6144 && floors <= 12000) : floors <= 4500;
+    case FloorWork::IMPORT: return floors <= (perlin ? 3072 : 4500);
+    case FloorWork::MUTATE: return floors <= 1850;     // Perlin worlds only
+    default: return floors <= 3072;
+    }
+}
+
+}  // namespace cf

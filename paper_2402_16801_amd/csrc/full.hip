@@ -1,5 +1,6 @@
 // Kernels and host entry points of the full-Craftax variant (nine floors, 43 actions).
 #include "full_api.hpp"
+#include "floor_route.hpp"
 #include "launch_limits.hpp"
 
 #include <hip/hip_runtime.h>
@@ -975,9 +976,6 @@ int check_kernels(const craftax_config* cfg, std::string* err)
     return ok ? CRAFTAX_OK : CRAFTAX_E_CONFIG;
 }
 
-// is this number of worlds generated by blocks of GEN_THREADS (else by single wavefronts)?
-static bool few_floors(long long worlds) { return worlds * FLOORS <= FEW_FLOORS; }
-
 int reset(void* state, const craftax_config* cfg, int n, const uint64_t* seeds, void* stream, std::string* err)
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
@@ -985,8 +983,9 @@ int reset(void* state, const craftax_config* cfg, int n, const uint64_t* seeds, 
         hipLaunchKernelGGL(kernel, dim3((unsigned)n * 2 * FLOORS), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, seeds, q.ls, gradients(cfg, q),
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0, make_params(state, cfg, n).unlocks);
     };
-    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) { if (few_floors(2ll * n)) go(kf_reset<true, GEN_THREADS>, GEN_THREADS); else go(kf_reset<true, FLOOR_THREADS>, FLOOR_THREADS); }
-    else { if (few_floors(2ll * n)) go(kf_reset<false, GEN_THREADS>, GEN_THREADS); else go(kf_reset<false, FLOOR_THREADS>, FLOOR_THREADS); }
+    const bool perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN, blocks = floors_by_blocks(FloorWork::RESET, perlin, 2ll * n * FLOORS);
+    if (perlin) { if (blocks) go(kf_reset<true, GEN_THREADS>, GEN_THREADS); else go(kf_reset<true, FLOOR_THREADS>, FLOOR_THREADS); }
+    else { if (blocks) go(kf_reset<false, GEN_THREADS>, GEN_THREADS); else go(kf_reset<false, FLOOR_THREADS>, FLOOR_THREADS); }
     return check_launch("craftax_reset", err);
 }
 
@@ -1068,9 +1067,10 @@ int rollout(void* state, const craftax_config* cfg, int n, const int32_t* action
     auto launch_drain = [&](auto kernel, int threads, long long blocks) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(blocks, (long long)FLOORS * n)), dim3((unsigned)threads), 0, st, q.envs, q.maps, q.luts, q.ls);
     };
-    // sixteen single wavefronts on each of 256 compute units, or six blocks
+    // by six blocks on each of 256 compute units or by sixteen single wavefronts
+    const bool by_blocks = floors_by_blocks(FloorWork::OWED, perlin, (long long)n * FLOORS);
     auto drain = [&]() {
-        if (few_floors(n)) { if (perlin) launch_drain(kf_drain<true, GEN_THREADS>, GEN_THREADS, 1536); else launch_drain(kf_drain<false, GEN_THREADS>, GEN_THREADS, 1536); }
+        if (by_blocks) { if (perlin) launch_drain(kf_drain<true, GEN_THREADS>, GEN_THREADS, 1536); else launch_drain(kf_drain<false, GEN_THREADS>, GEN_THREADS, 1536); }
         else { if (perlin) launch_drain(kf_drain<true, FLOOR_THREADS>, FLOOR_THREADS, 4096); else launch_drain(kf_drain<false, FLOOR_THREADS>, FLOOR_THREADS, 4096); }
     };
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, st, q.envs, q.maps, q.luts, actions, o, reward, done, q.ls, p, steps); };
@@ -1110,8 +1110,9 @@ int import_envs(void* state, const craftax_config* cfg, int n, int first, int co
                            static_cast<const craftax_full_env_dump*>(dumps), first, make_params(state, cfg, n), gradients(cfg, q),
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0);
     };
-    if (cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN) { if (few_floors(count)) go(kf_import<true, GEN_THREADS>, GEN_THREADS); else go(kf_import<true, FLOOR_THREADS>, FLOOR_THREADS); }
-    else { if (few_floors(count)) go(kf_import<false, GEN_THREADS>, GEN_THREADS); else go(kf_import<false, FLOOR_THREADS>, FLOOR_THREADS); }
+    const bool perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN, blocks = floors_by_blocks(FloorWork::IMPORT, perlin, (long long)count * FLOORS);
+    if (perlin) { if (blocks) go(kf_import<true, GEN_THREADS>, GEN_THREADS); else go(kf_import<true, FLOOR_THREADS>, FLOOR_THREADS); }
+    else { if (blocks) go(kf_import<false, GEN_THREADS>, GEN_THREADS); else go(kf_import<false, FLOOR_THREADS>, FLOOR_THREADS); }
     return check_launch("craftax_import_envs", err);
 }
 
@@ -1133,7 +1134,7 @@ int mutate_noise(void* state, const craftax_config* cfg, int n, int first, int c
         hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, theta, first, k0, k1,
                            round, amplitude);
     };
-    if (few_floors(count)) go(kf_mutate_noise<GEN_THREADS>, GEN_THREADS); else go(kf_mutate_noise<FLOOR_THREADS>, FLOOR_THREADS);
+    if (floors_by_blocks(FloorWork::MUTATE, true, (long long)count * FLOORS)) go(kf_mutate_noise<GEN_THREADS>, GEN_THREADS); else go(kf_mutate_noise<FLOOR_THREADS>, FLOOR_THREADS);
     return check_launch("craftax_mutate_noise", err);
 }
 

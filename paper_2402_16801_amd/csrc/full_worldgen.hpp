@@ -17,15 +17,9 @@ namespace cf {
 // A run of 8 cells: the draws of its cells are exactly one Philox block, it lies in one row and in one
 // column of lattice cells (of spacing 8 and of spacing 16), and both its maps are stored as 8 bytes.
 constexpr int RUN = 8, ROW_RUNS = W / RUN, RUNS = CELLS / RUN;   // 6 runs a row, 288 a floor
-// Threads that generate a floor.  A single wavefront (five passes over the 288 runs) where worlds are
-// made by the thousand: no wavefront waits while another one lays the floor out.  A block of five
-// wavefronts, one pass, as long as the chip holds all floors at once that way or nearly so (six blocks
-// on each of 256 compute units, two rounds): there a call lasts as long as one floor.  Measured, in
-// floors, blocks / single wavefronts, us: reset 288 24.7 / 32.0, 1,440 28.3 / 34.8, 3,060 34.9 / 37.1,
-// 7,200 50.9 / 46.1, 73,728 295 / 209; Perlin 288 29.0 / 44.9, 3,060 49.4 / 51.5, 7,200 79 / 85,
-// 73,728 555 / 378.
+// Threads that generate a floor: a single wavefront (five passes over the 288 runs) or a block of five
+// wavefronts (one pass); floor_route.hpp says when which.
 constexpr int FLOOR_THREADS = 64, GEN_THREADS = 320;
-constexpr long long FEW_FLOORS = 3072;
 constexpr int LAT0_U16 = 2 * 16 + 4 * 49;                 // overworld lattices: two 4x4 (spacing 16), four 7x7 (spacing 8)
 constexpr int LAT0_BLOCKS = (LAT0_U16 + 7) / 8;           // 29
 constexpr int LATC_U16 = 2 * 49, LATC_BLOCKS = (LATC_U16 + 7) / 8;   // cave floors: two 7x7 lattices, 13 blocks

@@ -1,0 +1,35 @@
+// The rule that gives floors to blocks or to single wavefronts (csrc/floor_route.hpp) against the sizes at
+// which both were measured, and its estimate of the worlds a rollout owes.
+#include <cstdio>
+
+#include "../../paper_2402_16801_amd/csrc/floor_route.hpp"
+
+using cf::FloorWork;
+
+struct Measured { FloorWork work; bool perlin; long long floors; double blocks_us, wavefronts_us; };
+
+int main()
+{
+    const Measured rows[] = {
+        { FloorWork::RESET, false, 288, 7.1, 16.0 },   { FloorWork::RESET, false, 3600, 19.6, 22.3 },  { FloorWork::RESET, false, 4194, 21.7, 22.9 },
+        { FloorWork::RESET, false, 4788, 23.8, 23.1 }, { FloorWork::RESET, false, 6138, 28.6, 24.5 },  { FloorWork::RESET, false, 7200, 32.3, 28.0 },
+        { FloorWork::RESET, false, 73728, 263, 174 },
+        { FloorWork::IMPORT, false, 288, 13.3, 23.1 }, { FloorWork::IMPORT, false, 4194, 33.6, 34.6 }, { FloorWork::IMPORT, false, 4797, 36.5, 35.6 },
+        { FloorWork::IMPORT, false, 18000, 114, 87 },
+        { FloorWork::RESET, true, 288, 11.8, 27.5 },   { FloorWork::RESET, true, 3600, 35.6, 38.0 },   { FloorWork::RESET, true, 4194, 39.7, 38.8 },
+        { FloorWork::RESET, true, 6138, 53.3, 44.2 },  { FloorWork::RESET, true, 7200, 61.2, 65.6 },   { FloorWork::RESET, true, 9720, 78.6, 84.9 },
+        { FloorWork::RESET, true, 11988, 94.3, 95.0 }, { FloorWork::RESET, true, 14400, 111, 104 },    { FloorWork::RESET, true, 73728, 525, 343 },
+        { FloorWork::IMPORT, true, 288, 18.5, 34.9 },  { FloorWork::IMPORT, true, 2592, 39.6, 42.2 },  { FloorWork::IMPORT, true, 3600, 48.0, 46.0 },
+        { FloorWork::IMPORT, true, 9720, 104, 97 },    { FloorWork::IMPORT, true, 18000, 191, 150 },
+        { FloorWork::MUTATE, true, 288, 23.0, 29.6 },  { FloorWork::MUTATE, true, 1440, 31.3, 34.2 },  { FloorWork::MUTATE, true, 2052, 36.2, 34.8 },
+        { FloorWork::MUTATE, true, 3069, 44.4, 35.3 }, { FloorWork::MUTATE, true, 18000, 158, 121 },
+    };
+    int bad = 0;
+    for (const Measured& m : rows)
+        if (cf::floors_by_blocks(m.work, m.perlin, m.floors) != (m.blocks_us < m.wavefronts_us)) {
+            std::printf("work %d, perlin %d, %lld floors: the slower form\n", (int)m.work, (int)m.perlin, m.floors);
+            ++bad;
+        }
+    if (bad == 0) std::printf("floor_route_test: ok\n");
+    return bad != 0;
+}

@@ -35,6 +35,13 @@ def test_regeneration_units_are_dealt_out_exactly_once(tmp_path):
     assert "regen_units_test: ok" in _run([exe])
 
 
+def test_floors_go_to_the_form_that_was_measured_faster(tmp_path):
+    """Blocks or single wavefronts for the floors of a call (csrc/floor_route.hpp)."""
+    exe = str(tmp_path / "floor_route_test")
+    _run(["g++", "-O1", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-o", exe, os.path.join(NATIVE, "floor_route_test.cpp")])
+    assert "floor_route_test: ok" in _run([exe])
+
+
 def test_public_header_compiles_as_c_and_as_cpp(tmp_path):
     """include/craftax.h on its own, with warnings as errors, as C11 and as C++17: no HIP or torch type
     in any signature, every struct complete."""
