@@ -11,6 +11,9 @@
 //     the first until it is nearly full:  7,200 61.2 / 65.6   9,720 78.6 / 84.9   11,988 94.3 / 95.0   14,400 111 / 104   73,728 525 / 343
 //   import, Perlin noise    288 18.5 / 34.9   2,592 39.6 / 42.2   3,069 43.2 / 43.1   3,600 48.0 / 46.0   9,720 104 / 97   18,000 191 / 150
 //   noise mutation          288 23.0 / 29.6   1,440 31.3 / 34.2   2,052 36.2 / 34.8   3,069 44.4 / 35.3   9,720  95 / 88   18,000 158 / 121
+//   owed by a rollout       us of a whole rollout with its two launches for owed worlds in the one or the other form, environments x steps (floors owed):
+//                           1,024 x 16 (819) 124 / 132   2,048 x 16 (1,638) 139.5 / 143.6   4,096 x 16 (3,276) 181.7 / 179.4   4,096 x 64 (13,107) 675 / 643
+//                           Perlin noise: 128 / 142   147.5 / 156.5   197.3 / 194.9   748 / 703
 // Plain C++ so that the rule itself can be tested without a GPU.
 #pragma once
 
@@ -26,6 +29,14 @@ inline bool floors_by_blocks(FloorWork work, bool perlin, long long floors)
     case FloorWork::MUTATE: return floors <= 1850;     // Perlin worlds only
     default: return floors <= 3072;
     }
+}
+
+// Worlds that n environments owe after `steps` steps, for the rule above (what is generated is what is on the
+// lists): one for each that has finished an episode, and episodes last about 180 steps unless the cap ends them.
+inline long long worlds_owed(long long n, long long steps, long long max_episode_steps)
+{
+    const long long length = max_episode_steps < 180 ? max_episode_steps : 180;
+    return steps >= length ? n : n * steps / length;
 }
 
 }  // namespace cf

@@ -23,6 +23,9 @@ int main()
         { FloorWork::IMPORT, true, 9720, 104, 97 },    { FloorWork::IMPORT, true, 18000, 191, 150 },
         { FloorWork::MUTATE, true, 288, 23.0, 29.6 },  { FloorWork::MUTATE, true, 1440, 31.3, 34.2 },  { FloorWork::MUTATE, true, 2052, 36.2, 34.8 },
         { FloorWork::MUTATE, true, 3069, 44.4, 35.3 }, { FloorWork::MUTATE, true, 18000, 158, 121 },
+        { FloorWork::OWED, false, 819, 124, 132 },     { FloorWork::OWED, false, 1638, 139.5, 143.6 }, { FloorWork::OWED, false, 3276, 181.7, 179.4 },
+        { FloorWork::OWED, false, 13107, 675, 643 },   { FloorWork::OWED, true, 819, 128, 142 },       { FloorWork::OWED, true, 1638, 147.5, 156.5 },
+        { FloorWork::OWED, true, 3276, 197.3, 194.9 }, { FloorWork::OWED, true, 13107, 748, 703 },
     };
     int bad = 0;
     for (const Measured& m : rows)
@@ -30,6 +33,8 @@ int main()
             std::printf("work %d, perlin %d, %lld floors: the slower form\n", (int)m.work, (int)m.perlin, m.floors);
             ++bad;
         }
+    bad += cf::worlds_owed(4096, 16, 100000) != 364 || cf::worlds_owed(4096, 500, 100000) != 4096 || cf::worlds_owed(343, 20, 13) != 343 ||
+           cf::worlds_owed(343, 1, 13) != 26 || cf::worlds_owed(7, 1, 1) != 7;
     if (bad == 0) std::printf("floor_route_test: ok\n");
     return bad != 0;
 }
