@@ -139,3 +139,33 @@ def test_full_game_runs_without_an_index_out_of_range(dbg, lanes):
         assert sim.export_envs().tobytes() == orc.envs.tobytes()
         sim.close()
         _clean(cx, f"Craftax, {lanes} lanes, observation layout {obs_mode}")
+
+
+@pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 501), (po.WORLDGEN_PERLIN, 670)])
+def test_full_game_floors_by_single_wavefronts_without_an_index_out_of_range(dbg, worldgen, n):
+    """Enough environments that reset, import, noise mutation and a rollout's owed worlds are generated by
+    single wavefronts."""
+    import torch
+    from test_gpu_full_parity import rich_scene
+    cx = dbg
+    cap, steps = 13, 20
+    sim = cx.Craftax(n, cx.default_config(cx.VARIANT_CRAFTAX, worldgen=worldgen, max_episode_steps=cap))
+    orc = po.FullOracle(n, po.full_default_config(worldgen=worldgen, max_episode_steps=cap))
+    seeds = synth.seeds_for(n, 23)
+    sim.reset(seeds); orc.reset(seeds)
+    rich_scene(orc.envs)
+    sim.import_envs(orc.envs.copy())
+    if worldgen == po.WORLDGEN_PERLIN:
+        theta = np.zeros((n, po.FULL_THETA_LEN), np.uint16)
+        sim.mutate_noise(torch.zeros((n, cx.FULL_THETA_LEN), dtype=torch.int16, device=sim.device), 9, 0, 300)
+        orc.mutate_noise(theta, 9, 0, 300)
+    acts = synth.action_block(n, steps, "uniform", 13, 0, 43)
+    rew = torch.empty((steps, n), dtype=torch.float32, device=sim.device)
+    done = torch.empty((steps, n), dtype=torch.uint8, device=sim.device)
+    cx.craftax_rollout(sim.state, torch.as_tensor(acts, device=sim.device), steps, sim.obs, rew, done, n, sim.stream)
+    for s in range(steps):
+        orc.step(acts[s], render=s == steps - 1)
+    assert np.array_equal(sim.obs.cpu().numpy(), orc.obs)
+    assert sim.export_envs().tobytes() == orc.envs.tobytes()
+    sim.close()
+    _clean(cx, f"Craftax, floors by single wavefronts, worldgen {worldgen}")

@@ -203,7 +203,7 @@ def test_full_perlin_worlds(cx):
     """The Perlin option for the open floors (appendix "World Generation"): 96 fresh worlds byte
     for byte, and they are not the value-noise worlds."""
     n = 96
-    seeds = synth.seeds_for(n, 0)
+    seeds = synth.seeds_for(n, 77)
     gcfg, ocfg = _cfgs(cx, 1, worldgen=po.WORLDGEN_PERLIN)
     sim = cx.Craftax(n, gcfg)
     orc = po.FullOracle(n, ocfg)
@@ -229,6 +229,64 @@ def test_full_worlds_over_many_seeds(cx, worldgen):
     compare_state(sim, orc, np.arange(n), "reset")
     built = [1, 3, 4]
     assert (orc.envs["ladder_up"][:, built] == orc.envs["ladder_down"][:, built]).all(axis=2).any(), "no such layout among these seeds"
+    sim.close()
+
+
+@pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 500), (po.WORLDGEN_VALUE, 501), (po.WORLDGEN_PERLIN, 205), (po.WORLDGEN_PERLIN, 206),
+                                        (po.WORLDGEN_PERLIN, 341), (po.WORLDGEN_PERLIN, 342)])
+def test_full_floors_by_blocks_and_by_single_wavefronts(cx, worldgen, n):
+    """Import, noise mutation and the worlds owed by a rollout on both sides of the lines at which their
+    floors go from blocks to single wavefronts (csrc/floor_route.hpp): every floor, and the spare
+    worlds as the episodes that follow reach them."""
+    import torch
+    cap = 13
+    gcfg, ocfg = _cfgs(cx, 1, worldgen=worldgen, max_episode_steps=cap)
+    sim = cx.Craftax(n, gcfg)
+    orc = po.FullOracle(n, ocfg)
+    ids = np.arange(n)
+    seeds = synth.seeds_for(n, 640)
+    sim.reset(seeds); orc.reset(seeds)
+    t = 0
+
+    def single(k):
+        nonlocal t
+        for _ in range(k):
+            a = synth.actions(ids, t, "skewed", 4, 43)
+            obs, rew, done = sim.step(torch.as_tensor(a, device=sim.device))
+            oobs, orew, odone = orc.step(a)
+            assert np.array_equal(done.cpu().numpy(), odone) and np.array_equal(obs.cpu().numpy(), oobs), f"step {t}"
+            t += 1
+
+    def rollout(k):
+        nonlocal t
+        acts = np.stack([synth.actions(ids, t + s, "skewed", 4, 43) for s in range(k)]).astype(np.int32)
+        rew = torch.zeros((k, n), dtype=torch.float32, device=sim.device)
+        done = torch.zeros((k, n), dtype=torch.uint8, device=sim.device)
+        cx.craftax_rollout(sim.state, torch.as_tensor(acts, device=sim.device), k, sim.obs, rew, done, n, sim.stream)
+        for s in range(k):
+            oobs, orew, odone = orc.step(acts[s], render=s == k - 1)
+            assert np.array_equal(done[s].cpu().numpy(), odone), f"rollout step {s}"
+            assert np.array_equal(rew[s].cpu().numpy().view(np.uint32), orew.view(np.uint32)), f"rollout step {s}"
+        assert np.array_equal(sim.obs.cpu().numpy(), oobs), "observation after a rollout"
+        t += k
+
+    single(5)
+    rich_scene(orc.envs)
+    sim.import_envs(orc.envs.copy())
+    compare_state(sim, orc, ids, "the import")
+    single(cap + 1)                                        # into the spare worlds of the import
+    compare_state(sim, orc, ids, "the episodes after the import")
+    if worldgen == po.WORLDGEN_PERLIN:
+        theta = np.zeros((n, po.FULL_THETA_LEN), np.uint16)
+        d_theta = torch.zeros((n, cx.FULL_THETA_LEN), dtype=torch.int16, device=sim.device)
+        sim.mutate_noise(d_theta, 0xACE, 1, 60); orc.mutate_noise(theta, 0xACE, 1, 60)
+        assert np.array_equal(d_theta.cpu().numpy().view(np.uint16), theta)
+        compare_state(sim, orc, ids, "the mutation")
+    rollout(cap + 7)                                       # every environment owes a world afterwards
+    compare_state(sim, orc, ids, "the rollout")
+    single(cap + 2)                                        # into the owed worlds
+    rollout(2 * cap + 3)
+    compare_state(sim, orc, ids, "the end")
     sim.close()
 
 
@@ -452,7 +510,7 @@ def test_full_null_observation_and_determinism(cx):
     outs = []
     for rep in range(2):
         sim = cx.Craftax(n, gcfg)
-        sim.reset(synth.seeds_for(n, 0))
+        sim.reset(synth.seeds_for(n, 77))
         for s in range(150):
             a = torch.as_tensor(synth.actions(np.arange(n), s, "skewed", 2, 43), device=sim.device)
             if rep == 0:
