@@ -313,7 +313,7 @@ __device__ __attribute__((noinline)) void generate_world(uint8_t* slot, Lds<Worl
 // one launch has no spare world; its wavefront generates the next world on the spot.  Generated by the
 // block at every end of an episode, worlds stalled whole blocks, and a launch lasted as long as the
 // block with the most of them (64 steps: 4,096 environments 1,072 -> 900 us, 1,024: 780 -> 580, 100
-// environments and 16 steps: 230 -> 150).
+// environments and 16 steps: 230 -> 150; with packed state, staged bytes and kept windows 660, 442, 117).
 // Before the launch the regeneration lists of the step kernel must be empty (the host runs a
 // list-only launch first).
 template <bool F32, bool PERLIN>
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__
 // turned lattice; the block of floor 0 also starts the episode over.  It writes every word of the
 // record but the episode and the seed, which the other blocks read and which stay as they are, so one
 // launch does it all (floor 0 in a launch of its own behind the others: 131 us for 1,000
-// levels, one launch: 92).
+// levels, one launch: 92, by single wavefronts 82).
 __device__ inline int theta_offset(int f)
 {
     return f == 0 ? 0 : LAT0_U16 + LATC_U16 * (f == 2 ? 0 : (f == 5 ? 1 : (f == 6 ? 2 : 3)));
@@ -549,8 +549,9 @@ __global__ __launch_bounds__(NT, 6) void kf_mutate_noise(uint32_t* __restrict__ 
 // ---------------------------------------------------------------------------------------------
 // canonical dumps: one block per (environment, floor), a thread moving runs of 8 cells of all three maps of
 // the dump (63 KB, so a copy with some arithmetic: byte by byte, one block per environment, 1,000
-// dumps took 34 us, now 16.5, 6.3 TB/s of the dumps and maps); the block of floor 0 also unpacks the record.  A dump is a multiple of 8
-// bytes long; the pieces are moved without assuming more than byte alignment of the caller's array.
+// dumps took 34 us, now 16.5, 6.3 TB/s of the dumps and maps); the block of floor 0 also unpacks the
+// record.  A dump is a multiple of 8 bytes long; the pieces are moved without assuming more than byte
+// alignment of the caller's array.
 __device__ inline uint2 load8(const uint8_t* p) { uint2 v; __builtin_memcpy(&v, p, 8); return v; }
 __device__ inline void store8(uint8_t* p, uint2 v) { __builtin_memcpy(p, &v, 8); }
 __global__ __launch_bounds__(GEN_THREADS) void kf_export(const uint32_t* __restrict__ envs, const uint8_t* __restrict__ maps,
@@ -672,7 +673,7 @@ __device__ inline void import_record(uint32_t* __restrict__ r, const Lists& ls, 
 // One block per (environment, floor): it takes the floor in, and generates the same floor of the world
 // of the next episode into the spare slot, so that the copy of some blocks overlaps the arithmetic of
 // others; the block of floor 0 also packs the record.  (A copy byte by byte and a second launch for
-// the spare worlds: 50 + 87 us for 1,000 Perlin worlds, now 101.)
+// the spare worlds: 50 + 87 us for 1,000 Perlin worlds, one launch 101, by single wavefronts 93.)
 template <bool PERLIN, int NT>
 __global__ __launch_bounds__(NT, PERLIN ? 6 : 8) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
                                                                         const craftax_full_env_dump* __restrict__ dumps, int first, Params p,
@@ -992,11 +993,11 @@ int reset(void* state, const craftax_config* cfg, int n, const uint64_t* seeds, 
 // Lanes per environment of the step kernel.  A whole wavefront (the default at every batch size)
 // keeps the player's state and the 43-action code on the scalar unit, which works beside the vector
 // unit.  Sixteen lanes put four environments in a wavefront and fill 14 of 16 lanes with mob slots
-// instead of 14 of 64, but the player's code then runs on the vector unit, the kernel needs 210
-// vector registers (two wavefronts per SIMD instead of five), and a wavefront renders four
-// observations one after the other: measured slower at every size (22.5 against 18.8 us per step at
-// 4,096 environments, 243 against 207 us at 65,536).  It stays selectable (cfg->group_lanes = 16)
-// and is tested like the default.
+// instead of 14 of 64, but the player's code then runs on the vector unit, the kernel needs up to 133
+// vector registers and 48 KB of LDS (three wavefronts per SIMD instead of five), and a wavefront
+// renders four observations one after the other.  us per step, 16 / 64 lanes: 20.9 / 11.0 at 1,024
+// environments, 21.4 / 14.4 at 4,096, 51.6 / 45.0 at 16,384, 172.6 / 178.6 at 65,536.  It is selectable
+// (cfg->group_lanes = 16) and tested like the default.
 static int group_lanes(const craftax_config* cfg, int n)
 {
     (void)n;

@@ -122,10 +122,11 @@ __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x0020408
 // cleared LDS area, which the lanes then read back in 16-byte pieces and store as whole cache lines.
 // LDS moves 128 bytes per clock beside the vector units, which bound the step kernels; in the earlier form
 // (the channels as single bits, every piece expanded from 16 of them) a quarter of the vector
-// instructions of a step expanded bits.  Measured: a step of 4,096 environments 18.3 -> 16.7 us, of
-// 32,768 115 -> 110, a rollout of 64 steps and 4,096 environments 897 -> 805 us.  The area covers 5,120 bytes at a time, so that five blocks of the step
-// kernel still share a compute unit.  A lane owns the cells l and l + 64; the second one lies in the
-// second part, the first one may reach into it.
+// instructions of a step expanded bits.  Measured, before the player's state was kept packed: a step of
+// 4,096 environments 18.3 -> 16.7 us, of 32,768 115 -> 110, a rollout of 64 steps and 4,096 environments
+// 897 -> 805 us.  The area covers 5,120 bytes at a time, so that five blocks of the step kernel still share
+// a compute unit.  A lane owns the cells l and l + 64; the second one lies in the second part, the first
+// one may reach into it.
 // For the float layout a staged byte v stands for v / 140: 140 is the 1 of a one-hot channel and 7 * level
 // the light level / 20.  Multiplying by the float nearest to 1/140 gives exactly those floats.
 constexpr int STAGE_REST = CELL_BYTES - STAGE_BYTES;
@@ -314,7 +315,7 @@ __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int w
         }
     };
     if (!F32) {
-                uint4* dst = reinterpret_cast<uint4*>(out);
+        uint4* dst = reinterpret_cast<uint4*>(out);
 #pragma unroll 3
         for (int it = 0; it < (STRIDE_U8 / 16 + GW - 1) / GW; ++it) {
             const int j = l + GW * it;

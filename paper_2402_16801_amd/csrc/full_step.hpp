@@ -1,8 +1,8 @@
 // One step of one full-Craftax environment by one wavefront.
 //
-// The player's state is unpacked into wave-uniform scalars (every lane computes the same
-// values, so the compiler keeps them in scalar registers and branches on them without
-// divergence); lane k < 14 holds mob slot k of the current floor, lane k < 10 plant slot k.
+// The player's state is wave-uniform and stays packed as in the record (every lane computes the same
+// values, so the compiler keeps them in scalar registers and branches on them without divergence; see
+// Player); lane k < 14 holds mob slot k of the current floor as one word, lane k < 10 plant slot k.
 // The phases follow section "Craftax: An Extension of Crafter ..." for what exists (floors,
 // ladders, combat with three damage elements, bow, spells, potions, enchanting, attributes,
 // boss waves); their order and every constant are this library's own frozen reading:

@@ -3,8 +3,9 @@
 // sewers, vault, troll mines, fire realm, ice realm, graveyard).  The paper does not print its
 // generators; here every cell of every floor is a pure integer function of (seed, env, episode,
 // floor, x, y): noise thresholds for the open floors, eight seeded rooms joined by L-shaped
-// corridors for the built ones.  One block per (environment, floor), a thread owning a run of 8
-// cells, so that a reset is nine short blocks instead of one long one.
+// corridors for the built ones.  A floor of an environment belongs to a block or to a single wavefront
+// (floor_route.hpp), a thread owning a run of 8 cells at a time, so that a reset is nine short pieces of
+// work instead of one long one.
 #pragma once
 
 #include <type_traits>
@@ -250,7 +251,7 @@ __device__ inline Ends ends_at(const uint32_t* lat, int width, int ix, int iy, u
 // dot-product arithmetic (worldgen.hpp).  A run of 8 cells instead of 4 uses all of its Philox block,
 // and the built floors are byte masks over whole runs.  Measured against runs of 4 cells in 32- and
 // 64-bit products: craftax_reset of 4,096 environments (8,192 worlds, 340 MB) 529 -> 295 us, with Perlin
-// noise 1081 -> 554 us.
+// noise 1081 -> 554 us; by single wavefronts instead of blocks 174 and 343 us.
 // LOOPED: the call stands in a loop over worlds; what a thread derives from its index is then derived
 // anew in every call instead of being kept (and spilled) across the loop.
 template <int NT = GEN_THREADS, bool CAN_PERLIN = false, bool LOOPED = false>

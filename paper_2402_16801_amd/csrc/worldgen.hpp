@@ -28,12 +28,12 @@ __host__ __device__ constexpr uint32_t smooth8(int k) { return (uint32_t)(12 * k
 __host__ __device__ constexpr uint32_t smooth16(int k) { return (uint32_t)((24 * k * k - k * k * k + 4) >> 3); }
 
 // The generators below are bound by vector instruction issue (a 64x64 world is 4 KB of stores against
-// some 400 instructions for every 64 runs of 8 cells), so they are written for few instructions:
+// 589 instructions for every 64 runs of 8 cells), so they are written for few instructions:
 // every product is one that a 24-bit multiply or a 16-bit dot product forms exactly, fields are
 // compared with their thresholds before the shift that would bring them to the 0..65535 scale, and
 // the rule is compares and selects whose masks combine on the scalar unit.  Measured against a
 // generator of 32-bit products and a branching rule: craftax_reset of 16,384 environments (32,768
-// worlds, 134 MB) 412 -> 264 us, with Perlin noise (which was in 64-bit integers) several times that.
+// worlds, 134 MB) 412 -> 263 us, of 8,192 with Perlin noise (which was in 64-bit integers) 455 -> 338.
 
 // exact products of values below 2^24 (one v_mul_u32_u24 / v_mad_u32_u24)
 __device__ inline uint32_t mul24u(uint32_t a, uint32_t b) { return (a & 0xFFFFFFu) * (b & 0xFFFFFFu); }
@@ -236,8 +236,9 @@ __device__ __forceinline__ void worldgen_block(uint8_t* __restrict__ map, uint32
     // The run in two halves of four cells, a loop that is not unrolled: half the code, and few enough
     // registers for the kernels that hold an environment's record meanwhile.  UNROLLED: for blocks that
     // generate one world after the other and last as long as the chain of a run (regeneration_block).
+    constexpr int HALVES_UNROLL = UNROLLED ? 2 : 1;
     auto halves = [&](auto&& cell) {
-#pragma unroll (UNROLLED ? 2 : 1)
+#pragma unroll HALVES_UNROLL
         for (int h = 0; h < 8; h += 4) {
             first = four;
             four = 0u;
