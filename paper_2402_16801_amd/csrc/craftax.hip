@@ -81,7 +81,7 @@ using la::NSUB;
 
 // reset: two blocks per environment, for the worlds of episodes 0 and 1
 template <bool PERLIN>
-__global__ __launch_bounds__(WG_THREADS) void k_reset(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
+__global__ __launch_bounds__(WG_THREADS, PERLIN ? 6 : 8) void k_reset(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                  const uint64_t* __restrict__ seeds, Lists ls, const Luts* __restrict__ luts,
                                                  uint32_t* __restrict__ unlocks)
 {
@@ -108,14 +108,10 @@ __device__ __forceinline__ void regeneration_block(uint8_t* __restrict__ maps, c
     // two blocks per world, one half (32 columns) each: a regeneration block is then as short as it can be
     // with one run of 8 cells per thread, and the tail it adds to the launch is half as long
     const uint32_t pair = rb / NSUB, half = pair & 1u;
-    // The halves of a run unrolled: where many episodes end in a launch these blocks go through several
-    // worlds each and the launch waits for them (8,192 environments with episodes of 10 steps 19.5 us with
-    // the loop, 18.5 unrolled; 16,384 32.0 / 30.2; no difference where few end).  Not for Perlin noise,
-    // whose step kernel would lose a wavefront per SIMD to the registers.
     for (uint32_t i = pair >> 1; i < count; i += nrb / NSUB / 2) {
         const uint4 entry = list[i];
         if (entry.x == ENTRY_VOID) continue;
-        worldgen_block<BLOCK, PERLIN, !PERLIN>(maps + map_offset(entry.x, entry.w), s_lat, entry.y, entry.z, entry.x, entry.w, nullptr,
+        worldgen_block<BLOCK, PERLIN, false>(maps + map_offset(entry.x, entry.w), s_lat, entry.y, entry.z, entry.x, entry.w, nullptr,
                                       (int)half * (STRIPS / 2), perlin_cs);
         if (threadIdx.x == 0) ls.tags[2 * entry.x + half] = make_uint2(entry.w, seq);
     }
@@ -145,7 +141,7 @@ __device__ __forceinline__ void regeneration_share(uint8_t* __restrict__ maps, c
         const uint4 entry = list[w.u >> 1];
         const uint32_t half = w.u & 1u;
         if (entry.x != ENTRY_VOID) {
-            worldgen_block<BLOCK, PERLIN>(maps + map_offset(entry.x, entry.w), s_lat, entry.y, entry.z, entry.x, entry.w, nullptr,
+            worldgen_block<BLOCK, PERLIN, false>(maps + map_offset(entry.x, entry.w), s_lat, entry.y, entry.z, entry.x, entry.w, nullptr,
                                           (int)half * (STRIPS / 2), perlin_cs);
             if (threadIdx.x == 0) ls.tags[2 * entry.x + half] = make_uint2(entry.w, seq);
         }
@@ -189,17 +185,15 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
     const uint32_t sub = (regen_role ? rb : blockIdx.x) % NSUB, per_sub = nrb / NSUB;
     const uint32_t nq = ((uint32_t)step_blocks + NSUB - 1u - sub) / NSUB;   // step blocks that append to this sub-list
 
+    // SHARE: a regeneration block's units, or this step block's share of the worlds owed from the previous
+    // launch while its records arrive (one call for both: the generator is in the kernel's code once)
+    if (SHARE && (regen_role || first_helper_unit(blockIdx.x / NSUB, per_sub) < 2u * regen_count))
+        regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, !regen_role, (regen_role ? rb : blockIdx.x) / NSUB, per_sub, nq, s_env, luts->perlin_cs);
     if (regen_role) {
-        if (SHARE)
-            regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, false, rb / NSUB, per_sub, nq, s_env, luts->perlin_cs);
-        else if (rb / NSUB / 2 < regen_count)
-            regeneration_block<PERLIN>(maps, ls, seq, regen_count, rb, nrb, s_env, luts->perlin_cs);
+        if (!SHARE && rb / NSUB / 2 < regen_count) regeneration_block<PERLIN>(maps, ls, seq, regen_count, rb, nrb, s_env, luts->perlin_cs);
         leave();
         return;
     }
-    // this block's share of the worlds owed from the previous launch, while its records arrive
-    if (SHARE && first_helper_unit(blockIdx.x / NSUB, per_sub) < 2u * regen_count)
-        regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, true, blockIdx.x / NSUB, per_sub, nq, s_env, luts->perlin_cs);
 
     if (tid == 0) s_ndone = 0;
     __syncthreads();
@@ -321,7 +315,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         const uint32_t tenv = (uint32_t)(blockIdx.x * EPB + gt), ep = rt[RW_EPISODE] + 1u, lo = rt[RW_SEED_LO], hi = rt[RW_SEED_HI];
 #pragma unroll 1
         for (int half = 0; half < 2; ++half)
-            worldgen_block<BLOCK, PERLIN>(maps + map_offset(tenv, ep), s_lat, lo, hi, tenv, ep, start_win, half * (STRIPS / 2), luts->perlin_cs);
+            worldgen_block<BLOCK, PERLIN, false>(maps + map_offset(tenv, ep), s_lat, lo, hi, tenv, ep, start_win, half * (STRIPS / 2), luts->perlin_cs);
     };
 
     // steps, then as many turns without a step as it takes to generate the spare worlds still owed

@@ -186,51 +186,62 @@ __device__ inline bool spot_in_run(uint32_t spot, int x0, int y) { return (spot 
 
 // What a cave floor makes of a cell's fields and draw u.  Open cells (cave field above 31000): a plant
 // where u < plant_below, a liquid where the second field is above its threshold, the floor's ground
-// elsewhere; rock: ore i where u < below_i for the first such i, stone elsewhere.
-struct CaveRule { uint32_t open, plant_below, plant, liquid_above, liquid, below0, below1, below2, below3, below4, ore0, ore1; };
+// elsewhere; rock: ore i where u < below_i for the first such i, stone elsewhere.  What a kind of floor
+// lacks is left out of its code: the gnomish mines have no liquid (and no need of the second field),
+// the troll mines no plants, the fire and ice realms two ores instead of five.
+// A cell is a code 0..7, its place in the floor's table of blocks, so that one byte permutation looks up
+// four cells: 0 stone, 1 2 3 4 5 the ores in order, 6 ground, 7 the plant, and the liquid is 7
+// where there are no plants and 5 where there are only two ores.
+enum CaveKind : int { GNOME_MINES, TROLL_MINES, REALM };
+struct CaveRule { uint32_t table_lo, table_hi, below1; };   // blocks of codes 0..3 and 4..7; realms: where the second ore ends, as a draw in the upper half
 __device__ inline CaveRule cave_rule(int f)
 {
-    const bool mines = f == 2 || f == 5;
+    using cx::four_bytes;
     CaveRule c;
-    c.open = f == 6 ? B_FIRE_GRASS : (f == 7 ? B_ICE_GRASS : B_PATH);
-    c.plant_below = f == 2 ? 1500u : (f == 5 ? 0u : 3000u);
-    c.plant = f == 2 ? B_STALAGMITE : (f == 6 ? B_FIRE_TREE : B_ICE_SHRUB);
-    c.liquid_above = f == 2 ? 65535u : (f == 5 ? 44000u : 43000u);
-    c.liquid = f == 6 ? B_LAVA : B_WATER;
-    c.ore0 = mines ? B_COAL : (f == 6 ? B_RUBY : B_SAPPHIRE);
-    c.ore1 = mines ? B_IRON : (f == 6 ? B_COAL : B_DIAMOND);
-    c.below0 = mines ? 5000u : 2500u;
-    c.below1 = mines ? 7500u : (f == 6 ? 6000u : 5000u);
-    c.below2 = mines ? 8000u : 0u;                          // diamond,
-    c.below3 = f == 2 ? 8600u : (f == 5 ? 9000u : 0u);      // sapphire,
-    c.below4 = f == 2 ? 9200u : (f == 5 ? 10000u : 0u);     // ruby
+    const bool mines = f == 2 || f == 5;
+    c.table_lo = mines ? four_bytes(B_STONE, B_COAL, B_IRON, B_DIAMOND) : f == 6 ? four_bytes(B_STONE, B_RUBY, B_COAL, B_STONE) : four_bytes(B_STONE, B_SAPPHIRE, B_DIAMOND, B_STONE);
+    c.table_hi = f == 2 ? four_bytes(B_SAPPHIRE, B_RUBY, B_PATH, B_STALAGMITE) : f == 5 ? four_bytes(B_SAPPHIRE, B_RUBY, B_PATH, B_WATER)
+               : f == 6 ? four_bytes(B_STONE, B_LAVA, B_FIRE_GRASS, B_FIRE_TREE) : four_bytes(B_STONE, B_WATER, B_ICE_GRASS, B_ICE_SHRUB);
+    c.below1 = (f == 6 ? 6000u : 5000u) << 16;
     return c;
 }
-// C, F: fields as cx::above takes them; u: the draw in the upper half
-template <bool PERLIN>
-__device__ __forceinline__ uint32_t classify_cave(const CaveRule& k, uint32_t C, uint32_t F, uint32_t u)
+__device__ inline uint32_t cave_ground(int f) { return f == 6 ? (uint32_t)B_FIRE_GRASS : (f == 7 ? (uint32_t)B_ICE_GRASS : (uint32_t)B_PATH); }
+// thresholds in scalar registers, as in cx::Thresholds: of the fields, of the draws
+template <bool PERLIN, int KIND>
+struct CaveThresholds {
+    template <int T> __device__ static uint32_t draw() { return cx::scalar_const<(uint32_t)T << 16>(); }
+    template <int T> __device__ static uint32_t field() { return cx::scalar_const<cx::first_above<PERLIN>(T)>(); }
+    static constexpr bool GNOME = KIND == GNOME_MINES, MINES = KIND != REALM;
+    uint32_t open = field<31000>(), liquid = field<MINES ? 44000 : 43000>(), plant = draw<GNOME ? 1500 : 3000>();
+    uint32_t b0 = draw<MINES ? 5000 : 2500>(), b1 = draw<7500>(), b2 = draw<8000>(), b3 = draw<GNOME ? 8600 : 9000>(), b4 = draw<GNOME ? 9200 : 10000>();
+};
+// Appends the cell's code to `word`, where a cell takes a byte.  C, F: the fields; u: the draw in the upper half
+template <bool PERLIN, int KIND>
+__device__ __forceinline__ void classify_cave(uint32_t& word, const CaveThresholds<PERLIN, KIND>& t, uint32_t below1, uint32_t C, uint32_t F, uint32_t u)
 {
-    uint32_t in = k.open, rock = B_STONE;
-    auto set = [](uint32_t& b, bool where, uint32_t block) { b = where ? block : b; };
-    set(in, u < (k.plant_below << 16), k.plant);
-    // (a threshold of 65535 is never exceeded)
-    const bool liquid = PERLIN ? (int)F >= (k.liquid_above == 65535u ? 0x7FFFFFFF : k.liquid_above == 44000u ? cx::perlin_above(44000) : cx::perlin_above(43000))
-                               : F > ((k.liquid_above << 16) | 0xFFFFu);
-    set(in, liquid, k.liquid);
-    set(rock, u < (k.below4 << 16), B_RUBY);
-    set(rock, u < (k.below3 << 16), B_SAPPHIRE);
-    set(rock, u < (k.below2 << 16), B_DIAMOND);
-    set(rock, u < (k.below1 << 16), k.ore1);
-    set(rock, u < (k.below0 << 16), k.ore0);
-    return cx::above<PERLIN>(C, 31000) ? in : rock;
+    using cx::Mask; using cx::mask_of; using cx::shift_in;
+    const Mask open = mask_of(C >= t.open), ore0 = mask_of(u < t.b0);
+    word <<= 5;
+    if (KIND == REALM) {
+        const Mask liquid = mask_of(F >= t.liquid);
+        cx::shift_in_compare(word, open);
+        shift_in(word, (open & ~liquid) | (mask_of(u < below1) & ~(ore0 | open)));
+        shift_in(word, (open & (liquid | mask_of(u < t.plant))) | (ore0 & ~open));
+    } else {
+        const Mask special = KIND == GNOME_MINES ? mask_of(u < t.plant) : mask_of(F >= t.liquid);
+        const Mask b2 = mask_of(u < t.b2), b4 = mask_of(u < t.b4);
+        shift_in(word, open | (b4 & ~b2));
+        shift_in(word, open | (b2 & ~ore0));
+        shift_in(word, (open & special) | ((ore0 | (b2 & ~mask_of(u < t.b1)) | (b4 & ~mask_of(u < t.b3))) & ~open));
+    }
 }
+__device__ inline uint32_t cave_blocks(const CaveRule& k, uint32_t word) { return __builtin_amdgcn_perm(k.table_hi, k.table_lo, word); }
 
-// The lattice columns left and right of a run in row y, blended vertically (see cx::across).
-struct Ends { uint32_t l, r; };
-__device__ inline Ends ends_at(const uint32_t* lat, int width, int ix, int iy, uint32_t weights)
+// The lattice columns left and right of a run in row y, blended vertically, from the run's last cell on (see cx::Line).
+__device__ inline cx::Line line_at(const uint32_t* lat, int width, int ix, int iy, uint32_t weights, double last)
 {
     const uint32_t* c = lat + CX_IDX(iy * width + ix, width * width - 1);
-    return { cx::dot16u(c[0], weights), cx::dot16u(c[1], weights) };
+    return cx::line_between(cx::dot16u(c[0], weights), cx::dot16u(c[1], weights), last);
 }
 
 // Generates floor f of one environment with the NT threads of the calling block (NT = 64: with the
@@ -247,11 +258,11 @@ __device__ inline Ends ends_at(const uint32_t* lat, int width, int ix, int iy, u
 // theta_f (with CAN_PERLIN; LDS, LAT_TOTAL entries, the same for the whole block): angle offsets in
 // 1024ths of a turn added to the upper ten bits of this floor's lattice numbers, the level of the
 // noise mutation (section "Craftax-1B: UED").
-// Bound by vector instruction issue, like the Classic generator, and written with the same 24-bit and
-// dot-product arithmetic (worldgen.hpp).  A run of 8 cells instead of 4 uses all of its Philox block,
-// and the built floors are byte masks over whole runs.  Measured against runs of 4 cells in 32- and
-// 64-bit products: craftax_reset of 4,096 environments (8,192 worlds, 340 MB) 529 -> 295 us, with Perlin
-// noise 1081 -> 554 us; by single wavefronts instead of blocks 174 and 343 us.
+// Bound by instruction issue, like the Classic generator, and written in the same way (worldgen.hpp): fields in
+// 64-bit floating point, masks on the scalar unit, a code per cell that byte permutations turn into
+// blocks.  A run of 8 cells uses all of its Philox block, and the built floors are byte masks over whole
+// runs.  Measured against integer products and selects: craftax_reset of 4,096 environments (8,192 worlds,
+// 340 MB) by single wavefronts 179 -> 150 us, with Perlin noise 346 -> 246, of 256 with Perlin noise 39 -> 29.
 // LOOPED: the call stands in a loop over worlds; what a thread derives from its index is then derived
 // anew in every call instead of being kept (and spilled) across the loop.
 template <int NT = GEN_THREADS, bool CAN_PERLIN = false, bool LOOPED = false>
@@ -328,6 +339,10 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         if (tid0 < W) cave_row_mask(L, f, tid0);
         barrier();
     }
+    if (CAN_PERLIN) cx::floor_rounding(tid0);
+    // A run's number and the number of its strip are even or odd together, and so is the lane's: whether a
+    // run is the right half of a spacing-16 lattice cell is the same in every pass.
+    static_assert(ROW_RUNS % 2 == 0 && NT % 2 == 0, "parity of the strips");
     // runs of 8 cells, one per thread and pass
 #pragma unroll 1
     for (int run = tid0; run < RUNS; run += NT) {
@@ -342,19 +357,8 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         if (j < 4u) { blocks.x = (blocks.x & keep) | (block << sh); items.x = (items.x & light) | (item << sh); }
         else { blocks.y = (blocks.y & keep) | (block << sh); items.y = (items.y & light) | (item << sh); }
     };
-    // The run two cells at a time, a loop that is not unrolled: less code, and few enough registers for
-    // the step kernels and for six to eight wavefronts per SIMD in the others (four cells at a time:
-    // UED turn over 1,000 Perlin levels 326 us, two: 302).  cell(j, u): block of cell j, u = its draw in
-    // the upper half.
-    auto cells = [&](auto&& cell) {
-#pragma unroll 1
-        for (int j = 0; j < RUN; j += 2) {
-            const uint32_t two = (uint32_t)cell(j, r.w[0] << 16) | ((uint32_t)cell(j + 1, r.w[0]) << 8);
-            blocks.x = __builtin_amdgcn_alignbit(blocks.y, blocks.x, 16);
-            blocks.y = (blocks.y >> 16) | (two << 16);
-            r.w[0] = r.w[1]; r.w[1] = r.w[2]; r.w[2] = r.w[3];
-        }
-    };
+    uint32_t word = 0u, second = 0u;                        // the cells under way, from right to left; the finished cells 4..7
+    auto draw = [&](auto j) { return (j & 1) ? r.w[j >> 1] : r.w[j >> 1] << 16; };   // draw of cell j, in the upper half
     // the floor is the same for the whole block: one kind of cell function per block
     if (f == 0) {
         const uint32_t* w16 = s_lat + LAT_AT16;
@@ -363,38 +367,59 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         const uint32_t* m8 = w8 + 49;
         const uint32_t* c8 = m8 + 49;
         const uint32_t* f8 = c8 + 49;
-        const int iy16 = y >> 4, iy8 = y >> 3, ix16 = x0 >> 4, odd8 = x0 & 8;
+        const int iy16 = y >> 4, iy8 = y >> 3, ix16 = x0 >> 4;
+        uint32_t odd = 0u - (uint32_t)(run & 1);            // all ones: right half of a spacing-16 lattice cell
+        asm volatile("" : "+v"(odd));                        // or the weights of all passes are computed, and spilled, before the first
         // 4 times the lowering (10 - d) * 2500 of W and M within Chebyshev distance d < 10 of the start
-        const int bias_y = max(0, START_BIAS_R - iabs(y - W / 2)) * (4 * START_BIAS);
-        auto cell = [&](int j, int W4, int M4, uint32_t C, uint32_t F, uint32_t u, auto perlin) {
-            const int bias = min(bias_y, max(0, START_BIAS_R - iabs(x0 + j - W / 2)) * (4 * START_BIAS));
-            const int b = cx::classify<decltype(perlin)::value>(W4 - bias, M4 - bias, C, F, u);
-            return bias >= (START_BIAS_R - START_CLEAR) * (4 * START_BIAS) ? (int)B_GRASS : b;
+        const int step = 4 * START_BIAS, bias_y = max(0, START_BIAS_R - iabs(y - W / 2)) * step;
+        const int bias_l = (START_BIAS_R + x0 - W / 2) * step, bias_r = (START_BIAS_R - x0 + W / 2) * step;
+        const bool near_rows = __any(bias_y != 0);          // a pass covers ten or eleven rows
+        auto put = [&](const auto& thresholds, auto j, int W4, int M4, uint32_t C, uint32_t F) {
+            uint32_t u = draw(j);
+            if (near_rows) cx::near_start(max(0, min(min(bias_l + j * step, bias_r - j * step), bias_y)), W4, M4, u);
+            cx::classify(word, thresholds, W4, M4, C, F, u);
+            cx::settle(word);
+            if (j == 4) second = word;                      // (the next four cells shift it out)
         };
         if (CAN_PERLIN && use_perlin) {
-            const cx::Gradients gW = cx::gradients_at(w16, 4, ix16, iy16), gM = cx::gradients_at(m16, 4, ix16, iy16);
-            const cx::Gradients hW = cx::gradients_at(w8, 7, strip, iy8), hM = cx::gradients_at(m8, 7, strip, iy8),
-                                hC = cx::gradients_at(c8, 7, strip, iy8), hF = cx::gradients_at(f8, 7, strip, iy8);
-            const int ky16 = y & 15, ky8 = y & 7, wy16 = cx::perlin_fade<16>(ky16), wy8 = cx::perlin_fade<8>(ky8);
-            auto coarse = [&](const cx::Gradients& g, int j, int wx) { return cx::perlin_value<16>(cx::perlin_n<16>(g, odd8 + j, ky16, wx, wy16)); };
-            auto fine = [&](const cx::Gradients& g, int j) { return cx::perlin_n<8>(g, j, ky8, cx::perlin_fade<8>(j), wy8); };
-            cells([&](int j, uint32_t u) {
-                const int wx16 = cx::perlin_fade<16>(odd8 + j);
-                return cell(j, 3 * coarse(gW, j, wx16) + cx::perlin_value<8>(fine(hW, j)), 3 * coarse(gM, j, wx16) + cx::perlin_value<8>(fine(hM, j)),
-                            (uint32_t)fine(hC, j), (uint32_t)fine(hF, j), u, std::integral_constant<bool, CAN_PERLIN>());
-            });
+            const int ky16 = y & 15, ky8 = y & 7, kx16 = x0 & 15;
+            const double wy16 = cx::perlin_fade<16>(ky16) * (1.0 / 65536.0), wy8 = cx::perlin_fade<8>(ky8) * (1.0 / 65536.0);
+            // One field after the other for the whole run (a line takes 16 registers); the last one with the rule.
+            // The empty statement keeps the loads of a field's gradients from being moved before the field at hand.
+            auto along = [&](cx::PerlinLine line, auto&& weight, double wy, auto&& cell) {
+                cx::for_run([&](auto j) { cell(j, line.field(weight(j), wy)); line.advance(); });
+                asm volatile("" ::: "memory");
+            };
+            auto wide = [&](const uint32_t* lat) { return cx::perlin_line<16>(cx::gradients_at(lat, 4, ix16, iy16), kx16 + 7, ky16); };
+            auto narrow = [&](const uint32_t* lat) { return cx::perlin_line<8>(cx::gradients_at(lat, 7, strip, iy8), 7, ky8); };
+            auto weight16 = [&](auto j) { return cx::pick<cx::high_half(cx::perlin_weight<16>(8 + j)), cx::high_half(cx::perlin_weight<16>(j))>(odd); };
+            auto weight8 = [&](auto j) { return cx::scalar_double<cx::high_half(cx::perlin_weight<8>(j))>(); };
+            int W4[RUN], M4[RUN];
+            uint32_t C[RUN];
+            const cx::PerlinScale<16> coarse;
+            const cx::PerlinScale<8> fine;
+            along(wide(w16), weight16, wy16, [&](int j, double v) { W4[j] = coarse.value(v); cx::settle(W4[j]); });
+            along(narrow(w8), weight8, wy8, [&](int j, double v) { W4[j] = 3 * W4[j] + fine.value(v); cx::settle(W4[j]); });
+            along(wide(m16), weight16, wy16, [&](int j, double v) { M4[j] = coarse.value(v); cx::settle(M4[j]); });
+            along(narrow(m8), weight8, wy8, [&](int j, double v) { M4[j] = 3 * M4[j] + fine.value(v); cx::settle(M4[j]); });
+            along(narrow(c8), weight8, wy8, [&](int j, double v) { C[j] = cx::settled(v); });
+            const cx::Thresholds<CAN_PERLIN> thresholds;
+            along(narrow(f8), weight8, wy8, [&](auto j, double v) { put(thresholds, j, W4[j], M4[j], C[j], (uint32_t)__double2loint(v)); });
         } else {
             const uint32_t v16 = cx::vertical_weights(cx::smooth16(y & 15)), v8 = cx::vertical_weights(cx::smooth8(y & 7));
-            const Ends W16 = ends_at(w16, 4, ix16, iy16, v16), M16 = ends_at(m16, 4, ix16, iy16, v16);
-            const Ends W8 = ends_at(w8, 7, strip, iy8, v8), M8 = ends_at(m8, 7, strip, iy8, v8), C8 = ends_at(c8, 7, strip, iy8, v8),
-                       F8 = ends_at(f8, 7, strip, iy8, v8);
-            cells([&](int j, uint32_t u) {
-                const uint32_t wx16 = cx::smooth16(odd8 + j), wx8 = cx::smooth8(j);
-                return cell(j, cx::mix31(cx::across(W16.l, W16.r, wx16), cx::across(W8.l, W8.r, wx8)),
-                            cx::mix31(cx::across(M16.l, M16.r, wx16), cx::across(M8.l, M8.r, wx8)), cx::across(C8.l, C8.r, wx8),
-                            cx::across(F8.l, F8.r, wx8), u, std::integral_constant<bool, false>());
+            const double last16 = cx::pick<cx::high_half(cx::LAST16_ODD), cx::high_half(cx::LAST16)>(odd);
+            cx::Line W16 = line_at(w16, 4, ix16, iy16, v16, last16), M16 = line_at(m16, 4, ix16, iy16, v16, last16);
+            cx::Line W8 = line_at(w8, 7, strip, iy8, v8, cx::LAST8), M8 = line_at(m8, 7, strip, iy8, v8, cx::LAST8);
+            cx::Line C8 = line_at(c8, 7, strip, iy8, v8, cx::LAST8), F8 = line_at(f8, 7, strip, iy8, v8, cx::LAST8);
+            const cx::Thresholds<false> thresholds;
+            cx::for_run([&](auto j) {
+                put(thresholds, j, cx::mix31(W16.field(), W8.field()), cx::mix31(M16.field(), M8.field()), C8.field(), F8.field());
+                const double s16 = cx::pick<cx::high_half(cx::step16(8 + j)), cx::high_half(cx::step16(j))>(odd);
+                W16.advance(s16); M16.advance(s16);
+                for (cx::Line* l : {&W8, &M8, &C8, &F8}) l->advance(cx::step8(j));
             });
         }
+        blocks = make_uint2(cx::blocks_of(word), cx::blocks_of(second));
         place(L.spot[SPOT_DOWN], B_PATH, IT_LADDER_DOWN);
     } else if (is_dungeon(f)) {
         const int yr = CX_IDX(y, W);
@@ -428,19 +453,41 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         const uint32_t* c8 = s_lat + LATC_AT8;
         const uint32_t* f8 = c8 + 49;
         const int iy8 = y >> 3;
-        if (CAN_PERLIN && use_perlin) {
-            const cx::Gradients hC = cx::gradients_at(c8, 7, strip, iy8), hF = cx::gradients_at(f8, 7, strip, iy8);
-            const int ky8 = y & 7, wy8 = cx::perlin_fade<8>(ky8);
-            auto fine = [&](const cx::Gradients& g, int j) { return (uint32_t)cx::perlin_n<8>(g, j, ky8, cx::perlin_fade<8>(j), wy8); };
-            cells([&](int j, uint32_t u) { return classify_cave<CAN_PERLIN>(rule, fine(hC, j), fine(hF, j), u); });
-        } else {
-            const uint32_t v8 = cx::vertical_weights(cx::smooth8(y & 7));
-            const Ends C8 = ends_at(c8, 7, strip, iy8, v8), F8 = ends_at(f8, 7, strip, iy8, v8);
-            cells([&](int j, uint32_t u) {
-                return classify_cave<false>(rule, cx::across(C8.l, C8.r, cx::smooth8(j)), cx::across(F8.l, F8.r, cx::smooth8(j)), u);
-            });
-        }
-        blocks = cells_where(blocks, (uint32_t)(L.row_mask[M_CAVE_OPEN][CX_IDX(y, W)] >> x0), rule.open);
+        auto cave = [&](auto kind) {
+            constexpr int KIND = decltype(kind)::value;
+            if (CAN_PERLIN && use_perlin) {
+                const int ky8 = y & 7;
+                const double wy8 = cx::perlin_fade<8>(ky8) * (1.0 / 65536.0);
+                uint32_t C[RUN];
+                auto weight8 = [&](auto j) { return cx::scalar_double<cx::high_half(cx::perlin_weight<8>(j))>(); };
+                cx::PerlinLine nC = cx::perlin_line<8>(cx::gradients_at(c8, 7, strip, iy8), 7, ky8);
+                cx::for_run([&](auto j) { C[j] = cx::settled(nC.field(weight8(j), wy8)); nC.advance(); });
+                asm volatile("" ::: "memory");
+                cx::PerlinLine nF = cx::perlin_line<8>(cx::gradients_at(f8, 7, strip, iy8), 7, ky8);
+                const CaveThresholds<CAN_PERLIN, KIND> thresholds;
+                cx::for_run([&](auto j) {
+                    classify_cave<CAN_PERLIN, KIND>(word, thresholds, rule.below1, C[j], KIND == GNOME_MINES ? 0u : (uint32_t)__double2loint(nF.field(weight8(j), wy8)), draw(j));
+                    cx::settle(word);
+                    if (j == 4) second = word;
+                    nF.advance();
+                });
+            } else {
+                const uint32_t v8 = cx::vertical_weights(cx::smooth8(y & 7));
+                cx::Line C8 = line_at(c8, 7, strip, iy8, v8, cx::LAST8), F8 = line_at(f8, 7, strip, iy8, v8, cx::LAST8);
+                const CaveThresholds<false, KIND> thresholds;
+                cx::for_run([&](auto j) {
+                    classify_cave<false, KIND>(word, thresholds, rule.below1, C8.field(), KIND == GNOME_MINES ? 0u : F8.field(), draw(j));
+                    cx::settle(word);
+                    if (j == 4) second = word;
+                    C8.advance(cx::step8(j)); F8.advance(cx::step8(j));
+                });
+            }
+        };
+        if (f == 2) cave(std::integral_constant<int, GNOME_MINES>());
+        else if (f == 5) cave(std::integral_constant<int, TROLL_MINES>());
+        else cave(std::integral_constant<int, REALM>());
+        blocks = make_uint2(cave_blocks(rule, word), cave_blocks(rule, second));
+        blocks = cells_where(blocks, (uint32_t)(L.row_mask[M_CAVE_OPEN][CX_IDX(y, W)] >> x0), cave_ground(f));
         place(L.spot[SPOT_UP], B_PATH, IT_LADDER_UP);
         place(L.spot[SPOT_DOWN], B_PATH, IT_LADDER_DOWN_BLOCKED);
     }
@@ -461,6 +508,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         }
     }
     }
+    if (CAN_PERLIN) cx::nearest_rounding(episode);
     barrier();
 }
 

@@ -17,7 +17,8 @@
 
 namespace cx {
 
-constexpr uint32_t HEAD_ROUNDS = 2u;
+// a step of 65,536 environments, 728 units in a launch: 43.0 us with one round, 43.5 with two, 44.0 with three
+constexpr uint32_t HEAD_ROUNDS = 1u;
 
 struct UnitWalk {
     uint32_t u;         // the unit to generate now; the walk is over once u >= 2 * count
