@@ -100,7 +100,7 @@ __global__ __launch_bounds__(WG_THREADS, PERLIN ? 6 : 8) void k_reset(uint4* __r
 
 // A regeneration block of the step grid: worlds for the episodes after next of the episodes that
 // ended in the previous launch.
-template <bool PERLIN>
+template <bool PERLIN, bool SPLIT = false>
 __device__ __forceinline__ void regeneration_block(uint8_t* __restrict__ maps, const Lists& ls, uint32_t seq, uint32_t count,
                                                    uint32_t rb, uint32_t nrb, uint32_t* s_lat, const uint32_t* __restrict__ perlin_cs)
 {
@@ -111,7 +111,7 @@ __device__ __forceinline__ void regeneration_block(uint8_t* __restrict__ maps, c
     for (uint32_t i = pair >> 1; i < count; i += nrb / NSUB / 2) {
         const uint4 entry = list[i];
         if (entry.x == ENTRY_VOID) continue;
-        worldgen_block<BLOCK, PERLIN, false>(maps + map_offset(entry.x, entry.w), s_lat, entry.y, entry.z, entry.x, entry.w, nullptr,
+        worldgen_block<BLOCK, PERLIN, SPLIT>(maps + map_offset(entry.x, entry.w), s_lat, entry.y, entry.z, entry.x, entry.w, nullptr,
                                       (int)half * (STRIPS / 2), perlin_cs);
         if (threadIdx.x == 0) ls.tags[2 * entry.x + half] = make_uint2(entry.w, seq);
     }
@@ -253,16 +253,26 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
     la::append_block_entries(ls, seq, s_list, nd, &s_base, blockIdx.x);
 }
 
-// A launch of regeneration blocks only (before a rollout): brings every spare world up to date and
-// empties the lists, with the bookkeeping of a step launch that has no step blocks.
+// A launch of regeneration blocks only (before and after a rollout): brings every spare world up to date
+// and empties the lists, with the bookkeeping of a step launch that has no step blocks.
 template <bool PERLIN>
-__global__ __launch_bounds__(BLOCK) void k_drain(uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
+__global__ __launch_bounds__(BLOCK, PERLIN ? 5 : 6) void k_drain(uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
 {
     __shared__ uint32_t s_lat[LAT_WORDS];
     const uint32_t rb = blockIdx.x, nrb = gridDim.x;
     const la::Ticket ticket = la::enter_launch(ls, true, rb);
-    if (rb / NSUB / 2 < ticket.regen_count) regeneration_block<PERLIN>(maps, ls, ticket.seq, ticket.regen_count, rb, nrb, s_lat, luts->perlin_cs);
+    if (rb / NSUB / 2 < ticket.regen_count) regeneration_block<PERLIN, true>(maps, ls, ticket.seq, ticket.regen_count, rb, nrb, s_lat, luts->perlin_cs);
     la::leave_launch(ls, ticket);
+}
+
+// Half a world by a whole block.  Not inlined: the rollout kernel's loop would pay for the generator's
+// registers in spills at every step.
+template <typename T> using Lds = T __attribute__((address_space(3)));
+template <bool PERLIN>
+__device__ __attribute__((noinline)) void generate_half(uint8_t* map, Lds<uint32_t>* lat, Lds<uint32_t>* start_win, uint32_t lo, uint32_t hi, uint32_t env,
+                                                        uint32_t ep, int half, const uint32_t* perlin_cs)
+{
+    worldgen_block<BLOCK, PERLIN, false>(map, (uint32_t*)lat, lo, hi, env, ep, (uint32_t*)start_win, half * (STRIPS / 2), perlin_cs);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -270,26 +280,31 @@ __global__ __launch_bounds__(BLOCK) void k_drain(uint8_t* __restrict__ maps, con
 // hand (a random or scripted policy; appendix "Optimistic Environment Resets" measures such
 // rollouts).  A block keeps its environments (64 at 4 lanes each, 16 at 16 lanes) in LDS for the whole launch and walks through
 // the steps on its own, so blocks drift apart and the memory traffic of some overlaps the
-// arithmetic of others; nothing is exchanged between blocks.  Worlds are generated one episode
-// ahead as in the step kernel, but by the block itself: an environment whose episode ends moves
-// into its spare world and queues for a new spare, and after every step the block generates at
-// most one queued world.  An episode that ends before its spare exists has its world generated on
-// the spot.  Before the launch the regeneration lists of the step kernel must be empty and every
-// spare world in place (the host entry point runs a list-only launch first); afterwards every
-// environment again has its spare, tagged as written by launch 0.
+// arithmetic of others; nothing is exchanged between blocks.  Worlds stay one episode ahead as in
+// the step kernel: an environment whose episode ends moves into its spare world.  The world after that
+// one is left to the regeneration launch behind this one, which generates all of them with the whole
+// chip, or, up to `own` of them after every step, generated by the block itself (see launch_rollout);
+// the environments that are owed a world at the end go on the regeneration list.  An environment whose
+// episode ends without a spare world has the next world generated on the spot.  Before the launch the
+// regeneration lists of the step kernel must be empty (the host runs a list-only launch first).
+// Measured against blocks that generate all their worlds, by code in the loop (64 steps, value noise /
+// Perlin): 12,000 environments 603 / 710 -> 569 / 614 us, 32,768: 1,164 / 1,367 -> 1,065 / 1,157,
+// 65,536: 1,801 / 2,051 -> 1,776 / 1,895; 517 environments and 29 steps 212 -> 186.
 template <int G, int OBS_MODE, bool PERLIN>
 __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                       const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                       uint8_t* __restrict__ obs, float* __restrict__ reward,
-                                                      uint8_t* __restrict__ done, uint2* __restrict__ tags, Params p, int steps)
+                                                      uint8_t* __restrict__ done, Lists ls, Params p, int steps, int own)
 {
     constexpr int EPB = Grp<G>::EPB;
     __shared__ uint32_t s_env[EPB * LDS_ENV_DWORDS];
-    __shared__ uint32_t s_lat[LAT_WORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t s_lat[LAT_WORDS];   // the generator's lattices; at the end the environments that are owed a world
+    static_assert(LAT_WORDS >= EPB * 4, "an entry per environment");
     __shared__ uint8_t s_queue[EPB];        // ring of environments (index in the block) waiting for a new spare world
     __shared__ uint8_t s_urgent[EPB];       // environments whose episode ended without a spare world
     __shared__ uint8_t s_spare_ok[EPB], s_pending[EPB];
     __shared__ int s_qhead, s_qtail, s_nurgent;
+    __shared__ uint32_t s_base;
     const int tid = threadIdx.x, g = tid / G, l = tid % G;
     const int env = blockIdx.x * EPB + g;
     const bool active = env < p.n;
@@ -300,7 +315,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
     if (active) load_record<G>(l, recs + (size_t)env * 8, e);
     __syncthreads();
     if (active && l == 0) {
-        const uint4 tag = reinterpret_cast<const uint4*>(tags)[env];
+        const uint4 tag = reinterpret_cast<const uint4*>(ls.tags)[env];
         const uint32_t next = e[LDS_REC + RW_EPISODE] + 1u;
         const bool ok = tag.x == next && tag.z == next;
         s_spare_ok[g] = ok ? 1 : 0;
@@ -315,13 +330,11 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         const uint32_t tenv = (uint32_t)(blockIdx.x * EPB + gt), ep = rt[RW_EPISODE] + 1u, lo = rt[RW_SEED_LO], hi = rt[RW_SEED_HI];
 #pragma unroll 1
         for (int half = 0; half < 2; ++half)
-            worldgen_block<BLOCK, PERLIN, false>(maps + map_offset(tenv, ep), s_lat, lo, hi, tenv, ep, start_win, half * (STRIPS / 2), luts->perlin_cs);
+            generate_half<PERLIN>(maps + map_offset(tenv, ep), (Lds<uint32_t>*)s_lat, (Lds<uint32_t>*)start_win, lo, hi, tenv, ep, half, luts->perlin_cs);
     };
 
-    // steps, then as many turns without a step as it takes to generate the spare worlds still owed
 #pragma unroll 1
-    for (int t = 0; t < steps || s_qhead != s_qtail; ++t) {
-        const bool stepping = t < steps;
+    for (int t = 0; t < steps; ++t) {
         // Everything a lane derives from its index is derived again in every turn: the compiler would
         // otherwise keep dozens of such values alive across the whole loop and spill them.
         int tid_t = threadIdx.x;
@@ -336,7 +349,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         bool fresh = false;        // this group starts a new episode in this step
         StepOut o;
         o.done = false; o.mvx = 0; o.mvy = 0; o.woff = 0; o.reward = 0.0f; o.unlocked = 0u;
-        if (active && stepping) {
+        if (active) {
             const uint32_t* rec = e + LDS_REC;
             const uint32_t ep = rec[RW_EPISODE], lo = rec[RW_SEED_LO], hi = rec[RW_SEED_HI];
             o = step_env<G, true>(l, (uint32_t)env, e, maps + map_offset((uint32_t)env, ep), luts, actions[(size_t)t * p.n + env], p);
@@ -365,8 +378,8 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
             }
         }
         __syncthreads();
-        // worlds that have to exist now, then at most one of the queued spare worlds
-        int budget = 1;
+        // worlds that have to exist now, then queued spare worlds
+        int budget = own;
 #pragma unroll 1
         while (true) {
             const int nurgent = s_nurgent, qhead = s_qhead, qtail = s_qtail;
@@ -397,11 +410,11 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         // with the window the generator left in LDS
         if (active && o.done && !fresh) { o.mvx = 0; o.mvy = 0; o.woff = (MAPW / 2 - WIN_COLS / 2) & 3; }
         bool staged = false;
-        if (active && stepping && obs != nullptr) {
+        if (active && obs != nullptr) {
             render_symbolic<G, OBS_MODE, true, !kBytes>(l, e, o.mvx, o.mvy, o.woff, luts, obs + (size_t)env * obs_stride(OBS_MODE));
             staged = kBytes;
         }
-        if (kBytes && stepping && obs != nullptr) {
+        if (kBytes && obs != nullptr) {
             if (l == 0) e[LDS_FLAG] = staged ? 1u : 0u;
             group_sync();
             const int first = (tid & ~63) / G;
@@ -410,11 +423,17 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         }
         __syncthreads();
     }
-    // the records and the tags of the spare slots
+    // the records; the tags of the spare worlds that the block has generated (the others are as they were);
+    // the worlds owed, for the regeneration launch (on the list that a step launch before it would fill)
+    uint4* s_list = reinterpret_cast<uint4*>(s_lat);
     if (active) {
         store_record<G>(l, recs + (size_t)env * 8, e);
-        if (l < 2) tags[2 * env + l] = make_uint2(e[LDS_REC + RW_EPISODE] + 1u, 0u);
+        if (s_spare_ok[g]) { if (own != 0 && l < 2) ls.tags[2 * env + l] = make_uint2(e[LDS_REC + RW_EPISODE] + 1u, 0u); }
+        else if (l == 0) s_list[atomicAdd(&s_nurgent, 1)] = make_uint4((uint32_t)env, e[LDS_REC + RW_SEED_LO], e[LDS_REC + RW_SEED_HI], e[LDS_REC + RW_EPISODE] + 1u);
     }
+    __syncthreads();
+    const int owed = s_nurgent;
+    if (owed != 0) la::append_block_entries(ls, *counter(ls, la::CT_SEQ) - 1u, s_list, owed, &s_base, blockIdx.x);
 }
 
 // Serves the slow list: generates the world of the new episode in place (one block each, looping
@@ -1020,6 +1039,8 @@ static int group_lanes(const craftax_config* cfg, int n)
 constexpr int RESET_GRID = 64;    // blocks of k_reset_list (the slow list is nearly always empty); each loops over the list
 constexpr int POOL_RESET_GRID = 512;   // the same with optimistic resets, where every finished episode is on that list
 constexpr int REGEN_BLOCKS = 1024; // regeneration blocks appended to the step grid (two per world); those beyond the list exit at once
+constexpr int OWN_WORLDS_FROM = 49152;   // environments from which a rollout's blocks generate worlds themselves
+constexpr int OWED_BLOCKS = 1536;   // regeneration blocks behind a rollout: six wavefronts per SIMD, what their registers allow
 constexpr int SHARED_REGEN_BLOCKS = 256;   // with four lanes per environment: one per compute unit, beside its four step blocks (see regeneration_share)
 
 template <int OBS_MODE>
@@ -1047,21 +1068,30 @@ template <int OBS_MODE>
 static void launch_rollout(int lanes, int n, hipStream_t st, const Ptrs& q, const int32_t* actions, int steps, uint8_t* o,
                            float* reward, uint8_t* done, const Params& p)
 {
-    // a launch of regeneration blocks only brings every spare world up to date and empties the lists
+    // launches of regeneration blocks only bring every spare world up to date and empty the lists: before
+    // the rollout for what steps left, behind it for the worlds that it owes
     const int regen = ((2 * n < REGEN_BLOCKS ? 2 * n : REGEN_BLOCKS) + 2 * NSUB - 1) / (2 * NSUB) * (2 * NSUB);
+    const int owed = ((2 * n < OWED_BLOCKS ? 2 * n : OWED_BLOCKS) + 2 * NSUB - 1) / (2 * NSUB) * (2 * NSUB);
     // lanes per environment as chosen for single steps: four (64 environments per block) where there
     // are enough environments to fill the chip that way, else sixteen (16 per block)
     const bool wide = lanes != 4;
+    // worlds a block generates itself after a step: none while the chip has room beside the blocks, because a
+    // block stops for its world; one where they nearly fill it, because the others' memory traffic then covers
+    // for it (64 steps, skewed actions, value noise / Perlin, none against one: 32,768 environments 1,065 / 1,157
+    // against 1,125 / 1,219 us, 49,152: 1,424 / 1,561 against 1,428 / 1,540, 65,536: 1,825 / 2,004 against 1,776 / 1,895)
+    const int own = !wide && n >= OWN_WORLDS_FROM ? 1 : 0;
     const int blocks = wide ? (n + 15) / 16 : (n + 63) / 64;
 #define CRAFTAX_LAUNCH_ROLLOUT(LANES, NOISE) \
     hipLaunchKernelGGL((k_rollout<LANES, OBS_MODE, NOISE>), dim3(blocks), dim3(BLOCK), 0, st, q.recs, q.maps, q.luts, actions, o, reward, \
-                       done, q.ls.tags, p, steps)
+                       done, q.ls, p, steps, own)
     if (p.worldgen == CRAFTAX_WORLDGEN_PERLIN) {
         hipLaunchKernelGGL(k_drain<true>, dim3(regen), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
         if (wide) CRAFTAX_LAUNCH_ROLLOUT(16, true); else CRAFTAX_LAUNCH_ROLLOUT(4, true);
+        hipLaunchKernelGGL(k_drain<true>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
     } else {
         hipLaunchKernelGGL(k_drain<false>, dim3(regen), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
         if (wide) CRAFTAX_LAUNCH_ROLLOUT(16, false); else CRAFTAX_LAUNCH_ROLLOUT(4, false);
+        hipLaunchKernelGGL(k_drain<false>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
     }
 #undef CRAFTAX_LAUNCH_ROLLOUT
 }
@@ -1179,7 +1209,8 @@ static int check_kernels(const craftax_config* cfg, int lanes, std::string* err)
 #undef CRAFTAX_CHECK_MODE
 #undef CRAFTAX_CHECK_ROLLOUT
     ok = ok && (perlin ? fits("k_reset", (const void*)k_reset<true>, WG_THREADS) : fits("k_reset", (const void*)k_reset<false>, WG_THREADS)) && fits("k_import_spare", (const void*)k_import_spare, WG_THREADS) &&
-         fits("k_mutate_noise", (const void*)k_mutate_noise, WG_THREADS);
+         fits("k_mutate_noise", (const void*)k_mutate_noise, WG_THREADS) &&
+         (perlin ? fits("k_drain", (const void*)k_drain<true>, BLOCK) : fits("k_drain", (const void*)k_drain<false>, BLOCK));
     return ok ? CRAFTAX_OK : CRAFTAX_E_CONFIG;
 }
 

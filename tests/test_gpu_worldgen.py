@@ -27,3 +27,32 @@ def test_worlds_match_oracle(full, n, perlin):
     got, want = sim.reset(seeds).cpu().numpy(), orc.reset(seeds)
     assert np.array_equal(got, want)
     assert sim.export_envs().tobytes() == orc.envs.tobytes()
+
+
+@pytest.mark.parametrize("perlin", [False, True])
+@pytest.mark.parametrize("n", [17, 49152])
+def test_classic_rollout_owes_worlds(n, perlin):
+    """A rollout in which episodes end once, twice and more often (a cap of 9 in 31 steps), below and at the
+    size from which its blocks generate worlds themselves: afterwards every spare world is in place, so
+    that steps go on exactly as in a batch that was stepped from the start."""
+    import torch
+    noise = cx.WORLDGEN_PERLIN if perlin else cx.WORLDGEN_VALUE
+    steps, after = 31, 12
+    cfg = cx.default_config(worldgen=noise, max_episode_steps=9)
+    seeds = np.arange(n, dtype=np.uint64) + np.uint64(77)
+    rolled, stepped = cx.Craftax(n, cfg), cx.Craftax(n, cfg)
+    rolled.reset(seeds)
+    stepped.reset(seeds)
+    acts = torch.empty((steps + after, n), dtype=torch.int32, device=rolled.device)
+    cx.craftax_synth_actions(acts, n, 0, steps + after, 3, 1, rolled.stream)
+    rew = torch.zeros((steps, n), dtype=torch.float32, device=rolled.device)
+    done = torch.zeros((steps, n), dtype=torch.uint8, device=rolled.device)
+    cx.craftax_rollout(rolled.state, acts[:steps].contiguous(), steps, rolled.obs, rew, done, n, rolled.stream)
+    for s in range(steps):
+        obs, r, d = stepped.step(acts[s])
+        assert torch.equal(r, rew[s]) and torch.equal(d, done[s]), s
+    assert torch.equal(obs, rolled.obs)
+    for s in range(steps, steps + after):
+        a, b = rolled.step(acts[s]), stepped.step(acts[s])
+        assert all(torch.equal(x, y) for x, y in zip(a, b)), s
+    assert rolled.export_envs().tobytes() == stepped.export_envs().tobytes()
