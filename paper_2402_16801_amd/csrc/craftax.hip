@@ -174,7 +174,24 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
     // counter of its own: the two round trips then overlap
     RecordRegs<G> fetched;
     int action = 0;
-    if (active) { fetch_record<G>(l, recs + (size_t)env * 8, fetched); action = actions[env]; }
+    // EAGER (16 lanes per environment, a launch of one short chain per wavefront): what an episode that ends
+    // needs (the tags of the spare world, the window of its start position) and the tables that the renderer
+    // looks scalars up in are fetched in advance, its place on the list is claimed before the rendering,
+    // and no wavefront waits for the others of its block.  The launch ends with its slowest
+    // wavefront, nearly always one with such an episode, and each of these was a trip to memory of its own
+    // at the end of that one's chain (4,096 environments 10.4 -> 9.3 us, 8,192: 12.2 -> 10.9, 500: 9.1 -> 8.2; one
+    // alone 7.5 either way).  With fewer lanes the chip is full, and the launch bound by memory and issue.
+    constexpr bool EAGER = G == 16, kFloats = OBS_MODE == CRAFTAX_OBS_SYM_U8_F32 || OBS_MODE == CRAFTAX_OBS_SYM_F32;
+    uint4 spare_tag = make_uint4(0u, 0u, 0u, 0u);
+    float lut_sqrt10 = 0.0f, lut_tenth = 0.0f;
+    if (active) {
+        fetch_record<G>(l, recs + (size_t)env * 8, fetched);
+        action = actions[env];
+        if (EAGER) {
+            spare_tag = reinterpret_cast<const uint4*>(ls.tags)[env];
+            if (kFloats) { lut_sqrt10 = luts->sqrt10[l]; lut_tenth = luts->tenth[l]; }
+        }
+    }
     // SHARE: every block reads the length of one sub-list of the consumed list, a regeneration block
     // its own, a step block the one it appends to (see regeneration_share)
     constexpr bool SHARE = G == 4;
@@ -195,8 +212,13 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
         return;
     }
 
-    if (tid == 0) s_ndone = 0;
-    __syncthreads();
+    if (!EAGER) {
+        if (tid == 0) s_ndone = 0;
+        __syncthreads();
+    }
+    bool queued = false;                 // EAGER: this group's episode ended; its place on the list is on its way
+    uint32_t list_at = 0u;
+    uint4 entry = make_uint4(0u, 0u, 0u, 0u);
     uint32_t* e = s_env + g * LY::STRIDE;
     constexpr bool kSymbolic = OBS_MODE != CRAFTAX_OBS_PIXELS_F32;
     constexpr bool kBytes = OBS_MODE == CRAFTAX_OBS_SYM_U8_I8 || OBS_MODE == CRAFTAX_OBS_SYM_U8_F32;
@@ -206,13 +228,24 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
         group_sync();
         const uint32_t* rec = e + LDS_REC;
         const uint32_t ep = rec[RW_EPISODE], lo = rec[RW_SEED_LO], hi = rec[RW_SEED_HI];
+        // the windows of the current position and of the spare world's start come together
+        StartWindow<G> spare;
+        if (EAGER) spare.fetch(l, maps + map_offset((uint32_t)env, ep + 1u));
+        float day_next = 0.0f, day_fresh = 0.0f;               // daylight of the state that will be rendered
+        uint32_t q7_next = 0u, q7_fresh = 0u;
+        if (EAGER) {
+            uint32_t phase = (rec[RW_VIT] >> 16) + 1u;
+            if (phase == p.day_length) phase = 0u;
+            if (kFloats) { day_next = luts->daylight[phase]; day_fresh = luts->daylight[0]; }
+            else if (kSymbolic) { q7_next = luts->light_q7[phase]; q7_fresh = luts->light_q7[0]; }
+        }
         StepOut o = step_env<G>(l, (uint32_t)env, e, maps + map_offset((uint32_t)env, ep), luts, action, p);
         if (l == 0) { reward[env] = o.reward; done[env] = o.done ? 1 : 0; }
         count_unlocks<G>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, o.unlocked);
         bool write_back = !o.done;
         if (o.done) {
             // the record in LDS is still the episode that just ended
-            const uint4 tag = reinterpret_cast<const uint4*>(ls.tags)[env];   // (episode, launch) of the two halves of the spare world
+            const uint4 tag = EAGER ? spare_tag : reinterpret_cast<const uint4*>(ls.tags)[env];   // (episode, launch) of the two halves of the spare world
             if (p.reset_mode == CRAFTAX_RESET_EXACT && tag.x == ep + 1u && tag.y < seq && tag.z == ep + 1u && tag.w < seq) {
                 // the next world is waiting in the other slot: start the new episode right here
                 group_sync();
@@ -221,11 +254,16 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
                     const int i = l + it * G;
                     if (i < REC_DWORDS) e[LDS_REC + i] = fresh_record_word(i, lo, hi, ep + 1u);
                 }
-                load_window<G>(l, MAPW / 2, MAPW / 2, maps + map_offset((uint32_t)env, ep + 1u), e + LDS_WIN);
+                if (EAGER) spare.park(l, e + LDS_WIN);
+                else load_window<G>(l, MAPW / 2, MAPW / 2, maps + map_offset((uint32_t)env, ep + 1u), e + LDS_WIN);
                 group_sync();
                 o.mvx = 0; o.mvy = 0; o.woff = (MAPW / 2 - WIN_COLS / 2) & 3;
                 write_back = true;
-                if (l == 0) s_list[atomicAdd(&s_ndone, 1)] = make_uint4((uint32_t)env, lo, hi, ep + 2u);
+                if (l == 0) {
+                    entry = make_uint4((uint32_t)env, lo, hi, ep + 2u);
+                    if (EAGER) { list_at = la::claim_entry(ls, seq, blockIdx.x); queued = true; }
+                    else s_list[atomicAdd(&s_ndone, 1)] = entry;
+                }
             } else if (l == 0) {
                 la::append_slow(ls, (uint32_t)p.n, make_uint4((uint32_t)env, lo, hi, ep + 1u));
             }
@@ -234,7 +272,8 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
             store_record<G>(l, recs + (size_t)env * 8, e);
             if (kSymbolic && obs != nullptr) {
                 // byte layouts are staged in LDS here and written by the whole wave below
-                render_symbolic<G, OBS_MODE, true, !kBytes, LY>(l, e, o.mvx, o.mvy, o.woff, luts, obs + (size_t)env * obs_stride(OBS_MODE));
+                const RenderLuts tables{lut_sqrt10, lut_tenth, o.done ? day_fresh : day_next, o.done ? q7_fresh : q7_next};
+                render_symbolic<G, OBS_MODE, true, !kBytes, LY, EAGER>(l, e, o.mvx, o.mvy, o.woff, luts, obs + (size_t)env * obs_stride(OBS_MODE), &tables);
                 staged = kBytes;
             }
         }
@@ -245,6 +284,12 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
         const int first = (tid & ~63) / G;                         // first environment of this wave within the block
         flush_wave_observations<G, OBS_MODE, LY>(s_env + first * LY::STRIDE,
                                              obs + (size_t)(blockIdx.x * EPB + first) * obs_stride(OBS_MODE));
+    }
+    if (EAGER) {
+        // an entry at a time, the place claimed before the rendering: no wavefront waits for the others of its block
+        if (queued) la::commit_entry(ls, seq, blockIdx.x, list_at, entry);
+        leave();
+        return;
     }
     __syncthreads();
     leave();

@@ -79,10 +79,14 @@ __device__ __forceinline__ void flush_wave_observations(uint32_t* wave_env, uint
 // flush_wave_observations.
 // LY: where the scalars are staged.  With StepLayout they overwrite the record, which is read
 // completely (position, tables, inventory, vitals) before the first of them is written.
-template <int G, int OBS_MODE, bool FILL_VEC = true, bool FLUSH = true, class LY = KeepLayout>
+// TABLES (16 lanes per environment): sqrt10 and tenth come as entry l of either table in lane l, with the
+// daylight of the state, all fetched long before; else they are looked up in memory here.
+struct RenderLuts { float sqrt10, tenth, day; uint32_t q7; };   // q7: the daylight of the int8 layout
+template <int G, int OBS_MODE, bool FILL_VEC = true, bool FLUSH = true, class LY = KeepLayout, bool TABLES = false>
 __device__ __forceinline__ void render_symbolic(int l, uint32_t* e, int mvx, int mvy, int woff, const Luts* __restrict__ luts,
-                                       uint8_t* __restrict__ obs_out)
+                                       uint8_t* __restrict__ obs_out, const RenderLuts* tables = nullptr)
 {
+    static_assert(!TABLES || G == 16, "a lane per table entry");
     const uint32_t* rec = e + LDS_REC;
     const uint8_t* win = reinterpret_cast<const uint8_t*>(e + LDS_WIN);
     uint32_t* bits = e + LDS_BITS;
@@ -130,7 +134,7 @@ __device__ __forceinline__ void render_symbolic(int l, uint32_t* e, int mvx, int
         if (i < 12) return (w_inv >> (18 + i)) & 1;
         if (i < 16) return (w_vit >> (4 * (i - 12))) & 15;
         if (i < 20) return dir == i - 15 ? 1 : 0;
-        if (i == 20) return (int)luts->light_q7[phase];
+        if (i == 20) return TABLES ? (int)tables->q7 : (int)luts->light_q7[phase];
         if (i == 21) return sleeping;
         return 0;
     };
@@ -152,8 +156,12 @@ __device__ __forceinline__ void render_symbolic(int l, uint32_t* e, int mvx, int
         if (i >= (24)) break;
             float v = 0.0f;
             if (i < NVEC) {
-                const int raw = raw_of(i);
-                if (i < 6) v = luts->sqrt10[raw];
+                const int raw = i == 20 ? 0 : raw_of(i);
+                if (TABLES) {
+                    // every lane of the group takes part in the exchange; counts and vitals are below 16
+                    const float root = __shfl(tables->sqrt10, raw & 15, G), tenth = __shfl(tables->tenth, raw & 15, G);
+                    v = i < 6 ? root : (i >= 12 && i < 16 ? tenth : (i == 20 ? tables->day : (float)raw));
+                } else if (i < 6) v = luts->sqrt10[raw];
                 else if (i >= 12 && i < 16) v = luts->tenth[raw];
                 else if (i == 20) v = luts->daylight[phase];
                 else v = (float)raw;

@@ -80,6 +80,26 @@ __device__ __forceinline__ void load_window(int l, int px, int py, const uint8_t
     load_window<G>(l, px, py, map, win, full_window());
 }
 
+// The window of a fresh episode's start position (inside the map on all sides), its load and its arrival apart.
+template <int G>
+struct StartWindow {
+    static constexpr int NIT = (WIN_DWORDS + G - 1) / G, X = (MAPW / 2 - WIN_COLS / 2) & ~3, Y = MAPW / 2 - WIN_ROWS / 2;
+    uint32_t v[NIT];
+    __device__ void fetch(int l, const uint8_t* __restrict__ map)
+    {
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) {
+            const int d = l + it * G < WIN_DWORDS ? l + it * G : 0;
+            v[it] = *reinterpret_cast<const uint32_t*>(map + map_index(X + ((d & 3) << 2), Y + (d >> 2)));
+        }
+    }
+    __device__ void park(int l, uint32_t* win) const
+    {
+#pragma unroll
+        for (int it = 0; it < NIT; ++it) if (l + it * G < WIN_DWORDS) win[CX_IDX(l + it * G, WIN_DWORDS)] = v[it];
+    }
+};
+
 // Mob and plant slots stay in their packed record form while the step runs: bit 0 alive,
 // bits 1..12 the cell (x | y<<6), so "is this live slot on cell c" is one AND and one compare
 // against key(c) = 1 | x<<1 | y<<7, a move is one bit-field insert and a kill is "= 0".
