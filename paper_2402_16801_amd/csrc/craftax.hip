@@ -698,15 +698,15 @@ __global__ __launch_bounds__(BLOCK) void k_import(uint4* __restrict__ recs, uint
 }
 
 // after an import: the world of the episode after the imported one, into the spare slot
-__global__ __launch_bounds__(WG_THREADS) void k_import_spare(const uint4* __restrict__ recs, uint8_t* __restrict__ maps, Lists ls, int first,
-                                                             const Luts* __restrict__ luts, int perlin)
+template <bool PERLIN>
+__global__ __launch_bounds__(WG_THREADS, PERLIN ? 6 : 8) void k_import_spare(const uint4* __restrict__ recs, uint8_t* __restrict__ maps, Lists ls, int first,
+                                                                             const Luts* __restrict__ luts)
 {
     __shared__ uint32_t s_lat[LAT_WORDS];
     const uint32_t env = (uint32_t)first + blockIdx.x;
     const uint32_t* r = reinterpret_cast<const uint32_t*>(recs + (size_t)env * 8);
     const uint32_t ep = r[RW_EPISODE] + 1u, lo = r[RW_SEED_LO], hi = r[RW_SEED_HI];
-    if (perlin) worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, lo, hi, env, ep, nullptr, 0, luts->perlin_cs);
-    else worldgen_block(maps + map_offset(env, ep), s_lat, lo, hi, env, ep);
+    worldgen_block<WG_THREADS, PERLIN>(maps + map_offset(env, ep), s_lat, lo, hi, env, ep, nullptr, 0, luts->perlin_cs);
     if (threadIdx.x < 2) ls.tags[2 * env + threadIdx.x] = make_uint2(ep, 0u);
 }
 
@@ -1253,7 +1253,7 @@ static int check_kernels(const craftax_config* cfg, int lanes, std::string* err)
     }
 #undef CRAFTAX_CHECK_MODE
 #undef CRAFTAX_CHECK_ROLLOUT
-    ok = ok && (perlin ? fits("k_reset", (const void*)k_reset<true>, WG_THREADS) : fits("k_reset", (const void*)k_reset<false>, WG_THREADS)) && fits("k_import_spare", (const void*)k_import_spare, WG_THREADS) &&
+    ok = ok && (perlin ? fits("k_reset", (const void*)k_reset<true>, WG_THREADS) : fits("k_reset", (const void*)k_reset<false>, WG_THREADS)) && (perlin ? fits("k_import_spare", (const void*)k_import_spare<true>, WG_THREADS) : fits("k_import_spare", (const void*)k_import_spare<false>, WG_THREADS)) &&
          fits("k_mutate_noise", (const void*)k_mutate_noise, WG_THREADS) &&
          (perlin ? fits("k_drain", (const void*)k_drain<true>, BLOCK) : fits("k_drain", (const void*)k_drain<false>, BLOCK));
     return ok ? CRAFTAX_OK : CRAFTAX_E_CONFIG;
@@ -1488,8 +1488,9 @@ int craftax_import_envs(void* state, int first, int count, const void* dumps, vo
     const Ptrs q = pointers(state, s);
     hipLaunchKernelGGL(k_import, dim3(count), dim3(BLOCK), 0, (hipStream_t)stream, q.recs, q.maps, q.ls,
                        static_cast<const craftax_env_dump*>(dumps), first, make_params(state, s));
-    hipLaunchKernelGGL(k_import_spare, dim3(count), dim3(WG_THREADS), 0, (hipStream_t)stream, q.recs, q.maps, q.ls, first, q.luts,
-                       (int)(s.cfg.worldgen == CRAFTAX_WORLDGEN_PERLIN));
+    if (s.cfg.worldgen == CRAFTAX_WORLDGEN_PERLIN)
+        hipLaunchKernelGGL(k_import_spare<true>, dim3(count), dim3(WG_THREADS), 0, (hipStream_t)stream, q.recs, q.maps, q.ls, first, q.luts);
+    else hipLaunchKernelGGL(k_import_spare<false>, dim3(count), dim3(WG_THREADS), 0, (hipStream_t)stream, q.recs, q.maps, q.ls, first, q.luts);
     note_edit(state);
     return check_launch("craftax_import_envs");
 }
