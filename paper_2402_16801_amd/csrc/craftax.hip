@@ -177,7 +177,7 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
     // EAGER (16 lanes per environment, a launch of one short chain per wavefront): what an episode that ends
     // needs (the tags of the spare world, the window of its start position) and the tables that the renderer
     // looks scalars up in are fetched in advance, its place on the list is claimed before the rendering,
-    // and no wavefront waits for the others of its block.  The launch ends with its slowest
+    // and no wavefront waits for the others of its block once all have the number of the launch.  The launch ends with its slowest
     // wavefront, nearly always one with such an episode, and each of these was a trip to memory of its own
     // at the end of that one's chain (4,096 environments 10.4 -> 9.3 us, 8,192: 12.2 -> 10.9, 500: 9.1 -> 8.2; one
     // alone 7.5 either way).  With fewer lanes the chip is full, and the launch bound by memory and issue.
@@ -196,7 +196,8 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
     // its own, a step block the one it appends to (see regeneration_share)
     constexpr bool SHARE = G == 4;
     static_assert(EPB * LY::STRIDE >= LAT_WORDS, "the environments' area, empty until the records are parked, doubles as lattice scratch");
-    const la::Ticket ticket = la::enter_launch(ls, SHARE || regen_role, regen_role ? rb : blockIdx.x);
+    if (!EAGER && tid == 0) s_ndone = 0;
+    const la::Ticket ticket = la::enter_launch(ls, SHARE || regen_role, regen_role ? rb : blockIdx.x);   // holds a block barrier
     const uint32_t seq = ticket.seq, regen_count = ticket.regen_count;
     auto leave = [&]() { la::leave_launch(ls, ticket); };
     const uint32_t sub = (regen_role ? rb : blockIdx.x) % NSUB, per_sub = nrb / NSUB;
@@ -212,10 +213,6 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
         return;
     }
 
-    if (!EAGER) {
-        if (tid == 0) s_ndone = 0;
-        __syncthreads();
-    }
     bool queued = false;                 // EAGER: this group's episode ended; its place on the list is on its way
     uint32_t list_at = 0u;
     uint4 entry = make_uint4(0u, 0u, 0u, 0u);

@@ -176,9 +176,8 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         if (l < NTAG) tag = ls.tags[(size_t)env * NTAG + l];
         if (l < FLOORS + 1) hdr = genv[SPARE_LADDER + l];
     }
-    const la::Ticket ticket = la::enter_launch(ls, false, 0u);
+    const la::Ticket ticket = la::enter_launch(ls, false, 0u);   // holds a block barrier: the conversion tables are in LDS
     const uint32_t seq = ticket.seq;
-    __syncthreads();                                          // the conversion tables are in LDS
     if (active) {
         uint32_t* e = s_env + w * ENV_DWORDS_LDS;
 #pragma unroll

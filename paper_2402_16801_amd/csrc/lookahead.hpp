@@ -62,9 +62,14 @@ __device__ inline void reset_counters(const Lists& ls)
 // once all blocks of the launch have done so, one thread advances the number and empties the
 // lists this launch consumes.  Counting is in two levels (NGROUP group counters, then one on
 // top) so that no counter sees more than a few dozen atomics.
+// A block counts itself in only when all its wavefronts have the numbers: behind a block barrier that
+// none of them reaches before its own loads have arrived.  A wavefront that read them later could see
+// the next launch's number, and put its entry on the list that is being emptied, or an emptied list, and
+// miss the barriers of a generator that the others of its block are in.
 struct Ticket { uint32_t seq, regen_count, started, gsize, grp; };
 
-// regen_role: this block is one of the nrb regeneration blocks (index rb) at the end of the grid
+// regen_role: this block is one of the nrb regeneration blocks (index rb) at the end of the grid.  All
+// threads of the block call; holds a block barrier.
 __device__ inline Ticket enter_launch(const Lists& ls, bool regen_role, uint32_t rb)
 {
     Ticket t;
@@ -74,7 +79,8 @@ __device__ inline Ticket enter_launch(const Lists& ls, bool regen_role, uint32_t
     t.gsize = (gridDim.x + NGROUP - 1) / NGROUP;
     t.grp = blockIdx.x / t.gsize;
     t.started = 0u;
-    asm volatile("" :: "v"(t.seq), "v"(t.regen_count) : "memory");   // both values have arrived before this block counts itself in
+    asm volatile("" :: "v"(t.seq), "v"(t.regen_count) : "memory");   // both values have arrived in this wavefront ...
+    __syncthreads();                                                  // ... and in the others of the block
     if (threadIdx.x == 0) t.started = atomicAdd(counter(ls, CT_GROUP + (int)t.grp), 1u);
     return t;
 }
@@ -94,8 +100,8 @@ __device__ inline void leave_launch(const Lists& ls, const Ticket& t)
 // regeneration block b of B takes the work units b, b + B, ... of that queue, so the work sits on
 // the first blocks of the grid and no counter is shared: a few hundred atomics on one address
 // would take microseconds).  The lengths of all NSUB sub-lists, as running totals, go to s_prefix
-// (LDS, NSUB words; s_prefix[NSUB - 1] = all entries) before the block counts itself in.  All
-// threads of the block call; ends with a block barrier.
+// (LDS, NSUB words; s_prefix[NSUB - 1] = all entries).  All threads of the block call; holds a block
+// barrier, behind which s_prefix can be read.
 __device__ inline Ticket enter_launch_queue(const Lists& ls, uint32_t* s_prefix)
 {
     Ticket t;
@@ -110,11 +116,11 @@ __device__ inline Ticket enter_launch_queue(const Lists& ls, uint32_t* s_prefix)
         }
         s_prefix[threadIdx.x] = c;
     }
-    __syncthreads();   // the lengths have arrived (they are in LDS) before this block counts itself in
+    asm volatile("" :: "v"(t.seq) : "memory");
+    __syncthreads();   // number and lengths (in LDS) have arrived before this block counts itself in
     t.gsize = (gridDim.x + NGROUP - 1) / NGROUP;
     t.grp = blockIdx.x / t.gsize;
     t.started = 0u;
-    asm volatile("" :: "v"(t.seq) : "memory");
     if (threadIdx.x == 0) t.started = atomicAdd(counter(ls, CT_GROUP + (int)t.grp), 1u);
     return t;
 }

@@ -35,6 +35,14 @@ def test_regeneration_units_are_dealt_out_exactly_once(tmp_path):
     assert "regen_units_test: ok" in _run([exe])
 
 
+def test_every_wavefront_of_a_launch_sees_its_number(tmp_path):
+    """The launch bookkeeping (csrc/lookahead.hpp) with any one wavefront served last, on the host."""
+    exe = str(tmp_path / "launch_order_test")
+    _run(["g++", "-O1", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-Wno-unknown-pragmas", "-I", os.path.join(NATIVE, "host_hip"), "-o", exe,
+          os.path.join(NATIVE, "launch_order_test.cpp")])
+    assert "launch_order_test: ok" in _run([exe])
+
+
 def test_floors_go_to_the_form_that_was_measured_faster(tmp_path):
     """Blocks or single wavefronts for the floors of a call (csrc/floor_route.hpp)."""
     exe = str(tmp_path / "floor_route_test")
