@@ -219,20 +219,20 @@ struct CaveThresholds {
 template <bool PERLIN, int KIND>
 __device__ __forceinline__ void classify_cave(uint32_t& word, const CaveThresholds<PERLIN, KIND>& t, uint32_t below1, uint32_t C, uint32_t F, uint32_t u)
 {
-    using cx::Mask; using cx::mask_of; using cx::shift_in;
+    using cx::Mask; using cx::mask_of; using cx::shift_in_or;
     const Mask open = mask_of(C >= t.open), ore0 = mask_of(u < t.b0);
     word <<= 5;
     if (KIND == REALM) {
         const Mask liquid = mask_of(F >= t.liquid);
-        cx::shift_in_compare(word, open);
-        shift_in(word, (open & ~liquid) | (mask_of(u < below1) & ~(ore0 | open)));
-        shift_in(word, (open & (liquid | mask_of(u < t.plant))) | (ore0 & ~open));
+        cx::shift_in(word, open);
+        shift_in_or(word, open & ~liquid, mask_of(u < below1) & ~(ore0 | open));
+        shift_in_or(word, open & (liquid | mask_of(u < t.plant)), ore0 & ~open);
     } else {
         const Mask special = KIND == GNOME_MINES ? mask_of(u < t.plant) : mask_of(F >= t.liquid);
         const Mask b2 = mask_of(u < t.b2), b4 = mask_of(u < t.b4);
-        shift_in(word, open | (b4 & ~b2));
-        shift_in(word, open | (b2 & ~ore0));
-        shift_in(word, (open & special) | ((ore0 | (b2 & ~mask_of(u < t.b1)) | (b4 & ~mask_of(u < t.b3))) & ~open));
+        shift_in_or(word, open, b4 & ~b2);
+        shift_in_or(word, open, b2 & ~ore0);
+        shift_in_or(word, open & special, (ore0 | (b2 & ~mask_of(u < t.b1)) | (b4 & ~mask_of(u < t.b3))) & ~open);
     }
 }
 __device__ inline uint32_t cave_blocks(const CaveRule& k, uint32_t word) { return __builtin_amdgcn_perm(k.table_hi, k.table_lo, word); }

@@ -213,11 +213,25 @@ __host__ __device__ constexpr uint32_t first_above(int t)      // smallest field
 // one bit per lane
 typedef uint64_t Mask;
 __device__ __forceinline__ Mask mask_of(bool b) { return __builtin_amdgcn_ballot_w64(b); }
-// 2 * word + the calling lane's bit of a mask that a scalar instruction has put together
-__device__ __forceinline__ void shift_in(uint32_t& word, Mask m) { asm("v_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word) : "s"(m) : "vcc"); }
-// the same for a mask straight out of a compare (a vector instruction may read what another one wrote to
-// scalar registers two wait states later; nobody else sees to that around inline assembly)
-__device__ __forceinline__ void shift_in_compare(uint32_t& word, Mask m) { asm("s_nop 1\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word) : "s"(m) : "vcc"); }
+// 2 * word + the calling lane's bit of a mask: of m, of a | b, of a & ~b.  The addition takes the mask from
+// a scalar instruction in the same statement.  Straight from a vector instruction (a compare, or the
+// v_readlane that brings a spilled mask back) it would read it two wait states too early, and nobody
+// else sees to that around inline assembly; a scalar instruction waits for it by itself.
+__device__ __forceinline__ void shift_in(uint32_t& word, Mask m)
+{
+    Mask t;
+    asm("s_mov_b64 %1, %2\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=&s"(t) : "s"(m) : "vcc");
+}
+__device__ __forceinline__ void shift_in_or(uint32_t& word, Mask a, Mask b)
+{
+    Mask t;
+    asm("s_or_b64 %1, %2, %3\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=&s"(t) : "s"(a), "s"(b) : "vcc", "scc");
+}
+__device__ __forceinline__ void shift_in_andn(uint32_t& word, Mask a, Mask b)
+{
+    Mask t;
+    asm("s_andn2_b64 %1, %2, %3\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=&s"(t) : "s"(a), "s"(b) : "vcc", "scc");
+}
 __host__ __device__ constexpr uint32_t four_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) { return a | (b << 8) | (c << 16) | (d << 24); }
 // The thresholds in scalar registers (an instruction that writes a mask takes no literal), moved there once
 // for a run.
@@ -252,11 +266,11 @@ __device__ __forceinline__ void classify(uint32_t& word, const Thresholds<PERLIN
     const Mask lava = mask_of(m > t.lava_m) & mask_of(F >= t.lava_f), gem = lava | (mask_of(m > t.diamond_m) & u500);
     const Mask coal = mask_of(u < t.coal) & ~u3000, iron = u3000 & ~(u500 | mask_of(F >= t.iron_f));
     word <<= 3;
-    shift_in_compare(word, shore);
-    shift_in(word, mask_of(w > t.water) | (tree & ~shore));
-    shift_in(word, gem | path);
-    shift_in(word, path | ((coal | iron) & rock & ~gem));
-    shift_in(word, rock & ~(coal | lava));
+    shift_in(word, shore);
+    shift_in_or(word, mask_of(w > t.water), tree & ~shore);
+    shift_in_or(word, gem, path);
+    shift_in_or(word, path, (coal | iron) & rock & ~gem);
+    shift_in_andn(word, rock, coal | lava);
 }
 // four cells, the first in the lowest byte
 __device__ inline uint32_t blocks_of(uint32_t word)

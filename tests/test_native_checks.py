@@ -43,6 +43,49 @@ def test_every_wavefront_of_a_launch_sees_its_number(tmp_path):
     assert "launch_order_test: ok" in _run([exe])
 
 
+def test_carry_masks_of_the_generators_come_from_a_scalar_instruction(tmp_path):
+    """The generators' inline assembly, as compiled: an addition whose carry is a mask in scalar registers has
+    it from a scalar instruction of the same statement.  What a vector instruction has just written there is not ready for the
+    next two, and the compiler does not look into the statement."""
+    src = tmp_path / "generators.hip"
+    csrc = os.path.join(ROOT, "paper_2402_16801_amd", "csrc")
+    src.write_text('''#include "worldgen.hpp"
+#include "full_common.hpp"
+#include "full_worldgen.hpp"
+template <bool PERLIN> __global__ void classic(uint8_t* maps, const uint32_t* cs)
+{
+    __shared__ uint32_t lat[cx::LAT_WORDS];
+    cx::worldgen_block<512, PERLIN>(maps, lat, 1u, 2u, 3u, 4u, nullptr, 0, cs);
+}
+template <bool PERLIN> __global__ void floors(uint8_t* maps, const uint32_t* cs)
+{
+    __shared__ uint32_t lat[cf::LAT_WORDS];
+    __shared__ cf::GenLayout layout;
+    cf::worldgen_floor_block<64, PERLIN>(maps, lat, layout, 1u, 2u, 3u, 4u, (int)blockIdx.x, nullptr, nullptr, cs);
+}
+template __global__ void classic<false>(uint8_t*, const uint32_t*);
+template __global__ void classic<true>(uint8_t*, const uint32_t*);
+template __global__ void floors<false>(uint8_t*, const uint32_t*);
+template __global__ void floors<true>(uint8_t*, const uint32_t*);
+''')
+    out = tmp_path / "generators.s"
+    from paper_2402_16801_amd.build import HIPCC_FLAGS
+
+    _run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")] +
+         ["-I", csrc, "-S", "--cuda-device-only", "-o", str(out), str(src)])
+    statements = re.findall(r";#?\s*APP\n(.*?);#?\s*NO_APP", out.read_text().replace("#ASMSTART", " APP").replace("#ASMEND", " NO_APP"), re.S)
+    adds = 0
+    for statement in statements:
+        lines = [line.split(";")[0].strip() for line in statement.splitlines() if line.split(";")[0].strip()]
+        for i, line in enumerate(lines):
+            m = re.match(r"v_addc_co_u32_e64 \S+ \S+ \S+ \S+ (s\[\d+:\d+\]|vcc)$", line.replace(",", " ").replace("  ", " "))
+            if not line.startswith("v_addc_co_u32_e64"):
+                continue
+            adds += 1
+            assert m and i > 0 and re.match(r"s_\w+_b64 " + re.escape(m.group(1)) + ",", lines[i - 1]), statement
+    assert adds > 8 * 2 * (5 + 3 + 3 + 3), adds
+
+
 def test_floors_go_to_the_form_that_was_measured_faster(tmp_path):
     """Blocks or single wavefronts for the floors of a call (csrc/floor_route.hpp)."""
     exe = str(tmp_path / "floor_route_test")
