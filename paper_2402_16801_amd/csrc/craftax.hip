@@ -18,6 +18,7 @@
 #include "lookahead.hpp"
 #include "regen_units.hpp"
 #include "render.hpp"
+#include "rollout_route.hpp"
 #include "step.hpp"
 #include "worldgen.hpp"
 
@@ -325,18 +326,18 @@ __device__ __attribute__((noinline)) void generate_half(uint8_t* map, Lds<uint32
 // arithmetic of others; nothing is exchanged between blocks.  Worlds stay one episode ahead as in
 // the step kernel: an environment whose episode ends moves into its spare world.  The world after that
 // one is left to the regeneration launch behind this one, which generates all of them with the whole
-// chip, or, up to `own` of them after every step, generated by the block itself (see launch_rollout);
+// chip, or, after step own_from and every later one, generated by the block itself (see rollout_route.hpp);
 // the environments that are owed a world at the end go on the regeneration list.  An environment whose
 // episode ends without a spare world has the next world generated on the spot.  Before the launch the
 // regeneration lists of the step kernel must be empty (the host runs a list-only launch first).
 // Measured against blocks that generate all their worlds, by code in the loop (64 steps, value noise /
 // Perlin): 12,000 environments 603 / 710 -> 569 / 614 us, 32,768: 1,164 / 1,367 -> 1,065 / 1,157,
-// 65,536: 1,801 / 2,051 -> 1,776 / 1,895; 517 environments and 29 steps 212 -> 186.
+// 65,536: 1,801 / 2,051 -> 1,761 / 1,877.
 template <int G, int OBS_MODE, bool PERLIN>
 __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                       const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                       uint8_t* __restrict__ obs, float* __restrict__ reward,
-                                                      uint8_t* __restrict__ done, Lists ls, Params p, int steps, int own)
+                                                      uint8_t* __restrict__ done, Lists ls, Params p, int steps, int own_from)
 {
     constexpr int EPB = Grp<G>::EPB;
     __shared__ uint32_t s_env[EPB * LDS_ENV_DWORDS];
@@ -421,14 +422,14 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         }
         __syncthreads();
         // worlds that have to exist now, then queued spare worlds
-        int budget = own;
+        const bool own = t >= own_from;
 #pragma unroll 1
         while (true) {
             const int nurgent = s_nurgent, qhead = s_qhead, qtail = s_qtail;
             int gt;
             bool urgent;
             if (nurgent > 0) { gt = s_urgent[nurgent - 1]; urgent = true; }
-            else if (budget > 0 && qhead != qtail) { gt = s_queue[qhead % EPB]; urgent = false; --budget; }
+            else if (own && qhead != qtail) { gt = s_queue[qhead % EPB]; urgent = false; }
             else break;
             __syncthreads();                               // everyone has read the counters
             uint32_t* et = s_env + gt * LDS_ENV_DWORDS;
@@ -470,7 +471,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
     uint4* s_list = reinterpret_cast<uint4*>(s_lat);
     if (active) {
         store_record<G>(l, recs + (size_t)env * 8, e);
-        if (s_spare_ok[g]) { if (own != 0 && l < 2) ls.tags[2 * env + l] = make_uint2(e[LDS_REC + RW_EPISODE] + 1u, 0u); }
+        if (s_spare_ok[g]) { if (own_from < steps && l < 2) ls.tags[2 * env + l] = make_uint2(e[LDS_REC + RW_EPISODE] + 1u, 0u); }
         else if (l == 0) s_list[atomicAdd(&s_nurgent, 1)] = make_uint4((uint32_t)env, e[LDS_REC + RW_SEED_LO], e[LDS_REC + RW_SEED_HI], e[LDS_REC + RW_EPISODE] + 1u);
     }
     __syncthreads();
@@ -1081,7 +1082,6 @@ static int group_lanes(const craftax_config* cfg, int n)
 constexpr int RESET_GRID = 64;    // blocks of k_reset_list (the slow list is nearly always empty); each loops over the list
 constexpr int POOL_RESET_GRID = 512;   // the same with optimistic resets, where every finished episode is on that list
 constexpr int REGEN_BLOCKS = 1024; // regeneration blocks appended to the step grid (two per world); those beyond the list exit at once
-constexpr int OWN_WORLDS_FROM = 49152;   // environments from which a rollout's blocks generate worlds themselves
 constexpr int OWED_BLOCKS = 1536;   // regeneration blocks behind a rollout: six wavefronts per SIMD, what their registers allow
 constexpr int SHARED_REGEN_BLOCKS = 256;   // with four lanes per environment: one per compute unit, beside its four step blocks (see regeneration_share)
 
@@ -1111,29 +1111,25 @@ static void launch_rollout(int lanes, int n, hipStream_t st, const Ptrs& q, cons
                            float* reward, uint8_t* done, const Params& p)
 {
     // launches of regeneration blocks only bring every spare world up to date and empty the lists: before
-    // the rollout for what steps left, behind it for the worlds that it owes
+    // the rollout for what steps left, behind it for the worlds that it owes, unless its blocks generate those
     const int regen = ((2 * n < REGEN_BLOCKS ? 2 * n : REGEN_BLOCKS) + 2 * NSUB - 1) / (2 * NSUB) * (2 * NSUB);
     const int owed = ((2 * n < OWED_BLOCKS ? 2 * n : OWED_BLOCKS) + 2 * NSUB - 1) / (2 * NSUB) * (2 * NSUB);
     // lanes per environment as chosen for single steps: four (64 environments per block) where there
     // are enough environments to fill the chip that way, else sixteen (16 per block)
     const bool wide = lanes != 4;
-    // worlds a block generates itself after a step: none while the chip has room beside the blocks, because a
-    // block stops for its world; one where they nearly fill it, because the others' memory traffic then covers
-    // for it (64 steps, skewed actions, value noise / Perlin, none against one: 32,768 environments 1,065 / 1,157
-    // against 1,125 / 1,219 us, 49,152: 1,424 / 1,561 against 1,428 / 1,540, 65,536: 1,825 / 2,004 against 1,776 / 1,895)
-    const int own = !wide && n >= OWN_WORLDS_FROM ? 1 : 0;
+    const int own_from = (int)rollout_own_from(!wide, p.worldgen == CRAFTAX_WORLDGEN_PERLIN, n, steps, p.max_episode_steps);
     const int blocks = wide ? (n + 15) / 16 : (n + 63) / 64;
 #define CRAFTAX_LAUNCH_ROLLOUT(LANES, NOISE) \
     hipLaunchKernelGGL((k_rollout<LANES, OBS_MODE, NOISE>), dim3(blocks), dim3(BLOCK), 0, st, q.recs, q.maps, q.luts, actions, o, reward, \
-                       done, q.ls, p, steps, own)
+                       done, q.ls, p, steps, own_from)
     if (p.worldgen == CRAFTAX_WORLDGEN_PERLIN) {
         hipLaunchKernelGGL(k_drain<true>, dim3(regen), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
         if (wide) CRAFTAX_LAUNCH_ROLLOUT(16, true); else CRAFTAX_LAUNCH_ROLLOUT(4, true);
-        hipLaunchKernelGGL(k_drain<true>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
+        if (own_from == steps) hipLaunchKernelGGL(k_drain<true>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
     } else {
         hipLaunchKernelGGL(k_drain<false>, dim3(regen), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
         if (wide) CRAFTAX_LAUNCH_ROLLOUT(16, false); else CRAFTAX_LAUNCH_ROLLOUT(4, false);
-        hipLaunchKernelGGL(k_drain<false>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
+        if (own_from == steps) hipLaunchKernelGGL(k_drain<false>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
     }
 #undef CRAFTAX_LAUNCH_ROLLOUT
 }

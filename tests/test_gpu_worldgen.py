@@ -56,3 +56,31 @@ def test_classic_rollout_owes_worlds(n, perlin):
         a, b = rolled.step(acts[s]), stepped.step(acts[s])
         assert all(torch.equal(x, y) for x, y in zip(a, b)), s
     assert rolled.export_envs().tobytes() == stepped.export_envs().tobytes()
+
+
+@pytest.mark.parametrize("perlin", [False, True])
+@pytest.mark.parametrize("n,pre,steps,cap", [(1, 0, 31, 2), (16, 98, 3, 100), (40, 58, 2, 60), (64, 170, 2, 171)])
+def test_classic_rollout_whose_blocks_generate_what_they_owe(n, pre, steps, cap, perlin):
+    """Rollouts short enough to have no launch behind them: one environment whose episodes end again and again, and
+    batches in which all episodes end together, so that a block generates a world for each of them after the last step."""
+    import torch
+    after = 2 * cap if cap < 10 else 6
+    cfg = cx.default_config(worldgen=cx.WORLDGEN_PERLIN if perlin else cx.WORLDGEN_VALUE, max_episode_steps=cap)
+    rolled, stepped = cx.Craftax(n, cfg), cx.Craftax(n, cfg)
+    acts = torch.empty((pre + steps + after, n), dtype=torch.int32, device=rolled.device)
+    cx.craftax_synth_actions(acts, n, 0, pre + steps + after, 5, 1, rolled.stream)
+    for sim in (rolled, stepped):
+        sim.reset(np.arange(n, dtype=np.uint64) + np.uint64(31))
+        for s in range(pre):
+            sim.step(acts[s])
+    rew = torch.zeros((steps, n), dtype=torch.float32, device=rolled.device)
+    done = torch.zeros((steps, n), dtype=torch.uint8, device=rolled.device)
+    cx.craftax_rollout(rolled.state, acts[pre:pre + steps].contiguous(), steps, rolled.obs, rew, done, n, rolled.stream)
+    for s in range(steps):
+        obs, r, d = stepped.step(acts[pre + s])
+        assert torch.equal(r, rew[s]) and torch.equal(d, done[s]), s
+    assert int(done.sum()) > n // 3 and torch.equal(obs, rolled.obs)
+    for s in range(pre + steps, pre + steps + after):
+        a, b = rolled.step(acts[s]), stepped.step(acts[s])
+        assert all(torch.equal(x, y) for x, y in zip(a, b)), s
+    assert rolled.export_envs().tobytes() == stepped.export_envs().tobytes()

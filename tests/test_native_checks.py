@@ -93,6 +93,13 @@ def test_floors_go_to_the_form_that_was_measured_faster(tmp_path):
     assert "floor_route_test: ok" in _run([exe])
 
 
+def test_worlds_owed_by_a_rollout_go_where_it_was_measured_faster(tmp_path):
+    """A launch behind a Classic rollout or its own blocks (csrc/rollout_route.hpp)."""
+    exe = str(tmp_path / "rollout_route_test")
+    _run(["g++", "-O1", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-o", exe, os.path.join(NATIVE, "rollout_route_test.cpp")])
+    assert "rollout_route_test: ok" in _run([exe])
+
+
 def test_public_header_compiles_as_c_and_as_cpp(tmp_path):
     """include/craftax.h on its own, with warnings as errors, as C11 and as C++17: no HIP or torch type
     in any signature, every struct complete."""
