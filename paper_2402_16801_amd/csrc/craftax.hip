@@ -121,7 +121,7 @@ __device__ __forceinline__ void regeneration_block(uint8_t* __restrict__ maps, c
 // Regeneration inside a step launch whose step blocks fill the chip (four lanes per environment),
 // shared between the regeneration blocks of the grid and the step blocks.  Sub-list s is seen as
 // units u = 2 * entry + half, u < 2 * count.  Its per_sub regeneration blocks (index pr among
-// them) take the head, units pr, pr + per_sub, ... (HEAD_ROUNDS of them): they sit in the one
+// them) take the head, units pr, pr + per_sub, ... (head_rounds of them): they sit in the one
 // place per compute unit that the step blocks leave free and work from the start of the launch.
 // The tail is dealt out to the step blocks that append to this sub-list (index q among the nq of
 // them) and, behind them, to the regeneration blocks again, so that a launch in which very many
@@ -134,11 +134,11 @@ __device__ __forceinline__ void regeneration_block(uint8_t* __restrict__ maps, c
 // The walk over the units is in regen_units.hpp (plain arithmetic, unit-tested on the host).
 template <bool PERLIN>
 __device__ __forceinline__ void regeneration_share(uint8_t* __restrict__ maps, const Lists& ls, uint32_t seq, uint32_t count, uint32_t sub,
-                                                   bool helper, uint32_t index, uint32_t per_sub, uint32_t nq, uint32_t* s_lat,
+                                                   bool helper, uint32_t index, uint32_t per_sub, uint32_t nq, uint32_t rounds, uint32_t* s_lat,
                                                    const uint32_t* __restrict__ perlin_cs)
 {
     const uint4* list = la::consumed_sub_list(ls, seq, sub);
-    for (UnitWalk w = first_unit(helper, index, per_sub); w.u < 2u * count; w = next_unit(w, helper, index, per_sub, nq)) {
+    for (UnitWalk w = first_unit(helper, index, per_sub, rounds); w.u < 2u * count; w = next_unit(w, helper, index, per_sub, nq, rounds)) {
         const uint4 entry = list[w.u >> 1];
         const uint32_t half = w.u & 1u;
         if (entry.x != ENTRY_VOID) {
@@ -153,8 +153,10 @@ __device__ __forceinline__ void regeneration_share(uint8_t* __restrict__ maps, c
 // step: G lanes per environment, 256/G environments per block, followed in the same grid by
 // the regeneration blocks for the episodes that ended in the previous launch (with four lanes per
 // environment the step blocks take a share of that work before they step: regeneration_share).
+constexpr int COMPUTE_UNITS = 256;
+constexpr int step_blocks_per_cu(bool perlin) { return perlin ? 4 : 5; }   // by registers: a wavefront of a block on each of the four SIMDs
 template <int G, int OBS_MODE, bool PERLIN>
-__global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
+__global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                    const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                    uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                    uint8_t* __restrict__ done, Lists ls, Params p, int step_blocks)
@@ -204,10 +206,11 @@ __global__ __launch_bounds__(BLOCK, PERLIN ? 4 : 5) void k_step(uint4* __restric
     const uint32_t sub = (regen_role ? rb : blockIdx.x) % NSUB, per_sub = nrb / NSUB;
     const uint32_t nq = ((uint32_t)step_blocks + NSUB - 1u - sub) / NSUB;   // step blocks that append to this sub-list
 
+    const uint32_t rounds = head_rounds((uint32_t)step_blocks, nrb, COMPUTE_UNITS * step_blocks_per_cu(PERLIN));
     // SHARE: a regeneration block's units, or this step block's share of the worlds owed from the previous
     // launch while its records arrive (one call for both: the generator is in the kernel's code once)
-    if (SHARE && (regen_role || first_helper_unit(blockIdx.x / NSUB, per_sub) < 2u * regen_count))
-        regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, !regen_role, (regen_role ? rb : blockIdx.x) / NSUB, per_sub, nq, s_env, luts->perlin_cs);
+    if (SHARE && (regen_role || first_helper_unit(blockIdx.x / NSUB, per_sub, rounds) < 2u * regen_count))
+        regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, !regen_role, (regen_role ? rb : blockIdx.x) / NSUB, per_sub, nq, rounds, s_env, luts->perlin_cs);
     if (regen_role) {
         if (!SHARE && rb / NSUB / 2 < regen_count) regeneration_block<PERLIN>(maps, ls, seq, regen_count, rb, nrb, s_env, luts->perlin_cs);
         leave();
