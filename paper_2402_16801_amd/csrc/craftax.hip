@@ -301,8 +301,11 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
 
 // A launch of regeneration blocks only (before and after a rollout): brings every spare world up to date
 // and empties the lists, with the bookkeeping of a step launch that has no step blocks.
+// Five blocks per compute unit: six take the registers of value noise away (9 spilled: rollouts of 32,768
+// environments and 16 steps 278 -> 272 us with five, of 4,096 115.2 -> 113.9, of 600 and one 18.6 -> 18.0).
+constexpr int DRAIN_BLOCKS_PER_CU = 5;
 template <bool PERLIN>
-__global__ __launch_bounds__(BLOCK, PERLIN ? 5 : 6) void k_drain(uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
+__global__ __launch_bounds__(BLOCK, DRAIN_BLOCKS_PER_CU) void k_drain(uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
 {
     __shared__ uint32_t s_lat[LAT_WORDS];
     const uint32_t rb = blockIdx.x, nrb = gridDim.x;
@@ -1085,7 +1088,7 @@ static int group_lanes(const craftax_config* cfg, int n)
 constexpr int RESET_GRID = 64;    // blocks of k_reset_list (the slow list is nearly always empty); each loops over the list
 constexpr int POOL_RESET_GRID = 512;   // the same with optimistic resets, where every finished episode is on that list
 constexpr int REGEN_BLOCKS = 1024; // regeneration blocks appended to the step grid (two per world); those beyond the list exit at once
-constexpr int OWED_BLOCKS = 1536;   // regeneration blocks behind a rollout: six wavefronts per SIMD, what their registers allow
+constexpr int OWED_BLOCKS = COMPUTE_UNITS * DRAIN_BLOCKS_PER_CU;   // regeneration blocks behind a rollout: all that the chip holds at once (a further 256 waited for these and gained nothing)
 constexpr int SHARED_REGEN_BLOCKS = 256;   // with four lanes per environment: one per compute unit, beside its four step blocks (see regeneration_share)
 
 template <int OBS_MODE>
