@@ -21,6 +21,20 @@ namespace cf {
 
 enum class FloorWork { RESET, IMPORT, MUTATE, OWED };
 
+// Wavefronts per SIMD that the generating kernels are bounded to.  With Perlin noise five cost no spilled registers;
+// six do, and are 3 to 8 % slower, but take 5,121 to 6,144 single wavefronts in one round.
+constexpr long long SIMDS = 1024;
+constexpr int VALUE_WAVES = 8, PERLIN_WAVES = 5, PERLIN_WAVES_TIGHT = 6;
+
+// Imports of Perlin worlds by single wavefronts whose second round would be short: five / six per SIMD, us:
+//   5,121 floors 41.9 / 44.9   5,148 48.7 / 45.1   5,400 49.5 / 45.8   5,580 51.3 / 46.1   6,138 55.8 / 47.5   6,300 56.7 / 57.2
+// A few wavefronts beyond a round do not make a second one: they run beside the last of the first.
+inline bool one_tight_round(FloorWork work, bool perlin, long long floors)
+{
+    constexpr long long FEW = 8;
+    return work == FloorWork::IMPORT && perlin && floors > SIMDS * PERLIN_WAVES + FEW && floors <= SIMDS * PERLIN_WAVES_TIGHT + FEW;
+}
+
 inline bool floors_by_blocks(FloorWork work, bool perlin, long long floors)
 {
     switch (work) {

@@ -53,7 +53,7 @@ __device__ inline void publish_world(uint32_t* __restrict__ genv, const GenLayou
 // ---------------------------------------------------------------------------------------------
 // reset of every environment: one block per (environment, episode 0 or 1, floor)
 template <bool PERLIN, int NT>
-__global__ __launch_bounds__(NT, PERLIN ? 5 : 8) void kf_reset(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
+__global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_reset(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                        const uint64_t* __restrict__ seeds, Lists ls, const uint32_t* __restrict__ perlin_cs,
                                                        int pool, uint32_t* __restrict__ unlocks)
 {
@@ -107,7 +107,7 @@ static_assert(REGEN_PREFIX_AT + NSUB <= ENVS_PER_BLOCK * L_ENV_DWORDS, "regenera
 // lists and empties them, with the bookkeeping of a step launch that has no step blocks.  A kernel
 // of its own, at the occupancy of the generator instead of that of the step kernel.
 template <bool PERLIN, int NT>
-__global__ __launch_bounds__(NT, PERLIN ? 5 : 8) void kf_drain(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
+__global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_drain(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
 {
     __shared__ WorldScratch s_gen;
     __shared__ uint32_t s_prefix[NSUB];
@@ -512,7 +512,7 @@ __device__ inline int theta_offset(int f)
     return f == 0 ? 0 : LAT0_U16 + LATC_U16 * (f == 2 ? 0 : (f == 5 ? 1 : (f == 6 ? 2 : 3)));
 }
 template <int NT>
-__global__ __launch_bounds__(NT, 5) void kf_mutate_noise(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts,
+__global__ __launch_bounds__(NT, PERLIN_WAVES) void kf_mutate_noise(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Luts* __restrict__ luts,
                                                                 uint16_t* __restrict__ theta, int first, uint32_t k0, uint32_t k1,
                                                                 uint32_t round, uint32_t amplitude)
 {
@@ -673,8 +673,8 @@ __device__ inline void import_record(uint32_t* __restrict__ r, const Lists& ls, 
 // of the next episode into the spare slot, so that the copy of some blocks overlaps the arithmetic of
 // others; the block of floor 0 also packs the record.  (A copy byte by byte and a second launch for
 // the spare worlds: 50 + 87 us for 1,000 Perlin worlds, one launch 101, by single wavefronts 93.)
-template <bool PERLIN, int NT>
-__global__ __launch_bounds__(NT, PERLIN ? 5 : 8) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
+template <bool PERLIN, int NT, int WAVES = PERLIN ? PERLIN_WAVES : VALUE_WAVES>
+__global__ __launch_bounds__(NT, WAVES) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
                                                                         const craftax_full_env_dump* __restrict__ dumps, int first, Params p,
                                                                         const uint32_t* __restrict__ perlin_cs, int pool)
 {
@@ -951,6 +951,7 @@ static bool kernels_fit(const Fits& fits)
            floors("kf_reset", (const void*)kf_reset<PERLIN, GEN_THREADS>, (const void*)kf_reset<PERLIN, FLOOR_THREADS>) &&
            floors("kf_drain", (const void*)kf_drain<PERLIN, GEN_THREADS>, (const void*)kf_drain<PERLIN, FLOOR_THREADS>) &&
            floors("kf_import", (const void*)kf_import<PERLIN, GEN_THREADS>, (const void*)kf_import<PERLIN, FLOOR_THREADS>) &&
+           (!PERLIN || fits("kf_import (six wavefronts)", (const void*)kf_import<true, FLOOR_THREADS, PERLIN_WAVES_TIGHT>, FLOOR_THREADS)) &&
            (!PERLIN || floors("kf_mutate_noise", (const void*)kf_mutate_noise<GEN_THREADS>, (const void*)kf_mutate_noise<FLOOR_THREADS>)) &&
            fits("kf_export", (const void*)kf_export, GEN_THREADS) && fits("kf_mutate_swap", (const void*)kf_mutate_swap, MUTATE_SWAP_THREADS);
 }
@@ -1113,7 +1114,8 @@ int import_envs(void* state, const craftax_config* cfg, int n, int first, int co
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0);
     };
     const bool perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN, blocks = floors_by_blocks(FloorWork::IMPORT, perlin, (long long)count * FLOORS);
-    if (perlin) { if (blocks) go(kf_import<true, GEN_THREADS>, GEN_THREADS); else go(kf_import<true, FLOOR_THREADS>, FLOOR_THREADS); }
+    if (one_tight_round(FloorWork::IMPORT, perlin, (long long)count * FLOORS)) go(kf_import<true, FLOOR_THREADS, PERLIN_WAVES_TIGHT>, FLOOR_THREADS);
+    else if (perlin) { if (blocks) go(kf_import<true, GEN_THREADS>, GEN_THREADS); else go(kf_import<true, FLOOR_THREADS>, FLOOR_THREADS); }
     else { if (blocks) go(kf_import<false, GEN_THREADS>, GEN_THREADS); else go(kf_import<false, FLOOR_THREADS>, FLOOR_THREADS); }
     return check_launch("craftax_import_envs", err);
 }

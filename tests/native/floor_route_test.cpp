@@ -33,6 +33,15 @@ int main()
             std::printf("work %d, perlin %d, %lld floors: the slower form\n", (int)m.work, (int)m.perlin, m.floors);
             ++bad;
         }
+    // Perlin imports by five and by six wavefronts per SIMD
+    const struct { long long floors; double five_us, six_us; } rounds[] = { { 5040, 41.8, 44.3 }, { 5121, 41.9, 44.9 }, { 5148, 48.7, 45.1 }, { 5400, 49.5, 45.8 },
+        { 6138, 55.8, 47.5 }, { 6300, 56.7, 57.2 }, { 18000, 123, 130 } };
+    for (const auto& m : rounds)
+        if (cf::one_tight_round(FloorWork::IMPORT, true, m.floors) != (m.six_us < m.five_us)) {
+            std::printf("import of %lld floors: the slower bound\n", m.floors);
+            ++bad;
+        }
+    bad += cf::one_tight_round(FloorWork::IMPORT, false, 5400) || cf::one_tight_round(FloorWork::RESET, true, 5400);
     bad += cf::worlds_owed(4096, 16, 100000) != 364 || cf::worlds_owed(4096, 500, 100000) != 4096 || cf::worlds_owed(343, 20, 13) != 343 ||
            cf::worlds_owed(343, 1, 13) != 26 || cf::worlds_owed(7, 1, 1) != 7;
     if (bad == 0) std::printf("floor_route_test: ok\n");

@@ -84,3 +84,22 @@ def test_classic_rollout_whose_blocks_generate_what_they_owe(n, pre, steps, cap,
         a, b = rolled.step(acts[s]), stepped.step(acts[s])
         assert all(torch.equal(x, y) for x, y in zip(a, b)), s
     assert rolled.export_envs().tobytes() == stepped.export_envs().tobytes()
+
+
+@pytest.mark.parametrize("n,perlin", [(250, True), (569, True), (570, True), (683, True), (684, True), (570, False)])
+def test_full_import_generates_the_worlds_a_reset_would(n, perlin):
+    """Imported levels have the spare worlds of the states they were exported from, whichever form of the generator takes the
+    floors: blocks, single wavefronts, and around the sizes (5,121 to 6,152 Perlin floors) that go to six wavefronts per SIMD."""
+    import torch
+    cfg = cx.default_config(cx.VARIANT_CRAFTAX, worldgen=cx.WORLDGEN_PERLIN if perlin else cx.WORLDGEN_VALUE, max_episode_steps=3)
+    seeds = np.arange(n, dtype=np.uint64) + np.uint64(900)
+    first, second = cx.Craftax(n, cfg), cx.Craftax(n, cfg)
+    first.reset(seeds)
+    second.reset(seeds + np.uint64(50000))
+    second.import_envs(first.export_envs())
+    acts = torch.empty((7, n), dtype=torch.int32, device=first.device)
+    cx.craftax_synth_actions(acts, n, 0, 7, 3, 2, first.stream)
+    for s in range(7):
+        a, b = first.step(acts[s]), second.step(acts[s])
+        assert all(torch.equal(x, y) for x, y in zip(a, b)), s
+    assert first.export_envs().tobytes() == second.export_envs().tobytes()
