@@ -4,16 +4,16 @@
 // a block works while the first one lays the floor out.  A few floors last as long as one of them, so
 // blocks are ahead; thousands are a matter of throughput, and single wavefronts are ahead.  The lines
 // lie between measured sizes (us, blocks / single wavefronts):
-//   reset, value noise      288  7.1 / 16.0   3,600 19.6 / 22.3   4,194 21.7 / 22.9   4,788 23.8 / 23.1   6,138 28.6 / 24.5   73,728 263 / 174
-//   import, value noise     288 13.3 / 23.1   3,600 30.8 / 33.6   4,194 33.6 / 34.6   4,797 36.5 / 35.6   6,138 43.6 / 38.0   18,000 114 / 87
-//   reset, Perlin noise     288 11.8 / 27.5   3,600 35.6 / 38.0   4,194 39.7 / 38.8   6,138 53.3 / 44.2
-//     6,144 single wavefronts run at once (six on each of 1,024 SIMDs); a second round costs as much as
-//     the first until it is nearly full:  7,200 61.2 / 65.6   9,720 78.6 / 84.9   11,988 94.3 / 95.0   14,400 111 / 104   73,728 525 / 343
-//   import, Perlin noise    288 18.5 / 34.9   2,592 39.6 / 42.2   3,069 43.2 / 43.1   3,600 48.0 / 46.0   9,720 104 / 97   18,000 191 / 150
-//   noise mutation          288 23.0 / 29.6   1,440 31.3 / 34.2   2,052 36.2 / 34.8   3,069 44.4 / 35.3   9,720  95 / 88   18,000 158 / 121
+//   reset, value noise      288  6.4 / 14.5   2,700 14.1 / 18.1   4,194 19.0 / 20.6   4,500 19.9 / 20.8   5,130 21.9 / 21.3   6,138 25.0 / 22.1   73,728 230 / 144
+//   import, value noise     288 12.6 / 22.3   3,600 28.5 / 32.7   4,500 33.1 / 33.9   4,797 34.7 / 34.6   5,121 36.2 / 34.9   18,000 112 / 89
+//   reset, Perlin noise     288  9.4 / 21.7   1,800 19.5 / 24.3   2,340 23.6 / 25.5   2,700 26.3 / 25.7   3,600 32.6 / 28.5
+//     5,120 single wavefronts run at once (PERLIN_WAVES on each SIMD); the second round costs less than blocks would:
+//     4,788 40.8 / 29.2   5,130 43.2 / 35.1   6,138 50.3 / 41.0   11,988 90.6 / 62.7   73,728 515 / 237
+//   import, Perlin noise    288 16.0 / 29.6   2,070 32.6 / 37.2   2,592 38.1 / 38.7   2,790 40.1 / 38.9   3,600 47.6 / 40.3   18,000 203 / 123
+//   noise mutation          288 19.5 / 23.1   720 22.0 / 23.8   1,080 24.1 / 25.3   1,440 27.5 / 25.8   2,052 31.4 / 26.2   18,000 152 / 85
 //   owed by a rollout       us of a whole rollout with its two launches for owed worlds in the one or the other form, environments x steps (floors owed):
-//                           1,024 x 16 (819) 124 / 132   2,048 x 16 (1,638) 139.5 / 143.6   4,096 x 16 (3,276) 181.7 / 179.4   4,096 x 64 (13,107) 675 / 643
-//                           Perlin noise: 128 / 142   147.5 / 156.5   197.3 / 194.9   748 / 703
+//                           1,024 x 16 (819) 119 / 128   2,600 x 16 (2,079) 151 / 155   3,600 x 16 (2,880) 173.4 / 175.9   4,096 x 20 (4,095) 218.7 / 216.7   4,096 x 64 (13,104) 661 / 637
+//                           Perlin noise: 125 / 134   160.8 / 162.9   185.5 / 184.0   234 / 227   724 / 674
 // Plain C++ so that the rule itself can be tested without a GPU.
 #pragma once
 
@@ -38,10 +38,10 @@ inline bool one_tight_round(FloorWork work, bool perlin, long long floors)
 inline bool floors_by_blocks(FloorWork work, bool perlin, long long floors)
 {
     switch (work) {
-    case FloorWork::RESET: return perlin ? floors <= 4000 || (floors > 6144 && floors <= 12000) : floors <= 4500;
-    case FloorWork::IMPORT: return floors <= (perlin ? 3072 : 4500);
-    case FloorWork::MUTATE: return floors <= 1850;     // Perlin worlds only
-    default: return floors <= 3072;
+    case FloorWork::RESET:
+    case FloorWork::IMPORT: return floors <= (perlin ? 2600 : 4650);
+    case FloorWork::MUTATE: return floors <= 1250;     // Perlin worlds only
+    default: return floors <= (perlin ? 2600 : 3200);
     }
 }
 

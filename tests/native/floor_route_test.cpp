@@ -11,21 +11,23 @@ struct Measured { FloorWork work; bool perlin; long long floors; double blocks_u
 int main()
 {
     const Measured rows[] = {
-        { FloorWork::RESET, false, 288, 7.1, 16.0 },   { FloorWork::RESET, false, 3600, 19.6, 22.3 },  { FloorWork::RESET, false, 4194, 21.7, 22.9 },
-        { FloorWork::RESET, false, 4788, 23.8, 23.1 }, { FloorWork::RESET, false, 6138, 28.6, 24.5 },  { FloorWork::RESET, false, 7200, 32.3, 28.0 },
-        { FloorWork::RESET, false, 73728, 263, 174 },
-        { FloorWork::IMPORT, false, 288, 13.3, 23.1 }, { FloorWork::IMPORT, false, 4194, 33.6, 34.6 }, { FloorWork::IMPORT, false, 4797, 36.5, 35.6 },
-        { FloorWork::IMPORT, false, 18000, 114, 87 },
-        { FloorWork::RESET, true, 288, 11.8, 27.5 },   { FloorWork::RESET, true, 3600, 35.6, 38.0 },   { FloorWork::RESET, true, 4194, 39.7, 38.8 },
-        { FloorWork::RESET, true, 6138, 53.3, 44.2 },  { FloorWork::RESET, true, 7200, 61.2, 65.6 },   { FloorWork::RESET, true, 9720, 78.6, 84.9 },
-        { FloorWork::RESET, true, 11988, 94.3, 95.0 }, { FloorWork::RESET, true, 14400, 111, 104 },    { FloorWork::RESET, true, 73728, 525, 343 },
-        { FloorWork::IMPORT, true, 288, 18.5, 34.9 },  { FloorWork::IMPORT, true, 2592, 39.6, 42.2 },  { FloorWork::IMPORT, true, 3600, 48.0, 46.0 },
-        { FloorWork::IMPORT, true, 9720, 104, 97 },    { FloorWork::IMPORT, true, 18000, 191, 150 },
-        { FloorWork::MUTATE, true, 288, 23.0, 29.6 },  { FloorWork::MUTATE, true, 1440, 31.3, 34.2 },  { FloorWork::MUTATE, true, 2052, 36.2, 34.8 },
-        { FloorWork::MUTATE, true, 3069, 44.4, 35.3 }, { FloorWork::MUTATE, true, 18000, 158, 121 },
-        { FloorWork::OWED, false, 819, 124, 132 },     { FloorWork::OWED, false, 1638, 139.5, 143.6 }, { FloorWork::OWED, false, 3276, 181.7, 179.4 },
-        { FloorWork::OWED, false, 13107, 675, 643 },   { FloorWork::OWED, true, 819, 128, 142 },       { FloorWork::OWED, true, 1638, 147.5, 156.5 },
-        { FloorWork::OWED, true, 3276, 197.3, 194.9 }, { FloorWork::OWED, true, 13107, 748, 703 },
+        { FloorWork::RESET, false, 288, 6.4, 14.5 },    { FloorWork::RESET, false, 2700, 14.1, 18.1 },  { FloorWork::RESET, false, 4194, 19.0, 20.6 },
+        { FloorWork::RESET, false, 4500, 19.9, 20.8 },  { FloorWork::RESET, false, 5130, 21.9, 21.3 },  { FloorWork::RESET, false, 6138, 25.0, 22.1 },
+        { FloorWork::RESET, false, 8640, 32.8, 30.6 },  { FloorWork::RESET, false, 73728, 230, 144 },
+        { FloorWork::IMPORT, false, 288, 12.6, 22.3 },  { FloorWork::IMPORT, false, 3600, 28.5, 32.7 }, { FloorWork::IMPORT, false, 4500, 33.1, 33.9 },
+        { FloorWork::IMPORT, false, 4797, 34.65, 34.6 }, { FloorWork::IMPORT, false, 5121, 36.2, 34.9 }, { FloorWork::IMPORT, false, 18000, 112, 89 },
+        { FloorWork::RESET, true, 288, 9.4, 21.7 },     { FloorWork::RESET, true, 1800, 19.5, 24.3 },   { FloorWork::RESET, true, 2340, 23.6, 25.5 },
+        { FloorWork::RESET, true, 2700, 26.3, 25.7 },   { FloorWork::RESET, true, 3600, 32.6, 28.5 },   { FloorWork::RESET, true, 5130, 43.2, 35.1 },
+        { FloorWork::RESET, true, 6138, 50.3, 41.0 },   { FloorWork::RESET, true, 8190, 64.5, 51.4 },   { FloorWork::RESET, true, 11988, 90.6, 62.7 },
+        { FloorWork::RESET, true, 73728, 515, 237 },
+        { FloorWork::IMPORT, true, 288, 16.0, 29.6 },   { FloorWork::IMPORT, true, 2070, 32.6, 37.2 },  { FloorWork::IMPORT, true, 2592, 38.1, 38.7 },
+        { FloorWork::IMPORT, true, 2790, 40.1, 38.9 },  { FloorWork::IMPORT, true, 3600, 47.6, 40.3 },  { FloorWork::IMPORT, true, 18000, 203, 123 },
+        { FloorWork::MUTATE, true, 288, 19.5, 23.1 },   { FloorWork::MUTATE, true, 720, 22.0, 23.8 },   { FloorWork::MUTATE, true, 1080, 24.1, 25.3 },
+        { FloorWork::MUTATE, true, 1440, 27.5, 25.8 },  { FloorWork::MUTATE, true, 2052, 31.4, 26.2 },  { FloorWork::MUTATE, true, 18000, 152, 85 },
+        { FloorWork::OWED, false, 819, 119.4, 127.7 },  { FloorWork::OWED, false, 2079, 151.0, 154.7 }, { FloorWork::OWED, false, 2880, 173.4, 175.9 },
+        { FloorWork::OWED, false, 4095, 218.7, 216.7 }, { FloorWork::OWED, false, 13104, 661, 637 },    { FloorWork::OWED, true, 819, 124.7, 134.2 },
+        { FloorWork::OWED, true, 2079, 160.8, 162.9 },  { FloorWork::OWED, true, 2880, 185.5, 184.0 },  { FloorWork::OWED, true, 4095, 233.9, 226.6 },
+        { FloorWork::OWED, true, 13104, 724, 674 },
     };
     int bad = 0;
     for (const Measured& m : rows)
