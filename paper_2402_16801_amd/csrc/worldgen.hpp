@@ -220,17 +220,17 @@ __device__ __forceinline__ Mask mask_of(bool b) { return __builtin_amdgcn_ballot
 __device__ __forceinline__ void shift_in(uint32_t& word, Mask m)
 {
     Mask t;
-    asm("s_mov_b64 %1, %2\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=&s"(t) : "s"(m) : "vcc");
+    asm("s_mov_b64 %1, %2\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=s"(t) : "s"(m) : "vcc");
 }
 __device__ __forceinline__ void shift_in_or(uint32_t& word, Mask a, Mask b)
 {
     Mask t;
-    asm("s_or_b64 %1, %2, %3\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=&s"(t) : "s"(a), "s"(b) : "vcc", "scc");
+    asm("s_or_b64 %1, %2, %3\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=s"(t) : "s"(a), "s"(b) : "vcc", "scc");
 }
 __device__ __forceinline__ void shift_in_andn(uint32_t& word, Mask a, Mask b)
 {
     Mask t;
-    asm("s_andn2_b64 %1, %2, %3\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=&s"(t) : "s"(a), "s"(b) : "vcc", "scc");
+    asm("s_andn2_b64 %1, %2, %3\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1" : "+v"(word), "=s"(t) : "s"(a), "s"(b) : "vcc", "scc");
 }
 __host__ __device__ constexpr uint32_t four_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) { return a | (b << 8) | (c << 16) | (d << 24); }
 // The thresholds in scalar registers (an instruction that writes a mask takes no literal), moved there once
