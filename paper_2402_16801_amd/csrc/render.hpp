@@ -157,11 +157,12 @@ __device__ __forceinline__ void render_symbolic(int l, uint32_t* e, int mvx, int
             float v = 0.0f;
             if (i < NVEC) {
                 const int raw = i == 20 ? 0 : raw_of(i);
-                if (TABLES) {
-                    // every lane of the group takes part in the exchange; counts and vitals are below 16
+                if (TABLES && it_i == 0) {
+                    // the first turn, in which every lane of the group takes part in the exchange; counts and vitals are below 16
                     const float root = __shfl(tables->sqrt10, raw & 15, G), tenth = __shfl(tables->tenth, raw & 15, G);
-                    v = i < 6 ? root : (i >= 12 && i < 16 ? tenth : (i == 20 ? tables->day : (float)raw));
-                } else if (i < 6) v = luts->sqrt10[raw];
+                    v = i < 6 ? root : (i >= 12 ? tenth : (float)raw);
+                } else if (TABLES) v = i == 20 ? tables->day : (float)raw;
+                else if (i < 6) v = luts->sqrt10[raw];
                 else if (i >= 12 && i < 16) v = luts->tenth[raw];
                 else if (i == 20) v = luts->daylight[phase];
                 else v = (float)raw;

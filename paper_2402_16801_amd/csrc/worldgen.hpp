@@ -63,22 +63,24 @@ __device__ __forceinline__ void for_run(F&& f)
     f(std::integral_constant<int, 3>()); f(std::integral_constant<int, 2>()); f(std::integral_constant<int, 1>()); f(std::integral_constant<int, 0>());
 }
 // High half of a double whose low half is zero: every weight below is a small whole number or a fraction of
-// sixteen bits.
+// sixteen bits.  NOT_A_HALF for a value that does not fit, which the functions that put it together refuse.
+constexpr uint32_t NOT_A_HALF = 0xFFFFFFFFu;
 __host__ __device__ constexpr uint32_t high_half(double v)
 {
     const uint64_t bits = __builtin_bit_cast(uint64_t, v);
-    return (uint32_t)(bits >> 32) | ((uint32_t)bits != 0u ? 0xFFFFFFFFu : 0u);      // NaN for a value that does not fit
+    return (uint32_t)bits != 0u ? NOT_A_HALF : (uint32_t)(bits >> 32);
 }
+static_assert(high_half(1.5) == 0x3FF80000u && high_half(1.0 / 3.0) == NOT_A_HALF, "a third has a low half");
 // such a constant in scalar registers, from where a multiply-add takes it as it is
 template <uint32_t V>
 __device__ __forceinline__ uint32_t scalar_const() { uint32_t s; asm("s_mov_b32 %0, %1" : "=s"(s) : "i"(V)); return s; }
 template <uint32_t HIGH>
-__device__ __forceinline__ double scalar_double() { return __hiloint2double((int)scalar_const<HIGH>(), 0); }
+__device__ __forceinline__ double scalar_double() { static_assert(HIGH != NOT_A_HALF, "a constant with a low half"); return __hiloint2double((int)scalar_const<HIGH>(), 0); }
 // which ? A : B, which: all ones or zero, a scalar or by lane
 template <uint32_t A, uint32_t B>
 __device__ __forceinline__ uint32_t half_of(uint32_t which) { return B ^ (which & (A ^ B)); }
 template <uint32_t A, uint32_t B>
-__device__ __forceinline__ double pick(uint32_t which) { return __hiloint2double((int)half_of<A, B>(which), 0); }
+__device__ __forceinline__ double pick(uint32_t which) { static_assert(A != NOT_A_HALF && B != NOT_A_HALF, "a constant with a low half"); return __hiloint2double((int)half_of<A, B>(which), 0); }
 
 // Bilinear value noise, evaluated column-first: two lattice rows are blended once per lattice
 // column (vertical weight wy), then every cell of a run blends two columns (horizontal weight wx).
@@ -144,7 +146,7 @@ __device__ inline Gradients gradients_at(const uint32_t* lat, int width, int ix,
 // A Perlin field along a run.  Along a row the dot products with the four corners are linear in kx:
 // top and bottom are those with the left corners, dtop and dbottom what the right ones are more, g* what
 // a cell further to the right adds to each.  top and bottom carry the offset 2^52 + 2^31: a multiply-add onto them,
-// rounded towards minus infinity (see FloorRounding), is then the blend with its floor in one
+// rounded towards minus infinity (see floor_rounding), is then the blend with its floor in one
 // instruction, and the low half of the last one is n + 2^31.
 constexpr uint32_t PERLIN_BIAS = 0x80000000u;
 struct PerlinLine {
@@ -189,7 +191,8 @@ __device__ inline void nearest_rounding(uint32_t& last) { asm volatile("s_setreg
 template <int S>
 struct PerlinScale {
     static constexpr double GAIN = PERLIN_GAIN / (1024.0 * S);
-    static constexpr double OFFSET = 6755399441055744.0 + 32768.0 - (4503599627370496.0 + 2147483648.0) * GAIN;   // a whole number below 2^53
+    static constexpr double OFFSET = 6755399441055744.0 + 32768.0 - (4503599627370496.0 + 2147483648.0) * GAIN;
+    static_assert(OFFSET == (double)(long long)OFFSET && OFFSET < 9007199254740992.0, "a whole number below 2^53");
     double gain = scalar_double<high_half(GAIN)>(), offset = OFFSET;
     __device__ int value(double field) const
     {
