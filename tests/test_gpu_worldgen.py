@@ -103,3 +103,12 @@ def test_full_import_generates_the_worlds_a_reset_would(n, perlin):
         a, b = first.step(acts[s]), second.step(acts[s])
         assert all(torch.equal(x, y) for x, y in zip(a, b)), s
     assert first.export_envs().tobytes() == second.export_envs().tobytes()
+
+
+@pytest.mark.parametrize("perlin", [False, True])
+@pytest.mark.parametrize("n", [24577, 49151, 57345, 70001])
+def test_classic_four_lanes_at_every_split_of_the_regeneration(n, perlin):
+    """Four lanes per environment: rollouts that leave their worlds to a launch (up to 49,151 environments) and that generate
+    them after every step, against steps whose regeneration blocks take two rounds of units, or one (57,345 with Perlin
+    noise, 70,001 with value noise: the chip holds the step blocks and a part of the regeneration blocks)."""
+    test_classic_rollout_owes_worlds(n, perlin)
