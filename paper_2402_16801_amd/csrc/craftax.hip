@@ -1123,7 +1123,7 @@ static void launch_rollout(int lanes, int n, hipStream_t st, const Ptrs& q, cons
     // lanes per environment as chosen for single steps: four (64 environments per block) where there
     // are enough environments to fill the chip that way, else sixteen (16 per block)
     const bool wide = lanes != 4;
-    const int own_from = (int)rollout_own_from(!wide, p.worldgen == CRAFTAX_WORLDGEN_PERLIN, n, steps, p.max_episode_steps);
+    const int own_from = (int)rollout_own_from(!wide, p.worldgen == CRAFTAX_WORLDGEN_PERLIN, o != nullptr, n, steps, p.max_episode_steps);
     const int blocks = wide ? (n + 15) / 16 : (n + 63) / 64;
 #define CRAFTAX_LAUNCH_ROLLOUT(LANES, NOISE) \
     hipLaunchKernelGGL((k_rollout<LANES, OBS_MODE, NOISE>), dim3(blocks), dim3(BLOCK), 0, st, q.recs, q.maps, q.luts, actions, o, reward, \

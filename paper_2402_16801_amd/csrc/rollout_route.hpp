@@ -15,7 +15,9 @@
 //    a step: 32,768 environments 1,065 / 1,157 against 1,125 / 1,219, 49,152: 1,424 / 1,561 against 1,428 / 1,540,
 //    65,536: 1,825 / 2,004 against 1,776 / 1,895; one and a launch against all that are owed: 49,152 1,421 / 1,534
 //    against 1,410 / 1,525, 65,536 1,769 / 1,889 against 1,761 / 1,877).  Not in a rollout of one step (65,536: 59.3 / 64.7
-//    with the launch, 59.5 / 67.3 without) or, with Perlin noise, two (49,152: 82.5 / 83.5).
+//    with the launch, 59.5 / 67.3 without) or, with Perlin noise, two (49,152: 82.5 / 83.5), and not in one that writes
+//    no observation, where there is no such traffic (65,536 x 64 with the launch 969 / 1,145, without 1,055 / 1,254;
+//    49,152 805 / 938 against 896 / 1,054).
 // Plain C++ so that the rule itself can be tested without a GPU.
 #pragma once
 
@@ -27,11 +29,11 @@ constexpr long long OWN_WORLDS_FROM = 49152;
 
 // The step (from 0) from which on a block generates the worlds that its environments are owed, all that there
 // are after each step, so that nothing is owed at the end and no launch follows; `steps`: never.
-// four_lanes: four lanes per environment, else sixteen.
-inline long long rollout_own_from(bool four_lanes, bool perlin, long long n, long long steps, long long max_episode_steps)
+// four_lanes: four lanes per environment, else sixteen; observed: the rollout writes observations.
+inline long long rollout_own_from(bool four_lanes, bool perlin, bool observed, long long n, long long steps, long long max_episode_steps)
 {
     if (cf::worlds_owed(n, steps, max_episode_steps) < (perlin ? 1 : 2)) return steps - 1;
-    return four_lanes && n >= OWN_WORLDS_FROM && steps > (perlin ? 2 : 1) ? 0 : steps;
+    return four_lanes && observed && n >= OWN_WORLDS_FROM && steps > (perlin ? 2 : 1) ? 0 : steps;
 }
 
 }  // namespace cx

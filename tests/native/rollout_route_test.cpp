@@ -19,14 +19,17 @@ int main()
     };
     int bad = 0;
     for (const Measured& m : rows)
-        if ((cx::rollout_own_from(false, m.perlin, m.n, m.steps, 10000) == m.steps - 1) != (m.block_us < m.launch_us)) {
+        if ((cx::rollout_own_from(false, m.perlin, true, m.n, m.steps, 10000) == m.steps - 1) != (m.block_us < m.launch_us)) {
             std::printf("perlin %d, %lld environments, %lld steps: the slower side\n", (int)m.perlin, m.n, m.steps);
             ++bad;
         }
     // short episodes owe worlds sooner; many environments generate after every step only with four lanes each
-    bad += cx::rollout_own_from(false, false, 16, 8, 9) != 8 || cx::rollout_own_from(true, false, 49151, 64, 10000) != 64 ||
-           cx::rollout_own_from(true, false, 49152, 64, 10000) != 0 || cx::rollout_own_from(true, true, 65536, 3, 10000) != 0 ||
-           cx::rollout_own_from(true, true, 65536, 2, 10000) != 2 || cx::rollout_own_from(true, false, 65536, 1, 10000) != 1 || cx::rollout_own_from(false, true, 65536, 64, 10000) != 64;
+    auto from = [](bool four_lanes, bool perlin, bool observed, long long n, long long steps, long long cap = 10000) {
+        return cx::rollout_own_from(four_lanes, perlin, observed, n, steps, cap);
+    };
+    bad += from(false, false, true, 16, 8, 9) != 8 || from(true, false, true, 49151, 64) != 64 || from(true, false, true, 49152, 64) != 0 ||
+           from(true, true, true, 65536, 3) != 0 || from(true, true, true, 65536, 2) != 2 || from(true, false, true, 65536, 1) != 1 ||
+           from(false, true, true, 65536, 64) != 64 || from(true, false, false, 65536, 64) != 64 || from(true, true, false, 49152, 16) != 16;
     if (bad == 0) std::printf("rollout_route_test: ok\n");
     return bad != 0;
 }

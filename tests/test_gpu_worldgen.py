@@ -112,3 +112,27 @@ def test_classic_four_lanes_at_every_split_of_the_regeneration(n, perlin):
     them after every step, against steps whose regeneration blocks take two rounds of units, or one (57,345 with Perlin
     noise, 70,001 with value noise: the chip holds the step blocks and a part of the regeneration blocks)."""
     test_classic_rollout_owes_worlds(n, perlin)
+
+
+def test_classic_rollout_without_observations_at_the_largest_batch():
+    """Without observations the worlds of a large batch are left to the launch behind the rollout: afterwards the state is
+    the one of a rollout that writes them, whose blocks generate after every step."""
+    import torch
+    n, steps = 49152, 21
+    cfg = cx.default_config(max_episode_steps=9)
+    seeds = np.arange(n, dtype=np.uint64) + np.uint64(5)
+    seen, unseen = cx.Craftax(n, cfg), cx.Craftax(n, cfg)
+    acts = torch.empty((steps, n), dtype=torch.int32, device=seen.device)
+    cx.craftax_synth_actions(acts, n, 0, steps, 3, 1, seen.stream)
+    out = []
+    for sim, obs in ((seen, seen.obs), (unseen, None)):
+        sim.reset(seeds)
+        rew = torch.zeros((steps, n), dtype=torch.float32, device=sim.device)
+        done = torch.zeros((steps, n), dtype=torch.uint8, device=sim.device)
+        cx.craftax_rollout(sim.state, acts, steps, obs, rew, done, n, sim.stream)
+        out.append((rew, done))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+    for s in range(steps):
+        a, b = seen.step(acts[s]), unseen.step(acts[s])
+        assert all(torch.equal(x, y) for x, y in zip(a, b)), s
+    assert seen.export_envs().tobytes() == unseen.export_envs().tobytes()
