@@ -332,7 +332,7 @@ __device__ __attribute__((noinline)) void generate_half(uint8_t* map, Lds<uint32
 // arithmetic of others; nothing is exchanged between blocks.  Worlds stay one episode ahead as in
 // the step kernel: an environment whose episode ends moves into its spare world.  The world after that
 // one is left to the regeneration launch behind this one, which generates all of them with the whole
-// chip, or, after step own_from and every later one, generated by the block itself (see rollout_route.hpp);
+// chip, or generated by the block itself after step own_from (see rollout_route.hpp);
 // the environments that are owed a world at the end go on the regeneration list.  An environment whose
 // episode ends without a spare world has the next world generated on the spot.  Before the launch the
 // regeneration lists of the step kernel must be empty (the host runs a list-only launch first).
@@ -428,14 +428,14 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         }
         __syncthreads();
         // worlds that have to exist now, then queued spare worlds
-        const bool own = t >= own_from;
+        bool own = t >= own_from;
 #pragma unroll 1
         while (true) {
             const int nurgent = s_nurgent, qhead = s_qhead, qtail = s_qtail;
             int gt;
             bool urgent;
             if (nurgent > 0) { gt = s_urgent[nurgent - 1]; urgent = true; }
-            else if (own && qhead != qtail) { gt = s_queue[qhead % EPB]; urgent = false; }
+            else if (own && qhead != qtail) { gt = s_queue[qhead % EPB]; urgent = false; own = own_from >= 0; }
             else break;
             __syncthreads();                               // everyone has read the counters
             uint32_t* et = s_env + gt * LDS_ENV_DWORDS;
@@ -1131,11 +1131,11 @@ static void launch_rollout(int lanes, int n, hipStream_t st, const Ptrs& q, cons
     if (p.worldgen == CRAFTAX_WORLDGEN_PERLIN) {
         hipLaunchKernelGGL(k_drain<true>, dim3(regen), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
         if (wide) CRAFTAX_LAUNCH_ROLLOUT(16, true); else CRAFTAX_LAUNCH_ROLLOUT(4, true);
-        if (own_from == steps) hipLaunchKernelGGL(k_drain<true>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
+        if (own_from != steps - 1) hipLaunchKernelGGL(k_drain<true>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
     } else {
         hipLaunchKernelGGL(k_drain<false>, dim3(regen), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
         if (wide) CRAFTAX_LAUNCH_ROLLOUT(16, false); else CRAFTAX_LAUNCH_ROLLOUT(4, false);
-        if (own_from == steps) hipLaunchKernelGGL(k_drain<false>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
+        if (own_from != steps - 1) hipLaunchKernelGGL(k_drain<false>, dim3(owed), dim3(BLOCK), 0, st, q.maps, q.luts, q.ls);
     }
 #undef CRAFTAX_LAUNCH_ROLLOUT
 }
