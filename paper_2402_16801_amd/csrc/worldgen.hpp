@@ -316,8 +316,8 @@ constexpr int LAT_WORDS = LAT_AT8 + (LAT_BLOCKS * 8 - 2 * LAT16_N) + 2;
 // can be rendered without reading the map back.
 // PERLIN: the fields are Perlin noise over the same lattices (perlin_cs: the gradient table).
 // SPLIT: the run's code once with and once without what a strip near the start needs, and the world's
-// identity in scalar registers: for kernels that do nothing else.  The step and rollout kernels carry the
-// code once (in two copies: spills, a step of 65,536 environments 43.0 -> 45.3 us).
+// identity in scalar registers, where the kernel has the registers for it.  Steps with four lanes carry the code
+// once (in two copies: spills, a step of 65,536 environments 43.0 -> 45.3 us), and rollouts (see generate_half).
 // theta (with PERLIN; may be null; LDS or global, LAT_TOTAL values): angle offsets of a mutated level
 // (section "Craftax-1B: UED"): every gradient angle, the upper ten bits of its lattice number, is
 // turned by theta[i] 1024ths of a turn.
