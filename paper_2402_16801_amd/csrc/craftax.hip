@@ -318,13 +318,15 @@ __global__ __launch_bounds__(BLOCK, DRAIN_BLOCKS_PER_CU) void k_drain(uint8_t* _
 }
 
 // Half a world by a whole block.  Not inlined: the rollout kernel's loop would pay for the generator's
-// registers in spills at every step.
+// registers in spills at every step.  SPLIT: see worldgen_block.  With four lanes per environment, where the blocks
+// fill the chip and short episodes make it a matter of throughput (65,536 environments, 32 steps in episodes of 5:
+// 4,615 us with the code once, 4,465 split); with sixteen the code once is ahead (4,096: 714 / 732).
 template <typename T> using Lds = T __attribute__((address_space(3)));
-template <bool PERLIN>
+template <bool PERLIN, bool SPLIT>
 __device__ __attribute__((noinline)) void generate_half(uint8_t* map, Lds<uint32_t>* lat, Lds<uint32_t>* start_win, uint32_t lo, uint32_t hi, uint32_t env,
                                                         uint32_t ep, int half, const uint32_t* perlin_cs)
 {
-    worldgen_block<BLOCK, PERLIN, false>(map, (uint32_t*)lat, lo, hi, env, ep, (uint32_t*)start_win, half * (STRIPS / 2), perlin_cs);
+    worldgen_block<BLOCK, PERLIN, SPLIT>(map, (uint32_t*)lat, lo, hi, env, ep, (uint32_t*)start_win, half * (STRIPS / 2), perlin_cs);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -382,7 +384,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         const uint32_t tenv = (uint32_t)(blockIdx.x * EPB + gt), ep = rt[RW_EPISODE] + 1u, lo = rt[RW_SEED_LO], hi = rt[RW_SEED_HI];
 #pragma unroll 1
         for (int half = 0; half < 2; ++half)
-            generate_half<PERLIN>(maps + map_offset(tenv, ep), (Lds<uint32_t>*)s_lat, (Lds<uint32_t>*)start_win, lo, hi, tenv, ep, half, luts->perlin_cs);
+            generate_half<PERLIN, G == 4>(maps + map_offset(tenv, ep), (Lds<uint32_t>*)s_lat, (Lds<uint32_t>*)start_win, lo, hi, tenv, ep, half, luts->perlin_cs);
     };
 
 #pragma unroll 1
