@@ -1091,7 +1091,7 @@ static int group_lanes(const craftax_config* cfg, int n)
 }
 
 constexpr int RESET_GRID = 64;    // blocks of k_reset_list (the slow list is nearly always empty); each loops over the list
-constexpr int POOL_RESET_GRID = 512;   // the same with optimistic resets, where every finished episode is on that list
+constexpr int FULL_LIST_GRID = 512;    // the same where every finished episode is on that list (4,096 environments with episodes of one step, 64 blocks 349 us, 512: 129)
 constexpr int REGEN_BLOCKS = 1024; // regeneration blocks appended to the step grid (two per world); those beyond the list exit at once
 constexpr int OWED_BLOCKS = COMPUTE_UNITS * DRAIN_BLOCKS_PER_CU;   // regeneration blocks behind a rollout: all that the chip holds at once (a further 256 waited for these and gained nothing)
 constexpr int SHARED_REGEN_BLOCKS = 256;   // with four lanes per environment: one per compute unit, beside its four step blocks (see regeneration_share)
@@ -1111,10 +1111,13 @@ static void launch_step(int G, int n, hipStream_t st, const Ptrs& q, const int32
     else if (G == 8) { if (perlin) CRAFTAX_LAUNCH_STEP(8, true); else CRAFTAX_LAUNCH_STEP(8, false); }
     else { if (perlin) CRAFTAX_LAUNCH_STEP(16, true); else CRAFTAX_LAUNCH_STEP(16, false); }
 #undef CRAFTAX_LAUNCH_STEP
-    if (p.reset_mode == CRAFTAX_RESET_POOL)   // every finished episode is served after the step: its world depends on who else finished
-        hipLaunchKernelGGL((k_reset_list<OBS_MODE>), dim3(n < POOL_RESET_GRID ? n : POOL_RESET_GRID), dim3(WG_THREADS), 0, st, q.recs, q.maps, q.luts, o, done, q.ls, p, 256 / G);
-    else if (p.max_episode_steps == 1u || serve_slow)   // the ways an episode can end before its spare world exists: see note_edit
-        hipLaunchKernelGGL((k_reset_list<OBS_MODE>), dim3(n < RESET_GRID ? n : RESET_GRID), dim3(WG_THREADS), 0, st, q.recs, q.maps, q.luts, o, done, q.ls, p, 256 / G);
+    // with optimistic resets every finished episode is served after the step, because its world depends on who else
+    // finished, and with an episode cap of 1 every episode has finished; else the list is nearly always empty, and it is
+    // served only where an episode can have ended before its spare world existed: see note_edit
+    const bool all = p.reset_mode == CRAFTAX_RESET_POOL || p.max_episode_steps == 1u;
+    const int most_served = all ? FULL_LIST_GRID : RESET_GRID;
+    if (all || serve_slow)
+        hipLaunchKernelGGL((k_reset_list<OBS_MODE>), dim3(n < most_served ? n : most_served), dim3(WG_THREADS), 0, st, q.recs, q.maps, q.luts, o, done, q.ls, p, 256 / G);
 }
 
 template <int OBS_MODE>
