@@ -158,6 +158,11 @@ __device__ __forceinline__ void regeneration_share(uint8_t* __restrict__ maps, c
 // environment the step blocks take a share of that work before they step: regeneration_share).
 constexpr int COMPUTE_UNITS = 256;
 constexpr int step_blocks_per_cu(bool perlin) { return perlin ? 4 : 5; }   // by registers: a wavefront of a block on each of the four SIMDs
+// Neighbouring environments whose entries go to the same sub-list of the regeneration list: those of a step block, which
+// appends them together, or, with 16 lanes, where an entry is appended by itself, one: a few environments whose episodes
+// end together then occupy the regeneration blocks of all sub-lists instead of those of one or two (16 environments,
+// episodes of 2 steps 27.1 -> 7.1 us, 64: 11.0 -> 7.4; ordinary episodes the same).
+constexpr int envs_per_list_turn(int lanes) { return lanes == 16 ? 1 : BLOCK / lanes; }
 template <int G, int OBS_MODE, bool PERLIN>
 __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                    const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
@@ -265,7 +270,7 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
                 write_back = true;
                 if (l == 0) {
                     entry = make_uint4((uint32_t)env, lo, hi, ep + 2u);
-                    if (EAGER) { list_at = la::claim_entry(ls, seq, blockIdx.x); queued = true; }
+                    if (EAGER) { list_at = la::claim_entry(ls, seq, (uint32_t)env); queued = true; }
                     else s_list[atomicAdd(&s_ndone, 1)] = entry;
                 }
             } else if (l == 0) {
@@ -291,7 +296,7 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
     }
     if (EAGER) {
         // an entry at a time, the place claimed before the rendering: no wavefront waits for the others of its block
-        if (queued) la::commit_entry(ls, seq, blockIdx.x, list_at, entry);
+        if (queued) la::commit_entry(ls, seq, (uint32_t)env, list_at, entry);
         leave();
         return;
     }
@@ -497,7 +502,7 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
 template <int OBS_MODE>
 __global__ __launch_bounds__(WG_THREADS) void k_reset_list(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                       const Luts* __restrict__ luts, uint8_t* __restrict__ obs,
-                                                      const uint8_t* __restrict__ done, Lists ls, Params p, int envs_per_step_block)
+                                                      const uint8_t* __restrict__ done, Lists ls, Params p, int envs_per_turn)
 {
     constexpr int G = 16;
     __shared__ uint32_t s_lat[LAT_WORDS];
@@ -549,7 +554,7 @@ __global__ __launch_bounds__(WG_THREADS) void k_reset_list(uint4* __restrict__ r
             grec[tid - 64] = w;
             s_env[LDS_REC + tid - 64] = w;
         }
-        if (tid == 96 && !pool) la::append_after_step(ls, env / (uint32_t)envs_per_step_block, make_uint4(env, lo, hi, ep + 1u));
+        if (tid == 96 && !pool) la::append_after_step(ls, env / (uint32_t)envs_per_turn, make_uint4(env, lo, hi, ep + 1u));
         // ends with a block barrier
         if (p.worldgen == CRAFTAX_WORLDGEN_PERLIN)
             worldgen_block<WG_THREADS, true>(maps + map_offset(env, ep), s_lat, wlo, whi, wenv, wep, s_env + LDS_WIN, 0, luts->perlin_cs);
@@ -1117,7 +1122,7 @@ static void launch_step(int G, int n, hipStream_t st, const Ptrs& q, const int32
     const bool all = p.reset_mode == CRAFTAX_RESET_POOL || p.max_episode_steps == 1u;
     const int most_served = all ? FULL_LIST_GRID : RESET_GRID;
     if (all || serve_slow)
-        hipLaunchKernelGGL((k_reset_list<OBS_MODE>), dim3(n < most_served ? n : most_served), dim3(WG_THREADS), 0, st, q.recs, q.maps, q.luts, o, done, q.ls, p, 256 / G);
+        hipLaunchKernelGGL((k_reset_list<OBS_MODE>), dim3(n < most_served ? n : most_served), dim3(WG_THREADS), 0, st, q.recs, q.maps, q.luts, o, done, q.ls, p, envs_per_list_turn(G));
 }
 
 template <int OBS_MODE>

@@ -16,8 +16,8 @@
 // A list entry carries what world generation needs: (env, seed low, seed high, episode index);
 // env = ENTRY_VOID marks an entry cancelled by an import.  Each of the two regeneration lists
 // (filled and consumed in alternate launches) is cut into NSUB sub-lists with their own counters
-// (step block b appends to sub-list b mod NSUB), so that the appending atomics do not
-// queue up on one address.
+// (step block b appends to sub-list b mod NSUB, or environment e by itself to e mod NSUB, the same way for all
+// entries of a list), so that the appending atomics do not queue up on one address.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -44,7 +44,8 @@ struct Lists { uint32_t* ctr; uint4* regen[2]; uint4* slow; uint2* tags; uint32_
 __device__ inline uint32_t* counter(const Lists& ls, int i) { return ls.ctr + (size_t)i * CTR_STRIDE; }
 
 // Entries a regeneration sub-list must hold: every environment of the step blocks that append to
-// it (plus one block of slack for the rounding of the narrower block shapes).
+// it (plus one block of slack for the rounding of the narrower block shapes), which is also more than every
+// NSUB-th environment.
 inline uint64_t sub_list_capacity(uint64_t n, uint64_t max_envs_per_block)
 {
     const uint64_t blocks = (n + max_envs_per_block - 1) / max_envs_per_block;
@@ -149,20 +150,21 @@ __device__ inline void append_block_entries(const Lists& ls, uint32_t seq, const
 }
 // The same for a single entry, in two halves so that the latency of the atomic hides behind whatever
 // the caller does in between: claim_entry reserves the place, commit_entry stores the entry there.
-__device__ inline uint32_t claim_entry(const Lists& ls, uint32_t seq, uint32_t step_block)
+// turn: the step block, or the environment (see above).
+__device__ inline uint32_t claim_entry(const Lists& ls, uint32_t seq, uint32_t turn)
 {
-    return atomicAdd(counter(ls, CT_REGEN + (int)((seq & 1u) * NSUB + step_block % NSUB)), 1u);
+    return atomicAdd(counter(ls, CT_REGEN + (int)((seq & 1u) * NSUB + turn % NSUB)), 1u);
 }
-__device__ inline void commit_entry(const Lists& ls, uint32_t seq, uint32_t step_block, uint32_t at, uint4 entry)
+__device__ inline void commit_entry(const Lists& ls, uint32_t seq, uint32_t turn, uint32_t at, uint4 entry)
 {
-    if (at < ls.sub_cap) ls.regen[seq & 1u][(size_t)(step_block % NSUB) * ls.sub_cap + at] = entry;   // always true: a sub-list holds every environment of its blocks
+    if (at < ls.sub_cap) ls.regen[seq & 1u][(size_t)(turn % NSUB) * ls.sub_cap + at] = entry;   // always true: a sub-list holds every environment of its blocks
 }
 // One entry for the list the NEXT launch consumes, from a kernel that runs after the step kernel
-// (which has already advanced the launch number); step_block = index of the step block that owns
-// the environment, so that no sub-list can overflow.
-__device__ inline void append_after_step(const Lists& ls, uint32_t step_block, uint4 entry)
+// (which has already advanced the launch number); turn as for the entries of that step, so that no
+// sub-list can overflow.
+__device__ inline void append_after_step(const Lists& ls, uint32_t turn, uint4 entry)
 {
-    const uint32_t next = (*counter(ls, CT_SEQ) & 1u) ^ 1u, sub = step_block % NSUB;
+    const uint32_t next = (*counter(ls, CT_SEQ) & 1u) ^ 1u, sub = turn % NSUB;
     const uint32_t at = atomicAdd(counter(ls, CT_REGEN + (int)(next * NSUB + sub)), 1u);
     if (at < ls.sub_cap) ls.regen[next][(size_t)sub * ls.sub_cap + at] = entry;
 }

@@ -140,6 +140,9 @@ int main()
                     expect(left == 0u && *counter(ls, CT_SEQ) == seq + 1u, "the launch ends with its list empty and the number advanced once", kernel, late_block, late_wave);
                     ++orders;
                 }
+    for (uint64_t n = 1; n < 300000; n += n < 5000 ? 1 : 977)
+        for (uint64_t most : { 16, 64 })
+            if (sub_list_capacity(n, most) < (n + NSUB - 1) / NSUB) expect(false, "a sub-list holds every NSUB-th environment", (int)n, (int)most, 0);
     if (failures) std::printf("launch_order_test: %d failures\n", failures);
     else std::printf("launch_order_test: ok (%ld orders)\n", orders);
     return failures ? 1 : 0;
