@@ -312,7 +312,8 @@ __device__ __attribute__((noinline)) void generate_world(uint8_t* slot, Lds<Worl
 // one launch has no spare world; its wavefront generates the next world on the spot.  Generated by the
 // block at every end of an episode, worlds stalled whole blocks, and a launch lasted as long as the
 // block with the most of them (64 steps: 4,096 environments 1,072 -> 900 us, 1,024: 780 -> 580, 100
-// environments and 16 steps: 230 -> 150; with packed state, staged bytes and kept windows 660, 442, 117).
+// environments and 16 steps: 230 -> 150; with packed state, staged bytes and kept windows 660, 442, 117;
+// the first 646 with the present generator).
 // Before the launch the regeneration lists of the step kernel must be empty (the host runs a
 // list-only launch first).
 template <bool F32, bool PERLIN>

@@ -40,7 +40,7 @@ __host__ __device__ constexpr uint32_t smooth16(int k) { return (uint32_t)((24 *
 //  - the rule's masks are combined on the scalar unit to a code of five bits, each shifted into the run's
 //    word by one add with carry, and one byte permutation looks up the blocks of four cells.
 // Measured against 24-bit integer products, a floor per blend and a select per rule: craftax_reset of 16,384
-// environments (32,768 worlds, 134 MB) 262 -> 224 us, with Perlin noise 631 -> 419.  Sign bits in place of
+// environments (32,768 worlds, 134 MB) 262 -> 224 us, with Perlin noise 669 -> 435.  Sign bits in place of
 // masks (a subtraction per comparison, bit operations on vector registers) took 276 us, selects in place
 // of the code of five bits 227.
 // a.lo * b.lo + a.hi * b.hi over 16-bit halves, unsigned and signed
