@@ -82,12 +82,12 @@ using la::NSUB;
 
 // reset: two blocks per environment, for the worlds of episodes 0 and 1
 template <bool PERLIN>
-__global__ __launch_bounds__(WG_THREADS, PERLIN ? 6 : 8) void k_reset(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
+__global__ __launch_bounds__(WG_THREADS, 8) void k_reset(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                  const uint64_t* __restrict__ seeds, Lists ls, const Luts* __restrict__ luts,
                                                  uint32_t* __restrict__ unlocks)
 {
     if (blockIdx.x == 0) la::reset_counters(ls);
-    __shared__ uint32_t s_lat[LAT_WORDS];
+    __shared__ uint32_t s_lat[lattice_words<PERLIN>];
     const uint32_t env = blockIdx.x >> 1, ep = blockIdx.x & 1u;
     const uint64_t seed = seeds[env];
     const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
     // SHARE: every block reads the length of one sub-list of the consumed list, a regeneration block
     // its own, a step block the one it appends to (see regeneration_share)
     constexpr bool SHARE = G == 4;
-    static_assert(EPB * LY::STRIDE >= LAT_WORDS, "the environments' area, empty until the records are parked, doubles as lattice scratch");
+    static_assert(EPB * LY::STRIDE >= lattice_words<PERLIN>, "the environments' area, empty until the records are parked, doubles as lattice scratch");
     if (!EAGER && tid == 0) s_ndone = 0;
     const la::Ticket ticket = la::enter_launch(ls, SHARE || regen_role, regen_role ? rb : blockIdx.x);   // holds a block barrier
     const uint32_t seq = ticket.seq, regen_count = ticket.regen_count;
@@ -309,13 +309,13 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
 
 // A launch of regeneration blocks only (before and after a rollout): brings every spare world up to date
 // and empties the lists, with the bookkeeping of a step launch that has no step blocks.
-// Five blocks per compute unit: six take the registers of value noise away (9 spilled: rollouts of 32,768
-// environments and 16 steps 278 -> 272 us with five, of 4,096 115.2 -> 113.9, of 600 and one 18.6 -> 18.0).
-constexpr int DRAIN_BLOCKS_PER_CU = 5;
+// Eight blocks per compute unit, which no longer take registers that the generator needs (five: rollouts of 16,384 environments and
+// 64 steps 662 us, 657 with eight, of 32,768 1,046 and 1,034; of 600 and one step 17.8 either way).
+constexpr int DRAIN_BLOCKS_PER_CU = 8;
 template <bool PERLIN>
 __global__ __launch_bounds__(BLOCK, DRAIN_BLOCKS_PER_CU) void k_drain(uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
 {
-    __shared__ uint32_t s_lat[LAT_WORDS];
+    __shared__ uint32_t s_lat[lattice_words<PERLIN>];
     const uint32_t rb = blockIdx.x, nrb = gridDim.x;
     const la::Ticket ticket = la::enter_launch(ls, true, rb);
     if (rb / NSUB / 2 < ticket.regen_count) regeneration_block<PERLIN>(maps, ls, ticket.seq, ticket.regen_count, rb, nrb, s_lat, luts->perlin_cs);
@@ -357,8 +357,8 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
 {
     constexpr int EPB = Grp<G>::EPB;
     __shared__ uint32_t s_env[EPB * LDS_ENV_DWORDS];
-    __shared__ __attribute__((aligned(16))) uint32_t s_lat[LAT_WORDS];   // the generator's lattices; at the end the environments that are owed a world
-    static_assert(LAT_WORDS >= EPB * 4, "an entry per environment");
+    __shared__ __attribute__((aligned(16))) uint32_t s_lat[lattice_words<PERLIN>];   // the generator's lattices; at the end the environments that are owed a world
+    static_assert(lattice_words<PERLIN> >= EPB * 4, "an entry per environment");
     __shared__ uint8_t s_queue[EPB];        // ring of environments (index in the block) waiting for a new spare world
     __shared__ uint8_t s_urgent[EPB];       // environments whose episode ended without a spare world
     __shared__ uint8_t s_spare_ok[EPB], s_pending[EPB];
@@ -713,10 +713,10 @@ __global__ __launch_bounds__(BLOCK) void k_import(uint4* __restrict__ recs, uint
 
 // after an import: the world of the episode after the imported one, into the spare slot
 template <bool PERLIN>
-__global__ __launch_bounds__(WG_THREADS, PERLIN ? 6 : 8) void k_import_spare(const uint4* __restrict__ recs, uint8_t* __restrict__ maps, Lists ls, int first,
+__global__ __launch_bounds__(WG_THREADS, 8) void k_import_spare(const uint4* __restrict__ recs, uint8_t* __restrict__ maps, Lists ls, int first,
                                                                              const Luts* __restrict__ luts)
 {
-    __shared__ uint32_t s_lat[LAT_WORDS];
+    __shared__ uint32_t s_lat[lattice_words<PERLIN>];
     const uint32_t env = (uint32_t)first + blockIdx.x;
     const uint32_t* r = reinterpret_cast<const uint32_t*>(recs + (size_t)env * 8);
     const uint32_t ep = r[RW_EPISODE] + 1u, lo = r[RW_SEED_LO], hi = r[RW_SEED_HI];
@@ -1098,7 +1098,7 @@ static int group_lanes(const craftax_config* cfg, int n)
 constexpr int RESET_GRID = 64;    // blocks of k_reset_list (the slow list is nearly always empty); each loops over the list
 constexpr int FULL_LIST_GRID = 512;    // the same where every finished episode is on that list (4,096 environments with episodes of one step, 64 blocks 349 us, 512: 129)
 constexpr int REGEN_BLOCKS = 1024; // regeneration blocks appended to the step grid (two per world); those beyond the list exit at once
-constexpr int OWED_BLOCKS = COMPUTE_UNITS * DRAIN_BLOCKS_PER_CU;   // regeneration blocks behind a rollout: all that the chip holds at once (a further 256 waited for these and gained nothing)
+constexpr int OWED_BLOCKS = COMPUTE_UNITS * DRAIN_BLOCKS_PER_CU;   // regeneration blocks behind a rollout: all that the chip holds at once 
 constexpr int SHARED_REGEN_BLOCKS = 256;   // with four lanes per environment: one per compute unit, beside its four step blocks (see regeneration_share)
 
 template <int OBS_MODE>

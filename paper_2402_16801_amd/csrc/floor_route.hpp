@@ -7,7 +7,7 @@
 //   reset, value noise      288  6.4 / 14.5   2,700 14.1 / 18.1   4,194 19.0 / 20.6   4,500 19.9 / 20.8   5,130 21.9 / 21.3   6,138 25.0 / 22.1   73,728 230 / 144
 //   import, value noise     288 12.6 / 22.3   3,600 28.5 / 32.7   4,500 33.1 / 33.9   4,797 34.7 / 34.6   5,121 36.2 / 34.9   18,000 112 / 89
 //   reset, Perlin noise     288  9.4 / 21.7   1,800 19.5 / 24.3   2,340 23.6 / 25.5   2,700 26.3 / 25.7   3,600 32.6 / 28.5
-//     5,120 single wavefronts run at once (PERLIN_WAVES on each SIMD); the second round costs less than blocks would:
+//     (5,120 single wavefronts ran at once then)
 //     4,788 40.8 / 29.2   5,130 43.2 / 35.1   6,138 50.3 / 41.0   11,988 90.6 / 62.7   73,728 515 / 237
 //   import, Perlin noise    288 16.0 / 29.6   2,070 32.6 / 37.2   2,592 38.1 / 38.7   2,790 40.1 / 38.9   3,600 47.6 / 40.3   18,000 203 / 123
 //   noise mutation          288 19.5 / 23.1   720 22.0 / 23.8   1,080 24.1 / 25.3   1,440 27.5 / 25.8   2,052 31.4 / 26.2   18,000 152 / 85
@@ -21,18 +21,20 @@ namespace cf {
 
 enum class FloorWork { RESET, IMPORT, MUTATE, OWED };
 
-// Wavefronts per SIMD that the generating kernels are bounded to.  With Perlin noise five cost no spilled registers;
-// six do, and are 3 to 8 % slower, but take 5,121 to 6,144 single wavefronts in one round.
+// Wavefronts per SIMD that the generating kernels are bounded to.  With Perlin noise six, which spill nothing (five:
+// resets of 4,096 environments 230 us, 218 with six; level turns over 256, 1,000 and 2,000 levels 69.7, 141 and 217 us, 65.7, 138 and 213 with six).
 constexpr long long SIMDS = 1024;
-constexpr int VALUE_WAVES = 8, PERLIN_WAVES = 5, PERLIN_WAVES_TIGHT = 6;
+constexpr int VALUE_WAVES = 8, PERLIN_WAVES = 6;
 
-// Imports of Perlin worlds by single wavefronts whose second round would be short: five / six per SIMD, us:
+// Imports of Perlin worlds by single wavefronts that six to a SIMD take in one round and five in two, by five / six per SIMD, us,
+// when six spilled registers:
 //   5,121 floors 41.9 / 44.9   5,148 48.7 / 45.1   5,400 49.5 / 45.8   5,580 51.3 / 46.1   6,138 55.8 / 47.5   6,300 56.7 / 57.2
-// A few wavefronts beyond a round do not make a second one: they run beside the last of the first.
+// A few wavefronts beyond a round do not make a second one: they run beside the last of the first.  No call asks this
+// since every import runs six to a SIMD; what it knows about rounds is kept with its test.
 inline bool one_tight_round(FloorWork work, bool perlin, long long floors)
 {
     constexpr long long FEW = 8;
-    return work == FloorWork::IMPORT && perlin && floors > SIMDS * PERLIN_WAVES + FEW && floors <= SIMDS * PERLIN_WAVES_TIGHT + FEW;
+    return work == FloorWork::IMPORT && perlin && floors > SIMDS * (PERLIN_WAVES - 1) + FEW && floors <= SIMDS * PERLIN_WAVES + FEW;
 }
 
 inline bool floors_by_blocks(FloorWork work, bool perlin, long long floors)

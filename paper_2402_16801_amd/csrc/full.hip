@@ -674,8 +674,8 @@ __device__ inline void import_record(uint32_t* __restrict__ r, const Lists& ls, 
 // of the next episode into the spare slot, so that the copy of some blocks overlaps the arithmetic of
 // others; the block of floor 0 also packs the record.  (A copy byte by byte and a second launch for
 // the spare worlds: 50 + 87 us for 1,000 Perlin worlds, one launch 101, by single wavefronts 93.)
-template <bool PERLIN, int NT, int WAVES = PERLIN ? PERLIN_WAVES : VALUE_WAVES>
-__global__ __launch_bounds__(NT, WAVES) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
+template <bool PERLIN, int NT>
+__global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
                                                                         const craftax_full_env_dump* __restrict__ dumps, int first, Params p,
                                                                         const uint32_t* __restrict__ perlin_cs, int pool)
 {
@@ -952,7 +952,6 @@ static bool kernels_fit(const Fits& fits)
            floors("kf_reset", (const void*)kf_reset<PERLIN, GEN_THREADS>, (const void*)kf_reset<PERLIN, FLOOR_THREADS>) &&
            floors("kf_drain", (const void*)kf_drain<PERLIN, GEN_THREADS>, (const void*)kf_drain<PERLIN, FLOOR_THREADS>) &&
            floors("kf_import", (const void*)kf_import<PERLIN, GEN_THREADS>, (const void*)kf_import<PERLIN, FLOOR_THREADS>) &&
-           (!PERLIN || fits("kf_import (six wavefronts)", (const void*)kf_import<true, FLOOR_THREADS, PERLIN_WAVES_TIGHT>, FLOOR_THREADS)) &&
            (!PERLIN || floors("kf_mutate_noise", (const void*)kf_mutate_noise<GEN_THREADS>, (const void*)kf_mutate_noise<FLOOR_THREADS>)) &&
            fits("kf_export", (const void*)kf_export, GEN_THREADS) && fits("kf_mutate_swap", (const void*)kf_mutate_swap, MUTATE_SWAP_THREADS);
 }
@@ -1115,8 +1114,7 @@ int import_envs(void* state, const craftax_config* cfg, int n, int first, int co
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0);
     };
     const bool perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN, blocks = floors_by_blocks(FloorWork::IMPORT, perlin, (long long)count * FLOORS);
-    if (one_tight_round(FloorWork::IMPORT, perlin, (long long)count * FLOORS)) go(kf_import<true, FLOOR_THREADS, PERLIN_WAVES_TIGHT>, FLOOR_THREADS);
-    else if (perlin) { if (blocks) go(kf_import<true, GEN_THREADS>, GEN_THREADS); else go(kf_import<true, FLOOR_THREADS>, FLOOR_THREADS); }
+    if (perlin) { if (blocks) go(kf_import<true, GEN_THREADS>, GEN_THREADS); else go(kf_import<true, FLOOR_THREADS>, FLOOR_THREADS); }
     else { if (blocks) go(kf_import<false, GEN_THREADS>, GEN_THREADS); else go(kf_import<false, FLOOR_THREADS>, FLOOR_THREADS); }
     return check_launch("craftax_import_envs", err);
 }

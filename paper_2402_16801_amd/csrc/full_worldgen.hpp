@@ -26,14 +26,12 @@ constexpr int LAT0_BLOCKS = (LAT0_U16 + 7) / 8;           // 29
 constexpr int LATC_U16 = 2 * 49, LATC_BLOCKS = (LATC_U16 + 7) / 8;   // cave floors: two 7x7 lattices, 13 blocks
 constexpr int LAT_TOTAL = LAT0_BLOCKS * 8;                // a block generates one floor: the largest lattice set
 
-// The lattices lie in LDS as in the Classic generator: one dword per point, for value noise the point
-// and, in the high half, the point below it (a column is then one dot product), for Perlin noise its
-// gradient.  4x4 lattices first, then 7x7; the gaps in front of both groups take the high halves
-// that the first row of a group leaves above itself, between lattices of one group they fall into the
-// last row of the previous one, whose high halves nobody reads.
-constexpr int WIDE0 = 2 * 16;                             // numbers of the overworld's 4x4 lattices come first
-constexpr int LAT_AT16 = 4, LAT_AT8 = 4 + WIDE0 + 7, LATC_AT8 = 7;
-constexpr int LAT_WORDS = LAT_AT8 + (LAT_TOTAL - WIDE0) + 1;
+// The lattices lie in LDS as in the Classic generator, one number after the other: as floats, for Perlin noise the
+// cosines.  The sines of a cave's lattices follow behind them; those of the overworld, which needs no row masks,
+// take the masks' place.  The overworld's 4x4 lattices come first.
+constexpr int WIDE0 = 2 * 16, LATC_N = LATC_BLOCKS * 8;
+constexpr int LAT_WORDS = LAT_TOTAL;
+static_assert(2 * LATC_N <= LAT_WORDS, "cosines and sines of a cave");
 
 struct Room { int x, y, w, h, cx, cy; };
 struct GenLayout {
@@ -47,7 +45,9 @@ struct GenLayout {
     // this floor has none).
     uint64_t row_mask[5][W];
     uint32_t spot[5];
+    __device__ float* overworld_sines() { return reinterpret_cast<float*>(row_mask); }
 };
+static_assert(sizeof(GenLayout::row_mask) >= LAT_TOTAL * sizeof(float), "sines of the overworld");
 
 __device__ inline int dungeon_index(int f) { return f == 1 ? 0 : (f == 3 ? 1 : 2); }
 __device__ inline bool is_dungeon(int f) { return f == 1 || f == 3 || f == 4; }
@@ -150,25 +150,21 @@ __device__ inline void make_cave_ladders(GenLayout& L, int f, const U4& r)
     L.down[f][0] = 32 + (int)choice(r.w[2], 6); L.down[f][1] = 32 + (int)choice(r.w[3], 6);
 }
 
-// The eight lattice numbers of Philox block `block`: number i of the set goes to dword at16 + i (i <
-// wide: 4x4 lattices) or at8 + i - wide (7x7 lattices).
-template <bool CAN_PERLIN>
-__device__ inline void put_lattice(uint32_t* s_lat, int at16, int at8, int wide, int block, const U4& r, const uint32_t* __restrict__ perlin_cs,
-                                   const uint16_t* theta_f)
+// The eight lattice numbers of Philox block `block`; sines: where those go with Perlin noise, of COUNT numbers
+template <bool CAN_PERLIN, int COUNT>
+__device__ inline void put_lattice(uint32_t* s_lat, float* sines, int block, const U4& r, const uint32_t* __restrict__ perlin_cs, const uint16_t* theta_f)
 {
+    float* lat = reinterpret_cast<float*>(s_lat);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int i = block * 8 + j;
+        const int i = CX_IDX(block * 8 + j, COUNT);
         uint32_t v = (j & 1) ? (r.w[j >> 1] >> 16) : (r.w[j >> 1] & 0xFFFFu);
-        const int at = i < wide ? at16 + i : at8 + i - wide, above = at - (i < wide ? 4 : 7);
         if (CAN_PERLIN && perlin_cs != nullptr) {
             if (theta_f != nullptr) v = (v + ((theta_f[i] & 1023u) << 6)) & 0xFFFFu;
-            s_lat[CX_IDX(at, LAT_WORDS)] = perlin_cs[v >> 6];
-        } else {
-            uint16_t* half = reinterpret_cast<uint16_t*>(s_lat);
-            half[CX_IDX(2 * at, 2 * LAT_WORDS)] = (uint16_t)v;
-            half[CX_IDX(2 * above + 1, 2 * LAT_WORDS)] = (uint16_t)v;
-        }
+            const uint32_t cs = perlin_cs[v >> 6];
+            lat[i] = (float)(int)(int16_t)(cs & 0xFFFFu);
+            sines[i] = (float)((int)cs >> 16);
+        } else lat[i] = (float)v;
     }
 }
 
@@ -210,14 +206,14 @@ __device__ inline uint32_t cave_ground(int f) { return f == 6 ? (uint32_t)B_FIRE
 template <bool PERLIN, int KIND>
 struct CaveThresholds {
     template <int T> __device__ static uint32_t draw() { return cx::scalar_const<(uint32_t)T << 16>(); }
-    template <int T> __device__ static uint32_t field() { return cx::scalar_const<cx::first_above<PERLIN>(T)>(); }
+    template <int T> __device__ static float field() { return __uint_as_float(cx::scalar_const<cx::f32_bits(cx::first_above<PERLIN>(T))>()); }
     static constexpr bool GNOME = KIND == GNOME_MINES, MINES = KIND != REALM;
-    uint32_t open = field<31000>(), liquid = field<MINES ? 44000 : 43000>(), plant = draw<GNOME ? 1500 : 3000>();
-    uint32_t b0 = draw<MINES ? 5000 : 2500>(), b1 = draw<7500>(), b2 = draw<8000>(), b3 = draw<GNOME ? 8600 : 9000>(), b4 = draw<GNOME ? 9200 : 10000>();
+    float open = field<31000>(), liquid = field<MINES ? 44000 : 43000>();
+    uint32_t plant = draw<GNOME ? 1500 : 3000>(), b0 = draw<MINES ? 5000 : 2500>(), b1 = draw<7500>(), b2 = draw<8000>(), b3 = draw<GNOME ? 8600 : 9000>(), b4 = draw<GNOME ? 9200 : 10000>();
 };
 // Appends the cell's code to `word`, where a cell takes a byte.  C, F: the fields; u: the draw in the upper half
 template <bool PERLIN, int KIND>
-__device__ __forceinline__ void classify_cave(uint32_t& word, const CaveThresholds<PERLIN, KIND>& t, uint32_t below1, uint32_t C, uint32_t F, uint32_t u)
+__device__ __forceinline__ void classify_cave(uint32_t& word, const CaveThresholds<PERLIN, KIND>& t, uint32_t below1, float C, float F, uint32_t u)
 {
     using cx::Mask; using cx::mask_of; using cx::shift_in_or;
     const Mask open = mask_of(C >= t.open), ore0 = mask_of(u < t.b0);
@@ -237,13 +233,6 @@ __device__ __forceinline__ void classify_cave(uint32_t& word, const CaveThreshol
 }
 __device__ inline uint32_t cave_blocks(const CaveRule& k, uint32_t word) { return __builtin_amdgcn_perm(k.table_hi, k.table_lo, word); }
 
-// The lattice columns left and right of a run in row y, blended vertically, from the run's last cell on (see cx::Line).
-__device__ inline cx::Line line_at(const uint32_t* lat, int width, int ix, int iy, uint32_t weights, double last)
-{
-    const uint32_t* c = lat + CX_IDX(iy * width + ix, width * width - 1);
-    return cx::line_between(cx::dot16u(c[0], weights), cx::dot16u(c[1], weights), last);
-}
-
 // Generates floor f of one environment with the NT threads of the calling block (NT = 64: with the
 // calling wavefront, whatever the other wavefronts of its block do): run t (of 288)
 // is the 8 cells [8t, 8t+8) of the floor (row t/6).  The block of floor 0 also derives the
@@ -259,10 +248,10 @@ __device__ inline cx::Line line_at(const uint32_t* lat, int width, int ix, int i
 // 1024ths of a turn added to the upper ten bits of this floor's lattice numbers, the level of the
 // noise mutation (section "Craftax-1B: UED").
 // Bound by instruction issue, like the Classic generator, and written in the same way (worldgen.hpp): fields in
-// 64-bit floating point, masks on the scalar unit, a code per cell that byte permutations turn into
+// 32-bit floating point rounded down, masks on the scalar unit, a code per cell that byte permutations turn into
 // blocks.  A run of 8 cells uses all of its Philox block, and the built floors are byte masks over whole
-// runs.  Measured against integer products and selects: craftax_reset of 4,096 environments (8,192 worlds,
-// 340 MB) by single wavefronts 179 -> 150 us, with Perlin noise 346 -> 246, of 256 with Perlin noise 39 -> 29.
+// runs.  Measured: craftax_reset with its observation, fields in 64 bits and in 32: 4,096 environments (8,192 worlds, 340 MB)
+// 176 -> 171 us, with Perlin noise 269 -> 218, of 256 with Perlin noise 46.3 -> 43.3.
 // LOOPED: the call stands in a loop over worlds; what a thread derives from its index is then derived
 // anew in every call instead of being kept (and spilled) across the loop.
 template <int NT = GEN_THREADS, bool CAN_PERLIN = false, bool LOOPED = false>
@@ -294,7 +283,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
             else if (tid >= 58) { stream = 63u; block = tid == 59 ? 1u : 0u; }
             const U4 r = wg_block(lo, hi, env, episode, stream, block);
             const uint32_t fifth = (uint32_t)__shfl((int)r.w[0], 59);
-            if (tid < LAT0_BLOCKS) put_lattice<CAN_PERLIN>(s_lat, LAT_AT16, LAT_AT8, WIDE0, tid, r, perlin_cs, theta_f);
+            if (tid < LAT0_BLOCKS) put_lattice<CAN_PERLIN, LAT_TOTAL>(s_lat, L.overworld_sines(), tid, r, perlin_cs, theta_f);
             else if (tid < 53) make_room(L, ff, (tid - 29) & 7, r);
             else if (tid < 57) make_cave_ladders(L, ff, r);
             else if (tid == 57) {
@@ -325,7 +314,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
             // lanes 0..12 lattice blocks, lane 13 the ladders
             if (tid <= LATC_BLOCKS) {
                 const U4 r = wg_block(lo, hi, env, episode, (uint32_t)f * 4u + (tid == LATC_BLOCKS ? 2u : 0u), tid == LATC_BLOCKS ? 0u : (uint32_t)tid);
-                if (tid < LATC_BLOCKS) put_lattice<CAN_PERLIN>(s_lat, 0, LATC_AT8, 0, tid, r, perlin_cs, theta_f);
+                if (tid < LATC_BLOCKS) put_lattice<CAN_PERLIN, LATC_N>(s_lat, reinterpret_cast<float*>(s_lat) + LATC_N, tid, r, perlin_cs, theta_f);
                 else make_cave_ladders(L, f, r);
             }
         }
@@ -339,7 +328,8 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         if (tid0 < W) cave_row_mask(L, f, tid0);
         barrier();
     }
-    if (CAN_PERLIN) cx::floor_rounding(tid0);
+    const float* lat = reinterpret_cast<const float*>(s_lat);
+    cx::floor_rounding(tid0);
     // A run's number and the number of its strip are even or odd together, and so is the lane's: whether a
     // run is the right half of a spacing-16 lattice cell is the same in every pass.
     static_assert(ROW_RUNS % 2 == 0 && NT % 2 == 0, "parity of the strips");
@@ -361,20 +351,16 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
     auto draw = [&](auto j) { return (j & 1) ? r.w[j >> 1] : r.w[j >> 1] << 16; };   // draw of cell j, in the upper half
     // the floor is the same for the whole block: one kind of cell function per block
     if (f == 0) {
-        const uint32_t* w16 = s_lat + LAT_AT16;
-        const uint32_t* m16 = w16 + 16;
-        const uint32_t* w8 = s_lat + LAT_AT8;
-        const uint32_t* m8 = w8 + 49;
-        const uint32_t* c8 = m8 + 49;
-        const uint32_t* f8 = c8 + 49;
-        const int iy16 = y >> 4, iy8 = y >> 3, ix16 = x0 >> 4;
+        // the points above and left of the run in the two lattices of spacing 16 and the four of spacing 8
+        const int at16 = CX_IDX((y >> 4) * 4 + (x0 >> 4), 16 - 5), at8 = WIDE0 + CX_IDX((y >> 3) * 7 + strip, 49 - 8);
+        const int w16 = at16, m16 = w16 + 16, w8 = at8, m8 = w8 + 49, c8 = m8 + 49, f8 = c8 + 49;
         uint32_t odd = 0u - (uint32_t)(run & 1);            // all ones: right half of a spacing-16 lattice cell
         asm volatile("" : "+v"(odd));                        // or the weights of all passes are computed, and spilled, before the first
         // 4 times the lowering (10 - d) * 2500 of W and M within Chebyshev distance d < 10 of the start
         const int step = 4 * START_BIAS, bias_y = max(0, START_BIAS_R - iabs(y - W / 2)) * step;
         const int bias_l = (START_BIAS_R + x0 - W / 2) * step, bias_r = (START_BIAS_R - x0 + W / 2) * step;
         const bool near_rows = __any(bias_y != 0);          // a pass covers ten or eleven rows
-        auto put = [&](const auto& thresholds, auto j, int W4, int M4, uint32_t C, uint32_t F) {
+        auto put = [&](const auto& thresholds, auto j, float W4, float M4, float C, float F) {
             uint32_t u = draw(j);
             if (near_rows) cx::near_start(max(0, min(min(bias_l + j * step, bias_r - j * step), bias_y)), W4, M4, u);
             cx::classify(word, thresholds, W4, M4, C, F, u);
@@ -382,41 +368,38 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
             if (j == 4) second = word;                      // (the next four cells shift it out)
         };
         if (CAN_PERLIN && use_perlin) {
-            const int ky16 = y & 15, ky8 = y & 7, kx16 = x0 & 15;
-            const double wy16 = cx::perlin_fade<16>(ky16) * (1.0 / 65536.0), wy8 = cx::perlin_fade<8>(ky8) * (1.0 / 65536.0);
-            // One field after the other for the whole run (a line takes 16 registers); the last one with the rule.
+            const int ky16 = y & 15, ky8 = y & 7;
+            const float wy16 = (float)cx::perlin_fade<16>(ky16) * (1.0f / 65536.0f), wy8 = (float)cx::perlin_fade<8>(ky8) * (1.0f / 65536.0f);
+            // One field after the other for the whole run; the last one with the rule.
             // The empty statement keeps the loads of a field's gradients from being moved before the field at hand.
-            auto along = [&](cx::PerlinLine line, auto&& weight, double wy, auto&& cell) {
+            auto along = [&](cx::PerlinLine line, auto&& weight, float wy, auto&& cell) {
                 cx::for_run([&](auto j) { cell(j, line.field(weight(j), wy)); line.advance(); });
                 asm volatile("" ::: "memory");
             };
-            auto wide = [&](const uint32_t* lat) { return cx::perlin_line<16>(cx::gradients_at(lat, 4, ix16, iy16), kx16 + 7, ky16); };
-            auto narrow = [&](const uint32_t* lat) { return cx::perlin_line<8>(cx::gradients_at(lat, 7, strip, iy8), 7, ky8); };
-            auto weight16 = [&](auto j) { return cx::pick<cx::high_half(cx::perlin_weight<16>(8 + j)), cx::high_half(cx::perlin_weight<16>(j))>(odd); };
-            auto weight8 = [&](auto j) { return cx::scalar_double<cx::high_half(cx::perlin_weight<8>(j))>(); };
-            int W4[RUN], M4[RUN];
-            uint32_t C[RUN];
+            const float* sines = L.overworld_sines();
+            auto wide = [&](int at) { return cx::perlin_line<16>(lat + at, sines + at, 4, (float)((x0 & 15) + 7), (float)ky16); };
+            auto narrow = [&](int at) { return cx::perlin_line<8>(lat + at, sines + at, 7, 7.0f, (float)ky8); };
+            auto wx16 = [&](auto j) { return cx::pick<cx::f32_bits(cx::perlin_weight<16>(8 + j)), cx::f32_bits(cx::perlin_weight<16>(j))>(odd); };
+            auto wx8 = [&](auto j) { return cx::perlin_weight<8>(j); };
+            float W4[RUN], M4[RUN], C[RUN];
             const cx::PerlinScale<16> coarse;
             const cx::PerlinScale<8> fine;
-            along(wide(w16), weight16, wy16, [&](int j, double v) { W4[j] = coarse.value(v); cx::settle(W4[j]); });
-            along(narrow(w8), weight8, wy8, [&](int j, double v) { W4[j] = 3 * W4[j] + fine.value(v); cx::settle(W4[j]); });
-            along(wide(m16), weight16, wy16, [&](int j, double v) { M4[j] = coarse.value(v); cx::settle(M4[j]); });
-            along(narrow(m8), weight8, wy8, [&](int j, double v) { M4[j] = 3 * M4[j] + fine.value(v); cx::settle(M4[j]); });
-            along(narrow(c8), weight8, wy8, [&](int j, double v) { C[j] = cx::settled(v); });
+            along(wide(w16), wx16, wy16, [&](int j, float v) { W4[j] = coarse.value(v); cx::settle(W4[j]); });
+            along(narrow(w8), wx8, wy8, [&](int j, float v) { W4[j] = cx::perlin_mix31(W4[j], fine.value(v)); cx::settle(W4[j]); });
+            along(wide(m16), wx16, wy16, [&](int j, float v) { M4[j] = coarse.value(v); cx::settle(M4[j]); });
+            along(narrow(m8), wx8, wy8, [&](int j, float v) { M4[j] = cx::perlin_mix31(M4[j], fine.value(v)); cx::settle(M4[j]); });
+            along(narrow(c8), wx8, wy8, [&](int j, float v) { C[j] = v; cx::settle(C[j]); });
             const cx::Thresholds<CAN_PERLIN> thresholds;
-            along(narrow(f8), weight8, wy8, [&](auto j, double v) { put(thresholds, j, W4[j], M4[j], C[j], (uint32_t)__double2loint(v)); });
+            along(narrow(f8), wx8, wy8, [&](auto j, float v) { put(thresholds, j, W4[j], M4[j], C[j], v); });
         } else {
-            const uint32_t v16 = cx::vertical_weights(cx::smooth16(y & 15)), v8 = cx::vertical_weights(cx::smooth8(y & 7));
-            const double last16 = cx::pick<cx::high_half(cx::LAST16_ODD), cx::high_half(cx::LAST16)>(odd);
-            cx::Line W16 = line_at(w16, 4, ix16, iy16, v16, last16), M16 = line_at(m16, 4, ix16, iy16, v16, last16);
-            cx::Line W8 = line_at(w8, 7, strip, iy8, v8, cx::LAST8), M8 = line_at(m8, 7, strip, iy8, v8, cx::LAST8);
-            cx::Line C8 = line_at(c8, 7, strip, iy8, v8, cx::LAST8), F8 = line_at(f8, 7, strip, iy8, v8, cx::LAST8);
+            const float wy16 = (float)cx::smooth16(y & 15) * (1.0f / 256.0f), wy8 = (float)cx::smooth8(y & 7) * (1.0f / 256.0f);
+            const cx::Line W16 = cx::line_at(lat + w16, 4, wy16), M16 = cx::line_at(lat + m16, 4, wy16);
+            const cx::Line W8 = cx::line_at(lat + w8, 7, wy8), M8 = cx::line_at(lat + m8, 7, wy8), C8 = cx::line_at(lat + c8, 7, wy8), F8 = cx::line_at(lat + f8, 7, wy8);
             const cx::Thresholds<false> thresholds;
             cx::for_run([&](auto j) {
-                put(thresholds, j, cx::mix31(W16.field(), W8.field()), cx::mix31(M16.field(), M8.field()), C8.field(), F8.field());
-                const double s16 = cx::pick<cx::high_half(cx::step16(8 + j)), cx::high_half(cx::step16(j))>(odd);
-                W16.advance(s16); M16.advance(s16);
-                for (cx::Line* l : {&W8, &M8, &C8, &F8}) l->advance(cx::step8(j));
+                const float wx16 = cx::pick<cx::f32_bits(cx::weight16(8 + j)), cx::f32_bits(cx::weight16(j))>(odd);
+                constexpr float wx8 = cx::weight8(j);
+                put(thresholds, j, cx::mix31(W16.at(wx16), W8.at(wx8)), cx::mix31(M16.at(wx16), M8.at(wx8)), C8.at(wx8), F8.at(wx8));
             });
         }
         blocks = make_uint2(cx::blocks_of(word), cx::blocks_of(second));
@@ -450,36 +433,34 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         place(24u | (42u << 8), B_PATH, IT_LADDER_UP);
     } else {
         const CaveRule rule = cave_rule(f);
-        const uint32_t* c8 = s_lat + LATC_AT8;
-        const uint32_t* f8 = c8 + 49;
-        const int iy8 = y >> 3;
+        const float* c8 = lat + CX_IDX((y >> 3) * 7 + strip, 49 - 8);
+        const float* f8 = c8 + 49;
         auto cave = [&](auto kind) {
             constexpr int KIND = decltype(kind)::value;
             if (CAN_PERLIN && use_perlin) {
                 const int ky8 = y & 7;
-                const double wy8 = cx::perlin_fade<8>(ky8) * (1.0 / 65536.0);
-                uint32_t C[RUN];
-                auto weight8 = [&](auto j) { return cx::scalar_double<cx::high_half(cx::perlin_weight<8>(j))>(); };
-                cx::PerlinLine nC = cx::perlin_line<8>(cx::gradients_at(c8, 7, strip, iy8), 7, ky8);
-                cx::for_run([&](auto j) { C[j] = cx::settled(nC.field(weight8(j), wy8)); nC.advance(); });
+                const float wy8 = (float)cx::perlin_fade<8>(ky8) * (1.0f / 65536.0f);
+                float C[RUN];
+                cx::PerlinLine nC = cx::perlin_line<8>(c8, c8 + LATC_N, 7, 7.0f, (float)ky8);
+                cx::for_run([&](auto j) { C[j] = nC.field(cx::perlin_weight<8>(j), wy8); cx::settle(C[j]); nC.advance(); });
                 asm volatile("" ::: "memory");
-                cx::PerlinLine nF = cx::perlin_line<8>(cx::gradients_at(f8, 7, strip, iy8), 7, ky8);
+                cx::PerlinLine nF = cx::perlin_line<8>(f8, f8 + LATC_N, 7, 7.0f, (float)ky8);
                 const CaveThresholds<CAN_PERLIN, KIND> thresholds;
                 cx::for_run([&](auto j) {
-                    classify_cave<CAN_PERLIN, KIND>(word, thresholds, rule.below1, C[j], KIND == GNOME_MINES ? 0u : (uint32_t)__double2loint(nF.field(weight8(j), wy8)), draw(j));
+                    classify_cave<CAN_PERLIN, KIND>(word, thresholds, rule.below1, C[j], KIND == GNOME_MINES ? 0.0f : nF.field(cx::perlin_weight<8>(j), wy8), draw(j));
                     cx::settle(word);
                     if (j == 4) second = word;
                     nF.advance();
                 });
             } else {
-                const uint32_t v8 = cx::vertical_weights(cx::smooth8(y & 7));
-                cx::Line C8 = line_at(c8, 7, strip, iy8, v8, cx::LAST8), F8 = line_at(f8, 7, strip, iy8, v8, cx::LAST8);
+                const float wy8 = (float)cx::smooth8(y & 7) * (1.0f / 256.0f);
+                const cx::Line C8 = cx::line_at(c8, 7, wy8), F8 = cx::line_at(f8, 7, wy8);
                 const CaveThresholds<false, KIND> thresholds;
                 cx::for_run([&](auto j) {
-                    classify_cave<false, KIND>(word, thresholds, rule.below1, C8.field(), KIND == GNOME_MINES ? 0u : F8.field(), draw(j));
+                    constexpr float wx8 = cx::weight8(j);
+                    classify_cave<false, KIND>(word, thresholds, rule.below1, C8.at(wx8), KIND == GNOME_MINES ? 0.0f : F8.at(wx8), draw(j));
                     cx::settle(word);
                     if (j == 4) second = word;
-                    C8.advance(cx::step8(j)); F8.advance(cx::step8(j));
                 });
             }
         };
@@ -508,7 +489,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         }
     }
     }
-    if (CAN_PERLIN) cx::nearest_rounding(episode);
+    cx::nearest_rounding(episode);
     barrier();
 }
 

@@ -136,3 +136,14 @@ def test_every_kernel_the_full_game_launches_is_checked_against_the_device():
     check = re.search(r"static bool kernels_fit\b.*?\n}\n", host, re.S).group(0)
     asked, launched = _kernel_instances(check), _kernel_instances(host.replace(check, ""))
     assert len(launched) > 20 and launched <= asked, sorted(launched - asked)
+
+
+def test_noise_fields_equal_the_oracle(tmp_path):
+    """The generators' fields in floating point rounded down (csrc/noise_fields.hpp) against the oracle's integers."""
+    exe, objs = str(tmp_path / "noise_fields_test"), []
+    for name in ("philox", "classic"):
+        objs.append(str(tmp_path / f"{name}.o"))
+        _run(["gcc", "-O2", "-std=c11", "-ffp-contract=off", "-c", "-o", objs[-1], os.path.join(ROOT, "oracle", name + ".c")])
+    _run(["g++", "-O2", "-march=native", "-frounding-math", "-ffp-contract=off", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-o", exe,
+          os.path.join(NATIVE, "noise_fields_test.cpp")] + objs + ["-lm"])
+    assert "noise_fields_test: ok" in _run([exe])
