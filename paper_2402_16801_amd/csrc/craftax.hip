@@ -163,15 +163,20 @@ constexpr int step_blocks_per_cu(bool perlin) { return perlin ? 4 : 5; }   // by
 // end together then occupy the regeneration blocks of all sub-lists instead of those of one or two (16 environments,
 // episodes of 2 steps 27.1 -> 7.1 us, 64: 11.0 -> 7.4; ordinary episodes the same).
 constexpr int envs_per_list_turn(int lanes) { return lanes == 16 ? 1 : BLOCK / lanes; }
-template <int G, int OBS_MODE, bool PERLIN>
+// DRAW (pixels, 16 lanes): a block holds one environment, whose 16 lanes step it, and all its threads then draw
+// the picture, from the record in LDS: one launch instead of two, and the pictures of some blocks hide the steps of others.
+template <int G, int OBS_MODE, bool PERLIN, bool DRAW = false>
 __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                    const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                    uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                    uint8_t* __restrict__ done, Lists ls, Params p, int step_blocks)
 {
-    constexpr int EPB = Grp<G>::EPB;
+    static_assert(!DRAW || (G == 16 && OBS_MODE == CRAFTAX_OBS_PIXELS_F32), "pictures are drawn behind a step with 16 lanes");
+    constexpr int EPB = DRAW ? 1 : Grp<G>::EPB;
     using LY = StepLayout;
-    __shared__ uint32_t s_env[EPB * LY::STRIDE];
+    constexpr int ENV_AT = DRAW ? PIX_STRIP_FLOATS : 0;     // the environments' areas, behind the strips of the picture's pixels
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENV_AT + EPB * LY::STRIDE];
+    __shared__ int s_tile[DRAW ? PIX_CELLS : 1], s_ent[DRAW ? PIX_CELLS : 1];
     __shared__ int s_ndone;
     __shared__ uint32_t s_base;
     __shared__ uint4 s_list[EPB];
@@ -179,8 +184,8 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
     const bool regen_role = (int)blockIdx.x >= step_blocks;
     const uint32_t rb = blockIdx.x - (uint32_t)step_blocks, nrb = gridDim.x - (uint32_t)step_blocks;
     const int g = tid / G, l = tid % G;
-    const int env = blockIdx.x * EPB + g;
-    const bool active = !regen_role && env < p.n;
+    const int env = blockIdx.x * EPB + (DRAW ? 0 : g);
+    const bool active = !regen_role && env < p.n && (!DRAW || tid < G);
     // the record and the action are asked for before the launch bookkeeping, which waits for a
     // counter of its own: the two round trips then overlap
     RecordRegs<G> fetched;
@@ -206,7 +211,7 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
     // SHARE: every block reads the length of one sub-list of the consumed list, a regeneration block
     // its own, a step block the one it appends to (see regeneration_share)
     constexpr bool SHARE = G == 4;
-    static_assert(EPB * LY::STRIDE >= lattice_words<PERLIN>, "the environments' area, empty until the records are parked, doubles as lattice scratch");
+    static_assert(ENV_AT + EPB * LY::STRIDE >= lattice_words<PERLIN>, "the environments' area, empty until the records are parked, doubles as lattice scratch");
     if (!EAGER && tid == 0) s_ndone = 0;
     const la::Ticket ticket = la::enter_launch(ls, SHARE || regen_role, regen_role ? rb : blockIdx.x);   // holds a block barrier
     const uint32_t seq = ticket.seq, regen_count = ticket.regen_count;
@@ -228,7 +233,7 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
     bool queued = false;                 // EAGER: this group's episode ended; its place on the list is on its way
     uint32_t list_at = 0u;
     uint4 entry = make_uint4(0u, 0u, 0u, 0u);
-    uint32_t* e = s_env + g * LY::STRIDE;
+    uint32_t* e = s_env + ENV_AT + (DRAW ? 0 : g) * LY::STRIDE;
     constexpr bool kSymbolic = OBS_MODE != CRAFTAX_OBS_PIXELS_F32;
     constexpr bool kBytes = OBS_MODE == CRAFTAX_OBS_SYM_U8_I8 || OBS_MODE == CRAFTAX_OBS_SYM_U8_F32;
     bool staged = false;
@@ -290,14 +295,23 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
     if (kBytes && obs != nullptr) {
         if (l == 0) e[LY::FLAG] = staged ? 1u : 0u;
         group_sync();
-        const int first = (tid & ~63) / G;                         // first environment of this wave within the block
-        flush_wave_observations<G, OBS_MODE, LY>(s_env + first * LY::STRIDE,
-                                             obs + (size_t)(blockIdx.x * EPB + first) * obs_stride(OBS_MODE));
+        const int first = __builtin_amdgcn_readfirstlane((tid & ~63) / G);   // first environment of this wave within the block
+        const uint32_t* wave_env = s_env + first * LY::STRIDE;
+        uint8_t* wave_obs = obs + (size_t)(blockIdx.x * EPB + first) * obs_stride(OBS_MODE);
+        flush_wave_observations<G, OBS_MODE, LY>(wave_env, wave_obs);
     }
     if (EAGER) {
         // an entry at a time, the place claimed before the rendering: no wavefront waits for the others of its block
         if (queued) la::commit_entry(ls, seq, (uint32_t)env, list_at, entry);
         leave();
+        if (DRAW) {
+            __syncthreads();                // the record is in LDS, the step's changes to the map have left for memory
+            const uint8_t* map = maps + map_offset((uint32_t)env, e[LDS_REC + RW_EPISODE]);
+            uint8_t* out = obs + (size_t)env * OBS_STRIDE_PIXELS;
+            float* strip = reinterpret_cast<float*>(s_env);
+            if (picture_kept(p.n, blockIdx.x)) render_pixels_block<Keep::THROUGH>(e + LDS_REC, map, luts, out, s_tile, s_ent, strip);
+            else render_pixels_block<Keep::STREAM>(e + LDS_REC, map, luts, out, s_tile, s_ent, strip);
+        }
         return;
     }
     __syncthreads();
@@ -605,13 +619,13 @@ __global__ __launch_bounds__(BLOCK) void k_pixels(const uint4* __restrict__ recs
                                                   const Luts* __restrict__ luts, uint8_t* __restrict__ obs, Params p)
 {
     __shared__ uint32_t s_rec[REC_DWORDS];
-    __shared__ int s_tile[81], s_ent[81];
-    __shared__ __attribute__((aligned(16))) float s_strip[(BLOCK / 64) * PIX_WAVE_FLOATS];
+    __shared__ int s_tile[PIX_CELLS], s_ent[PIX_CELLS];
+    __shared__ __attribute__((aligned(16))) float s_strip[PIX_STRIP_FLOATS];
     const int env = blockIdx.x;
     if (threadIdx.x < REC_DWORDS) s_rec[threadIdx.x] = reinterpret_cast<const uint32_t*>(recs + (size_t)env * 8)[threadIdx.x];
     __syncthreads();
-    render_pixels_block(s_rec, maps + map_offset((uint32_t)env, s_rec[RW_EPISODE]), luts, obs + (size_t)env * OBS_STRIDE_PIXELS,
-                        s_tile, s_ent, s_strip);
+    render_pixels_block<Keep::STREAM>(s_rec, maps + map_offset((uint32_t)env, s_rec[RW_EPISODE]), luts, obs + (size_t)env * OBS_STRIDE_PIXELS,
+                                      s_tile, s_ent, s_strip);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1110,19 +1124,27 @@ static void launch_step(int G, int n, hipStream_t st, const Ptrs& q, const int32
     const int regen = ((2 * n < most ? 2 * n : most) + 2 * NSUB - 1) / (2 * NSUB) * (2 * NSUB);   // a multiple of twice the sub-list count
     const int sb = (n + 256 / G - 1) / (256 / G);
     const bool perlin = p.worldgen == CRAFTAX_WORLDGEN_PERLIN;
+    // with optimistic resets every finished episode is served after the step, because its world depends on who else
+    // finished, and with an episode cap of 1 every episode has finished; else the list is nearly always empty, and it is
+    // served only where an episode can have ended before its spare world existed: see note_edit
+    const bool all = p.reset_mode == CRAFTAX_RESET_POOL || p.max_episode_steps == 1u;
+    if (OBS_MODE == CRAFTAX_OBS_PIXELS_F32 && o != nullptr && !all && !serve_slow) {
+        // step and picture in one launch, whatever the lanes of a step without
+        const int beside = ((2 * n < REGEN_BLOCKS ? 2 * n : REGEN_BLOCKS) + 2 * NSUB - 1) / (2 * NSUB) * (2 * NSUB);
+        if (perlin) hipLaunchKernelGGL((k_step<16, CRAFTAX_OBS_PIXELS_F32, true, true>), dim3(n + beside), block, 0, st, q.recs, q.maps, q.luts, actions, o, reward, done, q.ls, p, n);
+        else hipLaunchKernelGGL((k_step<16, CRAFTAX_OBS_PIXELS_F32, false, true>), dim3(n + beside), block, 0, st, q.recs, q.maps, q.luts, actions, o, reward, done, q.ls, p, n);
+        return;
+    }
 #define CRAFTAX_LAUNCH_STEP(LANES, NOISE) \
     hipLaunchKernelGGL((k_step<LANES, OBS_MODE, NOISE>), dim3(sb + regen), block, 0, st, q.recs, q.maps, q.luts, actions, o, reward, done, q.ls, p, sb)
     if (G == 4) { if (perlin) CRAFTAX_LAUNCH_STEP(4, true); else CRAFTAX_LAUNCH_STEP(4, false); }
     else if (G == 8) { if (perlin) CRAFTAX_LAUNCH_STEP(8, true); else CRAFTAX_LAUNCH_STEP(8, false); }
     else { if (perlin) CRAFTAX_LAUNCH_STEP(16, true); else CRAFTAX_LAUNCH_STEP(16, false); }
 #undef CRAFTAX_LAUNCH_STEP
-    // with optimistic resets every finished episode is served after the step, because its world depends on who else
-    // finished, and with an episode cap of 1 every episode has finished; else the list is nearly always empty, and it is
-    // served only where an episode can have ended before its spare world existed: see note_edit
-    const bool all = p.reset_mode == CRAFTAX_RESET_POOL || p.max_episode_steps == 1u;
     const int most_served = all ? FULL_LIST_GRID : RESET_GRID;
     if (all || serve_slow)
         hipLaunchKernelGGL((k_reset_list<OBS_MODE>), dim3(n < most_served ? n : most_served), dim3(WG_THREADS), 0, st, q.recs, q.maps, q.luts, o, done, q.ls, p, envs_per_list_turn(G));
+    if (OBS_MODE == CRAFTAX_OBS_PIXELS_F32 && o != nullptr) hipLaunchKernelGGL(k_pixels, dim3(n), block, 0, st, q.recs, q.maps, q.luts, o, p);
 }
 
 template <int OBS_MODE>
@@ -1261,7 +1283,8 @@ static int check_kernels(const craftax_config* cfg, int lanes, std::string* err)
     case CRAFTAX_OBS_SYM_U8_I8: CRAFTAX_CHECK_MODE(0); CRAFTAX_CHECK_ROLLOUT(0); break;
     case CRAFTAX_OBS_SYM_U8_F32: CRAFTAX_CHECK_MODE(1); CRAFTAX_CHECK_ROLLOUT(1); break;
     case CRAFTAX_OBS_SYM_F32: CRAFTAX_CHECK_MODE(2); CRAFTAX_CHECK_ROLLOUT(2); break;
-    default: CRAFTAX_CHECK_MODE(3); ok = ok && fits("k_pixels", (const void*)k_pixels, BLOCK); break;
+    default: CRAFTAX_CHECK_MODE(3); ok = ok && fits("k_pixels", (const void*)k_pixels, BLOCK) &&
+        (perlin ? fits("k_step with pictures", (const void*)k_step<16, 3, true, true>, BLOCK) : fits("k_step with pictures", (const void*)k_step<16, 3, false, true>, BLOCK)); break;
     }
 #undef CRAFTAX_CHECK_MODE
 #undef CRAFTAX_CHECK_ROLLOUT
@@ -1403,10 +1426,7 @@ int craftax_step(void* state, const int32_t* actions, void* obs, float* reward, 
     case CRAFTAX_OBS_SYM_U8_I8: launch_step<0>(G, n, st, q, actions, o, reward, done, p, s.serve_slow); break;
     case CRAFTAX_OBS_SYM_U8_F32: launch_step<1>(G, n, st, q, actions, o, reward, done, p, s.serve_slow); break;
     case CRAFTAX_OBS_SYM_F32: launch_step<2>(G, n, st, q, actions, o, reward, done, p, s.serve_slow); break;
-    default:
-        launch_step<3>(G, n, st, q, actions, o, reward, done, p, s.serve_slow);
-        if (o) hipLaunchKernelGGL(k_pixels, dim3(n), dim3(BLOCK), 0, st, q.recs, q.maps, q.luts, o, p);
-        break;
+    default: launch_step<3>(G, n, st, q, actions, o, reward, done, p, s.serve_slow); break;
     }
     if (s.serve_slow) update_state(state, true, false);
     return check_launch("craftax_step");

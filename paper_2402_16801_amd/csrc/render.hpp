@@ -20,6 +20,22 @@ __host__ __device__ constexpr int obs_stride(int mode)
     return mode == 0 ? OBS_STRIDE_U8_I8 : mode == 1 ? OBS_STRIDE_U8_F32 : mode == 2 ? OBS_STRIDE_F32 : OBS_STRIDE_PIXELS;
 }
 
+// How stores of observations go through the caches (measured on one state stepped over and over, on three in turn, and
+// on one whose observation is read behind every step):
+//  PLAIN    left in the L2, which holds 32 MB in all and is written back at the end of the launch;
+//  THROUGH  written through to the last-level cache (256 MB) as they come, so that the end of the launch waits for
+//           nothing and a reader still finds them there;
+//  STREAM   passed on without a place in either.
+enum class Keep { PLAIN, THROUGH, STREAM };
+typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
+// Writes a piece at byte `at` behind base, which is the same for the whole wavefront; limit: bytes that may be written from there on
+// (the hardware drops what lies beyond).
+__device__ __forceinline__ void store_through(uint8_t* base, int limit, int at, piece_t v)
+{
+    constexpr int SC1 = 16;      // cache policy bit of a buffer store: scope of the whole system
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, limit, 0x00027000), at, 0, SC1);
+}
+
 // four bits -> four 0/1 bytes (bit i -> byte i)
 __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x00204081u) & 0x01010101u; }
 
@@ -49,12 +65,10 @@ __device__ __forceinline__ uint4 staged_chunk(const uint32_t* e, int c)
 
 // Writes the staged observations of all environments of the calling wave (byte layouts).
 // Lanes regroup into runs of max(G, 8): a run writes 128 or 256 contiguous, line-aligned bytes
-// of one environment per store instruction, i.e. whole cache lines.  Plain stores: measured
-// against streaming (non-temporal) ones they are 5 % faster here, the observation buffer being
-// rewritten every step.  With G = 4 a run serves two environments in
-// turn.  wave_env: LDS area of the wave's first environment; wave_obs: its observation.
-template <int G, int OBS_MODE, class LY = KeepLayout>
-__device__ __forceinline__ void flush_wave_observations(uint32_t* wave_env, uint8_t* __restrict__ wave_obs)
+// of one environment per store instruction, i.e. whole cache lines.  With G = 4 a run serves two environments in
+// turn.  wave_env: LDS area of the wave's first environment; wave_obs: its observation, the same for the whole wavefront.
+template <int G, int OBS_MODE, class LY = KeepLayout, Keep KEEP = Keep::PLAIN>
+__device__ __forceinline__ void flush_wave_observations(const uint32_t* wave_env, uint8_t* __restrict__ wave_obs)
 {
     constexpr int RUN = G < 8 ? 8 : G, PASSES = RUN / G, STRIDE = obs_stride(OBS_MODE), NCHUNK = STRIDE / 16;
     const int w = threadIdx.x & 63, run = w / RUN, j = w % RUN;
@@ -69,7 +83,9 @@ __device__ __forceinline__ void flush_wave_observations(uint32_t* wave_env, uint
             const int c = it * RUN + j;
             if (c >= NCHUNK) break;
             const uint4 v = staged_chunk<OBS_MODE, LY>(e, c);
-            *reinterpret_cast<uint4*>(out + 4 * c) = v;
+            if constexpr (KEEP == Keep::THROUGH) store_through(wave_obs, 64 / G * STRIDE, ei * STRIDE + 16 * c, piece_t{v.x, v.y, v.z, v.w});
+            else if constexpr (KEEP == Keep::STREAM) __builtin_nontemporal_store(piece_t{v.x, v.y, v.z, v.w}, reinterpret_cast<piece_t*>(out + 4 * c));
+            else *reinterpret_cast<uint4*>(out + 4 * c) = v;
         }
     }
 }
@@ -200,6 +216,24 @@ __device__ __forceinline__ void render_symbolic(int l, uint32_t* e, int mvx, int
     group_sync();   // the staging area may be reused
 }
 
+// Where a buffer is larger than its share of the last-level cache: which blocks of a launch write through while the others stream.
+// Consecutive blocks go round the eight XCDs, each with an L2 of its own, so every fourth is two XCDs whose blocks all write
+// through.  Both ways out of the L2 are then in use at once, which is faster than either alone; with the same share spread over
+// all XCDs it is not (every third block of a step of 65,536: 31.4 us, 41.3 on three states in turn).
+__device__ inline bool written_through(uint32_t block) { return (block & 3u) == 0u; }
+// Pictures of n environments that are written through (see Keep) or, above, by every fourth block.  Fewer do not fill the L2 of the chip
+// and are as fast streamed.  Step with pictures, streamed / written through / every fourth block, us, one state | three in turn | one that is read:
+//     400 (19 MB) 12.1 / 12.9 | 12.4 / 13.1 | 23.3 / 23.5     700 (33 MB) 14.6 / 14.2 | 14.5 / 14.3 | 29.3 / 29.8
+//   1,024 (49 MB) 18.0 / 16.0 / 16.3 | 17.9 / 16.2 / 16.5 | 37.0 / 35.2 / 36.3     1,700 (81 MB) 27.1 / 24.3 | 27.5 / 25.0 | 53.0 / 50.5
+//   2,048 (98 MB) 28.9 / 26.9 / 26.3 | 29.2 / 30.3 / 26.8 | 61.1 / 58.7 / 60.6   4,096 (195 MB) 50.0 / 43.3 / 43.0 | 50.0 / 86.6 / 44.3 | 118 / 141 / 120
+//   8,000 (381 MB) streamed 92.0, every fourth block 94.4 on three in turn
+constexpr long long PICTURES_KEPT_FROM = 32ll << 20, PICTURES_KEPT_TO = 85ll << 20, PICTURES_SPLIT_TO = 256ll << 20;
+__device__ inline bool picture_kept(int n, uint32_t block)
+{
+    const long long bytes = (long long)n * OBS_STRIDE_PIXELS;
+    return bytes > PICTURES_KEPT_FROM && (bytes <= PICTURES_KEPT_TO || (bytes <= PICTURES_SPLIT_TO && written_through(block)));
+}
+
 // Pixel observation of one environment by a whole block (256 threads): 63x63x3 floats.
 // Each texel is one table value times the daylight value (a single IEEE multiply).
 // The picture is walked in linear pixel order, 1024 pixels per block iteration, 256 per wave:
@@ -212,8 +246,12 @@ constexpr int PIX_GROUP = 1024, PIX_WAVE = 256, PIX_WAVE_FLOATS = PIX_WAVE * 3;
 constexpr int PIX_FULL_GROUPS = OBS_STRIDE_PIXELS / 12 / PIX_GROUP;   // 3 whole groups, then a partial one
 static_assert((PIX_FULL_GROUPS + 1) * PIX_GROUP * 12 >= OBS_STRIDE_PIXELS && PIX_FULL_GROUPS * PIX_GROUP <= PIX_SIDE * PIX_SIDE, "pixel groups");
 
-// s_tile, s_ent: 81 ints each; s_strip: 4 * 768 floats, 16-byte aligned.  Writes the whole stride
+constexpr int PIX_CELLS = PIX_VIEW * PIX_VIEW, PIX_STRIP_FLOATS = PIX_GROUP / PIX_WAVE * PIX_WAVE_FLOATS;
+// s_tile, s_ent: PIX_CELLS ints each; s_strip: PIX_STRIP_FLOATS floats, 16-byte aligned.  Writes the whole stride
 // (the padding after the picture as zero).
+// KEEP: see picture_kept.  One kind of store in the loop: with a choice between two the compiler no longer knows how many
+// operations are under way and waits for all of them (1,024 pictures 16.3 -> 16.8 us, 4,096 50.0 -> 52.4).
+template <Keep KEEP>
 __device__ __forceinline__ void render_pixels_block(const uint32_t* __restrict__ rec, const uint8_t* __restrict__ map,
                                                     const Luts* __restrict__ luts, uint8_t* __restrict__ obs_out,
                                                     int* s_tile, int* s_ent, float* s_strip)
@@ -237,7 +275,6 @@ __device__ __forceinline__ void render_pixels_block(const uint32_t* __restrict__
     }
     __syncthreads();
     const float light = luts->daylight[rec[RW_VIT] >> 16];
-    float4* out = reinterpret_cast<float4*>(obs_out);
     const int w = tid >> 6, l = tid & 63;
     float* strip = s_strip + w * PIX_WAVE_FLOATS;
     float v[4][3], scale[4];
@@ -278,12 +315,10 @@ __device__ __forceinline__ void render_pixels_block(const uint32_t* __restrict__
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const int q = (g * PIX_GROUP + w * PIX_WAVE) * 3 / 4 + k * 64 + l;
-            if (!guarded || q < OBS_STRIDE_PIXELS / 16) {
-                __builtin_nontemporal_store(piece[k].x, &out[q].x);
-                __builtin_nontemporal_store(piece[k].y, &out[q].y);
-                __builtin_nontemporal_store(piece[k].z, &out[q].z);
-                __builtin_nontemporal_store(piece[k].w, &out[q].w);
-            }
+            if (guarded && q >= OBS_STRIDE_PIXELS / 16) continue;
+            const piece_t v = __builtin_bit_cast(piece_t, piece[k]);
+            if constexpr (KEEP == Keep::THROUGH) store_through(obs_out, OBS_STRIDE_PIXELS, 16 * q, v);
+            else __builtin_nontemporal_store(v, reinterpret_cast<piece_t*>(obs_out + 16 * q));
         }
     };
     fetch(0);

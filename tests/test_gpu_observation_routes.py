@@ -1,0 +1,46 @@
+"""How observations reach memory depends on the batch: pictures are drawn by the launch that steps, and stores are
+left in the caches, written through or streamed.  Every route against the kernel that only observes (which the parity
+tests compare with the oracle), and the rules against a run without observations."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2402_16801_amd import binding as cx, synth  # noqa: E402
+
+
+def _run(n, steps, variant, **kw):
+    cfg = cx.default_config(variant, **kw)
+    sim, blind = cx.Craftax(n, cfg), cx.Craftax(n, cfg)
+    seeds = synth.seeds_for(n)
+    sim.reset(seeds)
+    blind.reset(seeds)
+    sim.obs.fill_(0x5A if sim.obs.dtype == torch.uint8 else 7.0)
+    seen = torch.empty_like(sim.obs)
+    actions = torch.empty((steps, n), dtype=torch.int32, device=sim.device)
+    cx.craftax_synth_actions(actions, n, 0, steps, 3, 1 + 2 * (variant == cx.VARIANT_CRAFTAX), sim.stream)
+    reward, done = torch.empty(n, device=sim.device), torch.empty(n, dtype=torch.uint8, device=sim.device)
+    ended = 0
+    for t in range(steps):
+        obs, r, d = sim.step(actions[t])
+        cx.craftax_observe(sim.state, seen, n, sim.stream)
+        assert torch.equal(obs.view(torch.uint8), seen.view(torch.uint8)), f"observation at step {t}"
+        cx.craftax_step(blind.state, actions[t], None, reward, done, n, sim.stream)
+        assert torch.equal(r, reward) and torch.equal(d, done), f"reward or done at step {t}"
+        ended += int(d.sum())
+        if t == steps // 2:                                    # an edit: the next step serves episodes without a spare world
+            for s in (sim, blind):
+                cx.craftax_mutate_swap(s.state, 0, n, 7, 0, False, None, s.stream)
+    assert sim.export_envs().tobytes() == blind.export_envs().tobytes()
+    return ended
+
+
+# streamed, written through from 32 MiB on (705 pictures), by every fourth block from 85 MiB on (1,872), streamed again
+@pytest.mark.parametrize("n", [1, 17, 704, 705, 1871, 1872, 5700])
+def test_classic_pictures_of_a_step(n):
+    assert _run(n, 14, cx.VARIANT_CLASSIC, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=5) > 0
+
+
+def test_classic_pictures_of_a_perlin_step_with_four_lanes():
+    assert _run(33, 12, cx.VARIANT_CLASSIC, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=4, worldgen=cx.WORLDGEN_PERLIN, group_lanes=4) > 0
