@@ -44,3 +44,9 @@ def test_classic_pictures_of_a_step(n):
 
 def test_classic_pictures_of_a_perlin_step_with_four_lanes():
     assert _run(33, 12, cx.VARIANT_CLASSIC, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=4, worldgen=cx.WORLDGEN_PERLIN, group_lanes=4) > 0
+
+
+@pytest.mark.parametrize("mode", [cx.OBS_SYM_U8_I8, cx.OBS_SYM_U8_F32])
+@pytest.mark.parametrize("n", [3, 1499, 1500, 1501, 12289, 24577])
+def test_classic_byte_observations_of_a_step(n, mode):
+    assert _run(n, 10, cx.VARIANT_CLASSIC, obs_mode=mode, max_episode_steps=4) > 0
