@@ -272,7 +272,8 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
             if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
             if (obs != nullptr) {
                 aux.day = o.done ? day_fresh : day_next;
-                render_env<F32, GW>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux);
+                render_env<F32, GW>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux,
+                                    F32 && floats_written_through(p.n, blockIdx.x));
             }
         }
         if (queued && l == 0) la::commit_entry(ls, seq, step_block, list_at, make_uint4((uint32_t)env, lo, hi, ep + 2u));

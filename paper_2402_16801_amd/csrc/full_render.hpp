@@ -138,10 +138,12 @@ constexpr bool staged_floats_are_exact()
 }
 static_assert(staged_floats_are_exact(), "light levels through staged bytes");
 static_assert(STAGE_BYTES % 1024 == 0 && 64 * NCHAN >= STAGE_BYTES && NCELL <= 128, "the second cell of a lane lies in the second part");
+// through (floats): whether the observation is written through to the last-level cache (see cx::Keep) or streamed, as bytes are;
+// the same for the wavefront.
 template <bool F32>
 __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const int wx0, const int wy0, const int m_alive, const int m_x,
                                               const int m_y, const int m_type, const Luts* __restrict__ luts, uint8_t* __restrict__ out,
-                                              const RenderAux<64>* aux)
+                                              const RenderAux<64>* aux, const bool through)
 {
     const uint32_t* rec = e + L_REC;
     const uint8_t* wb = reinterpret_cast<const uint8_t*>(e + L_WB);
@@ -194,8 +196,8 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
             }
         }
     };
+    using cx::piece_t;
     if (!F32) {
-        typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
         piece_t* dst = reinterpret_cast<piece_t*>(out) + l;
         const piece_t* src = reinterpret_cast<const piece_t*>(stage) + l;
         constexpr int PIECES = STRIDE_U8 / 16, HEAD = STAGE_BYTES / 16;
@@ -211,18 +213,31 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
         for (int k = 0; k < (PIECES - HEAD + 63) / 64; ++k)
             if (64 * k + 64 <= PIECES - HEAD || l < PIECES - HEAD - 64 * k) __builtin_nontemporal_store(src[64 * k], dst + HEAD + 64 * k);
     } else {
-        float4* dst = reinterpret_cast<float4*>(out) + l;
         const uint32_t* src = reinterpret_cast<const uint32_t*>(stage) + l;
-        auto floats = [](uint32_t four) {
-            return make_float4((float)(four & 0xFFu) * F32_UNIT, (float)((four >> 8) & 0xFFu) * F32_UNIT, (float)((four >> 16) & 0xFFu) * F32_UNIT, (float)(four >> 24) * F32_UNIT);
+        auto floats = [&](int k) {
+            const uint32_t four = src[64 * k];
+            return __builtin_bit_cast(piece_t, make_float4((float)(four & 0xFFu) * F32_UNIT, (float)((four >> 8) & 0xFFu) * F32_UNIT, (float)((four >> 16) & 0xFFu) * F32_UNIT,
+                                                           (float)(four >> 24) * F32_UNIT));
+        };
+        // 16-byte pieces `first`, first + 64, ..., one per lane and turn, in a loop for each kind of store
+        auto store = [&](const int first, auto turns, auto&& piece) {
+            constexpr int TURNS = decltype(turns)::value;
+            if (through) {
+                const uintptr_t at = reinterpret_cast<uintptr_t>(out);
+                uint8_t* base = reinterpret_cast<uint8_t*>(((uintptr_t)uniu((uint32_t)(at >> 32)) << 32) | uniu((uint32_t)at));
+#pragma unroll 5
+                for (int k = 0; k < TURNS; ++k) cx::store_through(base, STRIDE_F32, 16 * (first + 64 * k + l), piece(k));
+            } else {
+#pragma unroll 5
+                for (int k = 0; k < TURNS; ++k) __builtin_nontemporal_store(piece(k), reinterpret_cast<piece_t*>(out) + first + 64 * k + l);
+            }
         };
         // pieces of four floats; from TAIL on they hold scalars (after one last light level)
         constexpr int PIECES = STRIDE_F32 / 16, HEAD = STAGE_BYTES / 4, TAIL = CELL_BYTES / 4, TAIL_AT = 3328;
         static_assert(TAIL_AT % 16 == 0 && TAIL_AT >= STRIDE_U8 - STAGE_BYTES && TAIL_AT + 16 * (PIECES - TAIL) <= STAGE_BYTES && CELL_BYTES == 4 * TAIL + 1, "tail of the float layout");
         fill(0);
         wave_sync();
-#pragma unroll 5
-        for (int k = 0; k < HEAD / 64; ++k) dst[64 * k] = floats(src[64 * k]);
+        store(0, std::integral_constant<int, HEAD / 64>(), floats);
         wave_sync();
         fill(1);
         float* tail = reinterpret_cast<float*>(stage + TAIL_AT);
@@ -231,24 +246,31 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
         if (l < 4 * (PIECES - TAIL) - 65) tail[65 + l] = 0.0f;
         if (l == NCELL - 1 - 64) tail[0] = (float)(LIGHT * (il[1] >> 3)) * F32_UNIT;
         wave_sync();
-#pragma unroll 4
-        for (int k = 0; k < (TAIL - HEAD) / 64; ++k) dst[HEAD + 64 * k] = floats(src[64 * k]);
-        constexpr int LEFT = (TAIL - HEAD) % 64, LAST = TAIL - LEFT;
-        if (l < LEFT) dst[LAST] = floats(src[LAST - HEAD]);
-        if (l < PIECES - TAIL) dst[TAIL] = reinterpret_cast<const float4*>(tail)[l];
+        constexpr int TURNS = (TAIL - HEAD) / 64, LEFT = (TAIL - HEAD) % 64;
+        store(HEAD, std::integral_constant<int, TURNS>(), floats);
+        if (l < LEFT) store(HEAD + 64 * TURNS, std::integral_constant<int, 1>(), [&](int) { return floats(TURNS); });
+        if (l < PIECES - TAIL) store(TAIL, std::integral_constant<int, 1>(), [&](int) { return reinterpret_cast<const piece_t*>(tail)[l]; });
     }
 }
+
+// Whether block `block` of a step of n environments writes its float observations through: up to CACHE_SHARE all of them do, beyond every
+// fourth block (us, plain / streamed / through / through by every fourth block, three states in turn | one that is read): 500 12.4 / 11.4 / 10.8 |
+// 21.5 / 21.5 / 21.8, 2,000 17.5 / 19.2 / 16.1 | 38.8 / 41.6 / 39.4, 4,096 35.6 / 31.8 / 34.8 / 26.6 | 67.5 / 74.1 / 68.1 / 69.2, 6,000 55.5 / 45.7 /
+// 54.5 / 43.8 | 120 / 124 / 122 / 117, 8,192 68.3 / 56.2 / 67.5 / 62.1 | 163 / 160 / 166 / 155.  Rollouts write all of them through (plain / streamed /
+// through: 256 514 / 512 / 499, 1,000 558 / 541 / 532, 4,096 1,233 / 1,699 / 1,163).  Bytes are streamed: through, 1,024 environments take 9.8
+// instead of 10.2 us and 4,096 15.2 instead of 14.6, 16,384 55.6 instead of 42.7; by a choice at run time, 4,096 lose 1 %.
+__device__ inline bool floats_written_through(int n, uint32_t block) { return (long long)n * STRIDE_F32 <= cx::CACHE_SHARE || cx::written_through(block); }
 
 // The same by GW < 64 lanes of a wavefront, whose areas have no room for staged bytes (L_ENV_DWORDS): the
 // one-hot bytes are staged as single bits (a few LDS atomics per cell) next to a light level per cell;
 // every lane then expands 16 bits at a time into one 16-byte piece of the output.
-// GW: lanes that render this environment (see Lanes); l: the calling lane's number among them.
+// GW: lanes that render this environment (see Lanes); l: the calling lane's number among them.  through: see render_staged.
 template <bool F32, int GW = 64>
 __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int wx0, const int wy0, const int m_alive, const int m_x,
                                   const int m_y, const int m_type, const Luts* __restrict__ luts, uint8_t* __restrict__ out,
-                                  const RenderAux<GW>* aux = nullptr)
+                                  const RenderAux<GW>* aux = nullptr, const bool through = true)
 {
-    if constexpr (GW == 64) { render_staged<F32>(l, e, wx0, wy0, m_alive, m_x, m_y, m_type, luts, out, aux); return; } else {
+    if constexpr (GW == 64) { render_staged<F32>(l, e, wx0, wy0, m_alive, m_x, m_y, m_type, luts, out, aux, through); return; } else {
     using G = Lanes<GW>;
     const uint32_t* rec = e + L_REC;
     const uint8_t* wb = reinterpret_cast<const uint8_t*>(e + L_WB);

@@ -20,22 +20,6 @@ __host__ __device__ constexpr int obs_stride(int mode)
     return mode == 0 ? OBS_STRIDE_U8_I8 : mode == 1 ? OBS_STRIDE_U8_F32 : mode == 2 ? OBS_STRIDE_F32 : OBS_STRIDE_PIXELS;
 }
 
-// How stores of observations go through the caches (measured on one state stepped over and over, on three in turn, and
-// on one whose observation is read behind every step):
-//  PLAIN    left in the L2, which holds 32 MB in all and is written back at the end of the launch;
-//  THROUGH  written through to the last-level cache (256 MB) as they come, so that the end of the launch waits for
-//           nothing and a reader still finds them there;
-//  STREAM   passed on without a place in either.
-enum class Keep { PLAIN, THROUGH, STREAM };
-typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
-// Writes a piece at byte `at` behind base, which is the same for the whole wavefront; limit: bytes that may be written from there on
-// (the hardware drops what lies beyond).
-__device__ __forceinline__ void store_through(uint8_t* base, int limit, int at, piece_t v)
-{
-    constexpr int SC1 = 16;      // cache policy bit of a buffer store: scope of the whole system
-    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, limit, 0x00027000), at, 0, SC1);
-}
-
 // four bits -> four 0/1 bytes (bit i -> byte i)
 __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x00204081u) & 0x01010101u; }
 
@@ -216,22 +200,17 @@ __device__ __forceinline__ void render_symbolic(int l, uint32_t* e, int mvx, int
     group_sync();   // the staging area may be reused
 }
 
-// Where a buffer is larger than its share of the last-level cache: which blocks of a launch write through while the others stream.
-// Consecutive blocks go round the eight XCDs, each with an L2 of its own, so every fourth is two XCDs whose blocks all write
-// through.  Both ways out of the L2 are then in use at once, which is faster than either alone; with the same share spread over
-// all XCDs it is not (every third block of a step of 65,536: 31.4 us, 41.3 on three states in turn).
-__device__ inline bool written_through(uint32_t block) { return (block & 3u) == 0u; }
 // Pictures of n environments that are written through (see Keep) or, above, by every fourth block.  Fewer do not fill the L2 of the chip
 // and are as fast streamed.  Step with pictures, streamed / written through / every fourth block, us, one state | three in turn | one that is read:
 //     400 (19 MB) 12.1 / 12.9 | 12.4 / 13.1 | 23.3 / 23.5     700 (33 MB) 14.6 / 14.2 | 14.5 / 14.3 | 29.3 / 29.8
 //   1,024 (49 MB) 18.0 / 16.0 / 16.3 | 17.9 / 16.2 / 16.5 | 37.0 / 35.2 / 36.3     1,700 (81 MB) 27.1 / 24.3 | 27.5 / 25.0 | 53.0 / 50.5
 //   2,048 (98 MB) 28.9 / 26.9 / 26.3 | 29.2 / 30.3 / 26.8 | 61.1 / 58.7 / 60.6   4,096 (195 MB) 50.0 / 43.3 / 43.0 | 50.0 / 86.6 / 44.3 | 118 / 141 / 120
 //   8,000 (381 MB) streamed 92.0, every fourth block 94.4 on three in turn
-constexpr long long PICTURES_KEPT_FROM = 32ll << 20, PICTURES_KEPT_TO = 85ll << 20, PICTURES_SPLIT_TO = 256ll << 20;
+constexpr long long PICTURES_KEPT_FROM = 32ll << 20, PICTURES_SPLIT_TO = 256ll << 20;
 __device__ inline bool picture_kept(int n, uint32_t block)
 {
     const long long bytes = (long long)n * OBS_STRIDE_PIXELS;
-    return bytes > PICTURES_KEPT_FROM && (bytes <= PICTURES_KEPT_TO || (bytes <= PICTURES_SPLIT_TO && written_through(block)));
+    return bytes > PICTURES_KEPT_FROM && (bytes <= CACHE_SHARE || (bytes <= PICTURES_SPLIT_TO && written_through(block)));
 }
 
 // Pixel observation of one environment by a whole block (256 threads): 63x63x3 floats.

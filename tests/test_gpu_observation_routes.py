@@ -50,3 +50,9 @@ def test_classic_pictures_of_a_perlin_step_with_four_lanes():
 @pytest.mark.parametrize("n", [3, 1499, 1500, 1501, 12289, 24577])
 def test_classic_byte_observations_of_a_step(n, mode):
     assert _run(n, 10, cx.VARIANT_CLASSIC, obs_mode=mode, max_episode_steps=4) > 0
+
+
+# floats written through up to 85 MiB in all (2,688 environments), then by every fourth block; bytes streamed
+@pytest.mark.parametrize("n,mode", [(1, cx.OBS_SYM_F32), (5, cx.OBS_SYM_F32), (2688, cx.OBS_SYM_F32), (2689, cx.OBS_SYM_F32), (5, cx.OBS_SYM_U8_F32)])
+def test_craftax_observations_of_a_step(n, mode):
+    assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=mode, max_episode_steps=3) > 0
