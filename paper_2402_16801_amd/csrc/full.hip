@@ -129,21 +129,28 @@ __global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_dr
 // kernel carries none of that code).
 // GW: lanes per environment (see Lanes): 64 = one wavefront per environment, four environments per
 // block; 16 = four environments per wavefront, sixteen per block.
-template <bool F32, bool EAGER, bool PERLIN, int GW>
+// DRAW (pixels): a block holds one environment, which its first wavefront steps, and all its wavefronts then draw the picture, from the
+// record and mobs in LDS.
+template <bool F32, bool EAGER, bool PERLIN, int GW, bool DRAW = false>
 __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                 const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                 uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                 uint8_t* __restrict__ done, Lists ls, Params p, int regen_blocks)
 {
     using G = Lanes<GW>;
-    constexpr int EPB = BLOCK / GW;                          // environments per block
+    static_assert(!DRAW || (GW == 64 && !F32), "pictures are drawn behind a step by a wavefront");
+    constexpr int EPB = DRAW ? 1 : BLOCK / GW;               // environments per block
     constexpr int REC_IT = REC_DWORDS / GW > 0 ? REC_DWORDS / GW : 1;
     constexpr int WIN_IT = (WIN_ROWS * WIN_COLS + GW - 1) / GW;
     static_assert(REC_DWORDS % GW == 0 || GW > REC_DWORDS, "the record is moved in whole turns of the group");
     static_assert(GW >= MOBTAB_DWORDS && GW >= NTAG && GW >= FLOORS + 1, "a group holds a mob table, the tags and the header in one turn");
     constexpr int ENV_DWORDS_LDS = GW == 64 ? L_STAGED_DWORDS : L_ENV_DWORDS;
-    __shared__ __attribute__((aligned(16))) uint32_t s_env[EPB * ENV_DWORDS_LDS];
+    constexpr int REGEN_DWORDS = REGEN_PREFIX_AT + NSUB;
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[EPB * ENV_DWORDS_LDS > REGEN_DWORDS ? EPB * ENV_DWORDS_LDS : REGEN_DWORDS];
     __shared__ float s_lut[LUT_FLOATS];
+    using Picture = std::conditional_t<DRAW, PictureScratch, uint32_t>;
+    __shared__ __attribute__((aligned(16))) Picture s_picture;
+    __shared__ uint32_t s_mob[DRAW ? 64 : 1];
     const int tid = threadIdx.x, w = tid / GW, l = tid % GW;
     if ((int)blockIdx.x < regen_blocks) {
         const la::Ticket ticket = la::enter_launch_queue(ls, s_env + REGEN_PREFIX_AT);
@@ -153,8 +160,8 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         return;
     }
     const uint32_t step_block = blockIdx.x - (uint32_t)regen_blocks;
-    const int env = (int)step_block * EPB + w;
-    const bool active = env < p.n;
+    const int env = (int)step_block * EPB + (DRAW ? 0 : w);
+    const bool active = env < p.n && (!DRAW || w == 0);
     uint32_t* genv = envs + (size_t)(active ? env : 0) * ENV_DWORDS;
     // Everything that depends on the environment's number alone is fetched before the launch
     // bookkeeping, whose own trip to memory then costs nothing extra: the record, the action, and
@@ -176,10 +183,11 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         if (l < NTAG) tag = ls.tags[(size_t)env * NTAG + l];
         if (l < FLOORS + 1) hdr = genv[SPARE_LADDER + l];
     }
+    if constexpr (DRAW) prepare_picture(s_picture, luts);
     const la::Ticket ticket = la::enter_launch(ls, false, 0u);   // holds a block barrier: the conversion tables are in LDS
     const uint32_t seq = ticket.seq;
     if (active) {
-        uint32_t* e = s_env + w * ENV_DWORDS_LDS;
+        uint32_t* e = s_env + (DRAW ? 0 : w) * ENV_DWORDS_LDS;
 #pragma unroll
         for (int it = 0; it < REC_IT; ++it) if (l + GW * it < REC_DWORDS) e[L_REC + l + GW * it] = rec_word[it];
         const int action = G::uni(action_raw);
@@ -270,15 +278,24 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
 #pragma unroll
             for (int it = 0; it < REC_IT; ++it) if (l + GW * it < REC_DWORDS) genv[l + GW * it] = e[L_REC + l + GW * it];
             if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
-            if (obs != nullptr) {
+            if (!DRAW && obs != nullptr) {
                 aux.day = o.done ? day_fresh : day_next;
                 render_env<F32, GW>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux,
                                     F32 && floats_written_through(p.n, blockIdx.x));
             }
         }
+        if (DRAW) s_mob[l] = l < NSLOT ? m.w : 0u;
         if (queued && l == 0) la::commit_entry(ls, seq, step_block, list_at, make_uint4((uint32_t)env, lo, hi, ep + 2u));
     }
     la::leave_launch(ls, ticket);
+    if constexpr (DRAW) {
+        __syncthreads();                    // record and mobs are in LDS, the step's changes to the map have left for memory
+        const uint32_t* rec = s_env + L_REC;
+        const uint8_t* map = maps + map_offset((uint32_t)env, rec[R_EPISODE]);
+        uint8_t* out = obs + (size_t)env * STRIDE_PIXELS;
+        if (cx::picture_kept(p.n, blockIdx.x, STRIDE_PIXELS)) draw_picture<cx::Keep::THROUGH>(s_picture, rec, s_mob, map, luts, out);
+        else draw_picture<cx::Keep::STREAM>(s_picture, rec, s_mob, map, luts, out);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -947,6 +964,7 @@ static bool kernels_fit(const Fits& fits)
     auto step = [&](const char* name, const void* eager, const void* plain) { return fits(name, eager, BLOCK) && fits(name, plain, BLOCK); };
     auto floors = [&](const char* name, const void* blocks, const void* wavefronts) { return fits(name, blocks, GEN_THREADS) && fits(name, wavefronts, FLOOR_THREADS); };
     return step("kf_step", (const void*)kf_step<F32, true, PERLIN, 64>, (const void*)kf_step<F32, false, PERLIN, 64>) &&
+           step("kf_step with pictures", (const void*)kf_step<false, true, PERLIN, 64, true>, (const void*)kf_step<false, false, PERLIN, 64, true>) &&
            step("kf_step (16 lanes)", (const void*)kf_step<F32, true, PERLIN, 16>, (const void*)kf_step<F32, false, PERLIN, 16>) &&
            fits("kf_rollout", (const void*)kf_rollout<F32, PERLIN>, BLOCK) && fits("kf_reset_list", (const void*)kf_reset_list<F32>, GEN_THREADS) &&
            fits("kf_observe", (const void*)kf_observe<F32>, BLOCK) && fits("kf_pixels", (const void*)kf_pixels, BLOCK) &&
@@ -1041,7 +1059,14 @@ int step(void* state, const craftax_config* cfg, int n, const int32_t* actions, 
     const bool eager = n <= EAGER_SPARE_ENVS && pool == 0;
     const int perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN ? 1 : 0;
     if (cfg->obs_mode == CRAFTAX_OBS_PIXELS_F32) {
-        // the step runs without rendering; the picture is drawn from the state it leaves
+        if (o != nullptr && !slow) {
+            // step and picture in one launch, whatever the lanes of a step without
+            auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)(rb + n)), dim3(BLOCK), 0, st, q.envs, q.maps, q.luts, actions, o, reward, done, q.ls, p, rb); };
+            if (perlin) { if (eager) go(kf_step<false, true, true, 64, true>); else go(kf_step<false, false, true, 64, true>); }
+            else { if (eager) go(kf_step<false, true, false, 64, true>); else go(kf_step<false, false, false, 64, true>); }
+            return check_launch("craftax_step", err);
+        }
+        // episodes are served behind the step: it runs without rendering, and the picture is drawn from the state both leave
         launch_step<false>(gw, eager, perlin != 0, grid, st, q, actions, nullptr, reward, done, p, rb);
         if (slow) hipLaunchKernelGGL(kf_reset_list<false>, rgrid, dim3(GEN_THREADS), 0, st, q.envs, q.maps, q.luts, (uint8_t*)nullptr, q.ls, perlin, done, n, pool);
         if (o != nullptr) hipLaunchKernelGGL(kf_pixels, dim3((unsigned)n), dim3(BLOCK), 0, st, q.envs, q.maps, q.luts, o);

@@ -16,6 +16,7 @@
 #pragma once
 
 #include "full_render.hpp"
+#include "render.hpp"
 
 namespace cf {
 
@@ -27,29 +28,35 @@ constexpr int PIX_UNROLL = 4, WAVE_PIXELS = 64 * PIX_UNROLL, GROUP_PIXELS = WAVE
 constexpr int FULL_GROUPS = STRIDE_PIXELS / 12 / GROUP_PIXELS;   // 13 whole groups of 1024 pixels, then a partial one
 static_assert((FULL_GROUPS + 1) * GROUP_PIXELS * 12 >= STRIDE_PIXELS && FULL_GROUPS * GROUP_PIXELS <= PIX_ROWS * PIX_COLS, "pixel groups");
 
-__global__ __launch_bounds__(BLOCK) void kf_pixels(const uint32_t* __restrict__ envs, const uint8_t* __restrict__ maps,
-                                                   const Luts* __restrict__ luts, uint8_t* __restrict__ obs)
+// LDS of a block that draws
+struct PictureScratch {
+    float strip[(BLOCK / 64) * WAVE_FLOATS];                  // first: 16-byte aligned
+    float scale[TILE_ROWS * VCOLS];
+    uint32_t tile[TILE_ROWS * VCOLS];                         // base tile | item tile << 8 | creature tile << 16 | player << 24
+    uint32_t cre[NCELL];
+    uint32_t mask[46 * TILE_PX / 2];                          // a 16-bit row of a mask each half
+};
+// what does not depend on the environment; a barrier follows before draw_picture
+__device__ __forceinline__ void prepare_picture(PictureScratch& s, const Luts* __restrict__ luts)
 {
-    __shared__ uint32_t s_rec[REC_DWORDS];
-    __shared__ uint32_t s_cre[NCELL];
-    __shared__ uint32_t s_tile[TILE_ROWS * VCOLS];            // base tile | item tile << 8 | creature tile << 16 | player << 24
-    __shared__ float s_scale[TILE_ROWS * VCOLS];
-    __shared__ __attribute__((aligned(4))) uint16_t s_mask[46 * TILE_PX];
-    __shared__ __attribute__((aligned(16))) float s_strip[(BLOCK / 64) * WAVE_FLOATS];
-    const int env = blockIdx.x, tid = threadIdx.x;
-    const uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
-    if (tid < REC_DWORDS) s_rec[tid] = genv[tid];
-    if (tid < 46 * TILE_PX / 2) reinterpret_cast<uint32_t*>(s_mask)[tid] = reinterpret_cast<const uint32_t*>(&luts->mask[0][0])[tid];
-    if (tid < NCELL) s_cre[tid] = 0xFFFFFFFFu;
-    __syncthreads();
-    const uint32_t pos = s_rec[R_POS];
+    const int tid = threadIdx.x;
+    if (tid < 46 * TILE_PX / 2) s.mask[tid] = reinterpret_cast<const uint32_t*>(&luts->mask[0][0])[tid];
+    if (tid < NCELL) s.cre[tid] = 0xFFFFFFFFu;
+}
+// Draws the picture of an environment with the whole block.  rec, mobs: its record and the mob table of its floor, in LDS; m: its map slot.
+// KEEP: see cx::picture_kept.
+template <cx::Keep KEEP>
+__device__ __forceinline__ void draw_picture(PictureScratch& s, const uint32_t* rec, const uint32_t* mobs, const uint8_t* __restrict__ m,
+                                             const Luts* __restrict__ luts, uint8_t* __restrict__ out)
+{
+    const int tid = threadIdx.x;
+    const uint32_t pos = rec[R_POS];
     const int px = pos & 0xFF, py = (pos >> 8) & 0xFF, f = (pos >> 24) & 0xF;
-    const uint8_t* m = maps + map_offset((uint32_t)env, s_rec[R_EPISODE]);
     if (tid < NSLOT) {
-        const Mob u = unpack_mob(genv[REC_DWORDS + f * MOBTAB_DWORDS + tid]);
+        const Mob u = unpack_mob(mobs[tid]);
         const int vr = (int)u.y - (py - VROWS / 2), vc = (int)u.x - (px - VCOLS / 2);
         if (u.alive && (unsigned)vr < (unsigned)VROWS && (unsigned)vc < (unsigned)VCOLS)
-            atomicMin(&s_cre[vr * VCOLS + vc], ((uint32_t)tid << 8) | (uint32_t)(creature_channel(tid, (int)u.type) - 42));   // lowest slot wins
+            atomicMin(&s.cre[vr * VCOLS + vc], ((uint32_t)tid << 8) | (uint32_t)(creature_channel(tid, (int)u.type) - 42));   // lowest slot wins
     }
     __syncthreads();
     if (tid < TILE_ROWS * VCOLS) {
@@ -64,7 +71,7 @@ __global__ __launch_bounds__(BLOCK) void kf_pixels(const uint32_t* __restrict__ 
                 block = min((int)m[block_off(f, x, y)], (int)B_COUNT - 1);     // ids beyond the table would index past the atlas
                 const int il = m[il_off(f, x, y)];
                 item = min(il & 7, (int)IT_COUNT - 1); lv = il >> 3;
-                const uint32_t cr = s_cre[tid];
+                const uint32_t cr = s.cre[tid];
                 if (cr != 0xFFFFFFFFu) cre = AT_CRE + (cr & 0xFFu);
             }
             info = (uint32_t)block | ((item != IT_NONE ? (uint32_t)(AT_ITEM + item) : (uint32_t)NO_TILE) << 8) | (cre << 16)
@@ -73,17 +80,16 @@ __global__ __launch_bounds__(BLOCK) void kf_pixels(const uint32_t* __restrict__ 
         } else {
             const int j = tid - NCELL;
             info = (uint32_t)(AT_ICON + j) | ((uint32_t)NO_TILE << 8) | ((uint32_t)NO_TILE << 16);
-            scale = fminf(scalar_value(j, s_rec, luts), 1.0f);
+            scale = fminf(scalar_value(j, rec, luts), 1.0f);
         }
-        s_tile[tid] = info;
-        s_scale[tid] = scale;
+        s.tile[tid] = info;
+        s.scale[tid] = scale;
     }
     __syncthreads();
-    float4* out = reinterpret_cast<float4*>(obs + (size_t)env * STRIDE_PIXELS);
     const int w = tid >> 6, l = tid & 63;
     const float* atlas = luts->atlas;
-    float* strip = s_strip + w * WAVE_FLOATS;
-    auto covered = [&](int overlay, int yi, int xi) { return (s_mask[overlay * TILE_PX + yi] >> xi) & 1u; };
+    float* strip = s.strip + w * WAVE_FLOATS;
+    auto covered = [&](int overlay, int yi, int xi) { return (reinterpret_cast<const uint16_t*>(s.mask)[overlay * TILE_PX + yi] >> xi) & 1u; };
     float v[PIX_UNROLL][3], scale[PIX_UNROLL];
     // Group g of the picture is 1024 consecutive pixels, 256 per wave, 4 per lane (64 apart).
     // fetch: the texels of this lane's four pixels of group g.
@@ -96,8 +102,8 @@ __global__ __launch_bounds__(BLOCK) void kf_pixels(const uint32_t* __restrict__ 
             const bool valid = y < PIX_ROWS;
             const int yy = valid ? y : 0;
             const int tr = yy / TILE_PX, yi = yy - tr * TILE_PX, tc = x / TILE_PX, xi = x - tc * TILE_PX;
-            const uint32_t info = s_tile[tr * VCOLS + tc];
-            scale[u] = valid ? s_scale[tr * VCOLS + tc] : 0.0f;
+            const uint32_t info = s.tile[tr * VCOLS + tc];
+            scale[u] = valid ? s.scale[tr * VCOLS + tc] : 0.0f;
             int tile = info & 0xFF;
             if ((info >> 8) != 0xFFFFu) {                     // an item, a creature or the player on this cell
                 const int item = (info >> 8) & 0xFF, cre = (info >> 16) & 0xFF;
@@ -130,12 +136,10 @@ __global__ __launch_bounds__(BLOCK) void kf_pixels(const uint32_t* __restrict__ 
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const int q = (g * GROUP_PIXELS + w * WAVE_PIXELS) * 3 / 4 + k * 64 + l;
-            if (!guarded || q < STRIDE_PIXELS / 16) {
-                __builtin_nontemporal_store(piece[k].x, &out[q].x);
-                __builtin_nontemporal_store(piece[k].y, &out[q].y);
-                __builtin_nontemporal_store(piece[k].z, &out[q].z);
-                __builtin_nontemporal_store(piece[k].w, &out[q].w);
-            }
+            if (guarded && q >= STRIDE_PIXELS / 16) continue;
+            const cx::piece_t v = __builtin_bit_cast(cx::piece_t, piece[k]);
+            if constexpr (KEEP == cx::Keep::THROUGH) cx::store_through(out, STRIDE_PIXELS, 16 * q, v);
+            else __builtin_nontemporal_store(v, reinterpret_cast<cx::piece_t*>(out + 16 * q));
         }
     };
     // The fetches of the next group are issued before the stores of this one: the memory
@@ -154,6 +158,21 @@ __global__ __launch_bounds__(BLOCK) void kf_pixels(const uint32_t* __restrict__ 
     }
     turn();
     store(FULL_GROUPS, true);
+}
+
+// The picture of the state as it stands.
+__global__ __launch_bounds__(BLOCK) void kf_pixels(const uint32_t* __restrict__ envs, const uint8_t* __restrict__ maps,
+                                                   const Luts* __restrict__ luts, uint8_t* __restrict__ obs)
+{
+    __shared__ uint32_t s_rec[REC_DWORDS], s_mob[NSLOT];
+    __shared__ __attribute__((aligned(16))) PictureScratch s;
+    const int env = blockIdx.x, tid = threadIdx.x;
+    const uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
+    if (tid < REC_DWORDS) s_rec[tid] = genv[tid];
+    prepare_picture(s, luts);
+    __syncthreads();
+    if (tid < NSLOT) s_mob[tid] = genv[REC_DWORDS + ((s_rec[R_POS] >> 24) & 0xFu) * MOBTAB_DWORDS + tid];   // read by the same threads
+    draw_picture<cx::Keep::STREAM>(s, s_rec, s_mob, maps + map_offset((uint32_t)env, s_rec[R_EPISODE]), luts, obs + (size_t)env * STRIDE_PIXELS);
 }
 
 }  // namespace cf

@@ -207,9 +207,9 @@ __device__ __forceinline__ void render_symbolic(int l, uint32_t* e, int mvx, int
 //   2,048 (98 MB) 28.9 / 26.9 / 26.3 | 29.2 / 30.3 / 26.8 | 61.1 / 58.7 / 60.6   4,096 (195 MB) 50.0 / 43.3 / 43.0 | 50.0 / 86.6 / 44.3 | 118 / 141 / 120
 //   8,000 (381 MB) streamed 92.0, every fourth block 94.4 on three in turn
 constexpr long long PICTURES_KEPT_FROM = 32ll << 20, PICTURES_SPLIT_TO = 256ll << 20;
-__device__ inline bool picture_kept(int n, uint32_t block)
+__device__ inline bool picture_kept(int n, uint32_t block, int stride = OBS_STRIDE_PIXELS)
 {
-    const long long bytes = (long long)n * OBS_STRIDE_PIXELS;
+    const long long bytes = (long long)n * stride;
     return bytes > PICTURES_KEPT_FROM && (bytes <= CACHE_SHARE || (bytes <= PICTURES_SPLIT_TO && written_through(block)));
 }
 

@@ -56,3 +56,13 @@ def test_classic_byte_observations_of_a_step(n, mode):
 @pytest.mark.parametrize("n,mode", [(1, cx.OBS_SYM_F32), (5, cx.OBS_SYM_F32), (2688, cx.OBS_SYM_F32), (2689, cx.OBS_SYM_F32), (5, cx.OBS_SYM_U8_F32)])
 def test_craftax_observations_of_a_step(n, mode):
     assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=mode, max_episode_steps=3) > 0
+
+
+# as for Classic: written through from 32 MiB on (196 pictures), by every fourth block from 85 MiB on (520), streamed from 256 MiB on (1,564)
+@pytest.mark.parametrize("n", [1, 3, 195, 196, 519, 520, 1564])
+def test_craftax_pictures_of_a_step(n):
+    assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=3) > 0
+
+
+def test_craftax_pictures_of_a_perlin_step_with_sixteen_lanes():
+    assert _run(9, 8, cx.VARIANT_CRAFTAX, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=3, worldgen=cx.WORLDGEN_PERLIN, group_lanes=16) > 0
