@@ -330,5 +330,7 @@ __device__ __forceinline__ void store_through(uint8_t* base, int limit, int at, 
 __device__ inline bool written_through(uint32_t block) { return (block & 3u) == 0u; }
 // What an observation buffer may take of the last-level cache, where other buffers lie too: three that are used in turn still fit.
 constexpr long long CACHE_SHARE = 85ll << 20;
+// In a larger one every fourth block writes through, up to this place in it: 64 MiB of it then.
+constexpr long long SPLIT_TO = 256ll << 20;
 
 }  // namespace cx

@@ -319,7 +319,7 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
             const uint8_t* map = maps + map_offset((uint32_t)env, e[LDS_REC + RW_EPISODE]);
             uint8_t* out = obs + (size_t)env * OBS_STRIDE_PIXELS;
             float* strip = reinterpret_cast<float*>(s_env);
-            if (picture_kept(p.n, blockIdx.x)) render_pixels_block<Keep::THROUGH>(e + LDS_REC, map, luts, out, s_tile, s_ent, strip);
+            if (picture_kept(p.n, env, blockIdx.x)) render_pixels_block<Keep::THROUGH>(e + LDS_REC, map, luts, out, s_tile, s_ent, strip);
             else render_pixels_block<Keep::STREAM>(e + LDS_REC, map, luts, out, s_tile, s_ent, strip);
         }
         return;

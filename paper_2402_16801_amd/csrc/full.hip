@@ -281,7 +281,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
             if (!DRAW && obs != nullptr) {
                 aux.day = o.done ? day_fresh : day_next;
                 render_env<F32, GW>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux,
-                                    F32 && floats_written_through(p.n, blockIdx.x));
+                                    F32 && floats_written_through(p.n, env, blockIdx.x));
             }
         }
         if (DRAW) s_mob[l] = l < NSLOT ? m.w : 0u;
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         const uint32_t* rec = s_env + L_REC;
         const uint8_t* map = maps + map_offset((uint32_t)env, rec[R_EPISODE]);
         uint8_t* out = obs + (size_t)env * STRIDE_PIXELS;
-        if (cx::picture_kept(p.n, blockIdx.x, STRIDE_PIXELS)) draw_picture<cx::Keep::THROUGH>(s_picture, rec, s_mob, map, luts, out);
+        if (cx::picture_kept(p.n, env, blockIdx.x, STRIDE_PIXELS)) draw_picture<cx::Keep::THROUGH>(s_picture, rec, s_mob, map, luts, out);
         else draw_picture<cx::Keep::STREAM>(s_picture, rec, s_mob, map, luts, out);
     }
 }

@@ -253,13 +253,16 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     }
 }
 
-// Whether block `block` of a step of n environments writes its float observations through: up to CACHE_SHARE all of them do, beyond every
-// fourth block (us, plain / streamed / through / through by every fourth block, three states in turn | one that is read): 500 12.4 / 11.4 / 10.8 |
+// Whether the float observation of environment env, of n, stepped by block `block`, is written through: up to CACHE_SHARE all of them are, beyond
+// those of every fourth block in the first SPLIT_TO bytes (us, plain / streamed / through / through by every fourth block, three states in turn | one that is read): 500 12.4 / 11.4 / 10.8 |
 // 21.5 / 21.5 / 21.8, 2,000 17.5 / 19.2 / 16.1 | 38.8 / 41.6 / 39.4, 4,096 35.6 / 31.8 / 34.8 / 26.6 | 67.5 / 74.1 / 68.1 / 69.2, 6,000 55.5 / 45.7 /
 // 54.5 / 43.8 | 120 / 124 / 122 / 117, 8,192 68.3 / 56.2 / 67.5 / 62.1 | 163 / 160 / 166 / 155.  Rollouts write all of them through (plain / streamed /
 // through: 256 514 / 512 / 499, 1,000 558 / 541 / 532, 4,096 1,233 / 1,699 / 1,163).  Bytes are streamed: through, 1,024 environments take 9.8
 // instead of 10.2 us and 4,096 15.2 instead of 14.6, 16,384 55.6 instead of 42.7; by a choice at run time, 4,096 lose 1 %.
-__device__ inline bool floats_written_through(int n, uint32_t block) { return (long long)n * STRIDE_F32 <= cx::CACHE_SHARE || cx::written_through(block); }
+__device__ inline bool floats_written_through(int n, int env, uint32_t block)
+{
+    return (long long)n * STRIDE_F32 <= cx::CACHE_SHARE || (cx::written_through(block) && (long long)env * STRIDE_F32 < cx::SPLIT_TO);
+}
 
 // The same by GW < 64 lanes of a wavefront, whose areas have no room for staged bytes (L_ENV_DWORDS): the
 // one-hot bytes are staged as single bits (a few LDS atomics per cell) next to a light level per cell;

@@ -200,17 +200,22 @@ __device__ __forceinline__ void render_symbolic(int l, uint32_t* e, int mvx, int
     group_sync();   // the staging area may be reused
 }
 
-// Pictures of n environments that are written through (see Keep) or, above, by every fourth block.  Fewer do not fill the L2 of the chip
-// and are as fast streamed.  Step with pictures, streamed / written through / every fourth block, us, one state | three in turn | one that is read:
+// Whether the picture of environment env, of n, drawn by block `block`, is written through (see Keep) or streamed.  Few pictures do not fill the
+// L2 of the chip and are as fast streamed; beyond, all of them while they have room in the last-level cache, then those of every
+// fourth block in the first SPLIT_TO bytes.  Classic step with pictures, streamed / written through / every fourth block, us, one state | three in turn |
+// one that is read:
 //     400 (19 MB) 12.1 / 12.9 | 12.4 / 13.1 | 23.3 / 23.5     700 (33 MB) 14.6 / 14.2 | 14.5 / 14.3 | 29.3 / 29.8
 //   1,024 (49 MB) 18.0 / 16.0 / 16.3 | 17.9 / 16.2 / 16.5 | 37.0 / 35.2 / 36.3     1,700 (81 MB) 27.1 / 24.3 | 27.5 / 25.0 | 53.0 / 50.5
 //   2,048 (98 MB) 28.9 / 26.9 / 26.3 | 29.2 / 30.3 / 26.8 | 61.1 / 58.7 / 60.6   4,096 (195 MB) 50.0 / 43.3 / 43.0 | 50.0 / 86.6 / 44.3 | 118 / 141 / 120
-//   8,000 (381 MB) streamed 92.0, every fourth block 94.4 on three in turn
-constexpr long long PICTURES_KEPT_FROM = 32ll << 20, PICTURES_SPLIT_TO = 256ll << 20;
-__device__ inline bool picture_kept(int n, uint32_t block, int stride = OBS_STRIDE_PIXELS)
+// and full game and Classic, streamed / every fourth block / every fourth in the first SPLIT_TO bytes / every eighth:
+//   2,048 (352 MB) 79.1 / 59.8 / 64.1 / 68.9 | 80.2 / 72.9 / 65.5 / 69.7 | 206 / 206 / 203 / 205   4,096 (703 MB) 147 / 110 / 135 / 126 | 148 / 164 / 139 / 154 |
+//   393 / 397 / 393 / 395   12,000 (572 MB) 137 / 111 / 121 / 119 | 136 / 147 / 119 / 129 | 334 / 343 / 336 / 343
+constexpr long long PICTURES_KEPT_FROM = 32ll << 20;
+__device__ inline bool picture_kept(int n, int env, uint32_t block, int stride = OBS_STRIDE_PIXELS)
 {
     const long long bytes = (long long)n * stride;
-    return bytes > PICTURES_KEPT_FROM && (bytes <= CACHE_SHARE || (bytes <= PICTURES_SPLIT_TO && written_through(block)));
+    if (bytes <= CACHE_SHARE) return bytes > PICTURES_KEPT_FROM;
+    return written_through(block) && (long long)env * stride < SPLIT_TO;
 }
 
 // Pixel observation of one environment by a whole block (256 threads): 63x63x3 floats.

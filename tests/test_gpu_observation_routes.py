@@ -58,7 +58,7 @@ def test_craftax_observations_of_a_step(n, mode):
     assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=mode, max_episode_steps=3) > 0
 
 
-# as for Classic: written through from 32 MiB on (196 pictures), by every fourth block from 85 MiB on (520), streamed from 256 MiB on (1,564)
+# as for Classic: written through from 32 MiB on (196 pictures), by every fourth block from 85 MiB on (520), streamed , those beyond 256 MiB in all (1,564) streamed
 @pytest.mark.parametrize("n", [1, 3, 195, 196, 519, 520, 1564])
 def test_craftax_pictures_of_a_step(n):
     assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=3) > 0
