@@ -422,7 +422,7 @@ PIXEL_BYTES_PER_ENV = 130 * 110 * 3 * 4 + 1024 + 2 * 99      # the picture + the
 
 
 def craftax_pixels_line(args) -> dict:
-    """Full Craftax with the 110 x 130 x 3 pixel observation: step kernel + drawing kernel."""
+    """Full Craftax with the 110 x 130 x 3 pixel observation: steps (one launch each), and the drawing kernel alone."""
     n = 4096 if args.envs is None else args.envs
     kind = "uniform" if args.kind is None else args.kind
     K, W = args.steps, args.warmup
@@ -441,7 +441,7 @@ def craftax_pixels_line(args) -> dict:
         "roofline": {
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
             "traffic": read_profile_traffic("craftax_full_pixels_4096env.txt"),
-            "kernel": "kf_pixels: one block per environment, launched after the step kernel",
+            "kernel": "kf_pixels: one block per environment, as craftax_observe launches it; a step draws with the same code in its own launch",
             "alg_bytes_per_env_step": PIXEL_BYTES_PER_ENV, "alg_bytes_per_launch": PIXEL_BYTES_PER_ENV * n,
             "avg_launch_us": run["draw_s"] * 1e6,
             "measured_copy_gbs": copy_ceiling_gbs(),

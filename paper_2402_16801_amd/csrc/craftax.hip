@@ -634,8 +634,10 @@ __global__ __launch_bounds__(BLOCK) void k_pixels(const uint4* __restrict__ recs
     const int env = blockIdx.x;
     if (threadIdx.x < REC_DWORDS) s_rec[threadIdx.x] = reinterpret_cast<const uint32_t*>(recs + (size_t)env * 8)[threadIdx.x];
     __syncthreads();
-    render_pixels_block<Keep::STREAM>(s_rec, maps + map_offset((uint32_t)env, s_rec[RW_EPISODE]), luts, obs + (size_t)env * OBS_STRIDE_PIXELS,
-                                      s_tile, s_ent, s_strip);
+    const uint8_t* map = maps + map_offset((uint32_t)env, s_rec[RW_EPISODE]);
+    uint8_t* out = obs + (size_t)env * OBS_STRIDE_PIXELS;
+    if (picture_kept(p.n, env, blockIdx.x)) render_pixels_block<Keep::THROUGH>(s_rec, map, luts, out, s_tile, s_ent, s_strip);
+    else render_pixels_block<Keep::STREAM>(s_rec, map, luts, out, s_tile, s_ent, s_strip);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -172,7 +172,10 @@ __global__ __launch_bounds__(BLOCK) void kf_pixels(const uint32_t* __restrict__ 
     prepare_picture(s, luts);
     __syncthreads();
     if (tid < NSLOT) s_mob[tid] = genv[REC_DWORDS + ((s_rec[R_POS] >> 24) & 0xFu) * MOBTAB_DWORDS + tid];   // read by the same threads
-    draw_picture<cx::Keep::STREAM>(s, s_rec, s_mob, maps + map_offset((uint32_t)env, s_rec[R_EPISODE]), luts, obs + (size_t)env * STRIDE_PIXELS);
+    const uint8_t* map = maps + map_offset((uint32_t)env, s_rec[R_EPISODE]);
+    uint8_t* out = obs + (size_t)env * STRIDE_PIXELS;
+    if (cx::picture_kept((int)gridDim.x, env, blockIdx.x, STRIDE_PIXELS)) draw_picture<cx::Keep::THROUGH>(s, s_rec, s_mob, map, luts, out);
+    else draw_picture<cx::Keep::STREAM>(s, s_rec, s_mob, map, luts, out);
 }
 
 }  // namespace cf
