@@ -73,8 +73,8 @@ enum { CRAFTAX_VARIANT_CLASSIC = 0, CRAFTAX_VARIANT_CRAFTAX = 1 };
  *               shows its block tile, overlaid by its item, creature and the player where their
  *               one-bit masks are set, times light level / 20; cells beyond the map edge show
  *               block 1 at full light; slot j shows icon j times min(scalar j, 1).  Stride 171648
- *               (171600 bytes of pixels, zero padding).  craftax_step draws the picture in a
- *               second kernel on the same stream.
+ *               (171600 bytes of pixels, zero padding).  craftax_step draws the picture in the
+ *               launch that steps, or on the same stream behind it.
  * Channels: 0..36 block id; 37..41 item (none, torch, ladder down, ladder up, blocked ladder
  * down); 42..81 creature = 42 + 8*class + type slot, classes melee, passive, ranged, mob
  * projectile, player projectile; melee and ranged type slot = the floor the creature lives on

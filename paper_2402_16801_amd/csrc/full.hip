@@ -150,7 +150,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
     __shared__ float s_lut[LUT_FLOATS];
     using Picture = std::conditional_t<DRAW, PictureScratch, uint32_t>;
     __shared__ __attribute__((aligned(16))) Picture s_picture;
-    __shared__ uint32_t s_mob[DRAW ? 64 : 1];
+    __shared__ uint32_t s_mob[DRAW ? NSLOT : 1];
     const int tid = threadIdx.x, w = tid / GW, l = tid % GW;
     if ((int)blockIdx.x < regen_blocks) {
         const la::Ticket ticket = la::enter_launch_queue(ls, s_env + REGEN_PREFIX_AT);
@@ -284,7 +284,8 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
                                     F32 && floats_written_through(p.n, env, blockIdx.x));
             }
         }
-        if (DRAW) s_mob[l] = l < NSLOT ? m.w : 0u;
+        // an episode that ended without a spare world is not started anew here: its picture is that of the state in memory
+        if (DRAW && l < NSLOT) s_mob[l] = write_back ? m.w : genv[REC_DWORDS + ((e[L_REC + R_POS] >> 24) & 0xFu) * MOBTAB_DWORDS + l];
         if (queued && l == 0) la::commit_entry(ls, seq, step_block, list_at, make_uint4((uint32_t)env, lo, hi, ep + 2u));
     }
     la::leave_launch(ls, ticket);

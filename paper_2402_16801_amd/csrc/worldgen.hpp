@@ -1,8 +1,8 @@
 // Block-cooperative generation of one 64x64 Craftax-Classic world (appendix "World
 // Generation" of the paper: noise thresholds carve grassland, forest, lakes, mountains with
 // caves, tunnels, ores and lava).  Two noises feed the same rule: seeded integer value noise
-// (the benchmark configurations) and Perlin gradient noise as the paper uses, evaluated in
-// integers; either way every cell is a pure integer function of (seed, env, episode).
+// (the benchmark configurations) and Perlin gradient noise as the paper uses, with the values of
+// integer arithmetic; either way every cell is a pure integer function of (seed, env, episode).
 #pragma once
 
 #include <type_traits>
