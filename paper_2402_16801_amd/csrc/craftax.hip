@@ -315,7 +315,9 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
         if (queued) la::commit_entry(ls, seq, (uint32_t)env, list_at, entry);
         leave();
         if (DRAW) {
-            __syncthreads();                // the record is in LDS, the step's changes to the map have left for memory
+            // the record is in LDS, the step's changes to the map have left for memory.  An episode that ended without a spare
+            // world shows the state in memory: step_env leaves the record in LDS alone when an episode ends.
+            __syncthreads();
             const uint8_t* map = maps + map_offset((uint32_t)env, e[LDS_REC + RW_EPISODE]);
             uint8_t* out = obs + (size_t)env * OBS_STRIDE_PIXELS;
             float* strip = reinterpret_cast<float*>(s_env);

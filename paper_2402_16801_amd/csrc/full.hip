@@ -284,8 +284,16 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
                                     F32 && floats_written_through(p.n, env, blockIdx.x));
             }
         }
-        // an episode that ended without a spare world is not started anew here: its picture is that of the state in memory
-        if (DRAW && l < NSLOT) s_mob[l] = write_back ? m.w : genv[REC_DWORDS + ((e[L_REC + R_POS] >> 24) & 0xFu) * MOBTAB_DWORDS + l];
+        if (DRAW) {
+            // an episode that ended without a spare world is not started anew here: its picture is that of the state in memory,
+            // record and mobs, whatever the step has changed of the copies
+            if (!write_back) {
+#pragma unroll
+                for (int it = 0; it < REC_IT; ++it) if (l + GW * it < REC_DWORDS) e[L_REC + l + GW * it] = genv[l + GW * it];
+                wave_sync();
+            }
+            if (l < NSLOT) s_mob[l] = write_back ? m.w : genv[REC_DWORDS + ((e[L_REC + R_POS] >> 24) & 0xFu) * MOBTAB_DWORDS + l];
+        }
         if (queued && l == 0) la::commit_entry(ls, seq, step_block, list_at, make_uint4((uint32_t)env, lo, hi, ep + 2u));
     }
     la::leave_launch(ls, ticket);

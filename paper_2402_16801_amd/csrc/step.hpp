@@ -521,7 +521,7 @@ __device__ __forceinline__ StepOut step_env(int l, uint32_t env, uint32_t* e, ui
     const uint32_t t1 = t + 1;
     phase = phase + 1 == p.day_length ? 0u : phase + 1;
     out.done = vit[0] <= 0 || t1 >= p.max_episode_steps;
-    if (out.done) return out;
+    if (out.done) return out;      // the record in LDS is still that of memory, which a step with pictures relies on
 
     // ---- pack the record back into LDS ------------------------------------------------------------------
     group_sync();

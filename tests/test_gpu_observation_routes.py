@@ -1,6 +1,7 @@
 """How observations reach memory depends on the batch: pictures are drawn by the launch that steps, and stores are
 left in the caches, written through or streamed.  Every route against the kernel that only observes (which the parity
 tests compare with the oracle), and the rules against a run without observations."""
+import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -66,3 +67,54 @@ def test_craftax_pictures_of_a_step(n):
 
 def test_craftax_pictures_of_a_perlin_step_with_sixteen_lanes():
     assert _run(9, 8, cx.VARIANT_CRAFTAX, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=3, worldgen=cx.WORLDGEN_PERLIN, group_lanes=16) > 0
+
+
+@pytest.mark.parametrize("variant,n", [("classic", 1500), ("craftax", 700)])
+def test_pictures_of_a_captured_step_that_ends_an_episode_without_a_spare_world(variant, n):
+    """A graph captured while no edit was pending launches no kernel behind the step.  All episodes start anew in one replay;
+    swaps then put lava beside the start of some, which the next replay walks into: their next world is not ready, the
+    state in memory stays as it is, and that is what the picture has to show."""
+    full, cap = variant == "craftax", 5
+    sim = cx.Craftax(n, cx.default_config(cx.VARIANT_CRAFTAX if full else cx.VARIANT_CLASSIC, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=cap))
+    sim.reset(synth.seeds_for(n, 900))
+    actions = torch.zeros(n, dtype=torch.int32, device=sim.device)
+    seen = torch.empty_like(sim.obs)
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            cx.craftax_step(sim.state, actions, sim.obs, sim.reward, sim.done, n, torch.cuda.current_stream())
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+
+    def replay(what):
+        graph.replay()
+        torch.cuda.synchronize()
+        cx.craftax_observe(sim.state, seen, n, sim.stream)
+        assert torch.equal(sim.obs.view(torch.uint8), seen.view(torch.uint8)), what
+        return sim.done.cpu().numpy().astype(bool)
+
+    for t in range(cap):
+        ended = replay(f"observation at step {t}")
+    assert ended.all()
+    lava, c = 14, 24 if full else 32
+    for round_ in range(400):
+        cx.craftax_mutate_swap(sim.state, 0, n, 11, round_, False, None, sim.stream)
+        if round_ % 20 == 19:
+            d = sim.export_envs().view(sim.dump_dtype).reshape(-1)
+            m = d["block"][:, 0] if full else d["map"].reshape(n, 64, 64)
+            near = np.stack([m[:, c, c - 1], m[:, c, c + 1], m[:, c - 1, c], m[:, c + 1, c]], 1) == lava     # LEFT, RIGHT, UP, DOWN
+            doomed = near.any(axis=1)
+            if doomed.sum() >= 3:
+                break
+    assert doomed.any(), "no swap put lava next to a start: raise n or the number of rounds"
+    actions.copy_(torch.as_tensor(np.where(doomed, 1 + near.argmax(axis=1), 0).astype(np.int32)))
+    before = sim.export_envs()
+    assert np.array_equal(replay("observation of the step into the lava"), doomed)
+    assert np.array_equal(sim.export_envs()[doomed], before[doomed]), "nothing behind the step: the ended episodes stay in memory"
+    actions.zero_()
+    obs, _, _ = sim.step(actions)                               # the edit is still pending: this one serves them
+    cx.craftax_observe(sim.state, seen, n, sim.stream)
+    assert torch.equal(obs.view(torch.uint8), seen.view(torch.uint8))
+    sim.close()
