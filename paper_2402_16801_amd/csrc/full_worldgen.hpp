@@ -489,7 +489,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
         }
     }
     }
-    cx::nearest_rounding(episode);
+    cx::nearest_rounding();                                  // every run has been stored
     barrier();
 }
 

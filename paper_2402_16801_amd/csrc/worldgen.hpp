@@ -62,8 +62,8 @@ __device__ __forceinline__ float pick(uint32_t which) { return __uint_as_float(B
 template <typename T>
 __device__ __forceinline__ void settle(T& v) { asm volatile("" : "+v"(v)); }
 // Sets the rounding of 32-bit floating point to "towards minus infinity" for what depends on `first`, and
-// back to nearest behind what `last` depends on.  Everything that these kernels compute in floating point
-// outside depends on memory that is read outside; the machine's own instruction keeps the rest in its place
+// back to nearest behind what every one of `last` depends on and what has been stored before.  Everything that these kernels compute in
+// floating point outside depends on memory that is read outside; the machine's own instruction keeps the rest in its place
 // (no floating-point instruction is scheduled across a change of the mode register).
 constexpr int MODE_ROUND_32 = 1 | (0 << 6) | ((2 - 1) << 11);   // bits 0 and 1 of the mode register
 __device__ inline void floor_rounding(int& first)
@@ -71,9 +71,11 @@ __device__ inline void floor_rounding(int& first)
     __builtin_amdgcn_s_setreg(MODE_ROUND_32, 2u);
     asm volatile("" : "+v"(first));
 }
-__device__ inline void nearest_rounding(uint32_t& last)
+template <typename... Words>
+__device__ inline void nearest_rounding(Words&... last)
 {
-    asm volatile("" : "+v"(last));
+    (settle(last), ...);
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_s_setreg(MODE_ROUND_32, 0u);
 }
 // one bit per lane
@@ -281,7 +283,7 @@ __device__ __forceinline__ void worldgen_block(uint8_t* __restrict__ map, uint32
             });
         });
     }
-    nearest_rounding(word);
+    nearest_rounding(word, four);
     const uint32_t first = blocks_of(word);
     four = blocks_of(four);
     *reinterpret_cast<uint2*>(map + map_index(x0, y)) = make_uint2(first, four);   // 8 cells inside one tile row

@@ -86,6 +86,47 @@ template __global__ void floors<true>(uint8_t*, const uint32_t*);
     assert adds > 8 * 2 * (5 + 3 + 3 + 3), adds
 
 
+def test_fields_are_computed_between_the_changes_of_the_rounding(tmp_path):
+    """The generators as compiled: nothing but conversions of whole numbers in 32-bit floating point in front of the change to
+    "towards minus infinity", and nothing at all behind the change back.  The source ties both ends to values and stores; what
+    the compiler makes of it is seen here."""
+    src = tmp_path / "fields.hip"
+    csrc = os.path.join(ROOT, "paper_2402_16801_amd", "csrc")
+    arguments = "(uint8_t*, uint32_t, uint32_t, const uint32_t*)"
+    instances = [f"classic<{nt}, {p}, {s}>" for nt, s in ((256, "false"), (256, "true"), (512, "true")) for p in ("false", "true")]
+    instances += [f"floors<{nt}, {p}>" for nt in (64, 320) for p in ("false", "true")]
+    src.write_text('''#include "worldgen.hpp"
+#include "full_common.hpp"
+#include "full_worldgen.hpp"
+template <int NT, bool PERLIN, bool SPLIT> __global__ void classic(uint8_t* maps, uint32_t lo, uint32_t hi, const uint32_t* cs)
+{
+    __shared__ uint32_t lat[cx::LAT_WORDS];
+    cx::worldgen_block<NT, PERLIN, SPLIT>(maps, lat, lo, hi, blockIdx.x, 4u, nullptr, 0, cs);
+}
+template <int NT, bool PERLIN> __global__ void floors(uint8_t* maps, uint32_t lo, uint32_t hi, const uint32_t* cs)
+{
+    __shared__ uint32_t lat[cf::LAT_WORDS];
+    __shared__ cf::GenLayout layout;
+    cf::worldgen_floor_block<NT, PERLIN>(maps, lat, layout, lo, hi, blockIdx.x, 4u, (int)blockIdx.y, nullptr, nullptr, cs);
+}
+''' + "".join(f"template __global__ void {i}{arguments};\n" for i in instances))
+    out = tmp_path / "fields.s"
+    from paper_2402_16801_amd.build import HIPCC_FLAGS
+
+    _run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + [f for f in HIPCC_FLAGS if f not in ("-shared", "-fPIC")] +
+         ["-I", csrc, "-S", "--cuda-device-only", "-o", str(out), str(src)])
+    kernels = re.findall(r"^(_Z\S+):(.*?)^\.Lfunc_end", out.read_text(), re.S | re.M)
+    assert len(kernels) == len(instances)
+    for name, body in kernels:
+        lines = [line.split(";")[0].strip() for line in body.splitlines()]
+        modes = [i for i, line in enumerate(lines) if line.startswith("s_setreg")]
+        assert len(modes) == 2 and lines[modes[0]].endswith(", 2") and lines[modes[1]].endswith(", 0"), (name, [lines[i] for i in modes])
+        floats = [i for i, line in enumerate(lines) if re.match(r"v_\w*f32", line)]
+        assert sum(modes[0] < i < modes[1] for i in floats) > 200, name
+        assert [lines[i] for i in floats if i < modes[0] and not lines[i].startswith("v_cvt_f32_")] == [], name
+        assert [lines[i] for i in floats if i > modes[1]] == [], name
+
+
 def test_floors_go_to_the_form_that_was_measured_faster(tmp_path):
     """Blocks or single wavefronts for the floors of a call (csrc/floor_route.hpp)."""
     exe = str(tmp_path / "floor_route_test")
