@@ -333,7 +333,10 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
     // A run's number and the number of its strip are even or odd together, and so is the lane's: whether a
     // run is the right half of a spacing-16 lattice cell is the same in every pass.
     static_assert(ROW_RUNS % 2 == 0 && NT % 2 == 0, "parity of the strips");
-    // runs of 8 cells, one per thread and pass
+    // runs of 8 cells, one per thread and pass.  A block that covers the floor in one pass is no loop: the range of tid0 is not known
+    // any more here, and in front of a loop the compiler kept the constants of every kind of floor in scalar registers and spilled
+    // 14 to 16 of them (craftax_reset of 64 and 256 environments 26.1 and 39.2 us, 25.3 and 35.8 without; level turns over 400 and 500
+    // 47.2 and 57.8, 45.6 and 56.4; Perlin resets of 64 29.7 and 27.2, Perlin level turns over 128 57.5 and 54.0).
 #pragma unroll 1
     for (int run = tid0; run < RUNS; run += NT) {
     const int y = run / ROW_RUNS, strip = run - y * ROW_RUNS, x0 = strip * RUN;
@@ -488,6 +491,7 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
             }
         }
     }
+    if (NT >= RUNS) break;
     }
     cx::nearest_rounding();                                  // every run has been stored
     barrier();
