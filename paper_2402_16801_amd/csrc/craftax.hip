@@ -233,7 +233,11 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
     // launch while its records arrive (one call for both: the generator is in the kernel's code once)
     if (SHARE && (regen_role || first_helper_unit(blockIdx.x / NSUB, per_sub, rounds) < 2u * regen_count))
         regeneration_share<PERLIN>(maps, ls, seq, regen_count, sub, !regen_role, (regen_role ? rb : blockIdx.x) / NSUB, per_sub, nq, rounds, s_env, luts->perlin_cs);
-    if (regen_role) {
+    // The hint is for what the generator costs the step: without it the compiler spills scalar registers for the generator in front
+    // of this branch, 22 of them with Perlin noise, and the step fetches them back one by one (steps with Perlin noise of 100
+    // environments 8.06 us, 7.92 with the hint, of 500 8.34 and 8.23, flat floats of 4,096 11.34 and 11.14).  A probability near
+    // one has the generator put into a function of its own, with a stack.
+    if (__builtin_expect_with_probability(regen_role, 0, 0.75)) {
         if (!SHARE && rb / NSUB / 2 < regen_count) regeneration_block<PERLIN>(maps, ls, seq, regen_count, rb, nrb, s_env, luts->perlin_cs);
         leave();
         return;
