@@ -163,14 +163,14 @@ constexpr int step_blocks_per_cu(bool perlin) { return perlin ? 4 : 5; }   // by
 // end together then occupy the regeneration blocks of all sub-lists instead of those of one or two (16 environments,
 // episodes of 2 steps 27.1 -> 7.1 us, 64: 11.0 -> 7.4; ordinary episodes the same).
 constexpr int envs_per_list_turn(int lanes) { return lanes == 16 ? 1 : BLOCK / lanes; }
-// Byte layouts, by lanes per environment (see Keep; us, plain / written through / streamed, three states in turn | one that is read).
-// Sixteen are written through from THROUGH_FROM environments on: 256 8.3 / 8.3 / 8.2 | 10.4 / 11.0 / 10.4, 1,500 8.7 / 8.6 / 8.7 |
-// 11.5 / 11.6 / 11.5, 4,096 9.3 / 8.8 / 9.1 | 13.9 / 13.5 / 13.9, 11,000 12.4 / 11.0 / 11.1 | 21.5 / 20.0 / 20.0.  Eight are
-// streamed: 13,000 14.7 / 14.9 / 14.5 | 24.8 / 24.0 / 23.6, 20,000 18.3 / 17.3 / 16.9 | 29.7 / 28.8 / 29.3, 24,000
-// 19.4 / 18.6 / 17.6 | 31.8 / 30.9 / 31.2.  With four every fourth block writes through and the others stream (written_through; one state
-// alone | three in turn | one that is read, all written through / all streamed / every other block / every fourth): 32,768 20.2 / 20.2 / 19.6 /
-// 19.5 | 22.2 / 21.4 / 21.0 / 20.8 | 36.7 / 38.1 / 37.7 / 38.2, 49,152 24.4 / 25.5 / 23.7 / 23.5 | 33.0 / 26.6 / 27.3 / 25.1 | 48.2 / 51.1 / 49.0 / 49.6,
-// 65,536 31.0 / 32.7 / 30.1 / 29.8 | 43.2 / 33.8 / 37.5 / 33.2 | 63.1 / 67.4 / 64.4 / 64.4 (plain 31.5 | 43.2 | 63.1).
+// Byte layouts are written through to the last-level cache, from THROUGH_FROM environments on where there are sixteen lanes (see Keep; us,
+// left in the L2 / written through, one state stepped over and over | three in turn | one whose observation a cast to bfloat16 reads
+// behind every step).  Sixteen lanes: 256 8.1 / 8.3 | 8.3 / 8.3 | -, 1,500 8.7 / 8.6 | 8.7 / 8.6 | 15.7 / 15.9, 4,096 9.2 / 8.8 |
+// 9.2 / 8.8 | 23.7 / 23.4, 11,000 12.1 / 10.5 | 12.5 / 11.0 | 44.6 / 42.5.  Eight and four, and streamed past the cache (with four
+// lanes three blocks of four, the fourth written through): 13,000 14.3 / 14.4 / 14.0 | 14.8 / 15.0 / 14.5 | 51.3 / 51.0 / 60.7,
+// 20,000 17.7 / 16.2 / 16.0 | 18.3 / 17.5 / 17.0 | 69.5 / 68.6 / 85.9, 32,768 21.4 / 19.8 / 19.4 | 23.2 / 22.1 / 20.7 | 102 / 101 / 129,
+// 49,152 25.8 / 24.3 / 23.4 | 31.9 / 33.9 / 25.1 | 145 / 145 / 186, 65,536 31.4 / 30.8 / 29.8 | 43.2 / 43.6 / 33.5 | 198 / 199 / 256:
+// what streaming saves the step, and more, whoever reads the observation waits for.
 constexpr int THROUGH_FROM = 1500;
 // DRAW (pixels, 16 lanes): a block holds one environment, whose 16 lanes step it, and all its threads then draw
 // the picture, from the record in LDS: one launch instead of two, and the pictures of some blocks hide the steps of others.
@@ -311,8 +311,8 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
         const int first = __builtin_amdgcn_readfirstlane((tid & ~63) / G);   // first environment of this wave within the block
         const uint32_t* wave_env = s_env + first * LY::STRIDE;
         uint8_t* wave_obs = obs + (size_t)(blockIdx.x * EPB + first) * obs_stride(OBS_MODE);
-        if (G == 4 ? written_through(blockIdx.x) : G == 16 && p.n >= THROUGH_FROM) flush_wave_observations<G, OBS_MODE, LY, Keep::THROUGH>(wave_env, wave_obs);
-        else flush_wave_observations<G, OBS_MODE, LY, G == 16 ? Keep::PLAIN : Keep::STREAM>(wave_env, wave_obs);
+        if (G == 16 && p.n < THROUGH_FROM) flush_wave_observations<G, OBS_MODE, LY, Keep::PLAIN>(wave_env, wave_obs);
+        else flush_wave_observations<G, OBS_MODE, LY, Keep::THROUGH>(wave_env, wave_obs);
     }
     if (EAGER) {
         // an entry at a time, the place claimed before the rendering: no wavefront waits for the others of its block

@@ -55,6 +55,7 @@ template <int G, int OBS_MODE, class LY = KeepLayout, Keep KEEP = Keep::PLAIN>
 __device__ __forceinline__ void flush_wave_observations(const uint32_t* wave_env, uint8_t* __restrict__ wave_obs)
 {
     constexpr int RUN = G < 8 ? 8 : G, PASSES = RUN / G, STRIDE = obs_stride(OBS_MODE), NCHUNK = STRIDE / 16;
+    static_assert(KEEP != Keep::STREAM, "not streamed: see THROUGH_FROM");
     const int w = threadIdx.x & 63, run = w / RUN, j = w % RUN;
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
@@ -68,7 +69,6 @@ __device__ __forceinline__ void flush_wave_observations(const uint32_t* wave_env
             if (c >= NCHUNK) break;
             const uint4 v = staged_chunk<OBS_MODE, LY>(e, c);
             if constexpr (KEEP == Keep::THROUGH) store_through(wave_obs, 64 / G * STRIDE, ei * STRIDE + 16 * c, piece_t{v.x, v.y, v.z, v.w});
-            else if constexpr (KEEP == Keep::STREAM) __builtin_nontemporal_store(piece_t{v.x, v.y, v.z, v.w}, reinterpret_cast<piece_t*>(out + 4 * c));
             else *reinterpret_cast<uint4*>(out + 4 * c) = v;
         }
     }

@@ -1,5 +1,5 @@
 """How observations reach memory depends on the batch: pictures are drawn by the launch that steps, and stores are
-left in the caches, written through or streamed.  Every route against the kernel that only observes (which the parity
+left in the L2, written through or streamed.  Every route against the kernel that only observes (which the parity
 tests compare with the oracle), and the rules against a run without observations."""
 import numpy as np
 import pytest
