@@ -308,8 +308,8 @@ struct KeepLayout { static constexpr int VEC = LDS_VEC, FLAG = LDS_FLAG, STRIDE 
 struct StepLayout { static constexpr int VEC = LDS_REC, FLAG = 110, STRIDE = 118; };
 static_assert(StepLayout::FLAG >= LDS_BITS + 42 && StepLayout::FLAG < StepLayout::STRIDE && REC_DWORDS >= 24, "single-step LDS layout");
 
-// How stores of observations go through the caches (measured on one state stepped over and over, on three in turn, and
-// on one whose observation is read behind every step):
+// How stores of observations go through the caches (to be measured with a reader behind the call, too: what a streamed store saves the
+// call, the reader waits for):
 //  PLAIN    left in the L2, which holds 32 MB in all and is written back at the end of the launch;
 //  THROUGH  written through to the last-level cache (256 MB) as they come, so that the end of the launch waits for
 //           nothing and a reader still finds them there;
@@ -320,17 +320,17 @@ typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
 // (the hardware drops what lies beyond).
 __device__ __forceinline__ void store_through(uint8_t* base, int limit, int at, piece_t v)
 {
-    constexpr int SC1 = 16;      // cache policy bit of a buffer store: scope of the whole system
+    constexpr int SC1 = 16;      // cache policy bit of a buffer store: scope of the device, whose XCDs have an L2 each
     __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, limit, 0x00027000), at, 0, SC1);
 }
-// Where a buffer is larger than its share of the last-level cache: which blocks of a launch write through while the others stream.
+// Where a buffer is too large for the last-level cache: which blocks of a launch write through while the others stream.
 // Consecutive blocks go round the eight XCDs, each with an L2 of its own, so every fourth is two XCDs whose blocks all write
-// through.  Both ways out of the L2 are then in use at once, which is faster than either alone; with the same share spread over
-// all XCDs it is not (every third block of a step of 65,536: 31.4 us, 41.3 on three states in turn).
+// through.  Both ways out of the L2 are then in use at once, which is faster than either alone.
 __device__ inline bool written_through(uint32_t block) { return (block & 3u) == 0u; }
-// What an observation buffer may take of the last-level cache, where other buffers lie too: three that are used in turn still fit.
+// Pictures, which are streamed otherwise: up to here all of them are written through (three such buffers that are used in turn still fit).
 constexpr long long CACHE_SHARE = 85ll << 20;
-// In a larger one every fourth block writes through, up to this place in it: 64 MiB of it then.
+// The size of the last-level cache.  Of a buffer too large for it (of pictures, beyond CACHE_SHARE) every fourth block writes through, up to this
+// place in it: 64 MiB of it then.
 constexpr long long SPLIT_TO = 256ll << 20;
 
 }  // namespace cx

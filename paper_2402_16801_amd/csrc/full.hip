@@ -523,7 +523,7 @@ __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__
     load_window(l, maps + map_offset((uint32_t)env, ep), f, px, py, reinterpret_cast<uint8_t*>(e + L_WB), reinterpret_cast<uint8_t*>(e + L_WI));
     wave_sync();
     render_env<F32>(l, e, px - WIN_COLS / 2, py - WIN_ROWS / 2, u.alive, u.x, u.y, u.type, luts,
-                    obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8));
+                    obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), (const RenderAux<64>*)nullptr, F32 && floats_written_through(n, env, blockIdx.x));
 }
 
 // Noise mutation (section "Craftax-1B: UED"): one block per (environment, floor).  The level is the

@@ -253,15 +253,23 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     }
 }
 
-// Whether the float observation of environment env, of n, stepped by block `block`, is written through: up to CACHE_SHARE all of them are, beyond
-// those of every fourth block in the first SPLIT_TO bytes (us, plain / streamed / through / through by every fourth block, three states in turn | one that is read): 500 12.4 / 11.4 / 10.8 |
-// 21.5 / 21.5 / 21.8, 2,000 17.5 / 19.2 / 16.1 | 38.8 / 41.6 / 39.4, 4,096 35.6 / 31.8 / 34.8 / 26.6 | 67.5 / 74.1 / 68.1 / 69.2, 6,000 55.5 / 45.7 /
-// 54.5 / 43.8 | 120 / 124 / 122 / 117, 8,192 68.3 / 56.2 / 67.5 / 62.1 | 163 / 160 / 166 / 155.  Rollouts write all of them through (plain / streamed /
-// through: 256 514 / 512 / 499, 1,000 558 / 541 / 532, 4,096 1,233 / 1,699 / 1,163).  Bytes are streamed: through, 1,024 environments take 9.8
-// instead of 10.2 us and 4,096 15.2 instead of 14.6, 16,384 55.6 instead of 42.7; by a choice at run time, 4,096 lose 1 %.
+// Whether the float observation of environment env, of n, written by block `block`, goes through to the last-level cache: all of them do where
+// that cache has room for them (FLOATS_KEPT; the rest is for what else lies there); in a larger buffer those of every fourth block do, in its
+// first SPLIT_TO bytes, and the others are streamed.  us, left in the L2 / through / by every fourth block, one state | three in turn | one
+// that a maximum over the observation reads | one that a cast to bfloat16 reads:
+//   500 12.1 / 10.9 | 12.4 / 11.0 | 28.3 / 27.4 | 44.2 / 44.5     1,000 13.3 / 11.5 | 13.5 / 11.6 | 35.6 / 36.2 | 71.6 / 72.8     2,688 20.4 / 18.6 | 22.3 / 20.9 | 46.1 / 46.9 | 161 / 162
+//   4,096 26.1 / 24.7 / 26.4 | 35.4 / 35.9 / 27.1 | 56.1 / 57.1 / 71.3 | 254 / 257 / 326     6,000 39.6 / 37.5 / 38.9 | 55.6 / 55.8 / 44.1 | 78.8 / 79.3 / 101 | 469 / 471 / 487
+//   7,200 49.6 / 45.0 / 42.6 | 61.1 / 63.5 / 52.2 | 99.6 / 103 / 116 | 580 / 581 / 581     7,800 52.9 / 49.5 / 45.3 | 61.1 / 60.7 / 53.6 | 119 / 122 / 123 | 631 / 626 / 619
+//   8,192 59.4 / 57.3 / 47.8 | 68.6 / 68.2 / 60.0 | 141 / 142 / 129 | 666 / 670 / 659     10,000 84.4 / 76.9 / 59.8 | 83.7 / 78.7 / 69.5 | 181 / 178 / 157 | 811 / 813 / 801
+// craftax_observe in the same order: 4,096 21.3 / 20.6 | 29.2 / 29.2 | 54.3 / 54.5 | 250 / 244     8,192 43.7 / 37.0 / 41.5 | 58.9 / 59.2 / 44.9 | 122 / 123 / 122 | 648 / 654 / 645
+//   12,000 81.3 / 77.1 / 65.0 | 81.2 / 84.0 / 71.7 | 191 / 196 / 178 | 948 / 954 / 944.
+// Rollouts write all of them through (plain / streamed / through: 256 514 / 512 / 499, 1,000 558 / 541 / 532, 4,096 1,233 / 1,699 / 1,163; with a cast behind
+// each of 8 steps, plain / through: 256 97.0 / 94.2, 4,096 413 / 404, 8,192 983 / 961).  Bytes are streamed: through, 1,024 environments take 9.8 instead
+// of 10.2 us and 4,096 15.2 instead of 14.6, 16,384 55.6 instead of 42.7; by a choice at run time, 4,096 lose 1 %.
+constexpr long long FLOATS_KEPT = 240ll << 20;
 __device__ inline bool floats_written_through(int n, int env, uint32_t block)
 {
-    return (long long)n * STRIDE_F32 <= cx::CACHE_SHARE || (cx::written_through(block) && (long long)env * STRIDE_F32 < cx::SPLIT_TO);
+    return (long long)n * STRIDE_F32 <= FLOATS_KEPT || (cx::written_through(block) && (long long)env * STRIDE_F32 < cx::SPLIT_TO);
 }
 
 // The same by GW < 64 lanes of a wavefront, whose areas have no room for staged bytes (L_ENV_DWORDS): the

@@ -53,8 +53,10 @@ def test_classic_byte_observations_of_a_step(n, mode):
     assert _run(n, 10, cx.VARIANT_CLASSIC, obs_mode=mode, max_episode_steps=4) > 0
 
 
-# floats written through up to 85 MiB in all (2,688 environments), then by every fourth block; bytes streamed
-@pytest.mark.parametrize("n,mode", [(1, cx.OBS_SYM_F32), (5, cx.OBS_SYM_F32), (2688, cx.OBS_SYM_F32), (2689, cx.OBS_SYM_F32), (5, cx.OBS_SYM_U8_F32)])
+# floats written through up to 240 MiB in all (7,591 environments), then by every fourth block where they start within the first
+# 256 MiB (up to environment 8,097, in step and observing blocks whose number divides by four) and streamed beyond; bytes streamed
+@pytest.mark.parametrize("n,mode", [(1, cx.OBS_SYM_F32), (5, cx.OBS_SYM_F32), (2688, cx.OBS_SYM_F32), (2689, cx.OBS_SYM_F32), (7591, cx.OBS_SYM_F32), (7592, cx.OBS_SYM_F32), (8101, cx.OBS_SYM_F32),
+                                    (5, cx.OBS_SYM_U8_F32)])
 def test_craftax_observations_of_a_step(n, mode):
     assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=mode, max_episode_steps=3) > 0
 
