@@ -141,10 +141,10 @@ def test_full_game_runs_without_an_index_out_of_range(dbg, lanes):
         _clean(cx, f"Craftax, {lanes} lanes, observation layout {obs_mode}")
 
 
-@pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 501), (po.WORLDGEN_PERLIN, 670)])
+@pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 501), (po.WORLDGEN_PERLIN, 670), (po.WORLDGEN_VALUE, 640), (po.WORLDGEN_PERLIN, 680)])
 def test_full_game_floors_by_single_wavefronts_without_an_index_out_of_range(dbg, worldgen, n):
-    """Enough environments that reset, import, noise mutation and a rollout's owed worlds are generated by
-    single wavefronts."""
+    """Enough environments that import, noise mutation and a rollout's owed worlds, and with 640 and 680 the worlds of a reset
+    too, are generated by single wavefronts (501 of value noise: everything still by blocks)."""
     import torch
     from test_gpu_full_parity import rich_scene
     cx = dbg

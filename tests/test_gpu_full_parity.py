@@ -233,9 +233,10 @@ def test_full_worlds_over_many_seeds(cx, worldgen):
 
 
 @pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 500), (po.WORLDGEN_VALUE, 501), (po.WORLDGEN_PERLIN, 205), (po.WORLDGEN_PERLIN, 206),
-                                        (po.WORLDGEN_PERLIN, 341), (po.WORLDGEN_PERLIN, 342)])
+                                        (po.WORLDGEN_PERLIN, 341), (po.WORLDGEN_PERLIN, 342)] +
+                         [(po.WORLDGEN_VALUE, n) for n in (405, 456, 556, 589, 623)] + [(po.WORLDGEN_PERLIN, n) for n in (183, 184, 316, 456, 512, 673)])
 def test_full_floors_by_blocks_and_by_single_wavefronts(cx, worldgen, n):
-    """Import, noise mutation and the worlds owed by a rollout on both sides of the lines at which their
+    """Reset, import, noise mutation and the worlds owed by a rollout on both sides of the lines at which their
     floors go from blocks to single wavefronts (csrc/floor_route.hpp): every floor, and the spare
     worlds as the episodes that follow reach them."""
     import torch
