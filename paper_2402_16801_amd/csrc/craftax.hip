@@ -157,7 +157,12 @@ __device__ __forceinline__ void regeneration_share(uint8_t* __restrict__ maps, c
 // the regeneration blocks for the episodes that ended in the previous launch (with four lanes per
 // environment the step blocks take a share of that work before they step: regeneration_share).
 constexpr int COMPUTE_UNITS = 256;
-constexpr int step_blocks_per_cu(bool perlin) { return perlin ? 4 : 5; }   // by registers: a wavefront of a block on each of the four SIMDs
+// Step blocks that a compute unit holds, by registers (a wavefront of a block on each of the four SIMDs): five with either noise.  With Perlin noise
+// four were dealt for while the generator took more registers (steps of 57,344 environments 45.6 us, 44.0 dealt for five, of 65,536 46.1 and
+// 43.9; one state alone 33.1 and 31.7).  The bound the compiler is given stays at four there, which it needs no spills for and beats anyway
+// (with five 40,000 environments take 29.4 instead of 28.5, 49,152 35.0 instead of 34.0).
+constexpr int STEP_BLOCKS_PER_CU = 5;
+constexpr int step_bound(bool perlin) { return perlin ? 4 : STEP_BLOCKS_PER_CU; }
 // Neighbouring environments whose entries go to the same sub-list of the regeneration list: those of a step block, which
 // appends them together, or, with 16 lanes, where an entry is appended by itself, one: a few environments whose episodes
 // end together then occupy the regeneration blocks of all sub-lists instead of those of one or two (16 environments,
@@ -175,7 +180,7 @@ constexpr int THROUGH_FROM = 1500;
 // DRAW (pixels, 16 lanes): a block holds one environment, whose 16 lanes step it, and all its threads then draw
 // the picture, from the record in LDS: one launch instead of two, and the pictures of some blocks hide the steps of others.
 template <int G, int OBS_MODE, bool PERLIN, bool DRAW = false>
-__global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
+__global__ __launch_bounds__(BLOCK, step_bound(PERLIN)) void k_step(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                    const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                    uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                    uint8_t* __restrict__ done, Lists ls, Params p, int step_blocks)
@@ -228,7 +233,7 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
     const uint32_t sub = (regen_role ? rb : blockIdx.x) % NSUB, per_sub = nrb / NSUB;
     const uint32_t nq = ((uint32_t)step_blocks + NSUB - 1u - sub) / NSUB;   // step blocks that append to this sub-list
 
-    const uint32_t rounds = head_rounds((uint32_t)step_blocks, nrb, COMPUTE_UNITS * step_blocks_per_cu(PERLIN));
+    const uint32_t rounds = head_rounds((uint32_t)step_blocks, nrb, COMPUTE_UNITS * STEP_BLOCKS_PER_CU);
     // SHARE: a regeneration block's units, or this step block's share of the worlds owed from the previous
     // launch while its records arrive (one call for both: the generator is in the kernel's code once)
     if (SHARE && (regen_role || first_helper_unit(blockIdx.x / NSUB, per_sub, rounds) < 2u * regen_count))
@@ -339,8 +344,10 @@ __global__ __launch_bounds__(BLOCK, step_blocks_per_cu(PERLIN)) void k_step(uint
 
 // A launch of regeneration blocks only (before and after a rollout): brings every spare world up to date
 // and empties the lists, with the bookkeeping of a step launch that has no step blocks.
-// Eight blocks per compute unit, which no longer take registers that the generator needs (five: rollouts of 16,384 environments and
-// 64 steps 662 us, 657 with eight, of 32,768 1,046 and 1,034; of 600 and one step 17.8 either way).
+// Eight blocks per compute unit (value noise, which needs no more registers: five: rollouts of 16,384 environments and 64 steps 662 us, 657
+// with eight, of 32,768 1,046 and 1,034; of 600 and one step 17.8 either way).  The Perlin generator spills a vector register for the eighth
+// (8 bytes of scratch) and 23 scalar ones; seven blocks, which spill no vector register: 256 environments and 16 steps 110.2 us, 110.8 with eight, 12,000
+// 152.1 and 151.3, 32,768 and 64 steps 1,072 and 1,071.
 constexpr int DRAIN_BLOCKS_PER_CU = 8;
 template <bool PERLIN>
 __global__ __launch_bounds__(BLOCK, DRAIN_BLOCKS_PER_CU) void k_drain(uint8_t* __restrict__ maps, const Luts* __restrict__ luts, Lists ls)
@@ -1130,7 +1137,7 @@ static int group_lanes(const craftax_config* cfg, int n)
 constexpr int RESET_GRID = 64;    // blocks of k_reset_list (the slow list is nearly always empty); each loops over the list
 constexpr int FULL_LIST_GRID = 512;    // the same where every finished episode is on that list (4,096 environments with episodes of one step, 64 blocks 349 us, 512: 129)
 constexpr int REGEN_BLOCKS = 1024; // regeneration blocks appended to the step grid (two per world); those beyond the list exit at once
-constexpr int OWED_BLOCKS = COMPUTE_UNITS * DRAIN_BLOCKS_PER_CU;   // regeneration blocks behind a rollout: all that the chip holds at once 
+constexpr int OWED_BLOCKS = COMPUTE_UNITS * DRAIN_BLOCKS_PER_CU;   // regeneration blocks behind a rollout: all that the chip holds at once
 constexpr int SHARED_REGEN_BLOCKS = 256;   // with four lanes per environment: one per compute unit, beside its four step blocks (see regeneration_share)
 
 template <int OBS_MODE>

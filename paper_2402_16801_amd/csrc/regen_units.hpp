@@ -24,8 +24,8 @@ namespace cx {
 // of the kernel that the chip holds.  Step in us with one round / two, skewed actions, on states in turn and on one:
 //   value noise (1,280 resident)   24,576 22.1 / 21.3   19.9 / 18.9   49,152 32.2 / 31.8   27.0 / 25.6   65,536 43.1 / 42.4   31.9 / 31.2
 //     67,584 48.9 / 49.8   33.7 / 33.8   73,728 54.6 / 55.6   35.6 / 36.0   81,920 56.3 / 56.7   38.3 / 40.1   131,072 102.4 / 99.6   95.3 / 93.4
-//   Perlin noise (1,024 resident)  24,576 22.5 / 21.9   21.3 / 19.6   49,152 35.2 / 34.4   29.3 / 27.3   57,344 42.6 / 40.4   32.6 / 34.0
-//     61,440 43.0 / 43.7   34.1 / 37.4   65,536 44.7 / 48.9   36.1 / 40.1   98,304 78.4 / 76.7   64.5 / 60.9
+//   Perlin noise (1,280 resident)  57,344 45.6 / 41.9   30.1 / 29.0   61,440 44.7 / 41.6   31.4 / 30.0   65,536 45.6 / 43.3   33.1 / 31.5
+//     67,584 50.8 / 49.7   34.8 / 34.9   73,728 57.2 / 56.4   36.8 / 37.6   81,920 57.5 / 57.2   40.7 / 43.0
 CX_UNITS_FN uint32_t head_rounds(uint32_t step_blocks, uint32_t regen_blocks, uint32_t resident)
 {
     return step_blocks <= resident && step_blocks + regen_blocks > resident ? 1u : 2u;

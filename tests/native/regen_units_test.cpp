@@ -54,13 +54,13 @@ int main()
         for (unsigned q = 0; q < nq; ++q) helpers_with_work += first_helper_unit(q, per_sub, rounds) < 2 * count;
         expect(helpers_with_work == 2 * count - rounds * per_sub, "the step blocks with the lowest numbers take the tail, one unit each", count, per_sub, nq);
     }
-    // one round or two where both were measured (value noise with 1,280 resident blocks, Perlin with
-    // 1,024; sums of the two figures in us): the faster one, or one within 2 %
+    // one round or two where both were measured (value noise, then Perlin noise, 1,280 resident
+    // blocks; sums of the two figures in us): the faster one, or one within 2 %
     const struct { unsigned envs, resident; double one, two; } measured[] = {
         { 24576, 1280, 42.0, 40.2 },  { 49152, 1280, 59.2, 57.4 },  { 65536, 1280, 75.0, 73.6 },  { 67584, 1280, 82.6, 83.6 },  { 73728, 1280, 90.2, 91.6 },
         { 81920, 1280, 94.6, 96.8 },  { 98304, 1280, 133.1, 131.1 }, { 131072, 1280, 197.7, 193.0 },
-        { 24576, 1024, 43.8, 41.5 },  { 49152, 1024, 64.5, 61.7 },  { 57344, 1024, 75.2, 74.4 },  { 61440, 1024, 77.1, 81.1 },  { 65536, 1024, 80.8, 89.0 },
-        { 98304, 1024, 142.9, 137.6 },
+        { 57344, 1280, 75.7, 70.9 },  { 61440, 1280, 76.1, 71.6 },  { 65536, 1280, 78.7, 74.8 },  { 67584, 1280, 85.6, 84.6 },  { 73728, 1280, 94.0, 94.0 },
+        { 81920, 1280, 98.2, 100.2 },
     };
     for (const auto& m : measured) {
         const bool two = head_rounds(m.envs / 64, 256, m.resident) == 2;

@@ -1,6 +1,6 @@
 """Generated worlds, cell by cell, against the oracle: both variants and both noises over seeds from the
-whole 64-bit range.  The comparison is exact: the generators evaluate integer fields in 64-bit floating
-point, where every step is exact (a blend below 2^36, a field below 2^33, offsets of 2^52)."""
+whole 64-bit range.  The comparison is exact: the generators evaluate integer fields in 32-bit floating
+point rounded down, where floors and comparisons are those of the integers."""
 import numpy as np
 import pytest
 
@@ -89,7 +89,7 @@ def test_classic_rollout_whose_blocks_generate_what_they_owe(n, pre, steps, cap,
 @pytest.mark.parametrize("n,perlin", [(250, True), (569, True), (570, True), (683, True), (684, True), (570, False)])
 def test_full_import_generates_the_worlds_a_reset_would(n, perlin):
     """Imported levels have the spare worlds of the states they were exported from, whichever form of the generator takes the
-    floors: blocks, single wavefronts, and around the sizes (5,121 to 6,152 Perlin floors) that go to six wavefronts per SIMD."""
+    floors: blocks, single wavefronts, and around the number of Perlin floors (6,144) that single wavefronts take in one round."""
     import torch
     cfg = cx.default_config(cx.VARIANT_CRAFTAX, worldgen=cx.WORLDGEN_PERLIN if perlin else cx.WORLDGEN_VALUE, max_episode_steps=3)
     seeds = np.arange(n, dtype=np.uint64) + np.uint64(900)
@@ -109,8 +109,8 @@ def test_full_import_generates_the_worlds_a_reset_would(n, perlin):
 @pytest.mark.parametrize("n", [24577, 49151, 57345, 70001])
 def test_classic_four_lanes_at_every_split_of_the_regeneration(n, perlin):
     """Four lanes per environment: rollouts that leave their worlds to a launch (up to 49,151 environments) and that generate
-    them after every step, against steps whose regeneration blocks take two rounds of units, or one (57,345 with Perlin
-    noise, 70,001 with value noise: the chip holds the step blocks and a part of the regeneration blocks)."""
+    them after every step, against steps whose regeneration blocks take two rounds of units, or one (70,001: the chip holds
+    the step blocks and a part of the regeneration blocks)."""
     test_classic_rollout_owes_worlds(n, perlin)
 
 

@@ -48,3 +48,14 @@ def test_floors_generated_by_blocks_spill_nothing(kernels):
     """A block covers a floor in one pass: seen as a loop, the compiler kept every kind of floor's constants in front of it."""
     spills = _spills(kernels, r"cf::(kf_reset|kf_import|kf_mutate_noise)<(\w+, )?320>")
     assert len(spills) == 5 and set(spills.values()) == {(0, 0)}, spills
+
+
+def test_generators_of_the_full_game_spill_no_vector_register(kernels):
+    """At the wavefronts per SIMD that they are bounded to (csrc/floor_route.hpp)."""
+    spills = _spills(kernels, r"cf::(kf_reset|kf_import|kf_drain|kf_mutate_noise)<")
+    assert len(spills) == 14 and {v for _, v in spills.values()} == {0}, spills
+
+
+def test_step_kernels_use_no_scratch(kernels):
+    scratch = {n: k["private_segment_fixed_size"] for n, k in kernels.items() if re.match(r"cx::k_step<|cf::kf_step<", n)}
+    assert len(scratch) > 20 and set(scratch.values()) == {0}, scratch
