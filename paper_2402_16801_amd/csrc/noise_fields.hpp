@@ -136,4 +136,27 @@ FIELD_FN constexpr float first_mix_above(int t)  // the same of a mix
     return (PERLIN ? 4.0f * PERLIN_BASE : MIX_BASE) + (float)(4 * t + 4);
 }
 
+constexpr uint32_t f32_bits(float v) { return __builtin_bit_cast(uint32_t, v); }
+// A field in a tunnel, |value - TH_TUNNEL_CENTER| < TH_TUNNEL_HALF, is one comparison of bit patterns: bits - FIRST < WIDTH, since those of
+// positive floats are in the order of their values.
+constexpr int TH_TUNNEL_CENTER = 30000, TH_TUNNEL_HALF = 1300;
+template <bool PERLIN>
+struct Tunnel {
+    static constexpr uint32_t FIRST = f32_bits(first_above<PERLIN>(TH_TUNNEL_CENTER - TH_TUNNEL_HALF)),
+                              WIDTH = f32_bits(first_above<PERLIN>(TH_TUNNEL_CENTER + TH_TUNNEL_HALF - 1)) - FIRST;
+};
+constexpr int START_CLEAR = 2, START_BIAS_R = 10, START_BIAS = 2500;
+// Near the start the fields W4 and M4 are lowered by `bias`, and where that is as large as it is within
+// START_CLEAR cells of it, the cell is grass: lowered below every threshold, its draw above every one.
+FIELD_FN void near_start(int bias, float& W4, float& M4, uint32_t& u)
+{
+    constexpr int FLAG = 1 << 20, CLEAR = (START_BIAS_R - START_CLEAR) * (4 * START_BIAS);
+    static_assert(CLEAR < FLAG && START_BIAS_R * 4 * START_BIAS < CLEAR + FLAG && 4 * 65536 < FLAG, "the flag is above every field and bias");
+    static_assert(MIX_BASE - 2.0f * FLAG >= 2.0f * TWO23 && 4.0f * PERLIN_BASE - 2.0f * FLAG >= 4.0f * TWO23 && (4 * START_BIAS) % 4 == 0, "the difference is exact");
+    const int flag = (bias + (FLAG - CLEAR)) & FLAG;
+    const float lower = (float)(bias + flag);
+    W4 -= lower; M4 -= lower;
+    u |= (uint32_t)flag << 11;
+}
+
 }  // namespace cx

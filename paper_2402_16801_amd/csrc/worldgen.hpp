@@ -20,12 +20,10 @@ constexpr int LAT_N = LAT_BLOCKS * 8;
 
 // terrain thresholds on 0..65535 scales
 constexpr int TH_MOUNTAIN = 39500, TH_CAVE_M = 41000, TH_CAVE_C = 43000;
-constexpr int TH_TUNNEL_CENTER = 30000, TH_TUNNEL_HALF = 1300;
 constexpr int TH_LAVA_M = 43000, TH_LAVA_F = 44000, TH_DIAMOND_M = 42000;
 constexpr int U_DIAMOND = 500, U_IRON = 3000, TH_IRON_F = 33000, U_COAL = 8000;
 constexpr int TH_WATER = 39500, TH_SAND = 37800, TH_FOREST_F = 33500;
 constexpr int U_TREE_FOREST = 26000, U_TREE_SPARSE = 1300;
-constexpr int START_CLEAR = 2, START_BIAS_R = 10, START_BIAS = 2500;
 
 // The generators below are bound by instruction issue (a 64x64 world is 4 KB of stores).  Most vector
 // instructions cost their SIMD four cycles: compares, byte permutations, additions with carry, dot products,
@@ -49,7 +47,6 @@ __device__ __forceinline__ void for_run(F&& f)
     f(std::integral_constant<int, 7>()); f(std::integral_constant<int, 6>()); f(std::integral_constant<int, 5>()); f(std::integral_constant<int, 4>());
     f(std::integral_constant<int, 3>()); f(std::integral_constant<int, 2>()); f(std::integral_constant<int, 1>()); f(std::integral_constant<int, 0>());
 }
-constexpr uint32_t f32_bits(float v) { return __builtin_bit_cast(uint32_t, v); }
 // a constant in a scalar register, from where any vector instruction takes it as it is
 template <uint32_t V>
 __device__ __forceinline__ uint32_t scalar_const() { uint32_t s; asm("s_mov_b32 %0, %1" : "=s"(s) : "i"(V)); return s; }
@@ -105,9 +102,6 @@ __host__ __device__ constexpr uint32_t four_bytes(uint32_t a, uint32_t b, uint32
 // for a run.
 template <bool PERLIN>
 struct Thresholds {
-    static constexpr int TUNNEL0 = TH_TUNNEL_CENTER - TH_TUNNEL_HALF, TUNNEL1 = TH_TUNNEL_CENTER + TH_TUNNEL_HALF;
-    // the tunnel's ends as bit patterns: those of positive floats are in the order of their values
-    static constexpr uint32_t TUNNEL0_BITS = f32_bits(first_above<PERLIN>(TUNNEL0)), TUNNEL_WIDTH = f32_bits(first_above<PERLIN>(TUNNEL1 - 1)) - TUNNEL0_BITS;
     static constexpr uint32_t draw(int t) { return (uint32_t)t << 16; }
     template <int T> __device__ static float mix() { return __uint_as_float(scalar_const<f32_bits(first_mix_above<PERLIN>(T))>()); }
     template <int T> __device__ static float field() { return __uint_as_float(scalar_const<f32_bits(first_above<PERLIN>(T))>()); }
@@ -115,7 +109,7 @@ struct Thresholds {
           diamond_m = mix<TH_DIAMOND_M>(), forest_f = field<TH_FOREST_F>(), iron_f = field<TH_IRON_F - 1>(), lava_f = field<TH_LAVA_F>(),
           cave_c = field<TH_CAVE_C>();
     uint32_t diamond = scalar_const<draw(U_DIAMOND)>(), iron = scalar_const<draw(U_IRON)>(), coal = scalar_const<draw(U_COAL)>(),
-             sparse = scalar_const<draw(U_TREE_SPARSE)>(), forest = scalar_const<draw(U_TREE_FOREST)>(), tunnel = scalar_const<TUNNEL_WIDTH>();
+             sparse = scalar_const<draw(U_TREE_SPARSE)>(), forest = scalar_const<draw(U_TREE_FOREST)>(), tunnel = scalar_const<Tunnel<PERLIN>::WIDTH>();
 };
 
 // The overworld's rule for one cell: appends five bits to `word`, where a cell takes a byte.  w, m: the
@@ -130,7 +124,7 @@ __device__ __forceinline__ void classify(uint32_t& word, const Thresholds<PERLIN
 {
     const Mask shore = mask_of(w >= t.sand), rock = mask_of(m >= t.mountain), u500 = mask_of(u < t.diamond), u3000 = mask_of(u < t.iron);
     const Mask tree = mask_of(u < t.sparse) | (mask_of(F >= t.forest_f) & mask_of(u < t.forest));
-    const Mask tunnel = mask_of(__float_as_uint(C) - Thresholds<PERLIN>::TUNNEL0_BITS < t.tunnel);
+    const Mask tunnel = mask_of(__float_as_uint(C) - Tunnel<PERLIN>::FIRST < t.tunnel);
     const Mask path = (mask_of(m >= t.cave_m) & mask_of(C >= t.cave_c)) | (tunnel & rock);
     const Mask lava = mask_of(m >= t.lava_m) & mask_of(F >= t.lava_f), gem = lava | (mask_of(m >= t.diamond_m) & u500);
     const Mask coal = mask_of(u < t.coal) & ~u3000, iron = u3000 & ~(u500 | mask_of(F >= t.iron_f));
@@ -148,18 +142,6 @@ __device__ inline uint32_t blocks_of(uint32_t word)
     const uint32_t on_rock = __builtin_amdgcn_perm(four_bytes(BK_LAVA, BK_DIAMOND, BK_PATH, BK_PATH), four_bytes(0, BK_STONE, BK_COAL, BK_IRON), rock);
     const uint32_t no_rock = __builtin_amdgcn_perm(0u, 0xFFu, rock), elsewhere = __builtin_amdgcn_perm(0u, four_bytes(BK_GRASS, BK_TREE, BK_SAND, BK_WATER), plain);
     return on_rock | (elsewhere & no_rock);
-}
-// Near the start the fields W4 and M4 are lowered by `bias`, and where that is as large as it is within
-// START_CLEAR cells of it, the cell is grass: lowered below every threshold, its draw above every one.
-__device__ inline void near_start(int bias, float& W4, float& M4, uint32_t& u)
-{
-    constexpr int FLAG = 1 << 20, CLEAR = (START_BIAS_R - START_CLEAR) * (4 * START_BIAS);
-    static_assert(CLEAR < FLAG && START_BIAS_R * 4 * START_BIAS < CLEAR + FLAG && 4 * 65536 < FLAG, "the flag is above every field and bias");
-    static_assert(MIX_BASE - 2.0f * FLAG >= 2.0f * TWO23 && 4.0f * PERLIN_BASE - 2.0f * FLAG >= 4.0f * TWO23 && (4 * START_BIAS) % 4 == 0, "the difference is exact");
-    const int flag = (bias + (FLAG - CLEAR)) & FLAG;
-    const float lower = (float)(bias + flag);
-    W4 -= lower; M4 -= lower;
-    u |= (uint32_t)flag << 11;
 }
 static_assert(TH_MOUNTAIN < TH_CAVE_M && TH_CAVE_M < TH_DIAMOND_M && TH_DIAMOND_M < TH_LAVA_M, "the mountain thresholds imply rock");
 

@@ -1,9 +1,10 @@
 // The generators' noise fields in 32-bit floating point rounded down (csrc/noise_fields.hpp) against the oracle's
-// integers: values, and every comparison with a threshold that the rules make of a field or a mix.  All offsets inside a
-// lattice cell, lattice numbers at their ends and at random.
+// integers: values, and every comparison that the rules make of a field or a mix: with thresholds, with the tunnel's two
+// ends, and of a mix lowered near the start.  All offsets inside a lattice cell, lattice numbers at their ends and at random.
 #include <cfenv>
 #include <cmath>
 #include <cstdio>
+#include <cstdlib>
 
 #include "../../paper_2402_16801_amd/csrc/noise_fields.hpp"
 
@@ -13,7 +14,7 @@ extern "C" uint32_t orc_perlin_noise(const uint16_t* lattice, int width, int spa
 static uint64_t rng = 12345;
 static uint32_t draw() { rng = rng * 6364136223846793005ull + 1442695040888963407ull; return (uint32_t)(rng >> 33); }
 static float cosine[1024], sine[1024];
-static long long bad = 0, clamped = 0;
+static long long bad = 0, clamped = 0, in_tunnel = 0;
 static void expect(bool ok, const char* what, int x, int y)
 {
     if (!ok && bad++ < 10) std::printf("%s at (%d, %d)\n", what, x, y);
@@ -30,6 +31,19 @@ static void compare(const Fields& f, int x, int y)
         if (v >= 0 && v < 65535) expect((f.f_field >= cx::first_above<PERLIN>(v)) == ((int)f.fine > v), "field", x, y);
         if (mix >= 0) expect(((PERLIN ? cx::perlin_mix31(f.f_coarse, f.f_fine) : cx::mix31(f.f_coarse, f.f_fine)) >= cx::first_mix_above<PERLIN>(mix)) ==
                              ((int)((3u * f.coarse + f.fine) >> 2) > mix), "mix", x, y);
+    }
+    const bool tunnel = std::abs((int)f.fine - cx::TH_TUNNEL_CENTER) < cx::TH_TUNNEL_HALF;
+    expect((cx::f32_bits(f.f_field) - cx::Tunnel<PERLIN>::FIRST < cx::Tunnel<PERLIN>::WIDTH) == tunnel, "tunnel", x, y);
+    in_tunnel += tunnel;
+    // a cell at distance d from the start: lowered, and below every threshold where it is cleared
+    for (int d = 0; d < cx::START_BIAS_R; ++d) {
+        float w = PERLIN ? cx::perlin_mix31(f.f_coarse, f.f_fine) : cx::mix31(f.f_coarse, f.f_fine), m = w;
+        uint32_t u = 0u;
+        cx::near_start((cx::START_BIAS_R - d) * 4 * cx::START_BIAS, w, m, u);
+        const int lowered = (int)((3u * f.coarse + f.fine) >> 2) - (cx::START_BIAS_R - d) * cx::START_BIAS;
+        expect(w == m && (u == 0x80000000u) == (d <= cx::START_CLEAR) && (u & 0x7FFFFFFFu) == 0u, "cleared", x, y);
+        for (int e = -1; e <= 1; ++e)
+            if (lowered + e >= 0) expect((w >= cx::first_mix_above<PERLIN>(lowered + e)) == (d > cx::START_CLEAR && e < 0), "near the start", x, y);
     }
 }
 
@@ -91,6 +105,7 @@ int main()
         }
         cell(a, b);
     }
+    if (in_tunnel < 1000) { std::printf("only %lld values in the tunnel\n", in_tunnel); ++bad; }
     if (clamped < 1000) { std::printf("only %lld clamped values\n", clamped); ++bad; }
     if (bad == 0) std::printf("noise_fields_test: ok\n");
     return bad != 0;
