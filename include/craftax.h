@@ -110,7 +110,8 @@ typedef struct craftax_config {
     uint32_t reset_mode;         /* CRAFTAX_RESET_*: where the world of a new episode comes from */
     uint32_t group_lanes;        /* tuning: lanes of a wavefront that share one environment in the step kernel; 0 = chosen
                                     from n (the default), else 4, 8 or 16 (Classic), 16 or 64 (CRAFTAX).  Results do not
-                                    depend on it. */
+                                    depend on it.  A step that draws pictures takes 16 (Classic) or 64 (CRAFTAX)
+                                    whatever it says, except where episodes are served behind the step. */
     uint32_t reserved;           /* must be 0 */
 } craftax_config;
 

@@ -61,10 +61,17 @@ def test_craftax_observations_of_a_step(n, mode):
     assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=mode, max_episode_steps=3) > 0
 
 
-# as for Classic: written through from 32 MiB on (196 pictures), by every fourth block from 85 MiB on (520), streamed , those beyond 256 MiB in all (1,564) streamed
-@pytest.mark.parametrize("n", [1, 3, 195, 196, 519, 520, 1564])
+# as for Classic: streamed, written through from 32 MiB on (196 pictures), by every fourth block from 85 MiB on (520); beyond the first
+# 256 MiB all are streamed, of 1,565 pictures the last one, whose block would write through
+@pytest.mark.parametrize("n", [1, 3, 195, 196, 519, 520, 1564, 1565])
 def test_craftax_pictures_of_a_step(n):
     assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=3) > 0
+
+
+# beyond 8,192 environments the window of a spare world's start is fetched only when an episode ends
+@pytest.mark.parametrize("worldgen", [cx.WORLDGEN_VALUE, cx.WORLDGEN_PERLIN])
+def test_craftax_pictures_of_a_step_of_a_large_batch(worldgen):
+    assert _run(8193, 5, cx.VARIANT_CRAFTAX, obs_mode=cx.OBS_PIXELS_F32, max_episode_steps=2, worldgen=worldgen) > 0
 
 
 def test_craftax_pictures_of_a_perlin_step_with_sixteen_lanes():
