@@ -6,6 +6,7 @@
 // reset catch up where they fill the chip exactly once (6,144 of Perlin noise, 8,192 of value noise run at the same time), and
 // fall back with the next round.  The lines lie between measured sizes (us, blocks / single wavefronts):
 //   reset, value noise      288  6.0 / 15.3   4,500 18.2 / 21.2   7,200 25.5 / 25.5   7,686 26.9 / 26.2   8,190 28.2 / 26.3   8,298 28.5 / 29.6   10,800 35.0 / 35.8   11,394 36.6 / 36.2   16,200 49.0 / 45.1   73,728 199 / 139
+//     (over maps that are not in the cache: calls with their observation of 6,300 40.5 / 41.4, of 7,056 43.0 / 42.0)
 //   import, value noise     288 12.5 / 22.8   3,600 28.2 / 32.5   4,797 33.9 / 34.8   5,193 35.6 / 35.9   5,400 36.4 / 36.1   6,003 39.2 / 37.1   9,000 52.6 / 46.4   18,000 108 / 78
 //   reset, Perlin noise     288  7.9 / 20.5   2,700 17.0 / 23.5   5,400 26.7 / 27.6   5,688 27.7 / 27.6   6,084 29.1 / 27.9   6,192 29.5 / 32.9   9,000 39.2 / 43.0   11,700 48.8 / 49.6   12,186 50.5 / 50.4   14,400 58.0 / 55.9   73,728 265 / 186
 //   import, Perlin noise    288 14.5 / 28.0   2,592 27.1 / 35.5   4,500 38.1 / 39.5   4,950 40.4 / 40.1   6,093 46.7 / 42.6   6,192 47.3 / 46.8   9,000 62.5 / 58.3   18,000 128 / 98
@@ -30,7 +31,7 @@ inline bool floors_by_blocks(FloorWork work, bool perlin, long long floors)
 {
     const bool one_round = floors <= SIMDS * (perlin ? PERLIN_WAVES : VALUE_WAVES);
     switch (work) {
-    case FloorWork::RESET: return floors <= (one_round ? (perlin ? 5650 : 7300) : (perlin ? 12100 : 11200));
+    case FloorWork::RESET: return floors <= (one_round ? (perlin ? 5650 : 6300) : (perlin ? 12100 : 11200));
     case FloorWork::IMPORT: return floors <= (perlin ? 4600 : 5300);
     case FloorWork::MUTATE: return floors <= 1650;     // Perlin worlds only
     default: return floors <= (perlin ? 4100 : 5000);

@@ -131,7 +131,8 @@ __global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_dr
 // block; 16 = four environments per wavefront, sixteen per block.
 // DRAW (pixels): a block holds one environment, which its first wavefront steps, and all its wavefronts then draw the picture, from the
 // record and mobs in LDS.
-template <bool F32, bool EAGER, bool PERLIN, int GW, bool DRAW = false>
+// FLOATS: see floats_kept.
+template <bool F32, bool EAGER, bool PERLIN, int GW, bool DRAW = false, cx::Keep FLOATS = cx::Keep::THROUGH>
 __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                 const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                 uint8_t* __restrict__ obs, float* __restrict__ reward,
@@ -280,8 +281,8 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
             if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
             if (!DRAW && obs != nullptr) {
                 aux.day = o.done ? day_fresh : day_next;
-                render_env<F32, GW>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux,
-                                    F32 && floats_written_through(p.n, env, blockIdx.x));
+                render_env<F32, GW, FLOATS>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux,
+                                            FLOATS == cx::Keep::STREAM && floats_written_through(env, blockIdx.x));
             }
         }
         if (DRAW) {
@@ -505,7 +506,7 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_reset_list(uint32_t* __restric
     }
 }
 
-template <bool F32>
+template <bool F32, cx::Keep FLOATS = cx::Keep::THROUGH>
 __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__ envs, const uint8_t* __restrict__ maps,
                                                    const Luts* __restrict__ luts, uint8_t* __restrict__ obs, int n)
 {
@@ -522,8 +523,8 @@ __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__
     const Mob u = unpack_mob(l < NSLOT ? genv[REC_DWORDS + f * MOBTAB_DWORDS + l] : 0u);
     load_window(l, maps + map_offset((uint32_t)env, ep), f, px, py, reinterpret_cast<uint8_t*>(e + L_WB), reinterpret_cast<uint8_t*>(e + L_WI));
     wave_sync();
-    render_env<F32>(l, e, px - WIN_COLS / 2, py - WIN_ROWS / 2, u.alive, u.x, u.y, u.type, luts,
-                    obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), (const RenderAux<64>*)nullptr, F32 && floats_written_through(n, env, blockIdx.x));
+    render_env<F32, 64, FLOATS>(l, e, px - WIN_COLS / 2, py - WIN_ROWS / 2, u.alive, u.x, u.y, u.type, luts,
+                                obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), nullptr, FLOATS == cx::Keep::STREAM && floats_written_through(env, blockIdx.x));
 }
 
 // Noise mutation (section "Craftax-1B: UED"): one block per (environment, floor).  The level is the
@@ -973,6 +974,8 @@ static bool kernels_fit(const Fits& fits)
     auto step = [&](const char* name, const void* eager, const void* plain) { return fits(name, eager, BLOCK) && fits(name, plain, BLOCK); };
     auto floors = [&](const char* name, const void* blocks, const void* wavefronts) { return fits(name, blocks, GEN_THREADS) && fits(name, wavefronts, FLOOR_THREADS); };
     return step("kf_step", (const void*)kf_step<F32, true, PERLIN, 64>, (const void*)kf_step<F32, false, PERLIN, 64>) &&
+           (!F32 || step("kf_step of large float buffers", (const void*)kf_step<true, true, PERLIN, 64, false, cx::Keep::PLAIN>, (const void*)kf_step<true, false, PERLIN, 64, false, cx::Keep::STREAM>)) &&
+           (!F32 || (fits("kf_observe of large float buffers", (const void*)kf_observe<true, cx::Keep::PLAIN>, BLOCK) && fits("kf_observe of larger ones", (const void*)kf_observe<true, cx::Keep::STREAM>, BLOCK))) &&
            step("kf_step with pictures", (const void*)kf_step<false, true, PERLIN, 64, true>, (const void*)kf_step<false, false, PERLIN, 64, true>) &&
            step("kf_step (16 lanes)", (const void*)kf_step<F32, true, PERLIN, 16>, (const void*)kf_step<F32, false, PERLIN, 16>) &&
            fits("kf_rollout", (const void*)kf_rollout<F32, PERLIN>, BLOCK) && fits("kf_reset_list", (const void*)kf_reset_list<F32>, GEN_THREADS) &&
@@ -1041,6 +1044,10 @@ static void launch_step(int gw, bool eager, bool perlin, dim3 grid, hipStream_t 
     if (gw == 16) {
         if (perlin) { if (eager) go(kf_step<F32, true, true, 16>); else go(kf_step<F32, false, true, 16>); }
         else { if (eager) go(kf_step<F32, true, false, 16>); else go(kf_step<F32, false, false, 16>); }
+    } else if (F32 && floats_kept(p.n) == cx::Keep::STREAM) {      // above EAGER_SPARE_ENVS but for a few hundred environments
+        if (perlin) go(kf_step<true, false, true, 64, false, cx::Keep::STREAM>); else go(kf_step<true, false, false, 64, false, cx::Keep::STREAM>);
+    } else if (F32 && eager && (p.n < FLOATS_THROUGH_FROM || floats_kept(p.n) == cx::Keep::PLAIN)) {
+        if (perlin) go(kf_step<true, true, true, 64, false, cx::Keep::PLAIN>); else go(kf_step<true, true, false, 64, false, cx::Keep::PLAIN>);
     } else {
         if (perlin) { if (eager) go(kf_step<F32, true, true, 64>); else go(kf_step<F32, false, true, 64>); }
         else { if (eager) go(kf_step<F32, true, false, 64>); else go(kf_step<F32, false, false, 64>); }
@@ -1127,7 +1134,14 @@ int observe(void* state, const craftax_config* cfg, int n, void* obs, void* stre
     const dim3 grid((n + ENVS_PER_BLOCK - 1) / ENVS_PER_BLOCK);
     uint8_t* o = static_cast<uint8_t*>(obs);
     if (cfg->obs_mode == CRAFTAX_OBS_PIXELS_F32) hipLaunchKernelGGL(kf_pixels, dim3((unsigned)n), dim3(BLOCK), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, o);
-    else if (cfg->obs_mode == CRAFTAX_OBS_SYM_F32) hipLaunchKernelGGL(kf_observe<true>, grid, dim3(BLOCK), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, o, n);
+    else if (cfg->obs_mode == CRAFTAX_OBS_SYM_F32) {
+        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, o, n); };
+        switch (floats_kept(n)) {
+        case cx::Keep::THROUGH: go(kf_observe<true>); break;
+        case cx::Keep::PLAIN: go(kf_observe<true, cx::Keep::PLAIN>); break;
+        case cx::Keep::STREAM: go(kf_observe<true, cx::Keep::STREAM>); break;
+        }
+    }
     else hipLaunchKernelGGL(kf_observe<false>, grid, dim3(BLOCK), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, o, n);
     return check_launch("craftax_observe", err);
 }

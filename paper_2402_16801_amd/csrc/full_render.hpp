@@ -138,9 +138,9 @@ constexpr bool staged_floats_are_exact()
 }
 static_assert(staged_floats_are_exact(), "light levels through staged bytes");
 static_assert(STAGE_BYTES % 1024 == 0 && 64 * NCHAN >= STAGE_BYTES && NCELL <= 128, "the second cell of a lane lies in the second part");
-// through (floats): whether the observation is written through to the last-level cache (see cx::Keep) or streamed, as bytes are;
-// the same for the wavefront.
-template <bool F32>
+// FLOATS: how they are stored (see floats_kept); where that is STREAM, through says whether this observation is written through
+// all the same (the same for the wavefront).  Bytes are streamed.
+template <bool F32, cx::Keep FLOATS>
 __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const int wx0, const int wy0, const int m_alive, const int m_x,
                                               const int m_y, const int m_type, const Luts* __restrict__ luts, uint8_t* __restrict__ out,
                                               const RenderAux<64>* aux, const bool through)
@@ -222,14 +222,18 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
         // 16-byte pieces `first`, first + 64, ..., one per lane and turn, in a loop for each kind of store
         auto store = [&](const int first, auto turns, auto&& piece) {
             constexpr int TURNS = decltype(turns)::value;
-            if (through) {
+            piece_t* dst = reinterpret_cast<piece_t*>(out) + first + l;
+            if constexpr (FLOATS == cx::Keep::PLAIN) {
+#pragma unroll 5
+                for (int k = 0; k < TURNS; ++k) dst[64 * k] = piece(k);
+            } else if (FLOATS == cx::Keep::THROUGH || through) {
                 const uintptr_t at = reinterpret_cast<uintptr_t>(out);
                 uint8_t* base = reinterpret_cast<uint8_t*>(((uintptr_t)uniu((uint32_t)(at >> 32)) << 32) | uniu((uint32_t)at));
 #pragma unroll 5
                 for (int k = 0; k < TURNS; ++k) cx::store_through(base, STRIDE_F32, 16 * (first + 64 * k + l), piece(k));
             } else {
 #pragma unroll 5
-                for (int k = 0; k < TURNS; ++k) __builtin_nontemporal_store(piece(k), reinterpret_cast<piece_t*>(out) + first + 64 * k + l);
+                for (int k = 0; k < TURNS; ++k) __builtin_nontemporal_store(piece(k), dst + 64 * k);
             }
         };
         // pieces of four floats; from TAIL on they hold scalars (after one last light level)
@@ -253,35 +257,43 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     }
 }
 
-// Whether the float observation of environment env, of n, written by block `block`, goes through to the last-level cache: all of them do where
-// that cache has room for them (FLOATS_KEPT; the rest is for what else lies there); in a larger buffer those of every fourth block do, in its
-// first SPLIT_TO bytes, and the others are streamed.  us, left in the L2 / through / by every fourth block, one state | three in turn | one
-// that a maximum over the observation reads | one that a cast to bfloat16 reads:
+// How the float observations of n environments are stored, by an instance of the kernel for each kind (a choice at run time: 16 environments
+// 9.7 -> 9.9 us, craftax_observe of 1,000 7.3 -> 7.8).  Up to CACHE_SHARE they are written through to the last-level cache, up to FLOATS_KEPT, which
+// that cache holds with what else lies there, left in the L2; of a larger buffer those of every fourth block are written through, in its first
+// SPLIT_TO bytes, and the others streamed.  us, left in the L2 / through / by every fourth block, one state | three in turn | one that a
+// maximum over the observation reads | one that a cast to bfloat16 reads:
 //   500 12.1 / 10.9 | 12.4 / 11.0 | 28.3 / 27.4 | 44.2 / 44.5     1,000 13.3 / 11.5 | 13.5 / 11.6 | 35.6 / 36.2 | 71.6 / 72.8     2,688 20.4 / 18.6 | 22.3 / 20.9 | 46.1 / 46.9 | 161 / 162
-//   4,096 26.1 / 24.7 / 26.4 | 35.4 / 35.9 / 27.1 | 56.1 / 57.1 / 71.3 | 254 / 257 / 326     6,000 39.6 / 37.5 / 38.9 | 55.6 / 55.8 / 44.1 | 78.8 / 79.3 / 101 | 469 / 471 / 487
-//   7,200 49.6 / 45.0 / 42.6 | 61.1 / 63.5 / 52.2 | 99.6 / 103 / 116 | 580 / 581 / 581     7,800 52.9 / 49.5 / 45.3 | 61.1 / 60.7 / 53.6 | 119 / 122 / 123 | 631 / 626 / 619
-//   8,192 59.4 / 57.3 / 47.8 | 68.6 / 68.2 / 60.0 | 141 / 142 / 129 | 666 / 670 / 659     10,000 84.4 / 76.9 / 59.8 | 83.7 / 78.7 / 69.5 | 181 / 178 / 157 | 811 / 813 / 801
+//   3,333 23.8 / 22.8 / 23.9 | 30.6 / 31.2 / 24.1 | 50.8 / 50.8 / 62.2 | 198 / 200 / 266     4,096 26.1 / 24.7 / 26.4 | 35.4 / 35.9 / 27.1 | 56.1 / 57.1 / 71.3 | 254 / 257 / 326
+//   6,000 39.6 / 37.5 / 38.9 | 55.6 / 55.8 / 44.1 | 78.8 / 79.3 / 101 | 469 / 471 / 487     7,200 49.6 / 45.0 / 42.6 | 61.1 / 63.5 / 52.2 | 99.6 / 103 / 116 | 580 / 581 / 581
+//   7,800 52.9 / 49.5 / 45.3 | 61.1 / 60.7 / 53.6 | 119 / 122 / 123 | 631 / 626 / 619     8,192 59.4 / 57.3 / 47.8 | 68.6 / 68.2 / 60.0 | 141 / 142 / 129 | 666 / 670 / 659
+//   10,000 84.4 / 76.9 / 59.8 | 83.7 / 78.7 / 69.5 | 181 / 178 / 157 | 811 / 813 / 801
 // craftax_observe in the same order: 4,096 21.3 / 20.6 | 29.2 / 29.2 | 54.3 / 54.5 | 250 / 244     8,192 43.7 / 37.0 / 41.5 | 58.9 / 59.2 / 44.9 | 122 / 123 / 122 | 648 / 654 / 645
 //   12,000 81.3 / 77.1 / 65.0 | 81.2 / 84.0 / 71.7 | 191 / 196 / 178 | 948 / 954 / 944.
 // Rollouts write all of them through (plain / streamed / through: 256 514 / 512 / 499, 1,000 558 / 541 / 532, 4,096 1,233 / 1,699 / 1,163; with a cast behind
 // each of 8 steps, plain / through: 256 97.0 / 94.2, 4,096 413 / 404, 8,192 983 / 961).  Bytes are streamed: through, 1,024 environments take 9.8 instead
 // of 10.2 us and 4,096 15.2 instead of 14.6, 16,384 55.6 instead of 42.7; by a choice at run time, 4,096 lose 1 %.
 constexpr long long FLOATS_KEPT = 240ll << 20;
-__device__ inline bool floats_written_through(int n, int env, uint32_t block)
+inline cx::Keep floats_kept(int n)
 {
-    return (long long)n * STRIDE_F32 <= FLOATS_KEPT || (cx::written_through(block) && (long long)env * STRIDE_F32 < cx::SPLIT_TO);
+    const long long bytes = (long long)n * STRIDE_F32;
+    return bytes <= cx::CACHE_SHARE ? cx::Keep::THROUGH : bytes <= FLOATS_KEPT ? cx::Keep::PLAIN : cx::Keep::STREAM;
 }
+// A step of a few environments leaves its floats in the L2, too, which takes less time to write back than they take to go through one by
+// one (1 environment 8.54 us left there, 8.86 written through, 4 9.38 and 9.50, 16 9.82 and 9.90, 32 10.3 either way, 64 10.6 and 10.5).
+constexpr int FLOATS_THROUGH_FROM = 32;
+// Where that is STREAM: whether the observation of environment env, written by block `block`, is written through.
+__device__ inline bool floats_written_through(int env, uint32_t block) { return cx::written_through(block) && (long long)env * STRIDE_F32 < cx::SPLIT_TO; }
 
 // The same by GW < 64 lanes of a wavefront, whose areas have no room for staged bytes (L_ENV_DWORDS): the
 // one-hot bytes are staged as single bits (a few LDS atomics per cell) next to a light level per cell;
 // every lane then expands 16 bits at a time into one 16-byte piece of the output.
-// GW: lanes that render this environment (see Lanes); l: the calling lane's number among them.  through: see render_staged.
-template <bool F32, int GW = 64>
+// GW: lanes that render this environment (see Lanes); l: the calling lane's number among them.  FLOATS, through: see render_staged.
+template <bool F32, int GW = 64, cx::Keep FLOATS = cx::Keep::THROUGH>
 __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int wx0, const int wy0, const int m_alive, const int m_x,
                                   const int m_y, const int m_type, const Luts* __restrict__ luts, uint8_t* __restrict__ out,
-                                  const RenderAux<GW>* aux = nullptr, const bool through = true)
+                                  const RenderAux<GW>* aux = nullptr, const bool through = false)
 {
-    if constexpr (GW == 64) { render_staged<F32>(l, e, wx0, wy0, m_alive, m_x, m_y, m_type, luts, out, aux, through); return; } else {
+    if constexpr (GW == 64) { render_staged<F32, FLOATS>(l, e, wx0, wy0, m_alive, m_x, m_y, m_type, luts, out, aux, through); return; } else {
     using G = Lanes<GW>;
     const uint32_t* rec = e + L_REC;
     const uint8_t* wb = reinterpret_cast<const uint8_t*>(e + L_WB);

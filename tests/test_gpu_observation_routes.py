@@ -53,12 +53,18 @@ def test_classic_byte_observations_of_a_step(n, mode):
     assert _run(n, 10, cx.VARIANT_CLASSIC, obs_mode=mode, max_episode_steps=4) > 0
 
 
-# floats written through up to 240 MiB in all (7,591 environments), then by every fourth block where they start within the first
-# 256 MiB (up to environment 8,097, in step and observing blocks whose number divides by four) and streamed beyond; bytes streamed
-@pytest.mark.parametrize("n,mode", [(1, cx.OBS_SYM_F32), (5, cx.OBS_SYM_F32), (2688, cx.OBS_SYM_F32), (2689, cx.OBS_SYM_F32), (7591, cx.OBS_SYM_F32), (7592, cx.OBS_SYM_F32), (8101, cx.OBS_SYM_F32),
+# floats left in the L2 (up to 31 environments), written through (up to 85 MiB in all, 2,688 environments), left in the L2 (up to 240 MiB,
+# 7,591), then written through by every fourth block where they start within the first 256 MiB (up to environment 8,097, in step
+# and observing blocks whose number divides by four) and streamed beyond; bytes streamed
+@pytest.mark.parametrize("n,mode", [(1, cx.OBS_SYM_F32), (5, cx.OBS_SYM_F32), (31, cx.OBS_SYM_F32), (32, cx.OBS_SYM_F32), (2688, cx.OBS_SYM_F32), (2689, cx.OBS_SYM_F32), (7591, cx.OBS_SYM_F32), (7592, cx.OBS_SYM_F32), (8101, cx.OBS_SYM_F32),
                                     (5, cx.OBS_SYM_U8_F32)])
 def test_craftax_observations_of_a_step(n, mode):
     assert _run(n, 8, cx.VARIANT_CRAFTAX, obs_mode=mode, max_episode_steps=3) > 0
+
+
+@pytest.mark.parametrize("n", [33, 2700, 7600])
+def test_craftax_floats_of_a_perlin_step(n):
+    assert _run(n, 6, cx.VARIANT_CRAFTAX, obs_mode=cx.OBS_SYM_F32, max_episode_steps=3, worldgen=cx.WORLDGEN_PERLIN) > 0
 
 
 # as for Classic: streamed, written through from 32 MiB on (196 pictures), by every fourth block from 85 MiB on (520); beyond the first
