@@ -142,7 +142,6 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
     static_assert(!DRAW || (GW == 64 && !F32), "pictures are drawn behind a step by a wavefront");
     constexpr int EPB = DRAW ? 1 : BLOCK / GW;               // environments per block
     constexpr int REC_IT = REC_DWORDS / GW > 0 ? REC_DWORDS / GW : 1;
-    constexpr int WIN_IT = (WIN_ROWS * WIN_COLS + GW - 1) / GW;
     static_assert(REC_DWORDS % GW == 0 || GW > REC_DWORDS, "the record is moved in whole turns of the group");
     static_assert(GW >= MOBTAB_DWORDS && GW >= NTAG && GW >= FLOORS + 1, "a group holds a mob table, the tags and the header in one turn");
     constexpr int ENV_DWORDS_LDS = GW == 64 ? L_STAGED_DWORDS : L_ENV_DWORDS;
@@ -202,29 +201,12 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         Player P;
         // the window of the spare world's start position comes with the current window
         const uint8_t* spare = maps + map_offset((uint32_t)env, ep + 1u);
-        uint32_t sw[WIN_IT];
-#pragma unroll
-        for (int it = 0; it < WIN_IT; ++it) {
-            const int i = l + GW * it;
-            sw[it] = 0u;
-            if (EAGER && i < WIN_ROWS * WIN_COLS) {
-                const int r = i / WIN_COLS, c = i - r * WIN_COLS;
-                const int x = W / 2 - WIN_COLS / 2 + c, y = W / 2 - WIN_ROWS / 2 + r;
-                sw[it] = (uint32_t)spare[block_off(0, x, y)] | ((uint32_t)spare[il_off(0, x, y)] << 8);
-            }
-        }
+        Window<GW> spare_window;
+        if (EAGER) spare_window.fetch(l, spare, 0, W / 2, W / 2);
         auto park = [&]() {
             if (l < NTAG) { e[L_SPARE_TAG + 2 * l] = tag.x; e[L_SPARE_TAG + 2 * l + 1] = tag.y; }
             if (l < FLOORS + 1) e[L_SPARE_HDR + l] = hdr;
-#pragma unroll
-            for (int it = 0; it < WIN_IT; ++it) {
-                const int i = l + GW * it;
-                if (EAGER && i < WIN_ROWS * WIN_COLS) {
-                    const int r = i / WIN_COLS, c = i - r * WIN_COLS;
-                    reinterpret_cast<uint8_t*>(e + L_SPARE_WB)[r * WIN_PITCH + c] = (uint8_t)sw[it];
-                    reinterpret_cast<uint8_t*>(e + L_SPARE_WI)[r * WIN_PITCH + c] = (uint8_t)(sw[it] >> 8);
-                }
-            }
+            if (EAGER) spare_window.park(l, e + L_SPARE_WB, e + L_SPARE_WI);
         };
         StepOut o = step_env<GW>(l, (uint32_t)env, e, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, park);
         if (l == 0) { reward[env] = o.reward; done[env] = o.done ? 1 : 0; }
@@ -251,13 +233,12 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
                     if (l + GW * it < REC_DWORDS) e[L_REC + l + GW * it] = fresh_record_word(l + GW * it, e + L_SPARE_HDR, lo, hi, ep + 1u);
                 if (EAGER) {
 #pragma unroll
-                    for (int it = 0; it < (WIN_ROWS * WIN_PITCH / 4 + GW - 1) / GW; ++it) {
+                    for (int it = 0; it < (WIN_DWORDS + GW - 1) / GW; ++it) {
                         const int i = l + GW * it;
-                        if (i < WIN_ROWS * WIN_PITCH / 4) { e[L_WB + i] = e[L_SPARE_WB + i]; e[L_WI + i] = e[L_SPARE_WI + i]; }
+                        if (i < WIN_DWORDS) { e[L_WB + i] = e[L_SPARE_WB + i]; e[L_WI + i] = e[L_SPARE_WI + i]; }
                     }
                 } else {
-                    load_window<GW>(l, maps + map_offset((uint32_t)env, ep + 1u), 0, W / 2, W / 2, reinterpret_cast<uint8_t*>(e + L_WB),
-                                    reinterpret_cast<uint8_t*>(e + L_WI));
+                    load_window<GW>(l, spare, 0, W / 2, W / 2, e);
                 }
 #pragma unroll
                 for (int it = 0; it < (FLOORS * MOBTAB_DWORDS + GW - 1) / GW; ++it) {
@@ -266,7 +247,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
                 }
                 clear_mob(m);
                 floor_now = 0;
-                o.wx0 = W / 2 - WIN_COLS / 2; o.wy0 = W / 2 - WIN_ROWS / 2;
+                o.wx0 = win_x0(W / 2); o.wy0 = win_y0(W / 2);
                 wave_sync();
                 write_back = true;
                 if (l == 0) list_at = la::claim_entry(ls, seq, step_block);   // the place on the list; the entry follows after the rendering
@@ -321,7 +302,7 @@ __device__ __attribute__((noinline)) void generate_world(uint8_t* slot, Lds<Worl
     const int l = threadIdx.x & 63;
 #pragma unroll 1
     for (int f = 0; f < FLOORS; ++f) {
-        worldgen_floor_block<64, PERLIN, true>(slot, s.lat, s.layout, lo, hi, env, ep, f, (uint8_t*)(uint32_t*)win_blocks, (uint8_t*)(uint32_t*)win_items, perlin_cs);
+        worldgen_floor_block<64, PERLIN, true>(slot, s.lat, s.layout, lo, hi, env, ep, f, (uint32_t*)win_blocks, (uint32_t*)win_items, perlin_cs);
         if (f == 0) {                             // the layout of floor 0 describes the whole world
             if (l < FLOORS + 1) s.words[l] = layout_word(s.layout, l);
             wave_sync();
@@ -409,7 +390,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
             uint32_t* words = e + L_SPARE_HDR;
             if (spare_ok) {
                 if (l < FLOORS + 1) words[l] = genv[SPARE_LADDER + l];
-                load_window(l, next, 0, W / 2, W / 2, reinterpret_cast<uint8_t*>(e + L_WB), reinterpret_cast<uint8_t*>(e + L_WI));
+                load_window(l, next, 0, W / 2, W / 2, e);
                 spare_ok = false;
             } else {
                 generate_world<PERLIN>(next, (Lds<WorldScratch>*)(s_gen + w), (Lds<uint32_t>*)(e + L_WB), (Lds<uint32_t>*)(e + L_WI), lo, hi, (uint32_t)env,
@@ -423,7 +404,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
             wave_sync();
             clear_mob(m);
             if (l == 0) e[L_WINKEY] = window_key(0, W / 2, W / 2);
-            o.wx0 = W / 2 - WIN_COLS / 2; o.wy0 = W / 2 - WIN_ROWS / 2;
+            o.wx0 = win_x0(W / 2); o.wy0 = win_y0(W / 2);
         }
         if (obs != nullptr) {
             aux.day = o.done ? day_fresh : day_next;
@@ -486,7 +467,7 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_reset_list(uint32_t* __restric
             wlo = pool_lo; whi = pool_hi; wenv = cx::POOL_ENV | ((cx::choice(sh.w[0], pool_size) + rank) % pool_size); wep = step_index;
         }
         worldgen_floor_block<GEN_THREADS, true>(maps + map_offset(env, ep), s_lat, s_layout, wlo, whi, wenv, wep, f,
-                                                reinterpret_cast<uint8_t*>(s_env + L_WB), reinterpret_cast<uint8_t*>(s_env + L_WI),
+                                                s_env + L_WB, s_env + L_WI,
                                                 perlin ? luts->perlin_cs : nullptr);
         if (f == 0) {
             publish_world(envs + (size_t)env * ENV_DWORDS, s_layout, lo, hi, ep, true, s_words);
@@ -494,7 +475,7 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_reset_list(uint32_t* __restric
             if (tid == 96 && !pool) la::append_after_step(ls, env / ENVS_PER_BLOCK, make_uint4(env, lo, hi, ep + 1u));
             __syncthreads();
             if (obs != nullptr && tid < 64)
-                render_env<F32>(tid, s_env, W / 2 - WIN_COLS / 2, W / 2 - WIN_ROWS / 2, 0, 0, 0, 0, luts,
+                render_env<F32>(tid, s_env, win_x0(W / 2), win_y0(W / 2), 0, 0, 0, 0, luts,
                                 obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8));
         }
         __syncthreads();
@@ -521,9 +502,9 @@ __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__
     const uint32_t pos = uniu(e[L_REC + R_POS]), ep = uniu(e[L_REC + R_EPISODE]);
     const int px = pos & 0xFF, py = (pos >> 8) & 0xFF, f = (pos >> 24) & 0xF;
     const Mob u = unpack_mob(l < NSLOT ? genv[REC_DWORDS + f * MOBTAB_DWORDS + l] : 0u);
-    load_window(l, maps + map_offset((uint32_t)env, ep), f, px, py, reinterpret_cast<uint8_t*>(e + L_WB), reinterpret_cast<uint8_t*>(e + L_WI));
+    load_window(l, maps + map_offset((uint32_t)env, ep), f, px, py, e);
     wave_sync();
-    render_env<F32, 64, FLOATS>(l, e, px - WIN_COLS / 2, py - WIN_ROWS / 2, u.alive, u.x, u.y, u.type, luts,
+    render_env<F32, 64, FLOATS>(l, e, win_x0(px), win_y0(py), u.alive, u.x, u.y, u.type, luts,
                                 obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), nullptr, FLOATS == cx::Keep::STREAM && floats_written_through(env, blockIdx.x));
 }
 

@@ -316,10 +316,14 @@ __device__ __forceinline__ void count_unlocks(int l, uint32_t* __restrict__ coun
 }
 
 // ---- per-environment LDS area (dword offsets) ----------------------------------------------------
-// Window: 11 rows x 13 columns (pitch 16 bytes) of the block map and of the item/light map
-// around the player's position at load time, one cell of margin on every side of the 9x11 view
-// so that a move of one cell needs no reload.  Cells outside the map read B_OOB / light 20.
-constexpr int WIN_ROWS = 11, WIN_COLS = 13, WIN_PITCH = 16;
+// Window: 11 rows x 16 columns of the block map and of the item/light map around the player's position
+// at load time, one cell of margin at least on every side of the 9x11 view so that a move of one cell needs no reload.
+// Its first column is a multiple of four, so that it is moved as aligned dwords, 44 of either map; the
+// sixteen columns hold the thirteen that are needed wherever these begin.  Cells outside the map read B_OOB / light 20.
+constexpr int WIN_ROWS = 11, WIN_COLS = 16, WIN_PITCH = 16, WIN_DWORDS = WIN_ROWS * WIN_PITCH / 4;
+__host__ __device__ constexpr int win_x0(int px) { return (px - (VCOLS / 2 + 1)) & ~3; }
+__host__ __device__ constexpr int win_y0(int py) { return py - WIN_ROWS / 2; }
+static_assert(WIN_COLS >= VCOLS + 2 + 3 && WIN_ROWS == VROWS + 2 && WIN_COLS == WIN_PITCH && W % 4 == 0, "a dword of a window lies inside the map or outside");
 constexpr int L_REC = 0;                         // 64 dwords
 constexpr int L_WB = 64;                         // 44 dwords: block window
 constexpr int L_WI = 108;                        // 44 dwords: item/light window

@@ -238,7 +238,7 @@ __device__ inline uint32_t cave_blocks(const CaveRule& k, uint32_t word) { retur
 // is the 8 cells [8t, 8t+8) of the floor (row t/6).  The block of floor 0 also derives the
 // ladders of every floor and the potion permutation (whole_layout), which the fresh record
 // needs, and may drop the cells around the start position into an LDS window (start_wb /
-// start_wi, 11 x 16 bytes each) for the first observation.  maps: this environment's 41472
+// start_wi, 44 dwords each) for the first observation.  maps: this environment's 41472
 // bytes.  s_lat (LAT_WORDS dwords), L: LDS scratch.  All arguments are the same for the whole block.
 // Ends with a barrier of those threads.
 // perlin_cs (with CAN_PERLIN): the gradient table; the fields of the overworld and of the caves are
@@ -256,8 +256,8 @@ __device__ inline uint32_t cave_blocks(const CaveRule& k, uint32_t word) { retur
 // anew in every call instead of being kept (and spilled) across the loop.
 template <int NT = GEN_THREADS, bool CAN_PERLIN = false, bool LOOPED = false>
 __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps, uint32_t* s_lat, GenLayout& L, uint32_t lo, uint32_t hi,
-                                            uint32_t env, uint32_t episode, int f, uint8_t* start_wb = nullptr,
-                                            uint8_t* start_wi = nullptr, const uint32_t* __restrict__ perlin_cs = nullptr,
+                                            uint32_t env, uint32_t episode, int f, uint32_t* start_wb = nullptr,
+                                            uint32_t* start_wi = nullptr, const uint32_t* __restrict__ perlin_cs = nullptr,
                                             const uint16_t* theta_f = nullptr)
 {
     const bool use_perlin = CAN_PERLIN && perlin_cs != nullptr;
@@ -478,17 +478,13 @@ __device__ __forceinline__ void worldgen_floor_block(uint8_t* __restrict__ maps,
     *reinterpret_cast<uint2*>(maps + block_off(f, x0, y)) = blocks;
     *reinterpret_cast<uint2*>(maps + il_off(f, x0, y)) = items;
     if (start_wb != nullptr && f == 0) {
-        // window of the start cell (24, 24): rows 19..29, columns 18..30
-        const int wr = y - (W / 2 - WIN_ROWS / 2);
-        if ((unsigned)wr < (unsigned)WIN_ROWS) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int wc = x0 + j - (W / 2 - WIN_COLS / 2);
-                if ((unsigned)wc < (unsigned)WIN_COLS) {
-                    start_wb[wr * WIN_PITCH + wc] = (uint8_t)((j < 4 ? blocks.x : blocks.y) >> (8 * (j & 3)));
-                    start_wi[wr * WIN_PITCH + wc] = (uint8_t)((j < 4 ? items.x : items.y) >> (8 * (j & 3)));
-                }
-            }
+        // window of the start cell (24, 24): rows 19..29, columns 16..31
+        const int wr = y - win_y0(W / 2), wc = x0 - win_x0(W / 2);
+        static_assert(win_x0(W / 2) % RUN == 0, "a run lies in the window or outside");
+        if ((unsigned)wr < (unsigned)WIN_ROWS && (unsigned)wc < (unsigned)WIN_COLS) {
+            const int at = CX_IDX(wr * (WIN_PITCH / 4) + wc / 4, WIN_DWORDS - 1);
+            start_wb[at] = blocks.x; start_wb[at + 1] = blocks.y;
+            start_wi[at] = items.x; start_wi[at + 1] = items.y;
         }
     }
     if (NT >= RUNS) break;

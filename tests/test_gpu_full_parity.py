@@ -775,6 +775,22 @@ def test_rollout_rich_scenes(cx):
     _rollout_full(cx, 90, 1, "uniform", pre=2, steps=150, post=10, prep=rich_scene)
 
 
+def test_windows_at_every_column_and_at_the_edges(cx):
+    """Windows begin at a multiple of four columns wherever the player stands, and a rollout keeps them while they cover
+    the view: every column, rows at and near the edges, players who walk."""
+    rows = (0, 1, 5, 24, 42, 46, 47)
+
+    def prep(envs):
+        for i in range(len(envs)):
+            e, f, x, y = envs[i], i % 8, i % 48, rows[(i // 48) % len(rows)]
+            e["floor"], e["px"], e["py"] = f, x, y
+            e["visited"] = (1 << (f + 1)) - 1
+            e["light"][f] = (np.arange(48)[:, None] + np.arange(48)[None, :] + i) % 21
+            e["block"][f][y], e["block"][f][:, x] = B_PATH, B_PATH
+
+    _rollout_full(cx, 48 * len(rows), 1, "skewed", pre=3, steps=24, post=3, prep=prep)
+
+
 def test_rollout_edge_cases(cx):
     # episodes of one and two steps, a single environment, a single step, a ragged last block
     _rollout_full(cx, 10, 1, "uniform", pre=2, steps=6, post=3, max_episode_steps=1)
