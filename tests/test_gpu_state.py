@@ -251,6 +251,33 @@ def test_full_boss_hit_count_stays_at_its_maximum(cx, lanes):
 
 
 @pytest.mark.parametrize("lanes", [64, 16])
+def test_full_armour_beyond_what_can_be_made(cx, lanes):
+    """An import accepts armour level 3 (crafting ends at 2): four such pieces ward off more than all physical damage, and an
+    attack then heals, as the formula has it.  Attackers of every kind: melee and shooters beside the player, projectiles."""
+    n = 24
+    gcfg = cx.default_config(cx.VARIANT_CRAFTAX, group_lanes=lanes)
+    sim, orc = cx.Craftax(n, gcfg), po.FullOracle(n, po.full_default_config(), po.FULL_OBS_U8_F32)
+    seeds = synth.seeds_for(n, 41)
+    sim.reset(seeds); orc.reset(seeds)
+    e = orc.envs
+    e["block"][:, 0, 18:31, 16:33] = GRASS
+    e["vit"][:] = 5
+    for i in range(n):
+        e["armour"][i] = [3, 3, 3, i % 4]
+        e["armour_ench"][i] = [i % 3, (i // 3) % 3, 0, 0]
+        e["sleeping"][i] = i % 2
+        melee, ranged = (0, 9, 13, 15, 17)[i % 5], (1, 12, 16, 18)[i % 4]      # zombie, lizard, troll, pigman, frost troll; skeleton, archer, elementals
+        e["mob"][i, 0, 0] = (1, 25, 24, 0, 5, 0, melee, 0)
+        e["mob"][i, 0, 3] = (1, 24, 22 + i % 2, 0, 5, 0, ranged, 0)
+        e["mob"][i, 0, 8] = (1, 22, 24, 2, 0, 0, ranged, 0)                    # flies towards the player
+    sim.import_envs(orc.envs.copy())
+    for s in range(4):
+        _step_both(sim, orc, np.zeros(n, np.int32), f"step {s}")
+    assert sim.export_envs().tobytes() == orc.envs.tobytes()
+    sim.close()
+
+
+@pytest.mark.parametrize("lanes", [64, 16])
 @pytest.mark.parametrize("layout", ["u8_f32", "f32"])
 def test_full_light_channel_holds_the_light_level_whatever_stands_there(cx, lanes, layout):
     """An import accepts every creature type in every slot.  Type 8 among the player's projectiles
