@@ -125,8 +125,8 @@ __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x0020408
 // instructions of a step expanded bits.  Measured, before the player's state was kept packed: a step of
 // 4,096 environments 18.3 -> 16.7 us, of 32,768 115 -> 110, a rollout of 64 steps and 4,096 environments
 // 897 -> 805 us.  The area covers 5,120 bytes at a time, so that five blocks of the step kernel still share
-// a compute unit.  A lane owns the cells l and l + 64; the second one lies in the second part, the first
-// one may reach into it.
+// a compute unit.  A lane owns cell l of the first part and cell LAST0 + l of the second; cell LAST0 lies in both, and has its bytes of the
+// other part beside the area, where nobody reads them, so that no byte is tested for its part.
 // For the float layout a staged byte v stands for v / 140: 140 is the 1 of a one-hot channel and 7 * level
 // the light level / 20.  Multiplying by the float nearest to 1/140 gives exactly those floats.
 constexpr int STAGE_REST = CELL_BYTES - STAGE_BYTES;
@@ -137,7 +137,8 @@ constexpr bool staged_floats_are_exact()
     return true;
 }
 static_assert(staged_floats_are_exact(), "light levels through staged bytes");
-static_assert(STAGE_BYTES % 1024 == 0 && 64 * NCHAN >= STAGE_BYTES && NCELL <= 128, "the second cell of a lane lies in the second part");
+constexpr int LAST0 = STAGE_BYTES / NCHAN, BEFORE1 = STAGE_BYTES - LAST0 * NCHAN;     // the cell on the border, its bytes in the first part
+static_assert(STAGE_BYTES % 1024 == 0 && LAST0 < 64 && NCELL - LAST0 <= 64 && BEFORE1 <= STAGE_BEFORE && NCHAN - BEFORE1 <= STAGE_BEHIND, "cells of the two parts");
 // FLOATS: how they are stored (see floats_kept); where that is STREAM, through says whether this observation is written through
 // all the same (the same for the wavefront).  Bytes are streamed.
 template <bool F32, cx::Keep FLOATS>
@@ -157,12 +158,13 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     // beyond the edge of the map the windows hold B_OOB at full light
     uint32_t il[2], block[2];
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const int cell = min(l + 64 * it, NCELL - 1), r = cell / VCOLS, at = CX_IDX(corner + r * WIN_PITCH + cell - r * VCOLS, WIN_ROWS * WIN_PITCH);
-        il[it] = wi[at];
-        block[it] = wb[at] & 63u;
+    for (int part = 0; part < 2; ++part) {
+        const int own = part == 0 ? LAST0 + 1 : NCELL - LAST0, cell = (part == 0 ? 0 : LAST0) + min(l, own - 1), r = cell / VCOLS;
+        const int at = CX_IDX(corner + r * WIN_PITCH + cell - r * VCOLS, WIN_ROWS * WIN_PITCH);
+        il[part] = wi[at];
+        block[part] = wb[at] & 63u;
+        if (l >= own) il[part] = 0u;
     }
-    if (l + 64 >= NCELL) il[1] = 0u;
     // the creature of a cell is the one in its lowest slot, and is seen where there is light
     const int vr = m_y - (py - VROWS / 2), vc = m_x - (px - VCOLS / 2), m_cell = vr * VCOLS + vc;
     const bool in_view = l < NSLOT && m_alive && (unsigned)vr < (unsigned)VROWS && (unsigned)vc < (unsigned)VCOLS;
@@ -177,23 +179,21 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     wave_sync();
     // part 0: bytes 0 .. STAGE_BYTES - 1; part 1: the rest
     auto fill = [&](int part) {
-        const uint32_t first = part == 0 ? 0u : (uint32_t)STAGE_BYTES, size = part == 0 ? (uint32_t)STAGE_BYTES : (uint32_t)STAGE_REST;
+        const uint32_t start = part == 0 ? 0u : (uint32_t)STAGE_BYTES, size = part == 0 ? (uint32_t)STAGE_BYTES : (uint32_t)STAGE_REST;
         uint4* clear = reinterpret_cast<uint4*>(stage) + l;
 #pragma unroll
         for (int k = 0; k < STAGE_BYTES / 1024; ++k) if (part == 0 || k * 1024 < STRIDE_U8 - STAGE_BYTES) clear[64 * k] = make_uint4(0u, 0u, 0u, 0u);
         wave_sync();
-        auto put = [&](uint32_t at, uint32_t v) { if (at - first < size) stage[CX_IDX(at - first, STAGE_BYTES)] = (uint8_t)v; };
-        put(m_byte, ONE);       // before the cells: an imported creature type may fall on a light channel, which holds the light level all the same
+        // before the cells: an imported creature type may fall on a light channel, which holds the light level all the same
+        if (m_byte - start < size) stage[CX_IDX(m_byte - start, STAGE_BYTES)] = (uint8_t)ONE;
         wave_sync();
-#pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            if (it == 1 && part == 0) continue;
-            if ((il[it] >> 3) != 0u) {              // cells darker than 0.05 stay blank
-                const uint32_t base = (uint32_t)((l + 64 * it) * NCHAN);
-                put(base + block[it], ONE);
-                put(base + 37u + (il[it] & 7u), ONE);
-                put(base + 82u, LIGHT * (il[it] >> 3));
-            }
+        if ((il[part] >> 3) != 0u) {                // cells darker than 0.05 stay blank
+            uint8_t* cell = stage - STAGE_BEFORE;
+            const int at = STAGE_BEFORE + l * NCHAN - (part == 0 ? 0 : BEFORE1);
+            constexpr int ROOM = STAGE_BEFORE + STAGE_BYTES + STAGE_BEHIND;
+            cell[CX_IDX(at + (int)block[part], ROOM)] = (uint8_t)ONE;
+            cell[CX_IDX(at + 37 + (int)(il[part] & 7u), ROOM)] = (uint8_t)ONE;
+            cell[CX_IDX(at + 82, ROOM)] = (uint8_t)(LIGHT * (il[part] >> 3));
         }
     };
     using cx::piece_t;
@@ -248,7 +248,7 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
         if (l < NVEC) tail[1 + l] = scalar;
         if (l >= NVEC) tail[1 + l] = 0.0f;
         if (l < 4 * (PIECES - TAIL) - 65) tail[65 + l] = 0.0f;
-        if (l == NCELL - 1 - 64) tail[0] = (float)(LIGHT * (il[1] >> 3)) * F32_UNIT;
+        if (l == NCELL - 1 - LAST0) tail[0] = (float)(LIGHT * (il[1] >> 3)) * F32_UNIT;
         wave_sync();
         constexpr int TURNS = (TAIL - HEAD) / 64, LEFT = (TAIL - HEAD) % 64;
         store(HEAD, std::integral_constant<int, TURNS>(), floats);
