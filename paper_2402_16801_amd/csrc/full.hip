@@ -173,9 +173,9 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
     for (int it = 0; it < REC_IT; ++it) rec_word[it] = 0u;
     // what the renderer looks up in tables: asked for now, used at the end of the step
     RenderAux<GW> aux;
-    fetch_scalar_specs<GW>(l, aux);
+    fetch_scalar_fields<GW>(l, aux);
     aux.lut = s_lut;
-    if (tid < LUT_FLOATS) s_lut[tid] = luts->sqrt10[tid];     // sqrt10, tenth and light20 lie one after the other
+    if (tid < LUT_FLOATS) s_lut[tid] = lut_entry(tid, luts);
     if (active) {
 #pragma unroll
         for (int it = 0; it < REC_IT; ++it) if (l + GW * it < REC_DWORDS) rec_word[it] = genv[l + GW * it];
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
     __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * L_STAGED_DWORDS];
     __shared__ WorldScratch s_gen[ENVS_PER_BLOCK];
     __shared__ float s_lut[LUT_FLOATS];
-    if (threadIdx.x < LUT_FLOATS) s_lut[threadIdx.x] = luts->sqrt10[threadIdx.x];   // sqrt10, tenth and light20 lie one after the other
+    if (threadIdx.x < LUT_FLOATS) s_lut[threadIdx.x] = lut_entry((int)threadIdx.x, luts);
     __syncthreads();
     bool spare_ok;           // the world of the next episode is complete in the other map slot
     MobRegs m;               // the mob table of the current floor; in memory it is brought up to date when the player leaves the floor and at the end
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
         uint32_t* e = s_env + w * L_STAGED_DWORDS;
         uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
         RenderAux<64> aux;
-        fetch_scalar_specs<64>(l, aux);
+        fetch_scalar_fields<64>(l, aux);
         aux.lut = s_lut;
         const int action = uni(action_next);
         if (t + 1 < steps) action_next = actions[(size_t)(t + 1) * p.n + env];

@@ -13,7 +13,7 @@ namespace cf {
 // integer becomes a float.  Direction, daylight and "floor cleared" are handled apart.
 enum Conv : int { CV_SQRT10 = 0, CV_TENTH, CV_HALF, CV_QUARTER, CV_RAW, CV_SPECIAL };
 struct ScalarSpec { uint8_t word, shift, mask, conv; };
-__device__ __constant__ const ScalarSpec SCALARS[NVEC] = {
+constexpr ScalarSpec SCALAR_ROWS[NVEC] = {
     { R_INV, 0, 255, CV_SQRT10 }, { R_INV, 8, 255, CV_SQRT10 }, { R_INV, 16, 255, CV_SQRT10 }, { R_INV, 24, 255, CV_SQRT10 },
     { R_INV + 1, 0, 255, CV_SQRT10 }, { R_INV + 1, 8, 255, CV_SQRT10 }, { R_INV + 1, 16, 255, CV_SQRT10 }, { R_INV + 1, 24, 255, CV_SQRT10 },
     { R_INV + 2, 0, 255, CV_SQRT10 }, { R_INV + 2, 8, 255, CV_SQRT10 },
@@ -42,10 +42,30 @@ __device__ __constant__ const ScalarSpec SCALARS[NVEC] = {
     { R_FLAGS, 17, 1, CV_RAW },        // boss vulnerable
 };
 
+// The same as the renderer of a step reads it, in one dword: the field (record word, shift, width) and where its value's float lies in
+// the tables in LDS (LUT_FLOATS below), which go up to `limit` there: a lookup without branches.
+constexpr int LUT_SQRT10 = 0, LUT_TENTH = 100, LUT_LIGHT20 = 132, LUT_HALF = 164, LUT_QUARTER = 168, LUT_RAW = 176, LUT_FLOATS = 180, LUT_COPIED = 164;
+struct ScalarTables { ScalarSpec rows[NVEC]; uint32_t fields[NVEC]; };
+constexpr ScalarTables scalar_tables()
+{
+    ScalarTables t{};
+    for (int i = 0; i < NVEC; ++i) {
+        const ScalarSpec s = SCALAR_ROWS[i];
+        uint32_t width = 0;
+        while ((s.mask >> width) != 0) ++width;
+        const uint32_t at = s.conv == CV_SQRT10 ? LUT_SQRT10 : s.conv == CV_TENTH ? LUT_TENTH : s.conv == CV_HALF ? LUT_HALF : s.conv == CV_QUARTER ? LUT_QUARTER : LUT_RAW;
+        const uint32_t limit = s.conv == CV_SQRT10 ? 99 : s.conv == CV_TENTH ? 31 : s.conv == CV_QUARTER ? 7 : 3;
+        t.rows[i] = s;
+        t.fields[i] = (uint32_t)s.word | ((uint32_t)s.shift << 6) | (width << 11) | (at << 16) | (limit << 24);
+    }
+    return t;
+}
+__device__ __constant__ const ScalarTables SCALARS = scalar_tables();
+
 // scalar `i` of the observation from the packed record in LDS
 __device__ __forceinline__ float scalar_value(int i, const uint32_t* rec, const Luts* __restrict__ luts)
 {
-    const ScalarSpec s = SCALARS[i];
+    const ScalarSpec s = SCALARS.rows[i];
     const uint32_t raw = (rec[s.word] >> s.shift) & s.mask;
     if (s.conv == CV_SQRT10) return luts->sqrt10[min(raw, 99u)];
     if (s.conv == CV_TENTH) return luts->tenth[min(raw, 31u)];
@@ -61,40 +81,35 @@ __device__ __forceinline__ float scalar_value(int i, const uint32_t* rec, const 
 }
 
 // What the step kernels fetch ahead of the renderer, so that it waits for no table in memory: the
-// specification of the scalars this lane writes (scalar l, l + GW, ...), the small conversion tables
-// (sqrt10, tenth, light20, as they lie in Luts) copied to LDS, and the daylight value of the
-// observation's phase.
-constexpr int LUT_FLOATS = 100 + 32 + 32;
+// fields of the scalars this lane writes (scalar l, l + GW, ...), the small conversion tables
+// in LDS, and the daylight value of the observation's phase.
 template <int GW>
 struct RenderAux {
-    uint32_t spec[(NVEC + 1 + GW - 1) / GW];    // ScalarSpec of scalar l + GW * it, as four bytes
-    const float* lut;                           // LDS: sqrt10[100], tenth[32], light20[32]
+    uint32_t field[(NVEC + 1 + GW - 1) / GW];   // of scalar l + GW * it
+    const float* lut;                           // LDS: sqrt10[100], tenth[32], light20[32], n / 2, n / 4, n
     float day;                                  // daylight[phase of the rendered state]
 };
 template <int GW>
-__device__ __forceinline__ void fetch_scalar_specs(int l, RenderAux<GW>& aux)
+__device__ __forceinline__ void fetch_scalar_fields(int l, RenderAux<GW>& aux)
 {
 #pragma unroll
-    for (int it = 0; it < (NVEC + 1 + GW - 1) / GW; ++it) {
-        const int i = l + GW * it;
-        aux.spec[it] = i < NVEC ? *reinterpret_cast<const uint32_t*>(&SCALARS[i]) : 0u;
-    }
+    for (int it = 0; it < (NVEC + 1 + GW - 1) / GW; ++it) aux.field[it] = SCALARS.fields[min(l + GW * it, NVEC - 1)];
 }
-static_assert(sizeof(ScalarSpec) == 4, "a scalar specification travels as one dword");
-__device__ __forceinline__ float scalar_value_fast(int i, uint32_t spec, const uint32_t* rec, const float* lut, float day)
+// entry i < LUT_FLOATS of the tables in LDS
+__device__ __forceinline__ float lut_entry(int i, const Luts* __restrict__ luts)
 {
-    const uint32_t word = spec & 0xFFu, shift = (spec >> 8) & 0xFFu, mask = (spec >> 16) & 0xFFu, conv = spec >> 24;
-    const uint32_t raw = (rec[word] >> shift) & mask;
-    if (conv == CV_SQRT10) return lut[min(raw, 99u)];
-    if (conv == CV_TENTH) return lut[100 + min(raw, 31u)];
-    if (conv == CV_HALF) return (float)raw * 0.5f;
-    if (conv == CV_QUARTER) return (float)raw * 0.25f;
-    if (conv == CV_RAW) return (float)raw;
-    if (i >= 39 && i < 43) return (int)raw == i - 38 ? 1.0f : 0.0f;
-    if (i == 43) return day;
-    const int f = (int)raw;
-    const int kills = (int)((rec[R_KILLS + (f >> 2)] >> (8 * (f & 3))) & 0xFFu);
-    return (f == 0 || kills >= KILLS_TO_CLEAR) ? 1.0f : 0.0f;
+    if (i < LUT_COPIED) return luts->sqrt10[i];          // sqrt10, tenth and light20 lie one after the other
+    return i < LUT_QUARTER ? (float)(i - LUT_HALF) * 0.5f : i < LUT_RAW ? (float)(i - LUT_QUARTER) * 0.25f : (float)(i - LUT_RAW);
+}
+__device__ __forceinline__ float scalar_value_fast(int i, uint32_t field, const uint32_t* rec, const float* lut, float day)
+{
+    const uint32_t raw = __builtin_amdgcn_ubfe(rec[field & 63u], (field >> 6) & 31u, (field >> 11) & 31u);
+    float v = lut[((field >> 16) & 0xFFu) + min(raw, field >> 24)];
+    // facing, daylight, floor cleared (the overworld always, deeper floors after enough kills)
+    if (i >= 39 && i < 43) v = (int)raw == i - 38 ? 1.0f : 0.0f;
+    if (i == 43) v = day;
+    if (i == 49) v = raw == 0u || ((rec[R_KILLS + ((raw >> 2) & 3u)] >> (8 * (raw & 3u))) & 0xFFu) >= (uint32_t)KILLS_TO_CLEAR ? 1.0f : 0.0f;
+    return v;
 }
 
 // Observation channel of the creature in slot k (class by slot range, type slot by creature).
@@ -175,7 +190,7 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     wave_sync();
     if (in_view && cre[CX_IDX(m_cell, NCELL)] == (uint32_t)l && (wi[CX_IDX(corner + vr * WIN_PITCH + vc, WIN_ROWS * WIN_PITCH)] >> 3) != 0)
         m_byte = (uint32_t)(m_cell * NCHAN + creature_channel(l, m_type));
-    const float scalar = l >= NVEC ? 0.0f : (aux != nullptr ? scalar_value_fast(l, aux->spec[0], rec, aux->lut, aux->day) : scalar_value(l, rec, luts));
+    const float scalar = l >= NVEC ? 0.0f : (aux != nullptr ? scalar_value_fast(l, aux->field[0], rec, aux->lut, aux->day) : scalar_value(l, rec, luts));
     wave_sync();
     // part 0: bytes 0 .. STAGE_BYTES - 1; part 1: the rest
     auto fill = [&](int part) {
@@ -323,7 +338,7 @@ __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int w
 #pragma unroll
     for (int it = 0; it < (NVEC + 1 + GW - 1) / GW; ++it) {
         const int i = l + GW * it;
-        if (i < NVEC + 1) vec[i] = i >= NVEC ? 0.0f : (aux != nullptr ? scalar_value_fast(i, aux->spec[it], rec, aux->lut, aux->day) : scalar_value(i, rec, luts));
+        if (i < NVEC + 1) vec[i] = i >= NVEC ? 0.0f : (aux != nullptr ? scalar_value_fast(i, aux->field[it], rec, aux->lut, aux->day) : scalar_value(i, rec, luts));
     }
     wave_sync();
     auto set_bit = [&](int i) { atomicOr(&bits[CX_IDX(i >> 5, 260)], 1u << (i & 31)); };
@@ -390,7 +405,7 @@ __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int w
             const uint32_t b16 = j < 520 ? (bits[j >> 1] >> ((j & 1) * 16)) & 0xFFFFu : 0u;
             int at, lv;
             light_in_piece(j, &at, &lv);
-            const float lf = aux != nullptr ? aux->lut[132 + lv] : luts->light20[lv];
+            const float lf = aux != nullptr ? aux->lut[LUT_LIGHT20 + lv] : luts->light20[lv];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float v[4];
