@@ -192,9 +192,10 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         for (int it = 0; it < REC_IT; ++it) if (l + GW * it < REC_DWORDS) e[L_REC + l + GW * it] = rec_word[it];
         const int action = G::uni(action_raw);
         wave_sync();
-        const uint32_t ep = G::uniu(e[L_REC + R_EPISODE]), lo = G::uniu(e[L_REC + R_SEED_LO]), hi = G::uniu(e[L_REC + R_SEED_HI]);
+        const RecordWords<GW> old{ e + L_REC, rec_word[0] };
+        const uint32_t ep = old[R_EPISODE], lo = old[R_SEED_LO], hi = old[R_SEED_HI];
         // daylight of the state that will be rendered: the next phase, or phase 0 of a fresh episode
-        const uint32_t phase_now = G::uniu(e[L_REC + R_MANA]) >> 16;
+        const uint32_t phase_now = old[R_MANA] >> 16;
         const float day_next = luts->daylight[phase_now + 1u == p.day_length ? 0u : phase_now + 1u], day_fresh = luts->daylight[0];
         MobRegs m;
         uint32_t qw;
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
             if (l < FLOORS + 1) e[L_SPARE_HDR + l] = hdr;
             if (EAGER) spare_window.park(l, e + L_SPARE_WB, e + L_SPARE_WI);
         };
-        StepOut o = step_env<GW>(l, (uint32_t)env, e, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, park);
+        StepOut o = step_env<GW>(l, (uint32_t)env, e, old, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, park);
         if (l == 0) { reward[env] = o.reward; done[env] = o.done ? 1 : 0; }
 #pragma unroll
         for (int aw = 0; aw < 3; ++aw) count_unlocks<GW>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, aw, o.unlocked[aw]);
@@ -370,13 +371,14 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
         aux.lut = s_lut;
         const int action = uni(action_next);
         if (t + 1 < steps) action_next = actions[(size_t)(t + 1) * p.n + env];
-        const uint32_t ep = uniu(e[L_REC + R_EPISODE]);
+        const RecordWords<64> old{ e + L_REC, e[L_REC + l] };
+        const uint32_t ep = old[R_EPISODE];
         // daylight of the state that will be rendered: the next phase, or phase 0 of a fresh episode
-        const uint32_t phase_now = uniu(e[L_REC + R_MANA]) >> 16;
+        const uint32_t phase_now = old[R_MANA] >> 16;
         const float day_next = luts->daylight[phase_now + 1u == p.day_length ? 0u : phase_now + 1u], day_fresh = luts->daylight[0];
         uint32_t qw;
         Player P;
-        StepOut o = step_env<64, true>(l, (uint32_t)env, e, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, []() {});
+        StepOut o = step_env<64, true>(l, (uint32_t)env, e, old, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, []() {});
         if (l == 0) { reward[(size_t)t * p.n + env] = o.reward; done[(size_t)t * p.n + env] = o.done ? 1 : 0; }
 #pragma unroll
         for (int aw = 0; aw < 3; ++aw) count_unlocks<64>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, aw, o.unlocked[aw]);
@@ -385,7 +387,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
             if (l < NPLANT) e[L_REC + R_PLANT + l] = qw;
             wave_sync();
         } else {
-            const uint32_t lo = uniu(e[L_REC + R_SEED_LO]), hi = uniu(e[L_REC + R_SEED_HI]);
+            const uint32_t lo = old[R_SEED_LO], hi = old[R_SEED_HI];
             uint8_t* next = maps + map_offset((uint32_t)env, ep + 1u);
             uint32_t* words = e + L_SPARE_HDR;
             if (spare_ok) {

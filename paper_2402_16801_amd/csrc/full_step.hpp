@@ -47,24 +47,32 @@ struct Player {
 
 __device__ inline int sext8(uint32_t v) { return (int)(int8_t)(v & 0xFFu); }
 
-template <int GW = 64>
-__device__ __forceinline__ void unpack_player(const uint32_t* rec, Player& P)
+// The record as it was before the step: a whole wavefront holds word l of it in lane l, from where a word is one
+// instruction away; a group of lanes reads it in LDS.
+template <int GW>
+struct RecordWords {
+    const uint32_t* rec;
+    uint32_t mine;
+    __device__ __forceinline__ uint32_t operator[](int i) const { return GW == 64 ? (uint32_t)lane_get((int)mine, i) : rec[i]; }
+};
+static_assert(REC_DWORDS == 64, "a record word per lane");
+template <int GW>
+__device__ __forceinline__ void unpack_player(const RecordWords<GW>& old, Player& P)
 {
-    using G = Lanes<GW>;
-    const uint32_t pos = G::uniu(rec[R_POS]);
+    const uint32_t pos = old[R_POS];
     P.px = pos & 0xFF; P.py = (pos >> 8) & 0xFF; P.dir = (pos >> 16) & 0xFF; P.floor = (pos >> 24) & 0xF;
-    P.f = __builtin_bit_cast(Flags, G::uniu(rec[R_FLAGS]));
-    P.a = __builtin_bit_cast(Attr, G::uniu(rec[R_ATTR]));
-    P.inv.lo = (uint64_t)G::uniu(rec[R_INV]) | ((uint64_t)G::uniu(rec[R_INV + 1]) << 32);
-    P.inv.hi = (uint64_t)G::uniu(rec[R_INV + 2]) | ((uint64_t)G::uniu(rec[R_POT]) << 32);
-    const uint32_t v = G::uniu(rec[R_VIT]);
-    P.mana_word = G::uniu(rec[R_MANA]);
+    P.f = __builtin_bit_cast(Flags, old[R_FLAGS]);
+    P.a = __builtin_bit_cast(Attr, old[R_ATTR]);
+    P.inv.lo = (uint64_t)old[R_INV] | ((uint64_t)old[R_INV + 1] << 32);
+    P.inv.hi = (uint64_t)old[R_INV + 2] | ((uint64_t)old[R_POT] << 32);
+    const uint32_t v = old[R_VIT];
+    P.mana_word = old[R_MANA];
 #pragma unroll
     for (int i = 0; i < 4; ++i) P.vit[i] = (v >> (8 * i)) & 0xFF;
     P.vit[V_MANA] = P.mana_word & 0xFF;
-    P.cnt = G::uniu(rec[R_CNT]);
+    P.cnt = old[R_CNT];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) P.ach[i] = G::uniu(rec[R_ACH + i]);
+    for (int i = 0; i < 3; ++i) P.ach[i] = old[R_ACH + i];
 }
 
 // packs everything that can change back into the LDS copy of the record (one lane writes); t: the new time
@@ -156,7 +164,7 @@ struct StepOut { bool done; float reward; int wx0, wy0; uint32_t t; uint32_t unl
 
 enum Intent : int { N_NONE = 0, N_DAMAGE, N_DAMAGE_DIE, N_DIE, N_MOVE, N_SHOOT, N_FLY, N_PPROJ };
 
-// e: this wave's LDS area with the record loaded.  genv: the environment's 1024-byte block in
+// e: this wave's LDS area with the record loaded; old: the record once more, as it was.  genv: the environment's 1024-byte block in
 // HBM.  maps: its floors.  m, qw: this lane's mob slot (current floor) and plant word.
 // KEEP (kernels that keep an environment from step to step): m comes in as the last step left it, and the
 // windows are only loaded if those in LDS are not the ones around the player's current position (a step to the side
@@ -167,7 +175,7 @@ enum Intent : int { N_NONE = 0, N_DAMAGE, N_DAMAGE_DIE, N_DIE, N_MOVE, N_SHOOT, 
 // wave waits for them (the caller parks data it fetched earlier there).
 __device__ inline uint32_t window_key(int f, int px, int py) { return 0x80000000u | ((uint32_t)win_x0(px) & 0xFFu) | ((uint32_t)py << 8) | ((uint32_t)f << 16); }
 template <int GW = 64, bool KEEP = false, typename AfterLoad>
-__device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uint32_t* e, uint32_t* __restrict__ genv,
+__device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uint32_t* e, const RecordWords<GW>& old, uint32_t* __restrict__ genv,
                                    uint8_t* __restrict__ maps, const Luts* __restrict__ luts, const int action_in,
                                    const Params& p, MobRegs& m, uint32_t& qw, Player& P, AfterLoad&& after_load)
 {
@@ -175,14 +183,14 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
     uint32_t* rec = e + L_REC;
     uint8_t* wb = reinterpret_cast<uint8_t*>(e + L_WB);
     uint8_t* wi = reinterpret_cast<uint8_t*>(e + L_WI);
-    unpack_player<GW>(rec, P);
+    unpack_player<GW>(old, P);
     const int phase = (int)(P.mana_word >> 16);
     // asked for now, needed in the spawn phase: by then it has long arrived
     const uint32_t zombie_thr = luts->zombie_thr[phase];
-    const uint32_t seed_lo = G::uniu(rec[R_SEED_LO]), seed_hi = G::uniu(rec[R_SEED_HI]);
+    const uint32_t seed_lo = old[R_SEED_LO], seed_hi = old[R_SEED_HI];
 
     // this step's draws: lane k computes Philox block k = (move k, decision k, plant-eaten k, misc k)
-    const U4 rnd = philox4x32_10(env, G::uniu(rec[R_T]), G::uniu(rec[R_EPISODE]), (cx::DOM_STEP << 16) | (uint32_t)(l < NSLOT ? l : 0), seed_lo, seed_hi);
+    const U4 rnd = philox4x32_10(env, old[R_T], old[R_EPISODE], (cx::DOM_STEP << 16) | (uint32_t)(l < NSLOT ? l : 0), seed_lo, seed_hi);
     auto misc = [&](int i) { return (uint32_t)G::get((int)rnd.w[3], i); };
 
     // mob table of the current floor and the window around the player
@@ -773,7 +781,7 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
     int gained = 0;
     StepOut o;
 #pragma unroll
-    for (int w = 0; w < 3; ++w) o.unlocked[w] = P.ach[w] & ~G::uniu(rec[R_ACH + w]);      // the record still holds the state before the step
+    for (int w = 0; w < 3; ++w) o.unlocked[w] = P.ach[w] & ~old[R_ACH + w];
     if ((o.unlocked[0] | o.unlocked[1] | o.unlocked[2]) != 0u) {
 #pragma unroll
         for (int w = 0; w < 3; ++w) {
@@ -783,7 +791,7 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
         }
     }
     o.reward = (float)(10 * gained + (P.vit[V_HEALTH] - health0)) * 0.1f;
-    o.t = G::uniu(rec[R_T]) + 1u;
+    o.t = old[R_T] + 1u;
     o.done = P.vit[V_HEALTH] <= 0 || o.t >= p.max_episode_steps;
     o.wx0 = wx0; o.wy0 = wy0;
     return o;
