@@ -279,8 +279,9 @@ constexpr uint32_t WALKABLE_MASK = (1u << BK_GRASS) | (1u << BK_SAND) | (1u << B
 constexpr uint32_t FLYABLE_MASK = WALKABLE_MASK | (1u << BK_WATER) | (1u << BK_LAVA);
 __device__ inline bool walkable_ground(int b) { return (WALKABLE_MASK >> b) & 1u; }
 __device__ inline bool arrow_flyable(int b) { return (FLYABLE_MASK >> b) & 1u; }
-__device__ inline int dir_dx(int d) { return d == 1 ? -1 : (d == 2 ? 1 : 0); }
-__device__ inline int dir_dy(int d) { return d == 3 ? -1 : (d == 4 ? 1 : 0); }
+// what a step in direction d (0 none, 1 left, 2 right, 3 up, 4 down; up to 7) adds to x and y: a field of two bits per direction
+__device__ inline int dir_dx(int d) { return (int)(((3u << 2) | (1u << 4)) << (30 - 2 * d)) >> 30; }
+__device__ inline int dir_dy(int d) { return (int)(((3u << 6) | (1u << 8)) << (30 - 2 * d)) >> 30; }
 __device__ inline int iabs(int v) { return v < 0 ? -v : v; }
 
 // Per-environment LDS area: record, map window, one-hot bit staging, scalar vector.

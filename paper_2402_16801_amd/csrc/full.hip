@@ -194,11 +194,9 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
         wave_sync();
         const RecordWords<GW> old{ e + L_REC, rec_word[0] };
         const uint32_t ep = old[R_EPISODE], lo = old[R_SEED_LO], hi = old[R_SEED_HI];
-        // daylight of the state that will be rendered: the next phase, or phase 0 of a fresh episode
-        const uint32_t phase_now = old[R_MANA] >> 16;
-        const float day_next = luts->daylight[phase_now + 1u == p.day_length ? 0u : phase_now + 1u], day_fresh = luts->daylight[0];
+        const uint32_t table = day_table<GW>(l, old[R_MANA] >> 16, p.day_length, luts);
         MobRegs m;
-        uint32_t qw;
+        uint32_t qw, kept = 0u;
         Player P;
         // the window of the spare world's start position comes with the current window
         const uint8_t* spare = maps + map_offset((uint32_t)env, ep + 1u);
@@ -209,7 +207,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
             if (l < FLOORS + 1) e[L_SPARE_HDR + l] = hdr;
             if (EAGER) spare_window.park(l, e + L_SPARE_WB, e + L_SPARE_WI);
         };
-        StepOut o = step_env<GW>(l, (uint32_t)env, e, old, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, park);
+        StepOut o = step_env<GW>(l, (uint32_t)env, e, old, genv, maps + map_offset((uint32_t)env, ep), action, table, p, m, qw, P, kept, park);
         if (l == 0) { reward[env] = o.reward; done[env] = o.done ? 1 : 0; }
 #pragma unroll
         for (int aw = 0; aw < 3; ++aw) count_unlocks<GW>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, aw, o.unlocked[aw]);
@@ -262,7 +260,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
             for (int it = 0; it < REC_IT; ++it) if (l + GW * it < REC_DWORDS) genv[l + GW * it] = e[L_REC + l + GW * it];
             if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
             if (!DRAW && obs != nullptr) {
-                aux.day = o.done ? day_fresh : day_next;
+                aux.day = day_of<GW>(table, o.done);
                 render_env<F32, GW, FLOATS>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux,
                                             FLOATS == cx::Keep::STREAM && floats_written_through(env, blockIdx.x));
             }
@@ -335,22 +333,24 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
     __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * L_STAGED_DWORDS];
     __shared__ WorldScratch s_gen[ENVS_PER_BLOCK];
     __shared__ float s_lut[LUT_FLOATS];
+    __shared__ uint32_t s_field[64];
     if (threadIdx.x < LUT_FLOATS) s_lut[threadIdx.x] = lut_entry((int)threadIdx.x, luts);
+    if (threadIdx.x < 64) s_field[threadIdx.x] = SCALARS.fields[min((int)threadIdx.x, NVEC - 1)];
     __syncthreads();
     bool spare_ok;           // the world of the next episode is complete in the other map slot
     MobRegs m;               // the mob table of the current floor; in memory it is brought up to date when the player leaves the floor and at the end
-    int action_next;         // fetched a step ahead
+    int action;              // fetched a step ahead
+    uint32_t kept = 0u;      // window_key of the windows in LDS
     {
         const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
         if (env >= p.n) return;
         uint32_t* e = s_env + w * L_STAGED_DWORDS;
         const uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
         e[L_REC + l] = genv[l];
-        if (l == 0) e[L_WINKEY] = 0u;
         wave_sync();
         const uint32_t ep = uniu(e[L_REC + R_EPISODE]);
         m.w = l < NSLOT ? genv[REC_DWORDS + (uniu(e[L_REC + R_POS]) >> 24) * MOBTAB_DWORDS + l] : 0u;
-        action_next = actions[env];
+        action = uni(actions[env]);
         constexpr uint64_t ALL = (1ull << NTAG) - 1ull;
         spare_ok = (__ballot(l < NTAG && ls.tags[(size_t)env * NTAG + (l < NTAG ? l : 0)].x == ep + 1u) & ALL) == ALL;
     }
@@ -366,19 +366,16 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
         const int env = blockIdx.x * ENVS_PER_BLOCK + w;
         uint32_t* e = s_env + w * L_STAGED_DWORDS;
         uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
-        RenderAux<64> aux;
-        fetch_scalar_fields<64>(l, aux);
-        aux.lut = s_lut;
-        const int action = uni(action_next);
-        if (t + 1 < steps) action_next = actions[(size_t)(t + 1) * p.n + env];
+        // The next action, asked for through a lane: a load to a scalar register would be waited for with the next access to LDS.
+        int action_lane = 0;
+        if (t + 1 < steps) action_lane = actions[(size_t)(t + 1) * p.n + blockIdx.x * ENVS_PER_BLOCK + (tid_t >> 6)];
         const RecordWords<64> old{ e + L_REC, e[L_REC + l] };
         const uint32_t ep = old[R_EPISODE];
-        // daylight of the state that will be rendered: the next phase, or phase 0 of a fresh episode
-        const uint32_t phase_now = old[R_MANA] >> 16;
-        const float day_next = luts->daylight[phase_now + 1u == p.day_length ? 0u : phase_now + 1u], day_fresh = luts->daylight[0];
+        const uint32_t table = day_table<64>(l, old[R_MANA] >> 16, p.day_length, luts);
         uint32_t qw;
         Player P;
-        StepOut o = step_env<64, true>(l, (uint32_t)env, e, old, genv, maps + map_offset((uint32_t)env, ep), luts, action, p, m, qw, P, []() {});
+        StepOut o = step_env<64, true>(l, (uint32_t)env, e, old, genv, maps + map_offset((uint32_t)env, ep), action, table, p, m, qw, P, kept, []() {});
+        action = uni(action_lane);          // arrived with what the step has read
         if (l == 0) { reward[(size_t)t * p.n + env] = o.reward; done[(size_t)t * p.n + env] = o.done ? 1 : 0; }
 #pragma unroll
         for (int aw = 0; aw < 3; ++aw) count_unlocks<64>(l, p.unlocks + (size_t)env * UNLOCK_STRIDE, aw, o.unlocked[aw]);
@@ -405,11 +402,14 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
             for (int i = l; i < FLOORS * MOBTAB_DWORDS; i += 64) genv[REC_DWORDS + i] = 0u;
             wave_sync();
             clear_mob(m);
-            if (l == 0) e[L_WINKEY] = window_key(0, W / 2, W / 2);
+            kept = window_key(0, W / 2, W / 2);
             o.wx0 = win_x0(W / 2); o.wy0 = win_y0(W / 2);
         }
         if (obs != nullptr) {
-            aux.day = o.done ? day_fresh : day_next;
+            RenderAux<64> aux;
+            aux.field[0] = s_field[l];
+            aux.lut = s_lut;
+            aux.day = day_of<64>(table, o.done);
             render_env<F32>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs_t + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux);
         }
         wave_sync();

@@ -338,9 +338,9 @@ constexpr int L_SPARE_HDR = 734;                 // 10 dwords: ladders and potio
 constexpr int L_ENV_DWORDS = 744;
 // A whole wavefront stages observation bytes from L_STAGE on (see render_staged), over everything but the
 // record and the windows, with room on either side for what a cell on the border of two parts has in the other
-// part.  L_WINKEY (rollout): what the windows were loaded for (see window_key), or 0.
+// part.
 constexpr int STAGE_BEFORE = 64, STAGE_BYTES = 5120, STAGE_BEHIND = 32;
-constexpr int L_STAGE = 152 + STAGE_BEFORE / 4, L_WINKEY = L_STAGE + (STAGE_BYTES + STAGE_BEHIND) / 4, L_STAGED_DWORDS = L_WINKEY + 4;
+constexpr int L_STAGE = 152 + STAGE_BEFORE / 4, L_STAGED_DWORDS = L_STAGE + (STAGE_BYTES + STAGE_BEHIND) / 4;
 static_assert(L_STAGED_DWORDS >= L_ENV_DWORDS && L_STAGE % 4 == 0 && L_STAGED_DWORDS % 4 == 0, "staging area");
 constexpr int ENVS_PER_BLOCK = 4, BLOCK = 256;
 

@@ -9,6 +9,7 @@
 
 namespace cf {
 
+constexpr int VEC_DAY = 43;      // the scalar that is the daylight
 // Where scalar i of the observation comes from: record word, shift, mask, and how the raw
 // integer becomes a float.  Direction, daylight and "floor cleared" are handled apart.
 enum Conv : int { CV_SQRT10 = 0, CV_TENTH, CV_HALF, CV_QUARTER, CV_RAW, CV_SPECIAL };
@@ -73,7 +74,7 @@ __device__ __forceinline__ float scalar_value(int i, const uint32_t* rec, const 
     if (s.conv == CV_QUARTER) return (float)raw * 0.25f;
     if (s.conv == CV_RAW) return (float)raw;
     if (i >= 39 && i < 43) return (int)raw == i - 38 ? 1.0f : 0.0f;
-    if (i == 43) return luts->daylight[rec[R_MANA] >> 16];
+    if (i == VEC_DAY) return luts->daylight[rec[R_MANA] >> 16];
     // floor cleared: the overworld always, deeper floors after enough kills
     const int f = (int)raw;
     const int kills = (int)((rec[R_KILLS + (f >> 2)] >> (8 * (f & 3))) & 0xFFu);
@@ -87,8 +88,21 @@ template <int GW>
 struct RenderAux {
     uint32_t field[(NVEC + 1 + GW - 1) / GW];   // of scalar l + GW * it
     const float* lut;                           // LDS: sqrt10[100], tenth[32], light20[32], n / 2, n / 4, n
-    float day;                                  // daylight[phase of the rendered state]
+    float day;                                  // in the lane that writes it: daylight[phase of the rendered state]
 };
+// What a step looks up by day phase, in one load: lane 0 gets the zombie threshold of the phase, the lane that writes the daylight
+// that of the next phase, lane 1 that of a fresh episode.  (Loads to scalar registers, one for each, held up the step: they are waited for
+// with the next access to LDS.)
+template <int GW>
+__device__ __forceinline__ uint32_t day_table(int l, uint32_t phase, uint32_t day_length, const Luts* __restrict__ luts)
+{
+    static_assert(VEC_DAY % GW > 1 && offsetof(Luts, zombie_thr) == offsetof(Luts, daylight) + 4 * MAX_DAY, "lanes of their own, one table after the other");
+    const uint32_t next = phase + 1u == day_length ? 0u : phase + 1u;
+    return reinterpret_cast<const uint32_t*>(luts->daylight)[l == 0 ? MAX_DAY + phase : l == VEC_DAY % GW ? next : 0u];
+}
+// the daylight of the rendered state in the lane that writes it
+template <int GW>
+__device__ __forceinline__ float day_of(uint32_t table, bool fresh) { return __uint_as_float(fresh ? (uint32_t)Lanes<GW>::get((int)table, 1) : table); }
 template <int GW>
 __device__ __forceinline__ void fetch_scalar_fields(int l, RenderAux<GW>& aux)
 {
@@ -107,7 +121,7 @@ __device__ __forceinline__ float scalar_value_fast(int i, uint32_t field, const 
     float v = lut[((field >> 16) & 0xFFu) + min(raw, field >> 24)];
     // facing, daylight, floor cleared (the overworld always, deeper floors after enough kills)
     if (i >= 39 && i < 43) v = (int)raw == i - 38 ? 1.0f : 0.0f;
-    if (i == 43) v = day;
+    if (i == VEC_DAY) v = day;
     if (i == 49) v = raw == 0u || ((rec[R_KILLS + ((raw >> 2) & 3u)] >> (8 * (raw & 3u))) & 0xFFu) >= (uint32_t)KILLS_TO_CLEAR ? 1.0f : 0.0f;
     return v;
 }

@@ -102,9 +102,6 @@ __device__ inline int cap_health(const Player& P) { return 9 + (5 * ((int)P.a.st
 __device__ inline int cap_need(const Player& P) { return 9 + 2 * ((int)P.a.dex - 1); }
 __device__ inline int cap_mana(const Player& P) { return 9 + 3 * ((int)P.a.intel - 1); }
 __device__ inline int toward(int dx, int dy) { const bool along = iabs(dx) >= iabs(dy); return (along ? 2 : 4) + ((along ? dx : dy) >> 31); }   // 1 left, 2 right, 3 up, 4 down
-// what a step in direction d adds to x and y, for a direction that differs from lane to lane: a field of two bits per direction
-__device__ inline int lane_dx(int d) { return __builtin_amdgcn_sbfe((3 << 2) | (1 << 4), 2 * d, 2); }
-__device__ inline int lane_dy(int d) { return __builtin_amdgcn_sbfe((3 << 6) | (1 << 8), 2 * d, 2); }
 // damage after defence: every element is reduced by its own percentage, integer parts
 __device__ inline int through(int ap, int af, int ai, int dp, int df, int di)
 {
@@ -167,17 +164,18 @@ enum Intent : int { N_NONE = 0, N_DAMAGE, N_DAMAGE_DIE, N_DIE, N_MOVE, N_SHOOT, 
 // e: this wave's LDS area with the record loaded; old: the record once more, as it was.  genv: the environment's 1024-byte block in
 // HBM.  maps: its floors.  m, qw: this lane's mob slot (current floor) and plant word.
 // KEEP (kernels that keep an environment from step to step): m comes in as the last step left it, and the
-// windows are only loaded if those in LDS are not the ones around the player's current position (a step to the side
+// windows are only loaded if those in LDS (kept: their window_key, or 0) are not the ones around the player's current position (a step to the side
 // leaves them as they are three times out of four);
 // every change a step makes to the maps inside the windows is made in the windows too, so kept ones
 // equal fresh ones.
+// table: lane 0 holds the zombie threshold of the day phase (see day_table).
 // after_load: called once the loads of the current window have been issued and stored, before the
 // wave waits for them (the caller parks data it fetched earlier there).
 __device__ inline uint32_t window_key(int f, int px, int py) { return 0x80000000u | ((uint32_t)win_x0(px) & 0xFFu) | ((uint32_t)py << 8) | ((uint32_t)f << 16); }
 template <int GW = 64, bool KEEP = false, typename AfterLoad>
 __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uint32_t* e, const RecordWords<GW>& old, uint32_t* __restrict__ genv,
-                                   uint8_t* __restrict__ maps, const Luts* __restrict__ luts, const int action_in,
-                                   const Params& p, MobRegs& m, uint32_t& qw, Player& P, AfterLoad&& after_load)
+                                   uint8_t* __restrict__ maps, const int action_in,
+                                   const uint32_t table, const Params& p, MobRegs& m, uint32_t& qw, Player& P, uint32_t& kept, AfterLoad&& after_load)
 {
     using G = Lanes<GW>;
     uint32_t* rec = e + L_REC;
@@ -185,8 +183,6 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
     uint8_t* wi = reinterpret_cast<uint8_t*>(e + L_WI);
     unpack_player<GW>(old, P);
     const int phase = (int)(P.mana_word >> 16);
-    // asked for now, needed in the spawn phase: by then it has long arrived
-    const uint32_t zombie_thr = luts->zombie_thr[phase];
     const uint32_t seed_lo = old[R_SEED_LO], seed_hi = old[R_SEED_HI];
 
     // this step's draws: lane k computes Philox block k = (move k, decision k, plant-eaten k, misc k)
@@ -200,9 +196,9 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
     int q_block = B_INVALID;
     if (qw & 1u) q_block = maps[block_off(0, (int)((qw >> 1) & 63u), (int)((qw >> 7) & 63u))];
     int wx0 = win_x0(P.px), wy0 = win_y0(P.py);
-    if (!KEEP || G::uniu(e[L_WINKEY]) != window_key(P.floor, P.px, P.py)) {
+    if (!KEEP || kept != window_key(P.floor, P.px, P.py)) {
         load_window<GW>(l, maps, P.floor, P.px, P.py, e);
-        if (KEEP && l == 0) e[L_WINKEY] = window_key(P.floor, P.px, P.py);
+        kept = window_key(P.floor, P.px, P.py);
     }
     after_load();
     wave_sync();
@@ -311,7 +307,7 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
         wave_sync();
         wx0 = win_x0(x); wy0 = win_y0(y);
         load_window<GW>(l, maps, nf, x, y, e);
-        if (KEEP && l == 0) e[L_WINKEY] = window_key(nf, x, y);
+        kept = window_key(nf, x, y);
         wave_sync();
     };
     auto stock = [&](int item, int n) { const int have = P.inv.get(item); P.inv.add(item, min(INV_MAX, have + n) - have); };
@@ -598,7 +594,7 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
                 tdir = m.dir();
                 kind = l < S_PPROJ0 ? N_FLY : N_PPROJ;
             }
-            tx = mx + lane_dx(tdir); ty = my + lane_dy(tdir);
+            tx = mx + dir_dx(tdir); ty = my + dir_dy(tdir);
             at_player = tx == P.px && ty == P.py;
             if (kind == N_FLY && at_player) kind = N_DAMAGE_DIE;
             if (kind == N_MOVE || kind == N_SHOOT || kind == N_FLY || kind == N_PPROJ) {
@@ -614,7 +610,7 @@ __device__ __forceinline__ StepOut step_env(const int l, const uint32_t env, uin
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 // overworld: zombies by darkness
-                const uint32_t thr = j == 0 ? (f == 0 ? zombie_thr : P_MELEE_SPAWN) : (j == 1 ? (f == 0 ? P_SKELETON_SPAWN : P_RANGED_SPAWN) : P_PASSIVE_SPAWN);
+                const uint32_t thr = j == 0 ? (f == 0 ? (uint32_t)G::get((int)table, 0) : P_MELEE_SPAWN) : (j == 1 ? (f == 0 ? P_SKELETON_SPAWN : P_RANGED_SPAWN) : P_PASSIVE_SPAWN);
                 if (type[j] >= 0 && misc(3 * j + 2) < thr) attempts |= 1u << j;
             }
         }
