@@ -26,7 +26,12 @@ using la::counter;
 using la::ENTRY_VOID;
 using la::NSUB;
 
-constexpr int EAGER_SPARE_ENVS = 8192;   // up to here a step fetches the spare world's start window in advance (see kf_step)
+// Up to here a step fetches the spare world's start window in advance (EAGER, see kf_step).  Steps with bytes: while the chip holds all blocks of such a
+// launch at once (six per compute unit, regeneration blocks among them, with Perlin noise five); beyond, the instance without, of which it holds
+// eight and six, is ahead.  us, with / without: 1,024 10.0 / 10.4, 4,096 13.2 / 13.5, 5,000 14.9 / 15.1, 5,300 17.2 / 15.8, 7,000 20.4 / 18.0,
+// 8,192 21.9 / 21.9; Perlin noise 4,096 13.7 / 13.6, 4,500 16.7 / 14.9, 5,800 19.1 / 18.8, 8,000 22.1 / 21.3.
+constexpr int EAGER_SPARE_ENVS = 8192;
+constexpr int eager_spare_envs(bool bytes, bool perlin, int lanes) { return !bytes || lanes != 64 ? EAGER_SPARE_ENVS : perlin ? 4096 : 5120; }
 constexpr int RESET_SLOTS = 64;    // environments served at once by kf_reset_list (nine blocks each)
 constexpr int MAX_ENVS_PER_STEP_BLOCK = 16;   // a step block holds 4 environments (a wavefront each) or 16 (16 lanes each)
 constexpr int REGEN_BLOCKS = 256;  // regeneration blocks at the head of the step grid: with 1,024 step blocks (4,096 environments) they fill the chip exactly
@@ -132,8 +137,12 @@ __global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_dr
 // DRAW (pixels): a block holds one environment, which its first wavefront steps, and all its wavefronts then draw the picture, from the
 // record and mobs in LDS.
 // FLOATS: see floats_kept.
+// Blocks per compute unit that the compiler is bounded to.  Without EAGER the chip is full, and every further block hides waits: eight,
+// the most that registers and LDS allow where worlds are of value noise (32,768 environments, bytes: 79.1 us with six, 76.3 with seven, 74.7
+// with eight).  Below that the launch waits for its slowest wavefronts, which spill fewer scalars with more registers (4,096: 13.4 us, 13.6).
+constexpr int step_bound(bool bytes, bool eager, bool perlin, int lanes) { return lanes != 64 ? 2 : eager || !bytes ? 5 : perlin ? 6 : 8; }
 template <bool F32, bool EAGER, bool PERLIN, int GW, bool DRAW = false, cx::Keep FLOATS = cx::Keep::THROUGH>
-__global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
+__global__ __launch_bounds__(BLOCK, step_bound(!F32 && !DRAW, EAGER, PERLIN, GW)) void kf_step(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                 const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                 uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                 uint8_t* __restrict__ done, Lists ls, Params p, int regen_blocks)
@@ -141,10 +150,11 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
     using G = Lanes<GW>;
     static_assert(!DRAW || (GW == 64 && !F32), "pictures are drawn behind a step by a wavefront");
     constexpr int EPB = DRAW ? 1 : BLOCK / GW;               // environments per block
+    constexpr bool HALVES = !F32 && !DRAW && !EAGER && GW == 64;
     constexpr int REC_IT = REC_DWORDS / GW > 0 ? REC_DWORDS / GW : 1;
     static_assert(REC_DWORDS % GW == 0 || GW > REC_DWORDS, "the record is moved in whole turns of the group");
     static_assert(GW >= MOBTAB_DWORDS && GW >= NTAG && GW >= FLOORS + 1, "a group holds a mob table, the tags and the header in one turn");
-    constexpr int ENV_DWORDS_LDS = GW == 64 ? L_STAGED_DWORDS : L_ENV_DWORDS;
+    constexpr int ENV_DWORDS_LDS = GW == 64 ? staged_dwords<HALVES> : L_ENV_DWORDS;
     constexpr int REGEN_DWORDS = REGEN_PREFIX_AT + NSUB;
     __shared__ __attribute__((aligned(16))) uint32_t s_env[EPB * ENV_DWORDS_LDS > REGEN_DWORDS ? EPB * ENV_DWORDS_LDS : REGEN_DWORDS];
     __shared__ float s_lut[LUT_FLOATS];
@@ -261,7 +271,7 @@ __global__ __launch_bounds__(BLOCK, GW == 64 ? 5 : 2) void kf_step(uint32_t* __r
             if (l < MOBTAB_DWORDS) genv[REC_DWORDS + floor_now * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
             if (!DRAW && obs != nullptr) {
                 aux.day = day_of<GW>(table, o.done);
-                render_env<F32, GW, FLOATS>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux,
+                render_env<F32, GW, FLOATS, HALVES>(l, e, o.wx0, o.wy0, m.alive(), m.x(), m.y(), m.type(), luts, obs + (size_t)env * (F32 ? STRIDE_F32 : STRIDE_U8), &aux,
                                             FLOATS == cx::Keep::STREAM && floats_written_through(env, blockIdx.x));
             }
         }
@@ -330,7 +340,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
                                                        uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                        uint8_t* __restrict__ done, Lists ls, Params p, int steps)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * L_STAGED_DWORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * staged_dwords<false>];
     __shared__ WorldScratch s_gen[ENVS_PER_BLOCK];
     __shared__ float s_lut[LUT_FLOATS];
     __shared__ uint32_t s_field[64];
@@ -344,7 +354,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
     {
         const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
         if (env >= p.n) return;
-        uint32_t* e = s_env + w * L_STAGED_DWORDS;
+        uint32_t* e = s_env + w * staged_dwords<false>;
         const uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
         e[L_REC + l] = genv[l];
         wave_sync();
@@ -364,7 +374,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
         asm volatile("" : "+s"(obs_t));
         const int w = uni(tid_t >> 6), l = tid_t & 63;
         const int env = blockIdx.x * ENVS_PER_BLOCK + w;
-        uint32_t* e = s_env + w * L_STAGED_DWORDS;
+        uint32_t* e = s_env + w * staged_dwords<false>;
         uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
         // The next action, asked for through a lane: a load to a scalar register would be waited for with the next access to LDS.
         int action_lane = 0;
@@ -416,7 +426,7 @@ __global__ __launch_bounds__(BLOCK, 4) void kf_rollout(uint32_t* __restrict__ en
     }
     // the record back; the world after this episode, if it is owed, for the regeneration launch
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, env = blockIdx.x * ENVS_PER_BLOCK + w;
-    const uint32_t* e = s_env + w * L_STAGED_DWORDS;
+    const uint32_t* e = s_env + w * staged_dwords<false>;
     uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
     genv[l] = e[L_REC + l];
     if (l < MOBTAB_DWORDS) genv[REC_DWORDS + (uniu(e[L_REC + R_POS]) >> 24) * MOBTAB_DWORDS + l] = l < NSLOT ? m.w : 0u;
@@ -436,7 +446,7 @@ __global__ __launch_bounds__(GEN_THREADS) void kf_reset_list(uint32_t* __restric
     __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
-    __shared__ __attribute__((aligned(16))) uint32_t s_env[L_STAGED_DWORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[staged_dwords<false>];
     __shared__ uint32_t s_rank[(GEN_THREADS + 63) / 64];
     // Optimistic resets (pool != 0): the world comes from this step's pool.  The step kernel has
     // already advanced the launch number: it is the index of the step just done + 2.  The pool is
@@ -493,11 +503,11 @@ template <bool F32, cx::Keep FLOATS = cx::Keep::THROUGH>
 __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__ envs, const uint8_t* __restrict__ maps,
                                                    const Luts* __restrict__ luts, uint8_t* __restrict__ obs, int n)
 {
-    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * L_STAGED_DWORDS];
+    __shared__ __attribute__((aligned(16))) uint32_t s_env[ENVS_PER_BLOCK * staged_dwords<false>];
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int env = blockIdx.x * ENVS_PER_BLOCK + w;
     if (env >= n) return;
-    uint32_t* e = s_env + w * L_STAGED_DWORDS;
+    uint32_t* e = s_env + w * staged_dwords<false>;
     const uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
     e[L_REC + l] = genv[l];
     wave_sync();
@@ -1055,8 +1065,9 @@ int step(void* state, const craftax_config* cfg, int n, const int32_t* actions, 
     // are no spare worlds and every finished episode is served there, its world depending on who
     // else finished
     const bool slow = p.max_episode_steps == 1u || pool != 0 || serve_slow;
-    const bool eager = n <= EAGER_SPARE_ENVS && pool == 0;
     const int perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN ? 1 : 0;
+    const bool bytes = cfg->obs_mode != CRAFTAX_OBS_SYM_F32 && cfg->obs_mode != CRAFTAX_OBS_PIXELS_F32;
+    const bool eager = n <= eager_spare_envs(bytes, perlin != 0, gw) && pool == 0;
     if (cfg->obs_mode == CRAFTAX_OBS_PIXELS_F32) {
         if (o != nullptr && !slow) {
             // step and picture in one launch, whatever the lanes of a step without

@@ -339,9 +339,11 @@ constexpr int L_ENV_DWORDS = 744;
 // A whole wavefront stages observation bytes from L_STAGE on (see render_staged), over everything but the
 // record and the windows, with room on either side for what a cell on the border of two parts has in the other
 // part.
-constexpr int STAGE_BEFORE = 64, STAGE_BYTES = 5120, STAGE_BEHIND = 32;
-constexpr int L_STAGE = 152 + STAGE_BEFORE / 4, L_STAGED_DWORDS = L_STAGE + (STAGE_BYTES + STAGE_BEHIND) / 4;
-static_assert(L_STAGED_DWORDS >= L_ENV_DWORDS && L_STAGE % 4 == 0 && L_STAGED_DWORDS % 4 == 0, "staging area");
+constexpr int STAGE_BEFORE = 80, L_STAGE = 152 + STAGE_BEFORE / 4;
+template <bool HALVES> constexpr int stage_bytes = HALVES ? STRIDE_U8 / 2 : 5120;
+template <bool HALVES> constexpr int stage_behind = HALVES ? 16 : 32;
+template <bool HALVES> constexpr int staged_dwords = L_STAGE + (stage_bytes<HALVES> + stage_behind<HALVES>) / 4;
+static_assert(staged_dwords<true> >= L_ENV_DWORDS && staged_dwords<false> >= L_ENV_DWORDS && L_STAGE % 4 == 0 && staged_dwords<true> % 4 == 0 && staged_dwords<false> % 4 == 0, "staging area");
 constexpr int ENVS_PER_BLOCK = 4, BLOCK = 256;
 
 __device__ inline void wave_sync()

@@ -142,7 +142,7 @@ __device__ inline int creature_channel(int k, int type)
 // one-hot nibble -> four bytes of 0/1
 __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x00204081u) & 0x01010101u; }
 
-// The observation of one environment by a whole wavefront.  e: its LDS area (L_STAGED_DWORDS) with the
+// The observation of one environment by a whole wavefront.  e: its LDS area (staged_dwords<HALVES>) with the
 // packed record (current) and the two windows with origin (wx0, wy0) on the current floor; m_*:
 // this lane's mob slot.  F32 = false: writes the 8448-byte layout; F32 = true: writes float[8268]
 // (+ zero padding to 33152 bytes).
@@ -153,12 +153,11 @@ __device__ inline uint32_t spread4(uint32_t nibble) { return (nibble * 0x0020408
 // (the channels as single bits, every piece expanded from 16 of them) a quarter of the vector
 // instructions of a step expanded bits.  Measured, before the player's state was kept packed: a step of
 // 4,096 environments 18.3 -> 16.7 us, of 32,768 115 -> 110, a rollout of 64 steps and 4,096 environments
-// 897 -> 805 us.  The area covers 5,120 bytes at a time, so that five blocks of the step kernel still share
-// a compute unit.  A lane owns cell l of the first part and cell LAST0 + l of the second; cell LAST0 lies in both, and has its bytes of the
+// 897 -> 805 us.  The area covers 5,120 bytes at a time, or (HALVES) half of them, with which eight blocks of the step kernel share
+// a compute unit (see step_bound); that takes a store more (rollout of 64 steps and 4,096 environments 537 us, 547 by halves).  A lane owns cell l of the first part and cell LAST0 + l of the second; cell LAST0 lies in both, and has its bytes of the
 // other part beside the area, where nobody reads them, so that no byte is tested for its part.
 // For the float layout a staged byte v stands for v / 140: 140 is the 1 of a one-hot channel and 7 * level
 // the light level / 20.  Multiplying by the float nearest to 1/140 gives exactly those floats.
-constexpr int STAGE_REST = CELL_BYTES - STAGE_BYTES;
 constexpr float F32_UNIT = 1.0f / 140.0f;
 constexpr bool staged_floats_are_exact()
 {
@@ -166,11 +165,14 @@ constexpr bool staged_floats_are_exact()
     return true;
 }
 static_assert(staged_floats_are_exact(), "light levels through staged bytes");
-constexpr int LAST0 = STAGE_BYTES / NCHAN, BEFORE1 = STAGE_BYTES - LAST0 * NCHAN;     // the cell on the border, its bytes in the first part
-static_assert(STAGE_BYTES % 1024 == 0 && LAST0 < 64 && NCELL - LAST0 <= 64 && BEFORE1 <= STAGE_BEFORE && NCHAN - BEFORE1 <= STAGE_BEHIND, "cells of the two parts");
+template <bool HALVES>
+struct Parts {
+    static constexpr int HEAD = stage_bytes<HALVES>, LAST0 = HEAD / NCHAN, BEFORE1 = HEAD - LAST0 * NCHAN;     // bytes of the first part, the cell on the border, its bytes there
+    static_assert(HEAD % 128 == 0 && STRIDE_U8 - HEAD <= HEAD && LAST0 < 64 && NCELL - LAST0 <= 64 && BEFORE1 <= STAGE_BEFORE && NCHAN - BEFORE1 <= stage_behind<HALVES>, "cells of the two parts");
+};
 // FLOATS: how they are stored (see floats_kept); where that is STREAM, through says whether this observation is written through
 // all the same (the same for the wavefront).  Bytes are streamed.
-template <bool F32, cx::Keep FLOATS>
+template <bool F32, cx::Keep FLOATS, bool HALVES>
 __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const int wx0, const int wy0, const int m_alive, const int m_x,
                                               const int m_y, const int m_type, const Luts* __restrict__ luts, uint8_t* __restrict__ out,
                                               const RenderAux<64>* aux, const bool through)
@@ -181,6 +183,8 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     uint32_t* cre = e + L_CRE;
     uint8_t* stage = reinterpret_cast<uint8_t*>(e + L_STAGE);
     constexpr uint32_t ONE = F32 ? 140u : 1u, LIGHT = F32 ? 7u : 1u;
+    constexpr int STAGE_BYTES = Parts<HALVES>::HEAD, LAST0 = Parts<HALVES>::LAST0, BEFORE1 = Parts<HALVES>::BEFORE1;
+    static_assert(!F32 || !HALVES, "a turn of floats is 64 pieces");
     const uint32_t pos = uniu(rec[R_POS]);
     const int px = pos & 0xFF, py = (pos >> 8) & 0xFF;
     const int corner = (py - VROWS / 2 - wy0) * WIN_PITCH + px - VCOLS / 2 - wx0;    // upper left cell of the view in the windows
@@ -208,10 +212,11 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
     wave_sync();
     // part 0: bytes 0 .. STAGE_BYTES - 1; part 1: the rest
     auto fill = [&](int part) {
-        const uint32_t start = part == 0 ? 0u : (uint32_t)STAGE_BYTES, size = part == 0 ? (uint32_t)STAGE_BYTES : (uint32_t)STAGE_REST;
+        const uint32_t start = part == 0 ? 0u : (uint32_t)STAGE_BYTES, size = part == 0 ? (uint32_t)STAGE_BYTES : (uint32_t)(CELL_BYTES - STAGE_BYTES);
         uint4* clear = reinterpret_cast<uint4*>(stage) + l;
 #pragma unroll
-        for (int k = 0; k < STAGE_BYTES / 1024; ++k) if (part == 0 || k * 1024 < STRIDE_U8 - STAGE_BYTES) clear[64 * k] = make_uint4(0u, 0u, 0u, 0u);
+        for (int k = 0; k < (STAGE_BYTES + 1023) / 1024; ++k)
+            if ((part == 0 || k * 1024 < STRIDE_U8 - STAGE_BYTES) && (64 * k + 64 <= STAGE_BYTES / 16 || l < STAGE_BYTES / 16 - 64 * k)) clear[64 * k] = make_uint4(0u, 0u, 0u, 0u);
         wave_sync();
         // before the cells: an imported creature type may fall on a light channel, which holds the light level all the same
         if (m_byte - start < size) stage[CX_IDX(m_byte - start, STAGE_BYTES)] = (uint8_t)ONE;
@@ -219,28 +224,31 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
         if ((il[part] >> 3) != 0u) {                // cells darker than 0.05 stay blank
             uint8_t* cell = stage - STAGE_BEFORE;
             const int at = STAGE_BEFORE + l * NCHAN - (part == 0 ? 0 : BEFORE1);
-            constexpr int ROOM = STAGE_BEFORE + STAGE_BYTES + STAGE_BEHIND;
+            constexpr int ROOM = STAGE_BEFORE + STAGE_BYTES + stage_behind<HALVES>;
             cell[CX_IDX(at + (int)block[part], ROOM)] = (uint8_t)ONE;
             cell[CX_IDX(at + 37 + (int)(il[part] & 7u), ROOM)] = (uint8_t)ONE;
             cell[CX_IDX(at + 82, ROOM)] = (uint8_t)(LIGHT * (il[part] >> 3));
         }
     };
     using cx::piece_t;
-    if (!F32) {
+    if constexpr (!F32) {
         piece_t* dst = reinterpret_cast<piece_t*>(out) + l;
         const piece_t* src = reinterpret_cast<const piece_t*>(stage) + l;
         constexpr int PIECES = STRIDE_U8 / 16, HEAD = STAGE_BYTES / 16;
+        // 16-byte streaming stores
+        auto store = [&](int first, int pieces) {
+#pragma unroll
+            for (int k = 0; k < (pieces + 63) / 64; ++k)
+                if (64 * k + 64 <= pieces || l < pieces - 64 * k) __builtin_nontemporal_store(src[64 * k], dst + first + 64 * k);
+        };
         fill(0);
         wave_sync();
-#pragma unroll
-        for (int k = 0; k < HEAD / 64; ++k) __builtin_nontemporal_store(src[64 * k], dst + 64 * k);   // 16-byte streaming stores
+        store(0, HEAD);
         wave_sync();
         fill(1);
         if (l < NVEC) reinterpret_cast<float*>(stage + (VEC_OFFSET - STAGE_BYTES))[l] = scalar;
         wave_sync();
-#pragma unroll
-        for (int k = 0; k < (PIECES - HEAD + 63) / 64; ++k)
-            if (64 * k + 64 <= PIECES - HEAD || l < PIECES - HEAD - 64 * k) __builtin_nontemporal_store(src[64 * k], dst + HEAD + 64 * k);
+        store(HEAD, PIECES - HEAD);
     } else {
         const uint32_t* src = reinterpret_cast<const uint32_t*>(stage) + l;
         auto floats = [&](int k) {
@@ -267,7 +275,7 @@ __device__ __forceinline__ void render_staged(const int l, uint32_t* e, const in
         };
         // pieces of four floats; from TAIL on they hold scalars (after one last light level)
         constexpr int PIECES = STRIDE_F32 / 16, HEAD = STAGE_BYTES / 4, TAIL = CELL_BYTES / 4, TAIL_AT = 3328;
-        static_assert(TAIL_AT % 16 == 0 && TAIL_AT >= STRIDE_U8 - STAGE_BYTES && TAIL_AT + 16 * (PIECES - TAIL) <= STAGE_BYTES && CELL_BYTES == 4 * TAIL + 1, "tail of the float layout");
+        static_assert(HEAD % 64 == 0 && TAIL_AT % 16 == 0 && TAIL_AT >= STRIDE_U8 - STAGE_BYTES && TAIL_AT + 16 * (PIECES - TAIL) <= STAGE_BYTES && CELL_BYTES == 4 * TAIL + 1, "tail of the float layout");
         fill(0);
         wave_sync();
         store(0, std::integral_constant<int, HEAD / 64>(), floats);
@@ -317,12 +325,12 @@ __device__ inline bool floats_written_through(int env, uint32_t block) { return 
 // one-hot bytes are staged as single bits (a few LDS atomics per cell) next to a light level per cell;
 // every lane then expands 16 bits at a time into one 16-byte piece of the output.
 // GW: lanes that render this environment (see Lanes); l: the calling lane's number among them.  FLOATS, through: see render_staged.
-template <bool F32, int GW = 64, cx::Keep FLOATS = cx::Keep::THROUGH>
+template <bool F32, int GW = 64, cx::Keep FLOATS = cx::Keep::THROUGH, bool HALVES = false>
 __device__ __forceinline__ void render_env(const int l, uint32_t* e, const int wx0, const int wy0, const int m_alive, const int m_x,
                                   const int m_y, const int m_type, const Luts* __restrict__ luts, uint8_t* __restrict__ out,
                                   const RenderAux<GW>* aux = nullptr, const bool through = false)
 {
-    if constexpr (GW == 64) { render_staged<F32, FLOATS>(l, e, wx0, wy0, m_alive, m_x, m_y, m_type, luts, out, aux, through); return; } else {
+    if constexpr (GW == 64) { render_staged<F32, FLOATS, HALVES>(l, e, wx0, wy0, m_alive, m_x, m_y, m_type, luts, out, aux, through); return; } else {
     using G = Lanes<GW>;
     const uint32_t* rec = e + L_REC;
     const uint8_t* wb = reinterpret_cast<const uint8_t*>(e + L_WB);

@@ -456,6 +456,13 @@ def test_full_ragged_counts(cx, n):
     run_full(cx, n, 120, kind="skewed", seed_base=50 + n)
 
 
+@pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 5120), (po.WORLDGEN_VALUE, 5121), (po.WORLDGEN_PERLIN, 4096), (po.WORLDGEN_PERLIN, 4097)])
+def test_full_steps_with_and_without_the_spare_window_fetched_ahead(cx, worldgen, n):
+    """The two instances of the byte step on either side of the line between them, with episodes that end in the spare world."""
+    finished, _, _ = run_full(cx, n, 14, sample=np.unique(np.r_[0:n:61, n - 3:n]), kind="skewed", max_episode_steps=5, worldgen=worldgen)
+    assert finished > 100
+
+
 def test_full_caps_and_short_episodes(cx):
     """Reduced mob caps, no plants, a 38-step day and a 60-step episode cap: many truncations."""
     finished, _, _ = run_full(cx, 40, 400, kind="skewed", cap_melee=1, cap_ranged=0, cap_passive=2, cap_plant=0, day_length=38,
