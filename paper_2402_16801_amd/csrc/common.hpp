@@ -232,20 +232,50 @@ struct Grp {
         const uint32_t half = (lane & 32u) ? (uint32_t)(m >> 32) : (uint32_t)m;
         return __builtin_amdgcn_ubfe(half, lane & 31u & ~(uint32_t)(G - 1), (uint32_t)G);
     }
-    // value of lane src_lane_in_group of this group.  Four lanes are a DPP quad: a lane number
-    // that the compiler knows (the unrolled loops over slots) turns into one quad-broadcast move
+    // value of lane src_lane_in_group of this group.  A lane number that the compiler knows (the unrolled loops over slots) turns
+    // into a move across lanes (four lanes are a DPP quad, sixteen a row, eight half a row, which takes two moves)
     // instead of a trip through the LDS permute unit.
+    template <int L>
+    __device__ static inline int lane_of_group(int v)
+    {
+        if constexpr (G == 4) return __builtin_amdgcn_mov_dpp(v, 0x55 * (L & 3), 0xF, 0xF, true);          // quad_perm
+        else {
+            constexpr int ROW_NEWBCAST = 0x150;
+            if constexpr (G == 16) return __builtin_amdgcn_mov_dpp(v, ROW_NEWBCAST + L, 0xF, 0xF, true);
+            const int low = __builtin_amdgcn_update_dpp(v, v, ROW_NEWBCAST + (L & 7), 0xF, 0x3, false);      // lanes 0..7 of the row
+            return __builtin_amdgcn_update_dpp(low, v, ROW_NEWBCAST + 8 + (L & 7), 0xF, 0xC, false);         // lanes 8..15
+        }
+    }
     __device__ static inline int shfl(int v, int src_lane_in_group)
     {
-        if (G == 4 && __builtin_constant_p(src_lane_in_group)) {
+        if (__builtin_constant_p(src_lane_in_group)) {
             switch (src_lane_in_group) {
-            case 0: return __builtin_amdgcn_mov_dpp(v, 0x00, 0xF, 0xF, true);
-            case 1: return __builtin_amdgcn_mov_dpp(v, 0x55, 0xF, 0xF, true);
-            case 2: return __builtin_amdgcn_mov_dpp(v, 0xAA, 0xF, 0xF, true);
-            default: return __builtin_amdgcn_mov_dpp(v, 0xFF, 0xF, 0xF, true);
+            case 0: return lane_of_group<0>(v);   case 1: return lane_of_group<1>(v);   case 2: return lane_of_group<2>(v);   case 3: return lane_of_group<3>(v);
+            case 4: return lane_of_group<4>(v);   case 5: return lane_of_group<5>(v);   case 6: return lane_of_group<6>(v);   case 7: return lane_of_group<7>(v);
+            case 8: return lane_of_group<8>(v);   case 9: return lane_of_group<9>(v);   case 10: return lane_of_group<10>(v); case 11: return lane_of_group<11>(v);
+            case 12: return lane_of_group<12>(v); case 13: return lane_of_group<13>(v); case 14: return lane_of_group<14>(v); default: return lane_of_group<15>(v);
             }
         }
         return __shfl(v, src_lane_in_group, G);
+    }
+    // bit i (i < G) = predicate of lane i of any group of the wavefront; the same for the whole wavefront
+    __device__ static inline uint32_t any_of_wave(bool pred)
+    {
+        const uint64_t m = __ballot(pred);
+        uint32_t a = (uint32_t)m | (uint32_t)(m >> 32);
+        a |= a >> 16;
+        if (G <= 8) a |= a >> 8;
+        if (G <= 4) a |= a >> 4;
+        return a;
+    }
+    // sum over the lanes of this group
+    __device__ static inline int sum(int v)
+    {
+        v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);                    // quad_perm 1 0 3 2
+        v += __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);                    // quad_perm 2 3 0 1
+        if (G >= 8) v += __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true);       // row_half_mirror
+        if (G >= 16) v += __builtin_amdgcn_mov_dpp(v, 0x140, 0xF, 0xF, true);      // row_mirror
+        return v;
     }
 };
 

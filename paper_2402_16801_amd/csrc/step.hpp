@@ -151,6 +151,10 @@ __device__ __forceinline__ StepOut step_env(int l, uint32_t env, uint32_t* e, ui
     // the window load fetches anyway (any other fixed cell would cost a line of its own)
     const int idle_cell = map_index(px0, py0);
     const int woff = (px0 - WIN_COLS / 2) & 3;      // where window column 0 sits in a row
+    // asked for with the window, since the spawn candidates' cells wait for it; not where a step of four lanes has the registers of
+    // five blocks per compute unit only (65,536 environments 42.4 us, 43.3 so)
+    constexpr bool THR_AHEAD = G != 4 || KEEP_WIN;
+    const uint32_t thr_ahead = THR_AHEAD ? luts->zombie_thr[w_vit >> 16] >> 20 : 0u;
     int vit[4], cnt[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) { vit[i] = (w_vit >> (4 * i)) & 15; cnt[i] = (int)(int8_t)(w_cnt >> (8 * i)); }
@@ -313,9 +317,6 @@ __device__ __forceinline__ StepOut step_env(int l, uint32_t env, uint32_t* e, ui
     const uint32_t pkey = cell_key(px, py);
 
     // ---- phase 2: mobs.  Intent of each slot from its own state, the player and its draws ----
-    // packed intent: kind | ok<<3 | at_player<<4 | target key<<8 | direction<<24
-    int packed[NSM];
-    int n_attack = 0, n_arrow = 0;
     int kind_[NSM], ndir_[NSM], tx_[NSM], ty_[NSM], tb_[NSM];
 #pragma unroll
     for (int s = 0; s < NSM; ++s) {
@@ -372,7 +373,7 @@ __device__ __forceinline__ StepOut step_env(int l, uint32_t env, uint32_t* e, ui
         const int dx = (int)(((sp_w & 1023u) * 31u) >> 10) - 15;
         const int dy = (int)((((sp_w >> 10) & 1023u) * 31u) >> 10) - 15;
         const uint32_t sp_p = sp_w >> 20;
-        const uint32_t thr = j == 0 ? luts->zombie_thr[phase] >> 20 : (j == 1 ? P_COW_SPAWN : P_SKELETON_SPAWN);
+        const uint32_t thr = j == 0 ? (THR_AHEAD ? thr_ahead : luts->zombie_thr[phase] >> 20) : (j == 1 ? P_COW_SPAWN : P_SKELETON_SPAWN);
         const int sx = px + dx, sy = py + dy;
         // a candidate only if the probability draw passes too: most attempts end here, and the
         // terrain byte (a whole cache line of traffic) is then not fetched at all
@@ -381,72 +382,81 @@ __device__ __forceinline__ StepOut step_env(int l, uint32_t env, uint32_t* e, ui
         sp_b[j] = (int)map[sp_cand[j] ? map_index(sx, sy) : idle_cell];
         if (!sp_cand[j]) sp_b[j] = BK_OOB;
     }
+    uint32_t tkey[NSM];              // target cell
+    uint32_t at[NSM];                // the slot's cell as it moves (0: empty); bits 13 and up of its word stay behind in mw
+    uint32_t acting[NSM], shooting[NSM];   // bit i: slot i + s * G of any group of the wavefront moves or shoots / shoots
+    bool moves[NSM], flies_on[NSM], shoots[NSM];
+    int damage = 0;
 #pragma unroll
     for (int s = 0; s < NSM; ++s) {
         const int kind = kind_[s], tx = tx_[s], ty = ty_[s];
         const bool t_in = in_map(tx, ty);
         int tb = (kind != K_NONE && kind != K_ATTACK && t_in) ? tb_[s] : (int)BK_OOB;
         if (ty * MAPW + tx == modcell && t_in) tb = modval;
-        const uint32_t tkey = cell_key(tx & 63, ty & 63);
-        const bool at_player = t_in && tkey == pkey;
-        const bool t_ok = t_in && (kind == K_MOVE ? walkable_ground(tb) : (kind == K_MOVE_PATH ? tb == BK_PATH : arrow_flyable(tb)));
-        packed[s] = kind | ((int)t_ok << 3) | ((int)at_player << 4) | (int)(tkey << 8) | (ndir_[s] << 24);
-        n_attack += __popc(Gr::ballot(kind == K_ATTACK));
-        n_arrow += __popc(Gr::ballot((kind == K_SHOOT || kind == K_FLY) && at_player));
+        tkey[s] = cell_key(tx & 63, ty & 63);
+        const bool at_player = t_in && tkey[s] == pkey;
+        const bool t_ok = t_in && !at_player && (kind == K_MOVE ? walkable_ground(tb) : (kind == K_MOVE_PATH ? tb == BK_PATH : arrow_flyable(tb)));
+        // what stops a slot whatever the others do is decided here; an arrow that is stopped still holds its cell until its turn
+        moves[s] = (kind == K_MOVE || kind == K_MOVE_PATH) && t_ok;
+        shoots[s] = kind == K_SHOOT && t_ok;
+        flies_on[s] = t_ok;
+        acting[s] = Gr::any_of_wave(moves[s] || shoots[s] || kind == K_FLY);
+        shooting[s] = Gr::any_of_wave(shoots[s]);
+        damage += kind == K_ATTACK ? (sleeping ? DMG_ZOMBIE_SLEEP : DMG_ZOMBIE) : ((kind == K_SHOOT || kind == K_FLY) && at_player ? DMG_ARROW : 0);
+        at[s] = mw[s] & KEY_MASK;
     }
-
-    const int damage = n_attack * (sleeping ? DMG_ZOMBIE_SLEEP : DMG_ZOMBIE) + n_arrow * DMG_ARROW;
+    damage = Gr::sum(damage);
 
     // Moves resolve one slot at a time in the order zombies, cows, arrows, skeletons; each sees
     // the positions left by the slots before it.  An arrow shot now first flies next step.
     // The slot index is a compile-time constant here, so each iteration only carries the code
-    // of its own mob type, and a wave-wide vote skips slots that are idle in all its groups.
+    // of its own mob type, and slots that are idle in all groups of the wavefront are skipped.  The slot's lane knows what the slot wants;
+    // the others only need its target, to look for it among the cells they hold.  A chain of twelve: with the targets by way of the
+    // LDS permute unit, whose answer each turn waited for, a vote per slot and the whole intent broadcast, a step of 4,096 environments took
+    // 8.7 us, now 7.95, of 64 8.1 and 7.4, a rollout of 32 steps and 16,384 329 and 301.
     constexpr int ORDER[NMOB] = { 0, 1, 2, 3, 4, 5, 9, 10, 11, 6, 7, 8 };
 #pragma unroll
     for (int i = 0; i < NMOB; ++i) {
         const int k = ORDER[i];
         const int ks = k / G, kl = k % G;           // owner sub-slot and lane (compile-time)
-        const int ik = Gr::shfl(packed[ks], kl);
-        const int kk = ik & 7;
-        if (!__any(kk != K_NONE && kk != K_ATTACK)) continue;
-        const bool k_ok = (ik >> 3) & 1, k_at = (ik >> 4) & 1;
-        const uint32_t tkey = ((uint32_t)ik >> 8) & KEY_MASK;
+        if (!((acting[ks] >> kl) & 1u)) continue;
+        const uint32_t target = (uint32_t)Gr::shfl((int)tkey[ks], kl);
         bool l_occ = false;
 #pragma unroll
-        for (int s = 0; s < NSM; ++s) l_occ = l_occ || (mw[s] & KEY_MASK) == tkey;
-        const bool blocked = Gr::ballot(l_occ) != 0 || k_at || !k_ok;
-        if (k < 6 || (k < 9 && kk == K_MOVE_PATH)) {
-            if ((kk == K_MOVE || kk == K_MOVE_PATH) && !blocked && l == kl) mw[ks] = mob_moved(mw[ks], tkey);
-        } else if (k < 9) {
-            if (kk == K_SHOOT && !blocked) {
-                const uint32_t arrows = (Gr::ballot(mw[9 / G] & 1u) >> (9 % G)) & 7u;   // bit j = arrow slot 9+j alive
+        for (int s = 0; s < NSM; ++s) l_occ = l_occ || at[s] == target;
+        const bool free_cell = Gr::ballot(l_occ) == 0;
+        if (k < 9) {
+            if (k >= 6 && ((shooting[ks] >> kl) & 1u)) {
+                const int info = Gr::shfl((shoots[ks] ? 8 : 0) | ndir_[ks], kl);
+                const uint32_t arrows = (Gr::ballot(at[9 / G] != 0u) >> (9 % G)) & 7u;   // bit j = arrow slot 9+j alive
                 const uint32_t free_arrows = ~arrows & ((1u << p.cap_arrow) - 1u) & 7u;
-                if (free_arrows) {
+                if ((info & 8) && free_cell && free_arrows) {
                     const int ka = 9 + __ffs((int)free_arrows) - 1;
-                    if (l == ka % G) mw[9 / G] = tkey | ((uint32_t)((ik >> 24) & 7) << 13);
+                    if (l == ka % G) { at[9 / G] = target; mw[9 / G] = (uint32_t)(info & 7) << 13; }
                 }
             }
+            if (moves[ks] && free_cell && l == kl) at[ks] = target;
         } else {
-            if (kk == K_FLY && l == kl) mw[ks] = blocked ? 0u : mob_moved(mw[ks], tkey);
+            if (kind_[ks] == K_FLY && l == kl) at[ks] = flies_on[ks] && free_cell ? target : 0u;
         }
     }
+#pragma unroll
+    for (int s = 0; s < NSM; ++s) mw[s] = at[s] ? ((mw[s] & ~KEY_MASK) | at[s]) : 0u;
     vit[0] = max(0, vit[0] - damage);
 
     // ---- phase 3: despawn far mobs, then one spawn attempt per type -----------------------------
 #pragma unroll
     for (int s = 0; s < NSM; ++s)
         if ((mw[s] & 1u) && max(iabs(mob_x(mw[s]) - px), iabs(mob_y(mw[s]) - py)) > DESPAWN_DIST) mw[s] = 0u;
+    uint32_t alive = 0;                              // bit k = slot k; an attempt only fills a slot of its own type
+#pragma unroll
+    for (int s = 0; s < NSM; ++s) alive |= Gr::ballot(mw[s] & 1u) << (s * G);
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        uint32_t taken = 0;                          // bit i = slot 3j+i alive
+        const uint32_t taken = alive >> (3 * j);     // bit i = slot 3j+i alive
         bool l_occ = false;
 #pragma unroll
         for (int s = 0; s < NSM; ++s) l_occ = l_occ || (mw[s] & KEY_MASK) == sp_key[j];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int ss = (3 * j + i) / G, sl = (3 * j + i) % G;
-            taken |= ((Gr::ballot(mw[ss] & 1u) >> sl) & 1u) << i;
-        }
         const bool occ = Gr::ballot(l_occ) != 0;
         const uint32_t cap = j == 0 ? p.cap_zombie : (j == 1 ? p.cap_cow : p.cap_skeleton);
         const uint32_t free_slots = ~taken & ((1u << cap) - 1u) & 7u;

@@ -250,6 +250,34 @@ def test_full_boss_hit_count_stays_at_its_maximum(cx, lanes):
     sim.close()
 
 
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+def test_classic_creatures_in_a_pen(cx, lanes):
+    """Twelve creatures in a pen around the player want each other's cells in most steps, and skeletons shoot between them: the order
+    in which slots move decides who gets a cell, for every number of lanes that share them."""
+    n = 83
+    sim = cx.Craftax(n, cx.default_config(obs_mode=cx.OBS_SYM_U8_F32, group_lanes=lanes))
+    orc = po.Oracle(n, po.default_config(), po.OBS_SYM_U8_F32)
+    seeds = synth.seeds_for(n, 51)
+    sim.reset(seeds); orc.reset(seeds)
+    rng = np.random.RandomState(5)
+    for i in range(n):
+        e, side = orc.envs[i], 5 + i % 3
+        e["map"][24:41, 24:41] = 4                                   # stone, and in it
+        x0, y0 = 32 - side // 2, 32 - side // 2
+        e["map"][y0:y0 + side, x0:x0 + side] = np.where(rng.rand(side, side) < 0.8, 7, 2)      # a pen of path and grass
+        cells = [(x0 + c % side, y0 + c // side) for c in rng.permutation(side * side)]
+        cells = [c for c in cells if c != (32, 32)][:12]
+        e["px"], e["py"] = 32, 32
+        for k in range(12):
+            alive = k < 9 or rng.rand() < 0.5
+            e["mob"][k] = (1, *cells[k], rng.randint(1, 5), 5 if k < 9 else 0, rng.randint(0, 3), (0, 0)) if alive else (0, 0, 0, 0, 0, 0, (0, 0))
+    sim.import_envs(orc.envs.copy())
+    for s in range(25):
+        _step_both(sim, orc, synth.actions(np.arange(n), s, "skewed"), f"step {s}")
+    assert sim.export_envs().tobytes() == orc.envs.tobytes()
+    sim.close()
+
+
 @pytest.mark.parametrize("lanes", [64, 16])
 def test_full_armour_beyond_what_can_be_made(cx, lanes):
     """An import accepts armour level 3 (crafting ends at 2): four such pieces ward off more than all physical damage, and an
