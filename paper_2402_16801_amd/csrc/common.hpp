@@ -349,11 +349,14 @@ enum class Keep { PLAIN, THROUGH, STREAM };
 typedef uint32_t piece_t __attribute__((ext_vector_type(4)));
 // Writes a piece at byte `at` behind base, which is the same for the whole wavefront; limit: bytes that may be written from there on
 // (the hardware drops what lies beyond).
-__device__ __forceinline__ void store_through(uint8_t* base, int limit, int at, piece_t v)
+template <Keep KEEP>
+__device__ __forceinline__ void store_piece(uint8_t* base, int limit, int at, piece_t v)
 {
+    static_assert(KEEP != Keep::STREAM, "streamed stores go by way of pointers");
     constexpr int SC1 = 16;      // cache policy bit of a buffer store: scope of the device, whose XCDs have an L2 each
-    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, limit, 0x00027000), at, 0, SC1);
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, limit, 0x00027000), at, 0, KEEP == Keep::THROUGH ? SC1 : 0);
 }
+__device__ __forceinline__ void store_through(uint8_t* base, int limit, int at, piece_t v) { store_piece<Keep::THROUGH>(base, limit, at, v); }
 // Where a buffer is too large for the last-level cache: which blocks of a launch write through while the others stream.
 // Consecutive blocks go round the eight XCDs, each with an L2 of its own, so every fourth is two XCDs whose blocks all write
 // through.  Both ways out of the L2 are then in use at once, which is faster than either alone.

@@ -325,20 +325,24 @@ __global__ __launch_bounds__(BLOCK, step_bound(PERLIN)) void k_step(uint4* __res
             if (RECORD_LAST && obs != nullptr) take_record<G>(l, e, fetched);
             else store_record<G>(l, recs + (size_t)env * 8, e);
             if (kSymbolic && obs != nullptr) {
-                // byte layouts are staged in LDS here and written by the whole wave below
+                // staged in LDS here and written by the whole wave below
                 const RenderLuts tables{lut_sqrt10, lut_tenth, o.done ? day_fresh : day_next, o.done ? q7_fresh : q7_next};
-                render_symbolic<G, OBS_MODE, true, !kBytes, LY, EAGER>(l, e, o.mvx, o.mvy, o.woff, luts, obs + (size_t)env * obs_stride(OBS_MODE), &tables);
-                staged = kBytes;
+                render_symbolic<G, OBS_MODE, true, false, LY, EAGER>(l, e, o.mvx, o.mvy, o.woff, luts, obs + (size_t)env * obs_stride(OBS_MODE), &tables);
+                staged = true;
             }
         }
     }
-    if (kBytes && obs != nullptr) {
+    if (kSymbolic && obs != nullptr) {
         if (l == 0) e[LY::FLAG] = staged ? 1u : 0u;
         group_sync();
         const int first = __builtin_amdgcn_readfirstlane((tid & ~63) / G);   // first environment of this wave within the block
         const uint32_t* wave_env = s_env + first * LY::STRIDE;
         uint8_t* wave_obs = obs + (size_t)(blockIdx.x * EPB + first) * obs_stride(OBS_MODE);
-        if (G == 16 && p.n < THROUGH_FROM) flush_wave_observations<G, OBS_MODE, LY, Keep::PLAIN>(wave_env, wave_obs);
+        if constexpr (!kBytes) {
+            if (G == 16 || (long long)p.n * OBS_STRIDE_F32 <= CACHE_SHARE) flush_wave_floats<G, LY, Keep::THROUGH>(wave_env, wave_obs, __ballot(staged));
+            else flush_wave_floats<G, LY, Keep::PLAIN>(wave_env, wave_obs, __ballot(staged));
+        }
+        else if (G == 16 && p.n < THROUGH_FROM) flush_wave_observations<G, OBS_MODE, LY, Keep::PLAIN>(wave_env, wave_obs);
         else flush_wave_observations<G, OBS_MODE, LY, Keep::THROUGH>(wave_env, wave_obs);
         if (RECORD_LAST && staged) put_record<G>(l, recs + (size_t)env * 8, fetched);
     }
@@ -530,15 +534,17 @@ __global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, 
         if (active && o.done && !fresh) { o.mvx = 0; o.mvy = 0; o.woff = (MAPW / 2 - WIN_COLS / 2) & 3; }
         bool staged = false;
         if (active && obs != nullptr) {
-            render_symbolic<G, OBS_MODE, true, !kBytes>(l, e, o.mvx, o.mvy, o.woff, luts, obs + (size_t)env * obs_stride(OBS_MODE));
-            staged = kBytes;
+            render_symbolic<G, OBS_MODE, true, false>(l, e, o.mvx, o.mvy, o.woff, luts, obs + (size_t)env * obs_stride(OBS_MODE));
+            staged = true;
         }
-        if (kBytes && obs != nullptr) {
+        if (obs != nullptr) {
             if (l == 0) e[LDS_FLAG] = staged ? 1u : 0u;
             group_sync();
-            const int first = (tid & ~63) / G;
-            flush_wave_observations<G, OBS_MODE>(s_env + first * LDS_ENV_DWORDS,
-                                                 obs + (size_t)(blockIdx.x * EPB + first) * obs_stride(OBS_MODE));
+            const int first = __builtin_amdgcn_readfirstlane((tid & ~63) / G);
+            const uint32_t* wave_env = s_env + first * LDS_ENV_DWORDS;
+            uint8_t* wave_obs = obs + (size_t)(blockIdx.x * EPB + first) * obs_stride(OBS_MODE);
+            if constexpr (kBytes) flush_wave_observations<G, OBS_MODE>(wave_env, wave_obs);
+            else flush_wave_floats<G, KeepLayout, G == 16 ? Keep::THROUGH : Keep::PLAIN>(wave_env, wave_obs, __ballot(staged));
         }
         __syncthreads();
     }

@@ -74,6 +74,57 @@ __device__ __forceinline__ void flush_wave_observations(const uint32_t* wave_env
     }
 }
 
+// The same for the flat layout, float[1345], whose stride is no multiple of a cache line: the whole wavefront writes one
+// environment after the other, in pieces of 16 bytes, 64 in a row, the first of which is moved so that every turn begins on a line.
+// (Run by run of an environment's lanes, a turn of four environments wrote twelve lines in part instead of eight as a whole.)
+// The pieces with scalars go out at the end, those of all environments together.  staged: which lanes' environments have staged one.
+// Whole lines can be written through (16,531 environments and more, with fewer than sixteen lanes, are left in the L2: three such buffers
+// in turn no longer fit the last-level cache).  Step, run by run and left in the L2 / so, us, one state stepped over and over | three in turn | one
+// that a cast to bfloat16 reads behind every step: 64 7.7 / 7.7 | 7.7 / 7.7, 1,500 9.0 / 8.4 | 9.0 / 8.5 | 14.0 / 13.4, 4,096 10.4 / 9.5 | 10.5 / 9.4 | 21.3 / 21.6,
+// 10,007 15.0 / 13.3 | 15.8 / 14.5 | 30.1 / 30.1, 16,384 27.1 / 19.8 | 30.1 / 24.4 | 46.6 / 42.3, 30,000 43.4 / 33.9 | 54.8 / 49.1 | 79.5 / 69.6
+// (written through 32.4 | 55.1); rollouts of 32 steps and 4,096 environments 236 / 212, of 16 and 30,000 672 / 404.
+template <int G, class LY, Keep KEEP>
+__device__ __forceinline__ void flush_wave_floats(const uint32_t* wave_env, uint8_t* __restrict__ wave_obs, const uint64_t staged)
+{
+    constexpr int ENVS = 64 / G, PIECES = OBS_STRIDE_F32 / 16, CELLS_TO = CELL_BYTES / 4, LINE = 128 / 16, TURNS = (CELLS_TO + LINE - 1 + 63) / 64,
+                  LIMIT = ENVS * OBS_STRIDE_F32, NOWHERE = 1 << 30;      // beyond the limit, where the hardware drops a piece
+    static_assert(CELL_BYTES % 4 == 3 && PIECES == (CELL_BYTES + NVEC + 3) / 4, "whole pieces of cells, one of three cells and a scalar, pieces of scalars");
+    const int lane = (int)(threadIdx.x & 63u);
+    auto one = [](uint32_t bits, int j) { return (uint32_t)__builtin_amdgcn_sbfe(bits, j, 1) & 0x3F800000u; };      // 1.0f where bit j is set
+#pragma unroll (G == 16 ? ENVS : 1)
+    for (int ei = 0; ei < ENVS; ++ei) {
+        const bool any = (staged >> (ei * G)) & 1u;
+        if (G != 16 && !any) continue;                     // few environments: no branch, so that the turns of one overlap those of the next
+        const uint32_t* bits = wave_env + ei * LY::STRIDE + LDS_BITS;
+        const int lead = (int)((reinterpret_cast<uintptr_t>(wave_obs) / 16 + (uint32_t)(ei * PIECES)) % LINE), c0 = lane - lead, shift = 4 * (c0 & 7);
+        const int at0 = any ? ei * OBS_STRIDE_F32 + 16 * c0 : NOWHERE;
+#pragma unroll
+        for (int it = 0; it < TURNS; ++it) {
+            const int c = c0 + 64 * it, w = (c0 >> 3) + 8 * it;
+            const uint32_t four = bits[CX_IDX(it == 0 ? max(w, 0) : (64 * it + 64 > CELLS_TO ? min(w, 41) : w), 42)] >> shift;
+            const bool wanted = (it > 0 || c >= 0) && (64 * it + 64 <= CELLS_TO || c < CELLS_TO);
+            store_piece<KEEP>(wave_obs, LIMIT, wanted ? at0 + 1024 * it : NOWHERE, piece_t{one(four, 0), one(four, 1), one(four, 2), one(four, 3)});
+        }
+    }
+    constexpr int TAIL = PIECES - CELLS_TO;
+#pragma unroll
+    for (int i = 0; i < (ENVS * TAIL + 63) / 64; ++i) {
+        const int k = 64 * i + lane, env = min(k / TAIL, ENVS - 1), first = 4 * (k - env * TAIL) - CELL_BYTES % 4;      // number of its first scalar
+        const uint32_t* e = wave_env + env * LY::STRIDE;
+        const bool wanted = k < ENVS * TAIL && ((staged >> (env * G)) & 1u);
+        const uint32_t last_cells = e[LDS_BITS + (CELL_BYTES >> 5)] >> (CELL_BYTES & ~3 & 31);
+        uint32_t v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int s = first + j;
+            v[j] = e[LY::VEC + max(0, min(s, NVEC - 1))];
+            if (s >= NVEC) v[j] = 0u;
+            if (j < CELL_BYTES % 4 && s < 0) v[j] = one(last_cells, j);
+        }
+        store_piece<KEEP>(wave_obs, LIMIT, wanted ? env * OBS_STRIDE_F32 + 16 * (CELLS_TO + k - env * TAIL) : NOWHERE, piece_t{v[0], v[1], v[2], v[3]});
+    }
+}
+
 // FILL_VEC = false: the caller has already put the 22 scalars into the LDS vector area.
 // FLUSH = false: stop after staging (bits and scalars in LDS); the caller writes them out with
 // flush_wave_observations.

@@ -53,6 +53,38 @@ def test_classic_byte_observations_of_a_step(n, mode):
     assert _run(n, 10, cx.VARIANT_CLASSIC, obs_mode=mode, max_episode_steps=4) > 0
 
 
+# written through (sixteen lanes; eight and four up to 85 MiB in all, 16,530 environments), left in the L2 beyond
+@pytest.mark.parametrize("n,lanes", [(1, 0), (5, 0), (66, 0), (700, 0), (12289, 0), (16530, 0), (16531, 0), (24577, 0), (131, 4), (37, 8), (16531, 16)])
+def test_classic_float_observations_of_a_step(n, lanes):
+    assert _run(n, 10, cx.VARIANT_CLASSIC, obs_mode=cx.OBS_SYM_F32, max_episode_steps=4, group_lanes=lanes) > 0
+
+
+# a turn of stores begins on a cache line wherever the buffer does, and writes nothing beside the observations
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+@pytest.mark.parametrize("n,shift", [(1, 0), (3, 16), (17, 48), (67, 80), (130, 112)])
+def test_classic_float_observations_in_a_buffer_off_the_cache_lines(n, shift, lanes):
+    sim = cx.Craftax(n, cx.default_config(obs_mode=cx.OBS_SYM_F32, max_episode_steps=6, group_lanes=lanes))
+    sim.reset(synth.seeds_for(n))
+    size, guard = sim.obs.numel(), 4096
+    room = torch.empty(size + 2 * guard, dtype=torch.uint8, device=sim.device)
+    assert room.data_ptr() % 128 == 0
+    steps, lo = 9, guard + shift
+    actions = torch.empty((steps, n), dtype=torch.int32, device=sim.device)
+    cx.craftax_synth_actions(actions, n, 0, steps, 3, 1, sim.stream)
+    reward, done = torch.empty((steps, n), device=sim.device), torch.empty((steps, n), dtype=torch.uint8, device=sim.device)
+
+    def check(step):
+        room.fill_(0x5A)
+        step(room[lo:lo + size])
+        cx.craftax_observe(sim.state, sim.obs, n, sim.stream)
+        assert torch.equal(room[lo:lo + size], sim.obs.view(-1)), "observation"
+        assert bool((room[:lo] == 0x5A).all()) and bool((room[lo + size:] == 0x5A).all()), "bytes beside the observations"
+
+    for t in range(steps):
+        check(lambda obs: cx.craftax_step(sim.state, actions[t], obs, reward[t], done[t], n, sim.stream))
+    check(lambda obs: cx.craftax_rollout(sim.state, actions, steps, obs, reward, done, n, sim.stream))
+
+
 # floats left in the L2 (up to 31 environments), written through (up to 85 MiB in all, 2,688 environments), left in the L2 (up to 240 MiB,
 # 7,591), then written through by every fourth block where they start within the first 256 MiB (up to environment 8,097, in step
 # and observing blocks whose number divides by four) and streamed beyond; bytes streamed
