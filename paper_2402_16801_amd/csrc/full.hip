@@ -36,6 +36,22 @@ constexpr int RESET_SLOTS = 64;    // environments served at once by kf_reset_li
 constexpr int MAX_ENVS_PER_STEP_BLOCK = 16;   // a step block holds 4 environments (a wavefront each) or 16 (16 lanes each)
 constexpr int REGEN_BLOCKS = 256;  // regeneration blocks at the head of the step grid: with 1,024 step blocks (4,096 environments) they fill the chip exactly
 
+// Floors in the order in which the blocks of a launch take them: all worlds' overworlds first (six fields), then the caves (two, two,
+// two, one), the floors built from masks last, so that a launch ends with short ones (world by world before: level turns over 1,000
+// Perlin worlds 138 us, 113 so, over 400 75 and 63, resets of 420 43.0 and 37.3, of 4,096 170 and 162, with Perlin noise 217 and 199).  A few floors are all on
+// the chip from the start; they go world by world, which keeps the long ones apart (level turns over 32 43.8 us, 46.7 by floors, over 64 43.7 and
+// 47.3, over 100 49.7 either way; resets of 48 22.6 and 23.6, of 85 25.8 and 24.9).
+__device__ inline int floor_in_turn(int turn) { return (int)((0x841325760ull >> (4 * turn)) & 15u); }
+constexpr long long FLOORS_BY_TURN_FROM = 1000;
+static dim3 floor_grid(unsigned worlds) { return (long long)worlds * FLOORS >= FLOORS_BY_TURN_FROM ? dim3(worlds, FLOORS) : dim3(worlds * FLOORS); }
+// which world and floor of such a launch a block takes
+struct FloorBlock { int world, floor; };
+__device__ inline FloorBlock floor_block()
+{
+    if (gridDim.y == (unsigned)FLOORS) return FloorBlock{ (int)blockIdx.x, floor_in_turn((int)blockIdx.y) };
+    return FloorBlock{ (int)(blockIdx.x / (unsigned)FLOORS), (int)(blockIdx.x % (unsigned)FLOORS) };
+}
+
 // What the block that generated floor 0 of a world leaves behind for the environment: as the
 // current world (fresh record, empty mob tables) or as the spare world (its ladders and potion map).
 // SAME_EPISODE: the record already holds this episode and seed (blocks of other floors may be reading
@@ -56,18 +72,19 @@ __device__ inline void publish_world(uint32_t* __restrict__ genv, const GenLayou
 }
 
 // ---------------------------------------------------------------------------------------------
-// reset of every environment: one block per (environment, episode 0 or 1, floor)
+// reset of every environment: one block per (environment, episode 0 or 1, floor); see floor_grid
 template <bool PERLIN, int NT>
 __global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_reset(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                        const uint64_t* __restrict__ seeds, Lists ls, const uint32_t* __restrict__ perlin_cs,
                                                        int pool, uint32_t* __restrict__ unlocks)
 {
-    if (blockIdx.x == 0) la::reset_counters(ls);
+    if (blockIdx.x == 0 && blockIdx.y == 0) la::reset_counters(ls);
     __shared__ uint32_t s_lat[LAT_WORDS];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
-    const uint32_t env = blockIdx.x / (2 * FLOORS), ep = (blockIdx.x / FLOORS) & 1u;
-    const int f = blockIdx.x % FLOORS;
+    const FloorBlock block = floor_block();
+    const uint32_t env = (uint32_t)block.world >> 1, ep = (uint32_t)block.world & 1u;
+    const int f = block.floor;
     const uint64_t seed = seeds[env];
     const uint32_t lo = (uint32_t)seed, hi = (uint32_t)(seed >> 32);
     worldgen_floor_block<NT, PERLIN>(maps + map_offset(env, ep), s_lat, s_layout, lo, hi, env, ep, f, nullptr, nullptr, perlin_cs);
@@ -92,11 +109,12 @@ __device__ __forceinline__ void regeneration_queue(uint32_t* __restrict__ envs, 
                                                    uint32_t seq, WorldScratch& s, const uint32_t* s_prefix, int regen_blocks,
                                                    const uint32_t* __restrict__ perlin_cs)
 {
-    const uint32_t units = s_prefix[NSUB - 1] * (uint32_t)FLOORS;
+    const uint32_t worlds = s_prefix[NSUB - 1], units = worlds * (uint32_t)FLOORS;
     for (uint32_t u = blockIdx.x; u < units; u += (uint32_t)regen_blocks) {
         __syncthreads();   // the previous unit's scratch has been read by everyone
-        const uint4 entry = la::queue_entry(ls, seq, s_prefix, u / FLOORS);
-        const int f = (int)(u % FLOORS);
+        const uint32_t turn = u / worlds;
+        const uint4 entry = la::queue_entry(ls, seq, s_prefix, u - turn * worlds);
+        const int f = floor_in_turn((int)turn);
         if (entry.x == ENTRY_VOID) continue;
         worldgen_floor_block<NT, PERLIN, true>(maps + map_offset(entry.x, entry.w), s.lat, s.layout, entry.y, entry.z, entry.x, entry.w, f, nullptr, nullptr,
                                          PERLIN ? perlin_cs : nullptr);
@@ -542,7 +560,8 @@ __global__ __launch_bounds__(NT, PERLIN_WAVES) void kf_mutate_noise(uint32_t* __
     __shared__ uint16_t s_theta[LAT_TOTAL];
     __shared__ GenLayout s_layout;
     __shared__ uint32_t s_words[FLOORS + 1];
-    const int tid = threadIdx.x, slot = blockIdx.x / FLOORS, f = blockIdx.x % FLOORS;
+    const FloorBlock block = floor_block();
+    const int tid = threadIdx.x, slot = block.world, f = block.floor;
     const uint32_t env = (uint32_t)first + (uint32_t)slot;
     uint32_t* genv = envs + (size_t)env * ENV_DWORDS;
     const uint32_t ep = genv[R_EPISODE], lo = genv[R_SEED_LO], hi = genv[R_SEED_HI];
@@ -701,7 +720,8 @@ __global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_im
                                                                         const uint32_t* __restrict__ perlin_cs, int pool)
 {
     __shared__ WorldScratch s_gen;
-    const int slot = blockIdx.x / FLOORS, floor = blockIdx.x % FLOORS, env = first + slot, tid = threadIdx.x;
+    const FloorBlock block = floor_block();
+    const int slot = block.world, floor = block.floor, env = first + slot, tid = threadIdx.x;
     const craftax_full_env_dump* d = dumps + slot;
     const uint32_t lo = (uint32_t)d->seed, hi = (uint32_t)(d->seed >> 32), ep = d->episode;
     uint32_t* r = envs + (size_t)env * ENV_DWORDS;
@@ -1005,7 +1025,7 @@ int reset(void* state, const craftax_config* cfg, int n, const uint64_t* seeds, 
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
     auto go = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)n * 2 * FLOORS), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, seeds, q.ls, gradients(cfg, q),
+        hipLaunchKernelGGL(kernel, floor_grid(2u * (unsigned)n), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, seeds, q.ls, gradients(cfg, q),
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0, make_params(state, cfg, n).unlocks);
     };
     const bool perlin = cfg->worldgen == CRAFTAX_WORLDGEN_PERLIN, blocks = floors_by_blocks(FloorWork::RESET, perlin, 2ll * n * FLOORS);
@@ -1152,7 +1172,7 @@ int import_envs(void* state, const craftax_config* cfg, int n, int first, int co
 {
     const Ptrs q = pointers(state, make_header(cfg, n));
     auto go = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, q.ls,
+        hipLaunchKernelGGL(kernel, floor_grid((unsigned)count), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, q.ls,
                            static_cast<const craftax_full_env_dump*>(dumps), first, make_params(state, cfg, n), gradients(cfg, q),
                            cfg->reset_mode == CRAFTAX_RESET_POOL ? 1 : 0);
     };
@@ -1177,7 +1197,7 @@ int mutate_noise(void* state, const craftax_config* cfg, int n, int first, int c
     const Ptrs q = pointers(state, make_header(cfg, n));
     const uint32_t k0 = (uint32_t)mutation_seed, k1 = (uint32_t)(mutation_seed >> 32);
     auto go = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)count * FLOORS), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, theta, first, k0, k1,
+        hipLaunchKernelGGL(kernel, floor_grid((unsigned)count), dim3((unsigned)threads), 0, (hipStream_t)stream, q.envs, q.maps, q.luts, theta, first, k0, k1,
                            round, amplitude);
     };
     if (floors_by_blocks(FloorWork::MUTATE, true, (long long)count * FLOORS)) go(kf_mutate_noise<GEN_THREADS>, GEN_THREADS); else go(kf_mutate_noise<FLOOR_THREADS>, FLOOR_THREADS);
