@@ -180,6 +180,11 @@ __device__ inline uint32_t slow_count(const Lists& ls, uint32_t capacity) { retu
 // Cancels everything queued for `env` (all threads of the block call).
 __device__ inline void cancel_entries(const Lists& ls, uint32_t env)
 {
+    // the lengths of all lists together: read one after the other, each waited for, they took longer than the rest of an import whose lists are empty
+    uint32_t any = *counter(ls, CT_SLOW);
+#pragma unroll
+    for (int li = 0; li < 2 * NSUB; ++li) any |= *counter(ls, CT_REGEN + li);
+    if (any == 0u) return;
     for (int li = 0; li < 2 * NSUB + 1; ++li) {
         uint4* list = li < 2 * NSUB ? ls.regen[li / NSUB] + (size_t)(li % NSUB) * ls.sub_cap : ls.slow;
         const uint32_t cnt = min(*counter(ls, li < 2 * NSUB ? CT_REGEN + li : CT_SLOW), li < 2 * NSUB ? ls.sub_cap : ls.slow_cap);
