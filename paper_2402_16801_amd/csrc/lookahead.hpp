@@ -177,19 +177,19 @@ __device__ inline void append_slow(const Lists& ls, uint32_t capacity, uint4 ent
     if (at < capacity) ls.slow[at] = entry;
 }
 __device__ inline uint32_t slow_count(const Lists& ls, uint32_t capacity) { return min(*counter(ls, CT_SLOW), capacity); }
-// Cancels everything queued for `env` (all threads of the block call).
+// Cancels everything queued for `env` (all threads of the block call; their number is a multiple of 32).  A thread reads the length of
+// one regeneration list, so that those of all lists come together, and walks that list with the others that have read it.  After
+// a step most of the sub-lists that it filled hold an entry or two, and read one list after the other each was a trip to memory that the next
+// one waited for.  A step and an import of all its environments, us, lists in turn / so: Classic, 64 20.0 / 18.2, 4,096 68.0 / 44.6, 16,384 239 / 149;
+// full game, 64 22.6 / 19.6, 1,000 Perlin worlds 69.4 / 59.2; an import into empty lists 9.4 / 9.3 and 47.1 / 47.1.
 __device__ inline void cancel_entries(const Lists& ls, uint32_t env)
 {
-    // the lengths of all lists together: read one after the other, each waited for, they took longer than the rest of an import whose lists are empty
-    uint32_t any = *counter(ls, CT_SLOW);
-#pragma unroll
-    for (int li = 0; li < 2 * NSUB; ++li) any |= *counter(ls, CT_REGEN + li);
-    if (any == 0u) return;
-    for (int li = 0; li < 2 * NSUB + 1; ++li) {
-        uint4* list = li < 2 * NSUB ? ls.regen[li / NSUB] + (size_t)(li % NSUB) * ls.sub_cap : ls.slow;
-        const uint32_t cnt = min(*counter(ls, li < 2 * NSUB ? CT_REGEN + li : CT_SLOW), li < 2 * NSUB ? ls.sub_cap : ls.slow_cap);
-        for (uint32_t i = threadIdx.x; i < cnt; i += blockDim.x) if (list[i].x == env) list[i].x = ENTRY_VOID;
-    }
+    static_assert(2 * NSUB == 32, "a list for each of 32 threads");
+    const uint32_t li = threadIdx.x % (2u * NSUB), part = threadIdx.x / (2u * NSUB), parts = blockDim.x / (2u * NSUB);
+    const uint32_t cnt = min(*counter(ls, CT_REGEN + (int)li), ls.sub_cap), slow = min(*counter(ls, CT_SLOW), ls.slow_cap);
+    uint4* list = (li < (uint32_t)NSUB ? ls.regen[0] : ls.regen[1]) + (size_t)(li % NSUB) * ls.sub_cap;
+    for (uint32_t i = part; i < cnt; i += parts) if (list[i].x == env) list[i].x = ENTRY_VOID;
+    for (uint32_t i = threadIdx.x; i < slow; i += blockDim.x) if (ls.slow[i].x == env) ls.slow[i].x = ENTRY_VOID;
 }
 // the last working block of a slow-list kernel empties the slow list
 __device__ inline void finish_slow_list(const Lists& ls, uint32_t count)

@@ -225,6 +225,26 @@ def test_full_import_brings_out_of_range_values_into_range(cx):
     sim.close()
 
 
+@pytest.mark.parametrize("variant,n,first,count,worldgen,cap", [("classic", 900, 301, 500, po.WORLDGEN_VALUE, 4), ("classic", 3, 1, 1, po.WORLDGEN_VALUE, 3),
+                                                                ("craftax", 150, 31, 100, po.WORLDGEN_VALUE, 4), ("craftax", 640, 20, 600, po.WORLDGEN_PERLIN, 3)])
+def test_imports_cancel_what_the_step_before_has_queued(cx, variant, n, first, count, worldgen, cap):
+    """All episodes end in one step, which queues a world for every environment, many per list (odd and even steps fill
+    different lists).  An import of the episode before then has that world's slot for its map: its entry must go, and those of all others must stay."""
+    sim, orc, n_actions = _pair(cx, variant, n, max_episode_steps=cap, worldgen=worldgen)
+    seeds = synth.seeds_for(n, 13)
+    sim.reset(seeds); orc.reset(seeds)
+    part = slice(first, first + count)
+    for s in range(3 * cap):
+        before = orc.envs[part].copy()
+        done = _step_both(sim, orc, synth.actions(np.arange(n), s, "skewed", 5, n_actions), f"step {s}")
+        if s == cap - 1:
+            assert done.all()
+            orc.envs[part] = before
+            sim.import_envs(before, first=first)
+        assert sim.export_envs().tobytes() == orc.envs.tobytes(), f"worlds after step {s}"
+    sim.close()
+
+
 @pytest.mark.parametrize("lanes", [64, 16])
 def test_full_boss_hit_count_stays_at_its_maximum(cx, lanes):
     """The record holds 0..15 hits on the necromancer; a winning hit on an imported state that is
