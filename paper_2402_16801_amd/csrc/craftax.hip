@@ -413,8 +413,12 @@ __device__ __attribute__((noinline)) void generate_half(uint8_t* map, Lds<uint32
 // Measured against blocks that generate all their worlds, by code in the loop (64 steps, value noise /
 // Perlin): 12,000 environments 603 / 710 -> 569 / 614 us, 32,768: 1,164 / 1,367 -> 1,065 / 1,157,
 // 65,536: 1,801 / 2,051 -> 1,761 / 1,877.
+// Blocks per compute unit: four of 64 environments, by LDS.  Of the blocks of 16 with float observations and value noise five, which needs no
+// spills (96 registers; unbounded 102, with which from 16,385 environments on the launch waits for a second round of blocks: 16 steps of 16,530
+// 342 us on states in turn and 270 on one, with five 303 and 232, of 20,480 392 and 296, now 335 and 264; 4,096 114.3 and 114.9).
+constexpr int rollout_bound(int lanes, int obs_mode, bool perlin) { return lanes == 16 && obs_mode == CRAFTAX_OBS_SYM_F32 && !perlin ? 5 : 4; }
 template <int G, int OBS_MODE, bool PERLIN>
-__global__ __launch_bounds__(BLOCK, 4) void k_rollout(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
+__global__ __launch_bounds__(BLOCK, rollout_bound(G, OBS_MODE, PERLIN)) void k_rollout(uint4* __restrict__ recs, uint8_t* __restrict__ maps,
                                                       const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                       uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                       uint8_t* __restrict__ done, Lists ls, Params p, int steps, int own_from)

@@ -59,3 +59,8 @@ def test_generators_of_the_full_game_spill_no_vector_register(kernels):
 def test_step_kernels_use_no_scratch(kernels):
     scratch = {n: k["private_segment_fixed_size"] for n, k in kernels.items() if re.match(r"cx::k_step<|cf::kf_step<", n)}
     assert len(scratch) > 20 and set(scratch.values()) == {0}, scratch
+
+
+def test_float_rollouts_of_sixteen_lanes_leave_registers_for_five_blocks(kernels):
+    """512 vector registers per SIMD, handed out by eights: with more than 96 a compute unit holds four blocks, 16,384 environments on the chip."""
+    assert kernels["cx::k_rollout<16, 2, false>"]["vgpr_count"] <= 96
