@@ -361,7 +361,8 @@ __device__ __forceinline__ void store_through(uint8_t* base, int limit, int at, 
 // Consecutive blocks go round the eight XCDs, each with an L2 of its own, so every fourth is two XCDs whose blocks all write
 // through.  Both ways out of the L2 are then in use at once, which is faster than either alone.
 __device__ inline bool written_through(uint32_t block) { return (block & 3u) == 0u; }
-// Pictures, which are streamed otherwise: up to here all of them are written through (three such buffers that are used in turn still fit).
+// Float observations and pictures, which are left in the L2 or streamed otherwise: buffers up to here are written through as a whole (three of
+// them that are used in turn still fit).
 constexpr long long CACHE_SHARE = 85ll << 20;
 // The size of the last-level cache.  Of a buffer too large for it (of pictures, beyond CACHE_SHARE) every fourth block writes through, up to this
 // place in it: 64 MiB of it then.

@@ -78,8 +78,8 @@ __device__ __forceinline__ void flush_wave_observations(const uint32_t* wave_env
 // environment after the other, in pieces of 16 bytes, 64 in a row, the first of which is moved so that every turn begins on a line.
 // (Run by run of an environment's lanes, a turn of four environments wrote twelve lines in part instead of eight as a whole.)
 // The pieces with scalars go out at the end, those of all environments together.  staged: which lanes' environments have staged one.
-// Whole lines can be written through (16,531 environments and more, with fewer than sixteen lanes, are left in the L2: three such buffers
-// in turn no longer fit the last-level cache).  Step, run by run and left in the L2 / so, us, one state stepped over and over | three in turn | one
+// Whole lines can be written through (by a step with fewer than sixteen lanes up to 16,529 environments; more are left in the L2: three such
+// buffers in turn no longer fit the last-level cache).  Step, run by run and left in the L2 / so, us, one state stepped over and over | three in turn | one
 // that a cast to bfloat16 reads behind every step: 64 7.7 / 7.7 | 7.7 / 7.7, 1,500 9.0 / 8.4 | 9.0 / 8.5 | 14.0 / 13.4, 4,096 10.4 / 9.5 | 10.5 / 9.4 | 21.3 / 21.6,
 // 10,007 15.0 / 13.3 | 15.8 / 14.5 | 30.1 / 30.1, 16,384 27.1 / 19.8 | 30.1 / 24.4 | 46.6 / 42.3, 30,000 43.4 / 33.9 | 54.8 / 49.1 | 79.5 / 69.6
 // (written through 32.4 | 55.1); rollouts of 32 steps and 4,096 environments 236 / 212, of 16 and 30,000 672 / 404.
@@ -88,6 +88,7 @@ __device__ __forceinline__ void flush_wave_floats(const uint32_t* wave_env, uint
 {
     constexpr int ENVS = 64 / G, PIECES = OBS_STRIDE_F32 / 16, CELLS_TO = CELL_BYTES / 4, LINE = 128 / 16, TURNS = (CELLS_TO + LINE - 1 + 63) / 64,
                   LIMIT = ENVS * OBS_STRIDE_F32, NOWHERE = 1 << 30;      // beyond the limit, where the hardware drops a piece
+    static_assert(16529ll * OBS_STRIDE_F32 <= CACHE_SHARE && 16530ll * OBS_STRIDE_F32 > CACHE_SHARE, "the line named above");
     static_assert(CELL_BYTES % 4 == 3 && PIECES == (CELL_BYTES + NVEC + 3) / 4, "whole pieces of cells, one of three cells and a scalar, pieces of scalars");
     const int lane = (int)(threadIdx.x & 63u);
     auto one = [](uint32_t bits, int j) { return (uint32_t)__builtin_amdgcn_sbfe(bits, j, 1) & 0x3F800000u; };      // 1.0f where bit j is set
