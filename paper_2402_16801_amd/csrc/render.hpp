@@ -78,8 +78,9 @@ __device__ __forceinline__ void flush_wave_observations(const uint32_t* wave_env
 // environment after the other, in pieces of 16 bytes, 64 in a row, the first of which is moved so that every turn begins on a line.
 // (Run by run of an environment's lanes, a turn of four environments wrote twelve lines in part instead of eight as a whole.)
 // The pieces with scalars go out at the end, those of all environments together.  staged: which lanes' environments have staged one.
-// Whole lines can be written through (by a step with fewer than sixteen lanes up to 16,529 environments; more are left in the L2: three such
-// buffers in turn no longer fit the last-level cache).  Step, run by run and left in the L2 / so, us, one state stepped over and over | three in turn | one
+// Whole lines can be written through (by a step up to 16,529 environments; more are left in the L2: three such buffers
+// in turn no longer fit the last-level cache, and with sixteen lanes 30,000 environments take 59.1 us written through, 52.4 so, 65,536 119 and 105; on one
+// buffer alone 32.9 and 34.4, 113 and 101).  Step, run by run and left in the L2 / so, us, one state stepped over and over | three in turn | one
 // that a cast to bfloat16 reads behind every step: 64 7.7 / 7.7 | 7.7 / 7.7, 1,500 9.0 / 8.4 | 9.0 / 8.5 | 14.0 / 13.4, 4,096 10.4 / 9.5 | 10.5 / 9.4 | 21.3 / 21.6,
 // 10,007 15.0 / 13.3 | 15.8 / 14.5 | 30.1 / 30.1, 16,384 27.1 / 19.8 | 30.1 / 24.4 | 46.6 / 42.3, 30,000 43.4 / 33.9 | 54.8 / 49.1 | 79.5 / 69.6
 // (written through 32.4 | 55.1); rollouts of 32 steps and 4,096 environments 236 / 212, of 16 and 30,000 672 / 404.

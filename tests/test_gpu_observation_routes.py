@@ -53,7 +53,7 @@ def test_classic_byte_observations_of_a_step(n, mode):
     assert _run(n, 10, cx.VARIANT_CLASSIC, obs_mode=mode, max_episode_steps=4) > 0
 
 
-# written through (sixteen lanes; eight and four up to 85 MiB in all, 16,529 environments), left in the L2 beyond
+# written through up to 85 MiB in all (16,529 environments), left in the L2 beyond
 @pytest.mark.parametrize("n,lanes", [(1, 0), (5, 0), (66, 0), (700, 0), (12289, 0), (16529, 0), (16530, 0), (16531, 0), (24577, 0), (131, 4), (37, 8), (16529, 16), (16530, 16),
                                      (16531, 16)])
 def test_classic_float_observations_of_a_step(n, lanes):
