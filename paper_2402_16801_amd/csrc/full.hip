@@ -32,6 +32,10 @@ using la::NSUB;
 // 8,192 21.9 / 21.9; Perlin noise 4,096 13.7 / 13.6, 4,500 16.7 / 14.9, 5,800 19.1 / 18.8, 8,000 22.1 / 21.3.
 constexpr int EAGER_SPARE_ENVS = 8192;
 constexpr int eager_spare_envs(bool bytes, bool perlin, int lanes) { return !bytes || lanes != 64 ? EAGER_SPARE_ENVS : perlin ? 4096 : 5120; }
+// The same line for steps with bytes that fetch nothing in advance at any size, because their episodes end without a spare world (optimistic
+// resets): beyond it the instance for a full chip, up to it one that is not bounded to as many blocks (us, with that of a full chip / so: 64
+// 12.3 / 12.2, 256 16.1 / 15.8, 1,024 18.8 / 18.5, 4,096 25.0 / 24.7, 5,120 28.0 / 27.6, 8,192 37.9 / 38.6; Perlin noise 1,024 20.2 / 20.1, 4,096 26.6 / 26.5).
+constexpr bool chip_is_full(int n, bool perlin) { return n > eager_spare_envs(true, perlin, 64); }
 constexpr int RESET_SLOTS = 64;    // environments served at once by kf_reset_list (nine blocks each)
 constexpr int MAX_ENVS_PER_STEP_BLOCK = 16;   // a step block holds 4 environments (a wavefront each) or 16 (16 lanes each)
 constexpr int REGEN_BLOCKS = 256;  // regeneration blocks at the head of the step grid: with 1,024 step blocks (4,096 environments) they fill the chip exactly
@@ -155,12 +159,12 @@ __global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_dr
 // DRAW (pixels): a block holds one environment, which its first wavefront steps, and all its wavefronts then draw the picture, from the
 // record and mobs in LDS.
 // FLOATS: see floats_kept.
-// Blocks per compute unit that the compiler is bounded to.  Without EAGER the chip is full, and every further block hides waits: eight,
+// FULL (bytes; see chip_is_full): every further block on a compute unit hides waits, and the compiler is bounded to as many: eight,
 // the most that registers and LDS allow where worlds are of value noise (32,768 environments, bytes: 79.1 us with six, 76.3 with seven, 74.7
 // with eight).  Below that the launch waits for its slowest wavefronts, which spill fewer scalars with more registers (4,096: 13.4 us, 13.6).
-constexpr int step_bound(bool bytes, bool eager, bool perlin, int lanes) { return lanes != 64 ? 2 : eager || !bytes ? 5 : perlin ? 6 : 8; }
-template <bool F32, bool EAGER, bool PERLIN, int GW, bool DRAW = false, cx::Keep FLOATS = cx::Keep::THROUGH>
-__global__ __launch_bounds__(BLOCK, step_bound(!F32 && !DRAW, EAGER, PERLIN, GW)) void kf_step(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
+constexpr int step_bound(bool bytes, bool full, bool perlin, int lanes) { return lanes != 64 ? 2 : !full || !bytes ? 5 : perlin ? 6 : 8; }
+template <bool F32, bool EAGER, bool PERLIN, int GW, bool DRAW = false, cx::Keep FLOATS = cx::Keep::THROUGH, bool FULL = !EAGER>
+__global__ __launch_bounds__(BLOCK, step_bound(!F32 && !DRAW, FULL, PERLIN, GW)) void kf_step(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps,
                                                 const Luts* __restrict__ luts, const int32_t* __restrict__ actions,
                                                 uint8_t* __restrict__ obs, float* __restrict__ reward,
                                                 uint8_t* __restrict__ done, Lists ls, Params p, int regen_blocks)
@@ -168,7 +172,7 @@ __global__ __launch_bounds__(BLOCK, step_bound(!F32 && !DRAW, EAGER, PERLIN, GW)
     using G = Lanes<GW>;
     static_assert(!DRAW || (GW == 64 && !F32), "pictures are drawn behind a step by a wavefront");
     constexpr int EPB = DRAW ? 1 : BLOCK / GW;               // environments per block
-    constexpr bool HALVES = !F32 && !DRAW && !EAGER && GW == 64;
+    constexpr bool HALVES = !F32 && !DRAW && FULL && GW == 64;
     constexpr int REC_IT = REC_DWORDS / GW > 0 ? REC_DWORDS / GW : 1;
     static_assert(REC_DWORDS % GW == 0 || GW > REC_DWORDS, "the record is moved in whole turns of the group");
     static_assert(GW >= MOBTAB_DWORDS && GW >= NTAG && GW >= FLOORS + 1, "a group holds a mob table, the tags and the header in one turn");
@@ -987,6 +991,7 @@ static bool kernels_fit(const Fits& fits)
     auto step = [&](const char* name, const void* eager, const void* plain) { return fits(name, eager, BLOCK) && fits(name, plain, BLOCK); };
     auto floors = [&](const char* name, const void* blocks, const void* wavefronts) { return fits(name, blocks, GEN_THREADS) && fits(name, wavefronts, FLOOR_THREADS); };
     return step("kf_step", (const void*)kf_step<F32, true, PERLIN, 64>, (const void*)kf_step<F32, false, PERLIN, 64>) &&
+           (F32 || fits("kf_step of small pooled batches", (const void*)kf_step<false, false, PERLIN, 64, false, cx::Keep::THROUGH, false>, BLOCK)) &&
            (!F32 || step("kf_step of large float buffers", (const void*)kf_step<true, true, PERLIN, 64, false, cx::Keep::PLAIN>, (const void*)kf_step<true, false, PERLIN, 64, false, cx::Keep::STREAM>)) &&
            (!F32 || (fits("kf_observe of large float buffers", (const void*)kf_observe<true, cx::Keep::PLAIN>, BLOCK) && fits("kf_observe of larger ones", (const void*)kf_observe<true, cx::Keep::STREAM>, BLOCK))) &&
            step("kf_step with pictures", (const void*)kf_step<false, true, PERLIN, 64, true>, (const void*)kf_step<false, false, PERLIN, 64, true>) &&
@@ -1061,6 +1066,8 @@ static void launch_step(int gw, bool eager, bool perlin, dim3 grid, hipStream_t 
         if (perlin) go(kf_step<true, false, true, 64, false, cx::Keep::STREAM>); else go(kf_step<true, false, false, 64, false, cx::Keep::STREAM>);
     } else if (F32 && eager && (p.n < FLOATS_THROUGH_FROM || floats_kept(p.n) == cx::Keep::PLAIN)) {
         if (perlin) go(kf_step<true, true, true, 64, false, cx::Keep::PLAIN>); else go(kf_step<true, true, false, 64, false, cx::Keep::PLAIN>);
+    } else if (!F32 && !eager && !chip_is_full(p.n, perlin)) {
+        if (perlin) go(kf_step<false, false, true, 64, false, cx::Keep::THROUGH, false>); else go(kf_step<false, false, false, 64, false, cx::Keep::THROUGH, false>);
     } else {
         if (perlin) { if (eager) go(kf_step<F32, true, true, 64>); else go(kf_step<F32, false, true, 64>); }
         else { if (eager) go(kf_step<F32, true, false, 64>); else go(kf_step<F32, false, false, 64>); }

@@ -463,6 +463,23 @@ def test_full_steps_with_and_without_the_spare_window_fetched_ahead(cx, worldgen
     assert finished > 100
 
 
+@pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 5120), (po.WORLDGEN_VALUE, 5121), (po.WORLDGEN_PERLIN, 4096), (po.WORLDGEN_PERLIN, 4097)])
+def test_full_pooled_steps_on_either_side_of_a_full_chip(cx, worldgen, n):
+    """Optimistic resets depend on all episodes that end with one: the two instances of the byte step against the one of sixteen lanes."""
+    import torch
+    both = [cx.Craftax(n, cx.default_config(cx.VARIANT_CRAFTAX, worldgen=worldgen, reset_mode=cx.RESET_POOL, max_episode_steps=5, group_lanes=lanes)) for lanes in (64, 16)]
+    acts = torch.empty((12, n), dtype=torch.int32, device=both[0].device)
+    cx.craftax_synth_actions(acts, n, 0, 12, 3, 3, both[0].stream)
+    for sim in both:
+        sim.reset(synth.seeds_for(n, 3))
+    for s in range(12):
+        a, b = (sim.step(acts[s]) for sim in both)
+        assert all(torch.equal(x, y) for x, y in zip(a, b)), s
+    assert both[0].export_envs().tobytes() == both[1].export_envs().tobytes()
+    for sim in both:
+        sim.close()
+
+
 def test_full_caps_and_short_episodes(cx):
     """Reduced mob caps, no plants, a 38-step day and a 60-step episode cap: many truncations."""
     finished, _, _ = run_full(cx, 40, 400, kind="skewed", cap_melee=1, cap_ranged=0, cap_passive=2, cap_plant=0, day_length=38,
