@@ -108,17 +108,25 @@ static_assert(sizeof(WorldScratch) % 8 == 0 && offsetof(WorldScratch, layout) % 
 // floor of one world each; block rb of nrb takes units rb, rb + nrb, ...  In the step grid the blocks
 // stand at the head: a step launch holds as many of them as the chip has room for beside the step
 // blocks, so every unit starts with the launch and none waits for a block that is scheduled late.
+// A unit's turn, sub-list and place come from votes in which a lane holds the end of one turn and of one sub-list, and what
+// the entry says is moved to scalar registers: the floor and its seed are the same for the wavefront, which an index divided by a number
+// from LDS hides from the compiler (with that division and a walk over the sub-lists, a step's us / so: 2,048 environments 10.6 / 10.2, without
+// an observation 10.1 / 9.6; with episodes of at most 20 steps, of every age, 4,096 34.0 / 31.9, 8,192 67.7 / 62.4, 16,384 128 / 118, Perlin noise 135 / 127).
 template <int NT, bool PERLIN>
 __device__ __forceinline__ void regeneration_queue(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Lists& ls,
                                                    uint32_t seq, WorldScratch& s, const uint32_t* s_prefix, int regen_blocks,
                                                    const uint32_t* __restrict__ perlin_cs)
 {
-    const uint32_t worlds = s_prefix[NSUB - 1], units = worlds * (uint32_t)FLOORS;
+    const uint32_t lane = threadIdx.x & 63u, total = s_prefix[lane < (uint32_t)NSUB ? lane : 0u];
+    const uint32_t worlds = (uint32_t)lane_get((int)total, NSUB - 1), units = worlds * (uint32_t)FLOORS, turn_ends = (lane + 1u) * worlds;
     for (uint32_t u = blockIdx.x; u < units; u += (uint32_t)regen_blocks) {
         __syncthreads();   // the previous unit's scratch has been read by everyone
-        const uint32_t turn = u / worlds;
-        const uint4 entry = la::queue_entry(ls, seq, s_prefix, u - turn * worlds);
-        const int f = floor_in_turn((int)turn);
+        const int turn = __popcll(__ballot(u >= turn_ends) & ((1ull << (FLOORS - 1)) - 1ull));
+        const uint32_t world = u - (uint32_t)turn * worlds;
+        const int sub = __popcll(__ballot(world >= total) & ((1ull << (NSUB - 1)) - 1ull));
+        const uint4 found = la::queue_entry(ls, seq, (uint32_t)sub, world - (sub == 0 ? 0u : (uint32_t)lane_get((int)total, sub - 1)));
+        const uint4 entry = make_uint4(uniu(found.x), uniu(found.y), uniu(found.z), uniu(found.w));
+        const int f = floor_in_turn(turn);
         if (entry.x == ENTRY_VOID) continue;
         worldgen_floor_block<NT, PERLIN, true>(maps + map_offset(entry.x, entry.w), s.lat, s.layout, entry.y, entry.z, entry.x, entry.w, f, nullptr, nullptr,
                                          PERLIN ? perlin_cs : nullptr);

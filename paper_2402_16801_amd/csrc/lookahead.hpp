@@ -125,13 +125,10 @@ __device__ inline Ticket enter_launch_queue(const Lists& ls, uint32_t* s_prefix)
     if (threadIdx.x == 0) t.started = atomicAdd(counter(ls, CT_GROUP + (int)t.grp), 1u);
     return t;
 }
-// Entry number g of the consumed list seen as one queue (g < s_prefix[NSUB - 1]).
-__device__ inline uint4 queue_entry(const Lists& ls, uint32_t seq, const uint32_t* s_prefix, uint32_t g)
+// Entry `at` of sub-list `sub` of the consumed list.
+__device__ inline uint4 queue_entry(const Lists& ls, uint32_t seq, uint32_t sub, uint32_t at)
 {
-    uint32_t sub = 0u, base = 0u;
-#pragma unroll
-    for (int k = 0; k < NSUB - 1; ++k) if (g >= s_prefix[k]) { sub = (uint32_t)k + 1u; base = s_prefix[k]; }
-    return ls.regen[(seq & 1u) ^ 1u][(size_t)sub * ls.sub_cap + (g - base)];
+    return ls.regen[(seq & 1u) ^ 1u][(size_t)sub * ls.sub_cap + at];
 }
 // the sub-list of the list consumed in this launch that regeneration block rb reads
 __device__ inline const uint4* consumed_sub_list(const Lists& ls, uint32_t seq, uint32_t rb)

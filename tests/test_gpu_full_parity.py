@@ -480,6 +480,15 @@ def test_full_pooled_steps_on_either_side_of_a_full_chip(cx, worldgen, n):
         sim.close()
 
 
+@pytest.mark.parametrize("worldgen", [po.WORLDGEN_VALUE, po.WORLDGEN_PERLIN])
+@pytest.mark.parametrize("n", [1, 28, 29, 57, 300])
+def test_full_worlds_owed_together(cx, n, worldgen):
+    """All episodes end in one step, and the next launch owes a world for each, in one to sixteen sub-lists: fewer floors than
+    the 256 regeneration blocks (28 worlds), a few more, two and more per block."""
+    finished, _, _ = run_full(cx, n, 11, kind="skewed", max_episode_steps=3, worldgen=worldgen, state_every=1, seed_base=n)
+    assert finished >= 3 * n
+
+
 def test_full_caps_and_short_episodes(cx):
     """Reduced mob caps, no plants, a 38-step day and a 60-step episode cap: many truncations."""
     finished, _, _ = run_full(cx, 40, 400, kind="skewed", cap_melee=1, cap_ranged=0, cap_passive=2, cap_plant=0, day_length=38,
