@@ -11,27 +11,31 @@ struct Measured { FloorWork work; bool perlin; long long floors; double blocks_u
 int main()
 {
     const Measured rows[] = {
-        { FloorWork::RESET, false, 288, 6.03, 15.29 }, { FloorWork::RESET, false, 2700, 13.16, 18.58 }, { FloorWork::RESET, false, 4500, 18.19, 21.18 }, { FloorWork::RESET, false, 5400, 20.66, 22.41 },
-        { FloorWork::RESET, false, 7686, 26.88, 26.15 }, { FloorWork::RESET, false, 7992, 27.66, 26.21 }, { FloorWork::RESET, false, 8190, 28.19, 26.26 }, { FloorWork::RESET, false, 8298, 28.5, 29.58 },
-        { FloorWork::RESET, false, 9000, 30.27, 31.63 }, { FloorWork::RESET, false, 10188, 33.29, 33.74 }, { FloorWork::RESET, false, 10800, 35.03, 35.82 }, { FloorWork::RESET, false, 11394, 36.62, 36.2 },
-        { FloorWork::RESET, false, 13500, 41.89, 40.37 }, { FloorWork::RESET, false, 36000, 100.56, 77.32 }, { FloorWork::RESET, false, 73728, 199.09, 138.92 },
-        { FloorWork::IMPORT, false, 288, 12.53, 22.83 }, { FloorWork::IMPORT, false, 3600, 28.16, 32.52 }, { FloorWork::IMPORT, false, 4797, 33.87, 34.77 }, { FloorWork::IMPORT, false, 5049, 34.99, 35.08 },
-        { FloorWork::IMPORT, false, 5193, 35.6, 35.93 }, { FloorWork::IMPORT, false, 5400, 36.44, 36.07 }, { FloorWork::IMPORT, false, 5697, 37.76, 36.69 }, { FloorWork::IMPORT, false, 9000, 52.62, 46.41 },
-        { FloorWork::IMPORT, false, 18000, 107.84, 77.92 },
-        { FloorWork::RESET, true, 288, 7.91, 20.47 }, { FloorWork::RESET, true, 2700, 17.03, 23.53 }, { FloorWork::RESET, true, 4500, 23.38, 26.34 }, { FloorWork::RESET, true, 5400, 26.67, 27.6 },
-        { FloorWork::RESET, true, 5688, 27.7, 27.61 }, { FloorWork::RESET, true, 5886, 28.43, 27.71 }, { FloorWork::RESET, true, 6084, 29.09, 27.85 }, { FloorWork::RESET, true, 6192, 29.46, 32.9 },
-        { FloorWork::RESET, true, 9000, 39.22, 42.96 }, { FloorWork::RESET, true, 10800, 45.44, 47.53 }, { FloorWork::RESET, true, 11700, 48.83, 49.57 }, { FloorWork::RESET, true, 12186, 50.54, 50.35 },
-        { FloorWork::RESET, true, 12996, 53.34, 52.64 }, { FloorWork::RESET, true, 18000, 70.47, 63.75 }, { FloorWork::RESET, true, 73728, 264.66, 185.82 },
-        { FloorWork::IMPORT, true, 288, 14.51, 28.03 }, { FloorWork::IMPORT, true, 2592, 27.06, 35.52 }, { FloorWork::IMPORT, true, 3600, 32.92, 37.9 }, { FloorWork::IMPORT, true, 4500, 38.06, 39.47 },
-        { FloorWork::IMPORT, true, 4950, 40.41, 40.13 }, { FloorWork::IMPORT, true, 5850, 45.34, 42.07 }, { FloorWork::IMPORT, true, 6192, 47.26, 46.84 },
-        { FloorWork::IMPORT, true, 9000, 62.47, 58.28 }, { FloorWork::IMPORT, true, 18000, 128.24, 97.56 },
-        { FloorWork::MUTATE, true, 288, 18.66, 22.11 }, { FloorWork::MUTATE, true, 720, 21.73, 22.78 }, { FloorWork::MUTATE, true, 1080, 22.7, 23.88 }, { FloorWork::MUTATE, true, 1440, 23.9, 24.31 },
-        { FloorWork::MUTATE, true, 1548, 24.09, 24.38 }, { FloorWork::MUTATE, true, 1620, 24.4, 24.46 }, { FloorWork::MUTATE, true, 1800, 24.84, 24.48 }, { FloorWork::MUTATE, true, 2160, 26.38, 25.03 },
-        { FloorWork::MUTATE, true, 3600, 32.18, 27.92 }, { FloorWork::MUTATE, true, 18000, 88.28, 68.55 },
-        { FloorWork::OWED, false, 819, 117.9, 127.7 }, { FloorWork::OWED, false, 2079, 149.0, 155.0 }, { FloorWork::OWED, false, 2880, 172.3, 177.4 }, { FloorWork::OWED, false, 4095, 217.3, 218.5 },
-        { FloorWork::OWED, false, 4914, 257.2, 257.5 }, { FloorWork::OWED, false, 5526, 287.8, 286.1 }, { FloorWork::OWED, false, 6138, 317.1, 314.6 }, { FloorWork::OWED, false, 8190, 418.3, 412.6 },
-        { FloorWork::OWED, true, 819, 120.1, 132.6 }, { FloorWork::OWED, true, 2079, 153.2, 160.0 }, { FloorWork::OWED, true, 2880, 178.1, 182.4 }, { FloorWork::OWED, true, 4095, 224.38, 224.43 },
-        { FloorWork::OWED, true, 4914, 265.9, 264.0 }, { FloorWork::OWED, true, 5526, 297.3, 292.9 }, { FloorWork::OWED, true, 8190, 439.6, 426.4 },
+        { FloorWork::RESET, false, 288, 6.07, 15.44 }, { FloorWork::RESET, false, 2700, 10.76, 16.34 }, { FloorWork::RESET, false, 3600, 13.33, 16.67 }, { FloorWork::RESET, false, 4500, 15.73, 16.77 },
+        { FloorWork::RESET, false, 4680, 16.18, 16.8 }, { FloorWork::RESET, false, 4860, 16.5, 16.84 }, { FloorWork::RESET, false, 4950, 16.76, 16.89 }, { FloorWork::RESET, false, 5040, 17.04, 16.79 },
+        { FloorWork::RESET, false, 5220, 17.43, 16.92 }, { FloorWork::RESET, false, 5400, 17.98, 16.91 }, { FloorWork::RESET, false, 6300, 20.22, 18.65 }, { FloorWork::RESET, false, 7200, 22.67, 20.17 },
+        { FloorWork::RESET, false, 8298, 25.7, 22.26 }, { FloorWork::RESET, false, 9360, 28.28, 24.24 }, { FloorWork::RESET, false, 10800, 31.96, 26.19 }, { FloorWork::RESET, false, 11520, 33.81, 27.45 },
+        { FloorWork::RESET, false, 18000, 50.3, 37.61 },
+        { FloorWork::IMPORT, false, 288, 8.34, 18.55 }, { FloorWork::IMPORT, false, 1800, 10.52, 20.42 }, { FloorWork::IMPORT, false, 3600, 17.3, 22.8 }, { FloorWork::IMPORT, false, 4797, 21.48, 24.85 },
+        { FloorWork::IMPORT, false, 5400, 23.51, 25.52 }, { FloorWork::IMPORT, false, 5850, 24.83, 26.09 }, { FloorWork::IMPORT, false, 6300, 26.43, 26.47 }, { FloorWork::IMPORT, false, 6480, 27.02, 26.49 },
+        { FloorWork::IMPORT, false, 6660, 27.63, 26.73 }, { FloorWork::IMPORT, false, 7200, 29.57, 28.24 }, { FloorWork::IMPORT, false, 9000, 35.87, 33.91 }, { FloorWork::IMPORT, false, 18000, 82.05, 59.58 },
+        { FloorWork::RESET, true, 288, 7.98, 20.67 }, { FloorWork::RESET, true, 2700, 14.17, 21.53 }, { FloorWork::RESET, true, 3600, 17.03, 21.7 }, { FloorWork::RESET, true, 4500, 20.43, 21.82 },
+        { FloorWork::RESET, true, 4680, 20.97, 21.76 }, { FloorWork::RESET, true, 4860, 21.56, 21.77 }, { FloorWork::RESET, true, 4950, 21.96, 21.8 }, { FloorWork::RESET, true, 5040, 22.31, 21.81 },
+        { FloorWork::RESET, true, 5400, 23.5, 21.93 }, { FloorWork::RESET, true, 6300, 26.77, 24.4 }, { FloorWork::RESET, true, 7200, 29.98, 26.46 }, { FloorWork::RESET, true, 9360, 37.15, 30.38 },
+        { FloorWork::RESET, true, 12240, 47.24, 35.11 }, { FloorWork::RESET, true, 18000, 67.63, 47.81 },
+        { FloorWork::IMPORT, true, 288, 10.03, 23.82 }, { FloorWork::IMPORT, true, 2592, 16.08, 26.69 }, { FloorWork::IMPORT, true, 3600, 20.34, 28.27 }, { FloorWork::IMPORT, true, 4500, 24.09, 29.83 },
+        { FloorWork::IMPORT, true, 4797, 25.58, 30.39 }, { FloorWork::IMPORT, true, 5400, 28.28, 31.12 }, { FloorWork::IMPORT, true, 5850, 30.03, 31.59 }, { FloorWork::IMPORT, true, 6300, 31.98, 32.84 },
+        { FloorWork::IMPORT, true, 6480, 32.94, 31.67 }, { FloorWork::IMPORT, true, 6660, 33.67, 31.52 }, { FloorWork::IMPORT, true, 7200, 36.38, 34.43 }, { FloorWork::IMPORT, true, 9000, 43.92, 39.17 },
+        { FloorWork::IMPORT, true, 18000, 101.01, 78.86 },
+        { FloorWork::MUTATE, true, 288, 18.77, 22.57 }, { FloorWork::MUTATE, true, 999, 22.86, 23.51 }, { FloorWork::MUTATE, true, 1080, 22.1, 23.14 }, { FloorWork::MUTATE, true, 1350, 22.85, 23.4 },
+        { FloorWork::MUTATE, true, 1620, 22.84, 23.45 }, { FloorWork::MUTATE, true, 1800, 22.4, 23.37 }, { FloorWork::MUTATE, true, 1935, 22.89, 23.82 }, { FloorWork::MUTATE, true, 2070, 23.97, 23.68 },
+        { FloorWork::MUTATE, true, 2250, 24.74, 23.82 }, { FloorWork::MUTATE, true, 2700, 26.35, 23.83 }, { FloorWork::MUTATE, true, 3600, 29.72, 23.97 }, { FloorWork::MUTATE, true, 9000, 49.46, 30.94 },
+        { FloorWork::OWED, false, 819, 91.67, 101.72 }, { FloorWork::OWED, false, 2880, 135.1, 139.06 }, { FloorWork::OWED, false, 3276, 137.87, 140.15 }, { FloorWork::OWED, false, 3681, 154.66, 155.04 },
+        { FloorWork::OWED, false, 4500, 185.3, 186.13 }, { FloorWork::OWED, false, 4914, 198.49, 200.96 }, { FloorWork::OWED, false, 5526, 222.13, 222.87 }, { FloorWork::OWED, false, 6138, 247.17, 246.42 },
+        { FloorWork::OWED, false, 6750, 269.62, 268.78 }, { FloorWork::OWED, false, 7371, 295.67, 290.76 }, { FloorWork::OWED, false, 8190, 326.02, 319.1 },
+        { FloorWork::OWED, true, 819, 93.35, 106.73 }, { FloorWork::OWED, true, 2880, 139.88, 145.49 }, { FloorWork::OWED, true, 3276, 143.87, 147.5 }, { FloorWork::OWED, true, 3681, 160.59, 162.37 },
+        { FloorWork::OWED, true, 4500, 193.1, 194.3 }, { FloorWork::OWED, true, 4914, 210.55, 211.62 }, { FloorWork::OWED, true, 5526, 233.07, 233.42 }, { FloorWork::OWED, true, 6138, 260.51, 258.96 },
+        { FloorWork::OWED, true, 6750, 284.56, 278.93 }, { FloorWork::OWED, true, 7371, 312.91, 305.74 }, { FloorWork::OWED, true, 8190, 348.33, 339.51 },
     };
     int bad = 0;
     for (const Measured& m : rows)

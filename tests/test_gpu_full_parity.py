@@ -234,7 +234,8 @@ def test_full_worlds_over_many_seeds(cx, worldgen):
 
 @pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 9), (po.WORLDGEN_VALUE, 55), (po.WORLDGEN_VALUE, 56), (po.WORLDGEN_PERLIN, 111), (po.WORLDGEN_PERLIN, 112), (po.WORLDGEN_VALUE, 500), (po.WORLDGEN_VALUE, 501), (po.WORLDGEN_PERLIN, 205), (po.WORLDGEN_PERLIN, 206),
                                         (po.WORLDGEN_PERLIN, 341), (po.WORLDGEN_PERLIN, 342)] +
-                         [(po.WORLDGEN_VALUE, n) for n in (405, 456, 556, 589, 623)] + [(po.WORLDGEN_PERLIN, n) for n in (183, 184, 316, 456, 512, 673)])
+                         [(po.WORLDGEN_VALUE, n) for n in (405, 456, 556, 589, 623)] + [(po.WORLDGEN_PERLIN, n) for n in (183, 184, 316, 456, 512, 673)] +
+                         [(po.WORLDGEN_VALUE, n) for n in (277, 278, 644, 645, 711, 712)] + [(po.WORLDGEN_PERLIN, n) for n in (222, 223, 272, 273, 644, 645, 711, 712)])
 def test_full_floors_by_blocks_and_by_single_wavefronts(cx, worldgen, n):
     """Reset, import, noise mutation and the worlds owed by a rollout on both sides of the lines at which their
     floors go from blocks to single wavefronts (csrc/floor_route.hpp): every floor, and the spare
