@@ -107,7 +107,6 @@ constexpr uint32_t KEY_MASK = 0x1FFFu;
 __device__ inline uint32_t cell_key(int x, int y) { return 1u | ((uint32_t)x << 1) | ((uint32_t)y << 7); }
 __device__ inline int mob_x(uint32_t w) { return (int)__builtin_amdgcn_ubfe(w, 1, 6); }
 __device__ inline int mob_y(uint32_t w) { return (int)__builtin_amdgcn_ubfe(w, 7, 6); }
-__device__ inline uint32_t mob_moved(uint32_t w, uint32_t key) { return (w & ~KEY_MASK) | key; }
 
 // Small per-block-id tables of the DO action, packed into 64-bit constants (ids 0..10):
 // item picked up (+1, 0 = none), pickaxe needed (0 none, 1 wood, 2 stone, 3 iron), achievement.

@@ -141,10 +141,11 @@ def test_full_game_runs_without_an_index_out_of_range(dbg, lanes):
         _clean(cx, f"Craftax, {lanes} lanes, observation layout {obs_mode}")
 
 
-@pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 501), (po.WORLDGEN_PERLIN, 670), (po.WORLDGEN_VALUE, 640), (po.WORLDGEN_PERLIN, 680)])
+@pytest.mark.parametrize("worldgen,n", [(po.WORLDGEN_VALUE, 501), (po.WORLDGEN_PERLIN, 670), (po.WORLDGEN_VALUE, 640), (po.WORLDGEN_PERLIN, 680),
+                                        (po.WORLDGEN_VALUE, 720), (po.WORLDGEN_PERLIN, 720)])
 def test_full_game_floors_by_single_wavefronts_without_an_index_out_of_range(dbg, worldgen, n):
-    """Enough environments that import, noise mutation and a rollout's owed worlds, and with 640 and 680 the worlds of a reset
-    too, are generated by single wavefronts (501 of value noise: everything still by blocks)."""
+    """Enough environments that the worlds of a reset and of a noise mutation, from 645 on those owed by a rollout and with 720 those of an
+    import are generated by single wavefronts (csrc/floor_route.hpp)."""
     import torch
     from test_gpu_full_parity import rich_scene
     cx = dbg
@@ -169,3 +170,35 @@ def test_full_game_floors_by_single_wavefronts_without_an_index_out_of_range(dbg
     assert sim.export_envs().tobytes() == orc.envs.tobytes()
     sim.close()
     _clean(cx, f"Craftax, floors by single wavefronts, worldgen {worldgen}")
+
+
+@pytest.mark.parametrize("worldgen,n,reset_mode", [(po.WORLDGEN_VALUE, 5121, po.RESET_EXACT), (po.WORLDGEN_PERLIN, 4097, po.RESET_EXACT),
+                                                   (po.WORLDGEN_VALUE, 90, po.RESET_POOL), (po.WORLDGEN_PERLIN, 90, po.RESET_POOL)])
+def test_full_game_byte_steps_of_a_full_chip_without_an_index_out_of_range(dbg, worldgen, n, reset_mode):
+    """Batches of more environments than the chip holds at once stage their observations by halves, and a cell on the border of two
+    parts has its bytes of the other part beside the area: every floor, map corners and edges, episodes that end.  Pooled resets of a few
+    environments take the instance that fetches nothing ahead and stages whole parts."""
+    import torch
+    from test_gpu_full_parity import rich_scene
+    cx = dbg
+    seen, cap, steps = 90, 11, 24
+    sim = cx.Craftax(n, cx.default_config(cx.VARIANT_CRAFTAX, worldgen=worldgen, reset_mode=reset_mode, max_episode_steps=cap, group_lanes=64))
+    orc = po.FullOracle(seen, po.full_default_config(worldgen=worldgen, reset_mode=reset_mode, max_episode_steps=cap), po.FULL_OBS_U8_F32)
+    seeds = synth.seeds_for(n, 29)
+    sim.reset(seeds); orc.reset(seeds[:seen])
+    rich_scene(orc.envs)
+    for i, (x, y) in enumerate(((0, 0), (47, 0), (0, 47), (47, 47), (24, 0), (0, 24), (47, 23), (23, 47))):
+        e = orc.envs[9 + 2 * i]
+        f = int(e["floor"])
+        e["px"], e["py"] = x, y
+        e["block"][f, y, x] = 7
+        e["item"][f, y, x] = 0
+    sim.import_envs(orc.envs.copy())
+    for s in range(steps):
+        a = synth.actions(np.arange(n), s, "uniform", 12, 43)
+        obs, rew, done = sim.step(torch.as_tensor(a, device=sim.device))
+        oobs, orew, odone = orc.step(a[:seen])
+        assert np.array_equal(done[:seen].cpu().numpy(), odone) and np.array_equal(obs[:seen].cpu().numpy(), oobs), s
+    assert sim.export_envs(0, seen).tobytes() == orc.envs.tobytes()
+    sim.close()
+    _clean(cx, f"Craftax, {n} environments, worldgen {worldgen}, reset mode {reset_mode}")
