@@ -333,7 +333,7 @@ __global__ __launch_bounds__(BLOCK, step_bound(PERLIN)) void k_step(uint4* __res
         }
     }
     if (kSymbolic && obs != nullptr) {
-        if (l == 0) e[LY::FLAG] = staged ? 1u : 0u;
+        if (kBytes && l == 0) e[LY::FLAG] = staged ? 1u : 0u;      // floats are told by a vote
         group_sync();
         const int first = __builtin_amdgcn_readfirstlane((tid & ~63) / G);   // first environment of this wave within the block
         const uint32_t* wave_env = s_env + first * LY::STRIDE;
@@ -542,7 +542,7 @@ __global__ __launch_bounds__(BLOCK, rollout_bound(G, OBS_MODE, PERLIN)) void k_r
             staged = true;
         }
         if (obs != nullptr) {
-            if (l == 0) e[LDS_FLAG] = staged ? 1u : 0u;
+            if (kBytes && l == 0) e[LDS_FLAG] = staged ? 1u : 0u;
             group_sync();
             const int first = __builtin_amdgcn_readfirstlane((tid & ~63) / G);
             const uint32_t* wave_env = s_env + first * LDS_ENV_DWORDS;
