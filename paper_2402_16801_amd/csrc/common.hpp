@@ -332,7 +332,7 @@ constexpr int LDS_ENV_DWORDS = 142;
 static_assert(LDS_VEC + 24 <= LDS_ENV_DWORDS, "per-environment LDS area overflows");
 // The layout above keeps the record intact while the observation is staged (the rollout kernel
 // carries records from step to step).  The single-step kernel has written its record back before
-// it renders, so there the scalar vector takes the record's place: 118 dwords per environment
+// it renders, or holds it in registers to write it behind the observation (RECORD_LAST), so there the scalar vector takes the record's place: 118 dwords per environment
 // (again distinct even banks for the environments of a wave), which lets five blocks of 64
 // environments share a compute unit's 160 KB instead of four.
 struct KeepLayout { static constexpr int VEC = LDS_VEC, FLAG = LDS_FLAG, STRIDE = LDS_ENV_DWORDS; };

@@ -1162,12 +1162,17 @@ static Ptrs pointers(const void* state, const HostState& s)
 // Lanes per environment: few lanes amortise the per-environment scalar work over more
 // environments per wave and win once there are enough environments to fill the chip; many
 // lanes give more, shorter waves and win for small batches.  cfg->group_lanes = 4, 8 or 16
-// overrides the choice (for tuning).
+// overrides the choice (for tuning).  The lanes belong to the state, whatever its calls are, and no line suits all of these (us with 16 / 8 / 4 lanes,
+// three states in turn).  Steps without an observation 12,288 9.7 / 10.0 / 11.2, 16,384 11.3 / 10.3 / 11.3, 32,768 17.7 / 14.3 / 14.8, 45,000 22.0 / 17.9 / 16.7;
+// floats 12,288 16.7 / 19.0 / 20.6, 14,000 22.0 / 20.4 / 22.1, 32,768 55.2 / 51.0 / 54.5, 65,536 104.8 / 102.2 / 103.7; bytes 8,192
+// 9.2 / 12.3 / 14.6, 16,384 13.9 / 15.3 / 15.7, 20,480 16.2 / 17.1 / 19.5, 24,576 18.8 / 18.1 / 20.2, 32,768 26.2 / 20.8 / 22.4, 45,000
+// 35.0 / 33.3 / 29.9.  The lower line is that of the first two (bytes alone would stay with sixteen lanes to about 21,000), the upper one that
+// of rollouts, which have sixteen lanes or four (a step of a rollout 20,000 13.1 / 13.3, 24,576 14.5 / 13.7, 32,768 18.0 / 14.8; steps alone would stay with eight to about 41,000).
 static int group_lanes(const craftax_config* cfg, int n)
 {
     const int g = (int)cfg->group_lanes;
     if (g == 4 || g == 8 || g == 16) return g;
-    return n >= 24576 ? 4 : (n >= 12288 ? 8 : 16);   // measured: 8,192 -> 16 lanes (11.9 us against 12.9 and 14.8), 16,384 -> 8, 32,768 -> 4
+    return n >= 24576 ? 4 : (n >= 12288 ? 8 : 16);
 }
 
 constexpr int RESET_GRID = 64;    // blocks of k_reset_list (the slow list is nearly always empty); each loops over the list

@@ -557,8 +557,8 @@ __global__ __launch_bounds__(BLOCK) void kf_observe(const uint32_t* __restrict__
 // counted over the whole vector) and generates the floor of the current episode again from the
 // turned lattice; the block of floor 0 also starts the episode over.  It writes every word of the
 // record but the episode and the seed, which the other blocks read and which stay as they are, so one
-// launch does it all (floor 0 in a launch of its own behind the others: 131 us for 1,000
-// levels, one launch: 92, by single wavefronts 82).
+// launch does it all (1,000 levels, floor 0 in a launch of its own behind the others: 131 us, one launch 92 then; now 49 by blocks
+// and 31 by single wavefronts).
 __device__ inline int theta_offset(int f)
 {
     return f == 0 ? 0 : LAT0_U16 + LATC_U16 * (f == 2 ? 0 : (f == 5 ? 1 : (f == 6 ? 2 : 3)));
@@ -725,7 +725,7 @@ __device__ inline void import_record(uint32_t* __restrict__ r, const Lists& ls, 
 // One block per (environment, floor): it takes the floor in, and generates the same floor of the world
 // of the next episode into the spare slot, so that the copy of some blocks overlaps the arithmetic of
 // others; the block of floor 0 also packs the record.  (A copy byte by byte and a second launch for
-// the spare worlds: 50 + 87 us for 1,000 Perlin worlds, one launch 101, by single wavefronts 93.)
+// the spare worlds: 50 + 87 us for 1,000 Perlin worlds, one launch 101 then; now 44 by blocks and 39 by single wavefronts.)
 template <bool PERLIN, int NT>
 __global__ __launch_bounds__(NT, PERLIN ? PERLIN_WAVES : VALUE_WAVES) void kf_import(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, Lists ls,
                                                                         const craftax_full_env_dump* __restrict__ dumps, int first, Params p,
@@ -1050,10 +1050,10 @@ int reset(void* state, const craftax_config* cfg, int n, const uint64_t* seeds, 
 // Lanes per environment of the step kernel.  A whole wavefront (the default at every batch size)
 // keeps the player's state and the 43-action code on the scalar unit, which works beside the vector
 // unit.  Sixteen lanes put four environments in a wavefront and fill 14 of 16 lanes with mob slots
-// instead of 14 of 64, but the player's code then runs on the vector unit, the kernel needs up to 133
-// vector registers and 48 KB of LDS (three wavefronts per SIMD instead of five), and a wavefront
-// renders four observations one after the other.  us per step, 16 / 64 lanes: 20.9 / 11.0 at 1,024
-// environments, 21.4 / 14.4 at 4,096, 51.6 / 45.0 at 16,384, 172.6 / 178.6 at 65,536.  It is selectable
+// instead of 14 of 64, but the player's code then runs on the vector unit, the kernel needs 48 KB
+// of LDS (three wavefronts per SIMD instead of six to eight), and a wavefront
+// renders four observations one after the other.  us per step, 16 / 64 lanes: 16.8 / 9.9 at 1,024
+// environments, 17.4 / 12.8 at 4,096, 43.4 / 34.0 at 16,384, 138 / 118 at 65,536.  It is selectable
 // (cfg->group_lanes = 16) and tested like the default.
 static int group_lanes(const craftax_config* cfg, int n)
 {
