@@ -112,6 +112,9 @@ static_assert(sizeof(WorldScratch) % 8 == 0 && offsetof(WorldScratch, layout) % 
 // the entry says is moved to scalar registers: the floor and its seed are the same for the wavefront, which an index divided by a number
 // from LDS hides from the compiler (with that division and a walk over the sub-lists, a step's us / so: 2,048 environments 10.6 / 10.2, without
 // an observation 10.1 / 9.6; with episodes of at most 20 steps, of every age, 4,096 34.0 / 31.9, 8,192 67.7 / 62.4, 16,384 128 / 118, Perlin noise 135 / 127).
+// By turn at every length (see floor_grid; us, world by world / by turn): up to a floor per block either is as fast (64 environments 7.9 / 7.9, 1,000 9.9 / 9.9, 2,048
+// 10.2 / 10.3, with Perlin noise 12.5 / 12.5), beyond that the first has blocks that get two overworlds (4,096 with episodes of at most 100 steps 14.5 / 14.0,
+// of 20 33.2 / 31.8, Perlin noise 17.7 / 15.6 and 38.2 / 35.5, 16,384 of 20 119 / 118 and 128 / 127).
 template <int NT, bool PERLIN>
 __device__ __forceinline__ void regeneration_queue(uint32_t* __restrict__ envs, uint8_t* __restrict__ maps, const Lists& ls,
                                                    uint32_t seq, WorldScratch& s, const uint32_t* s_prefix, int regen_blocks,
